@@ -405,7 +405,7 @@ def splitk_points(b, torch, steps, count_flag, shapes=((256, 1024, 8192), (128, 
 
 
 CALIB_COPY_BYTES = 256 << 20
-GEMM_KERNEL_TAGS = ("gemm_tile_async_kernel", "gemm_tile_kernel", "gemm_smallm_kernel")
+GEMM_KERNEL_TAGS = ("gemm_tile_async_kernel", "gemm_smallm_kernel")
 
 
 def pmc_child(args):

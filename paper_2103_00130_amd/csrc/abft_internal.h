@@ -126,11 +126,9 @@ struct GemmParams {
     int32_t* ws;               // workspace: counting words in the first kWsHeaderInts ints, then the per-row words
 };
 
-constexpr int kWsHeaderInts = 64;   // top arrival word, 16 group arrival words (any-alignment kernel), word of finished rows
-constexpr int kTicketGroups = 16;
+constexpr int kWsHeaderInts = 64;
 constexpr int kWsDoneWord = 48;     // int offset, inside the header, of the 64-bit word that counts finished rows (low half)
-                                    // and corrupted ones among them (high half): direct-to-LDS tile kernels, streaming kernel
-constexpr int kTicketFlatMax = 128;  // grids up to this size count their arrivals on one word
+                                    // and corrupted ones among them (high half)
 // the streaming kernel spreads its per-row sums over kSmallMSlots slots of kSmallMRows rows
 constexpr int kSmallMSlots = 32;
 constexpr int kSmallMRows = 64;
@@ -142,6 +140,14 @@ inline size_t ws_base_ints(int M) {
     const size_t streaming = 2 * ((size_t)kSmallMSlots * kSmallMRows + kSmallMRows);
     return (size_t)kWsHeaderInts + (rows > streaming ? rows : streaming);
 }
+
+// What some calls need beyond those words - the tile tickets and partial tiles of a K split, a copy of A with padded rows -
+// lies behind the words of any call of up to kWsRows rows, so that one workspace can serve calls of different sizes: the
+// words (tickets among them) are zero between calls, the scratch behind them holds whatever the last call left.
+constexpr int kWsRows = 131072;
+constexpr size_t kWsTicketsOff = (size_t)kWsHeaderInts + 2 * (size_t)kWsRows;
+constexpr size_t kWsTickets = 1024;
+constexpr size_t kWsScratchOff = kWsTicketsOff + kWsTickets;
 
 // Split-K across workgroups (64x64 tiles, grids that would leave most compute units idle): how many K slices,
 // and where the tile tickets and the partial tiles lie in the workspace behind the row words.  One place for
@@ -161,15 +167,40 @@ inline SplitKPlan splitk_plan(int M, int N, int stages) {
     // about forty stages on (measured: 256x512x4096 8.1 us split against 8.5 unsplit, 256x1024x8192 10.5 against
     // 14.0, 128x128x16384 9.8 against 33.9; 256x512x2048 7.6 against 5.9), and slices of fewer than four stages
     // are all overhead.
-    if (stages >= 40)
+    if (stages >= 40 && M <= kWsRows)
         for (int z = 16; z >= 2; z >>= 1)
             if (tiles * z <= 256 && stages % z == 0 && stages / z >= 4) {
                 pl.z = z;
                 break;
             }
-    pl.tickets_off = ws_base_ints(M);
-    pl.part_off = pl.tickets_off + (size_t)((tiles + 63) / 64 * 64);
-    pl.total_ints = pl.z > 1 ? pl.part_off + (size_t)tiles * pl.z * kSplitKPartInts : pl.tickets_off;
+    pl.tickets_off = kWsTicketsOff;   // (at most 256 tiles are split)
+    pl.part_off = kWsScratchOff;
+    pl.total_ints = pl.z > 1 ? pl.part_off + (size_t)tiles * pl.z * kSplitKPartInts : ws_base_ints(M);
+    return pl;
+}
+
+// Rows of A that are no whole, aligned 16-byte chunks (K no multiple of 16, or such a base or leading dimension): either the
+// 64x64 kernel with loads through registers takes them as they lie, or a copy with padded rows is made first, in the
+// workspace, for the direct-to-LDS kernels.  The copy costs about 3 us (a launch and a pass over A); the loads through
+// registers cost 0.2-0.3 us more for every stage that a compute unit works through, and the large tiles and K splits are
+// out of reach, so the copy pays from about twenty stages per unit on (measured in us, loads through registers / copy:
+// 2000x1000x1001, 16 stages per unit, 11.5 / 11.8; 256x512x2049, 17, 10.8 / 11.4; 1111x3333x777, 28, 16.5 / 14.9;
+// 1000x1000x4097, 33, 20.3 / 16.9; 4096x2048x1023, 64, 30.2 / 23.1; 4096x4096x4095, 512, 148 / 74).
+// abft_gemm_workspace_bytes includes the room when K is no multiple of 16 and the copy would be made (copies above 512 MiB
+// are not); a workspace without it runs without the copy.
+struct RealignPlan {
+    bool copy;
+    size_t off, total_ints;    // ints into the workspace; the copy starts on the next 16-byte boundary
+    int64_t lda;               // bytes of a padded row
+};
+inline RealignPlan realign_plan(int M, int N, int K, int stages) {
+    RealignPlan pl;
+    const SplitKPlan sk = splitk_plan(M, N, stages);
+    const int64_t tiles = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
+    pl.lda = ((int64_t)K + 15) / 16 * 16;
+    pl.copy = (tiles + 255) / 256 * stages >= 20 && M <= kWsRows && pl.lda * M <= (512ll << 20);
+    pl.off = sk.z > 1 ? sk.total_ints : kWsScratchOff;
+    pl.total_ints = pl.off + (size_t)(pl.lda * M / 4) + 4;
     return pl;
 }
 
@@ -177,39 +208,20 @@ inline SplitKPlan splitk_plan(int M, int N, int stages) {
 __host__ __device__ inline int share_begin(int c, int q, int r) { return c * q + (c < r ? c : r); }
 
 #ifdef __HIPCC__
-// Arrival count of the workgroups of a grid in two levels, so that no workspace word takes more
-// than a few dozen atomics at once (hundreds of returned atomics on one address serialise for
-// microseconds): a workgroup arrives at the word of its group (block id modulo kTicketGroups) with
-// its contribution `mine` in the high half; the last of a group carries the group's sum on to
-// the top word (grids of at most kTicketFlatMax workgroups skip the first level).  True for the
-// one workgroup that completes the top word, *total then holds the sum over the grid; both levels leave their words at zero.  Everything a workgroup did with
-// returned device-scope atomics before it arrives is complete when the last one gets here.
-__device__ inline bool arrive_two_level(int32_t* ws, uint32_t mine, uint32_t n_blocks, uint32_t block, uint32_t* total) {
-    unsigned long long* const top0 = reinterpret_cast<unsigned long long*>(ws);
-    if (n_blocks <= (uint32_t)kTicketFlatMax) {
-        // a small grid arrives at the top word directly: one round trip less
-        const unsigned long long old0 = __hip_atomic_fetch_add(top0, ((unsigned long long)mine << 32) | 1ull, __ATOMIC_RELAXED,
-                                                               __HIP_MEMORY_SCOPE_AGENT);
-        if ((uint32_t)old0 != n_blocks - 1u) return false;
-        *total = (uint32_t)(old0 >> 32) + mine;
-        __hip_atomic_store(top0, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return true;
+// The sixteen bytes of v (four 32-bit words) moved down by n places, zeros coming in; n is 1..15.  For the end of a row whose length is no multiple of 16: its last sixteen bytes, loaded as they lie,
+// become the last chunk.
+typedef int shift_v4i __attribute__((ext_vector_type(4)));
+__device__ inline shift_v4i shift_down(shift_v4i v, int n) {
+    const uint64_t lo = ((uint64_t)(uint32_t)v.y << 32) | (uint32_t)v.x, hi = ((uint64_t)(uint32_t)v.w << 32) | (uint32_t)v.z;
+    uint64_t l, h;
+    if (n < 8) {
+        l = (lo >> (8 * n)) | (hi << (64 - 8 * n));
+        h = hi >> (8 * n);
+    } else {
+        l = hi >> (8 * n - 64);
+        h = 0;
     }
-    const uint32_t g = block & (kTicketGroups - 1);
-    const uint32_t n_g = (n_blocks - g + kTicketGroups - 1) / kTicketGroups;
-    const uint32_t n_active = n_blocks < (uint32_t)kTicketGroups ? n_blocks : (uint32_t)kTicketGroups;
-    unsigned long long* const top = reinterpret_cast<unsigned long long*>(ws);
-    unsigned long long* const grp = reinterpret_cast<unsigned long long*>(ws + 16) + g;
-    unsigned long long old = __hip_atomic_fetch_add(grp, ((unsigned long long)mine << 32) | 1ull, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT);
-    if ((uint32_t)old != n_g - 1u) return false;
-    const uint32_t gsum = (uint32_t)(old >> 32) + mine;
-    __hip_atomic_store(grp, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    old = __hip_atomic_fetch_add(top, ((unsigned long long)gsum << 32) | 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if ((uint32_t)old != n_active - 1u) return false;
-    *total = (uint32_t)(old >> 32) + gsum;
-    __hip_atomic_store(top, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return true;
+    return shift_v4i{(int)(uint32_t)l, (int)(uint32_t)(l >> 32), (int)(uint32_t)h, (int)(uint32_t)(h >> 32)};
 }
 #endif
 
@@ -222,7 +234,10 @@ hipError_t launch_flip_checksum_bit(abft_packed_b* h, int k, int bit, hipStream_
 hipError_t launch_flip_checksum127_bit(abft_packed_b* h, int k, int bit, hipStream_t s);
 hipError_t launch_fill_zero(int32_t* p, size_t n_ints, hipStream_t s);
 hipError_t launch_gemm_tile(int variant, bool check, bool want_c, bool want_q, const GemmParams& p, hipStream_t s);
-hipError_t launch_gemm_smallm(bool check, bool want_c, bool want_q, const GemmParams& p, hipStream_t s);
+// any_a: A of any alignment and K >= 16 is taken too (else only whole, aligned 16-byte chunks)
+hipError_t launch_gemm_smallm(bool any_a, bool check, bool want_c, bool want_q, const GemmParams& p, hipStream_t s);
+// A's rows copied to rows of lda2 bytes (a multiple of 16), zeros behind K
+hipError_t launch_realign(const uint8_t* A, int64_t lda, int M, int K, uint8_t* A2, int64_t lda2, hipStream_t s);
 hipError_t launch_requantize(const int32_t* C, int64_t ldc, int M, int N, const int32_t* colsum,
                              const RequantDev& rq, uint8_t* Cq, int64_t ldcq, hipStream_t s);
 hipError_t launch_verify_rows(const int32_t* C, int64_t ldc, int M, int N, const int32_t* row_chk,

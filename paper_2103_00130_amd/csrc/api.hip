@@ -152,7 +152,12 @@ void abft_packed_b_destroy(abft_packed_b* Bp) { free_handle(Bp); }
 size_t abft_gemm_workspace_bytes(int M, const abft_packed_b* Bp) {
     if (M < 1) return 0;
     // with the weight known: room for the partial tiles of a K split across workgroups, where one would be used
-    if (Bp) return abft::splitk_plan(M, Bp->N, Bp->KB / 2).total_ints * sizeof(int32_t);
+    // and, where rows of Bp->K bytes are no whole chunks, for the copy with padded rows
+    if (Bp) {
+        const abft::RealignPlan ra = abft::realign_plan(M, Bp->N, Bp->K, Bp->KB / 2);
+        if (Bp->K % 16 != 0 && ra.copy) return ra.total_ints * sizeof(int32_t);
+        return abft::splitk_plan(M, Bp->N, Bp->KB / 2).total_ints * sizeof(int32_t);
+    }
     return ws_ints(M) * sizeof(int32_t);
 }
 
@@ -256,10 +261,22 @@ int abft_gemm_u8s8s32_checked(const uint8_t* A, int64_t lda, int M, const abft_p
     const bool streaming = M <= 32 || (M <= 64 && (int64_t)Bp->N * Bp->K >= (int64_t)1 << 22);
     if (!chosen) variant = streaming ? (int)abft::kSmallM : pick_tile();
     hipError_t e;
+    if (variant != abft::kSmallM && !mod127 && !(p.a_vec_ok && p.K % 16 == 0)) {
+        const abft::RealignPlan ra = abft::realign_plan(M, Bp->N, Bp->K, p.KB2);
+        if (ra.copy && workspace && p.ws_ints >= ra.total_ints) {
+            uint8_t* const A2 = (uint8_t*)(((uintptr_t)(p.ws + ra.off) + 15) & ~(uintptr_t)15);
+            e = abft::launch_realign(A, lda, M, p.K, A2, ra.lda, (hipStream_t)stream);
+            if (e != hipSuccess) return hip_fail(e, fn);
+            p.A = A2;
+            p.lda = ra.lda;
+            p.a_vec_ok = 1;
+            p.K = (int)ra.lda;    // (the padding meets rows of zeros in the packed weight)
+        }
+    }
     if (variant == abft::kSmallM) {
         if (M > 64) return fail(ABFT_EUNSUPPORTED, "%s: the streaming variant takes M <= 64, got %d", fn, M);
-        e = abft::launch_gemm_smallm(check, want_c, want_q, p, (hipStream_t)stream);
-        if (e == hipErrorNotSupported && !chosen)  // unaligned A: the general tiled path takes it
+        e = abft::launch_gemm_smallm(!chosen, check, want_c, want_q, p, (hipStream_t)stream);
+        if (e == hipErrorNotSupported && !chosen)  // rows shorter than a 16-byte chunk: the tiled path takes them
             e = abft::launch_gemm_tile(pick_tile(), check, want_c, want_q, p, (hipStream_t)stream);
     } else if (variant >= abft::kTile256 && variant < abft::kVariantEnd) {
         e = abft::launch_gemm_tile(variant, check, want_c, want_q, p, (hipStream_t)stream);

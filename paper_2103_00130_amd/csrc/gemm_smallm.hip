@@ -25,6 +25,7 @@ namespace abft {
 namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v4i_any __attribute__((ext_vector_type(4), aligned(1)));  // sixteen bytes at any address
 constexpr int kOutC = 1, kOutQ = 2;
 constexpr int kSmallMWideN = 8192;   // from this width on a workgroup owns 32 columns (M <= 32): at least 256 workgroups remain (with fewer, 16 x 4096 x 2048 runs in 5.6 us instead of 4.7)
 
@@ -49,7 +50,9 @@ __device__ inline int32_t floor_mod127(long long v) {
 // 4 KiB of contiguous memory instead of every other 256 bytes of it, and one A operand serves two or four matrix
 // instructions (wide weights, where the column blocks alone fill the chip many times over; measured at M = 16 on
 // 16384 x 32768 int8: 0.49 of the HBM peak with NCB = 1, 0.64 with 2, 0.70 with 4).
-template <int RB, int NCB, bool kCheck, int kOut>
+// kAny: A of any alignment, leading dimension and K >= 16.  The same chunks come in with loads from any byte address; the
+// one chunk that holds the end of a row, loaded from K - 16, is shifted down to its place before it is used.
+template <int RB, int NCB, bool kCheck, int kOut, bool kAny>
 __global__ __launch_bounds__(256) void gemm_smallm_kernel(const GemmParams p, const int n_blocks) {
     constexpr int BATCH = (RB == 1 ? 8 : 4) / NCB > 0 ? (RB == 1 ? 8 : 4) / NCB : 1;  // k-blocks per wave per batch of loads
     constexpr bool kWantC = (kOut & kOutC) != 0, kWantQ = (kOut & kOutQ) != 0;
@@ -88,6 +91,7 @@ __global__ __launch_bounds__(256) void gemm_smallm_kernel(const GemmParams p, co
 #pragma unroll
     for (int c = 0; c < NCB; ++c) bsum[c] = 0;
 
+    const int over = kAny ? (16 - (p.K & 15)) & 15 : 0;   // bytes the end chunk of a row moves down
     v4i fb[2][BATCH][NCB], fa[2][BATCH][RB], fl[2][BATCH];
     auto issue = [&](int kb0, int s) __attribute__((always_inline)) {
 #pragma unroll
@@ -100,7 +104,10 @@ __global__ __launch_bounds__(256) void gemm_smallm_kernel(const GemmParams p, co
                 fb[s][u][c] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(b_src + (int64_t)kbc * B_KB_STRIDE + (c >> 1) * kUnitBytes + (c & 1) * 256));
             const int k = min(kbc * 64 + lkg * 16, p.K - 16);
 #pragma unroll
-            for (int rb = 0; rb < RB; ++rb) fa[s][u][rb] = *reinterpret_cast<const v4i*>(a_row[rb] + k);
+            for (int rb = 0; rb < RB; ++rb) {
+                if constexpr (kAny) fa[s][u][rb] = *reinterpret_cast<const v4i_any*>(a_row[rb] + k);
+                else fa[s][u][rb] = *reinterpret_cast<const v4i*>(a_row[rb] + k);
+            }
             if (kCheck) {
                 fl[s][u] = v4i{0, 0, 0, 0};
                 if (kb >= lo && kb < hi && lcol < kLimbs)
@@ -122,6 +129,14 @@ __global__ __launch_bounds__(256) void gemm_smallm_kernel(const GemmParams p, co
                 bsum[c] = __builtin_amdgcn_sad_u8((uint32_t)b[c].y ^ 0x80808080u, 0u, bsum[c]);
                 bsum[c] = __builtin_amdgcn_sad_u8((uint32_t)b[c].z ^ 0x80808080u, 0u, bsum[c]);
                 bsum[c] = __builtin_amdgcn_sad_u8((uint32_t)b[c].w ^ 0x80808080u, 0u, bsum[c]);
+            }
+            // (chunks past the end of a row, and bytes of its last chunk past it, meet zero rows of B)
+            if (kAny && over != 0 && kb == (p.K >> 6)) {
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) {
+                    const v4i m = shift_down(fa[s][u][rb], over);
+                    if (lkg == ((p.K >> 4) & 3)) fa[s][u][rb] = m;
+                }
             }
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
@@ -313,8 +328,8 @@ __global__ __launch_bounds__(256) void gemm_smallm_kernel(const GemmParams p, co
     }
 }
 
-template <int RB, int NCB>
-hipError_t launch_rb(bool check, bool want_c, bool want_q, const GemmParams& p_in, hipStream_t s) {
+template <int RB, int NCB, bool kAny>
+hipError_t launch_any(bool check, bool want_c, bool want_q, const GemmParams& p_in, hipStream_t s) {
     GemmParams p = p_in;
     const int n_blocks = (p.N + 16 * NCB - 1) / (16 * NCB);
     p.share_q = p.KB / n_blocks;   // k-blocks of the checksum product per column block
@@ -322,7 +337,7 @@ hipError_t launch_rb(bool check, bool want_c, bool want_q, const GemmParams& p_i
     const dim3 grid((unsigned)n_blocks), block(256);
 #define ABFT_LAUNCH(CK, OUT)                                                         \
     do {                                                                             \
-        gemm_smallm_kernel<RB, NCB, CK, OUT><<<grid, block, 0, s>>>(p, n_blocks);    \
+        gemm_smallm_kernel<RB, NCB, CK, OUT, kAny><<<grid, block, 0, s>>>(p, n_blocks);    \
         return hipGetLastError();                                                    \
     } while (0)
 #define ABFT_OUT(CK)                                          \
@@ -337,10 +352,18 @@ hipError_t launch_rb(bool check, bool want_c, bool want_q, const GemmParams& p_i
 #undef ABFT_LAUNCH
 }
 
+template <int RB, int NCB>
+hipError_t launch_rb(bool check, bool want_c, bool want_q, const GemmParams& p, hipStream_t s) {
+    if (p.a_vec_ok && p.K % 16 == 0) return launch_any<RB, NCB, false>(check, want_c, want_q, p, s);
+    return launch_any<RB, NCB, true>(check, want_c, want_q, p, s);
+}
+
 }  // namespace
 
-hipError_t launch_gemm_smallm(bool check, bool want_c, bool want_q, const GemmParams& p, hipStream_t s) {
-    if (p.M > 64 || !p.a_vec_ok || p.K % 16 != 0) return hipErrorNotSupported;
+hipError_t launch_gemm_smallm(bool any_a, bool check, bool want_c, bool want_q, const GemmParams& p, hipStream_t s) {
+    if (p.M > 64) return hipErrorNotSupported;
+    if (!p.a_vec_ok || p.K % 16 != 0)
+        if (!any_a || p.mod127 || p.K < 16) return hipErrorNotSupported;
     // whole 32-column units per workgroup once the 16-column blocks alone would fill the chip at least twice
     const bool wide = p.N >= kSmallMWideN;
     if (p.M <= 16 && p.N >= 2 * kSmallMWideN) return launch_rb<1, 4>(check, want_c, want_q, p, s);

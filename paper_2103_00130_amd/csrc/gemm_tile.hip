@@ -12,7 +12,6 @@ ABFT_DECL(a64r8);
 ABFT_DECL(a64r4);
 ABFT_DECL(a64s);
 ABFT_DECL(a64k2);
-ABFT_DECL(g128);
 ABFT_DECL(g64);
 #undef ABFT_DECL
 
@@ -22,8 +21,7 @@ hipError_t launch_gemm_tile(int variant, bool check, bool want_c, bool want_q, c
     const bool fast_a = p.a_vec_ok && (p.K % 16 == 0) && ((int64_t)(p.M - 1) * p.lda + p.K <= 0x7fffffffll);
     if (!fast_a) {
         if (p.mod127) return hipErrorNotSupported;
-        if (variant == kTile64) return launch_gemm_tile_g64(check, want_c, want_q, p, s);
-        return launch_gemm_tile_g128(check, want_c, want_q, p, s);
+        return launch_gemm_tile_g64(check, want_c, want_q, p, s);   // (whichever tile was asked for: the results are the same)
     }
     switch (variant) {
         case kTile256: return launch_gemm_tile_a256(check, want_c, want_q, p, s);

@@ -38,6 +38,7 @@ namespace atile {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
+typedef int v4i_any __attribute__((ext_vector_type(4), aligned(1)));  // sixteen bytes at any address
 
 constexpr int kOutC = 1, kOutQ = 2;
 constexpr int BK = 128;  // k-values per stage
@@ -112,7 +113,7 @@ constexpr size_t group_lds_bytes() {
 // of every run of stages is dealt out to the tile columns as before, so every workgroup contributes its share
 // of it to the row words directly (the comparison of Eq. 2b is linear in the K slices) and only the last one
 // contributes row sums.  For grids of 64x64 tiles that would leave most compute units idle.
-template <int BM, int BN, int WGM, int WGN, int kStages, bool kCheck, int kOut, bool kBlockSums, int WGK, bool kSplitK = false>
+template <int BM, int BN, int WGM, int WGN, int kStages, bool kCheck, int kOut, bool kBlockSums, int WGK, bool kSplitK = false, int kAnyA = 0>
 __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(const GemmParams p, const int tiles_m,
                                                                              const int tiles_n) {
     constexpr int NW = WGM * WGN, NT = NW * 64;    // wavefronts and threads of one group
@@ -121,6 +122,7 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     constexpr int A_STAGE = BM * BK, B_STAGE = BN * BK;
     constexpr int S = kStages;                     // stages resident in LDS
     static_assert(S >= 2, "at least a double buffer");
+    static_assert(kAnyA == 0 || (S == 2 && WGK == 1 && kAnyA % 2 == 0), "register-staged loads: a double buffer in LDS");
     constexpr int A_LD = (BM / 8) / NW;            // async A loads per wave per stage (8 rows each)
     constexpr int B_LD = (BN / 8) / NW;            // async B loads per wave per stage (1 KiB each)
     constexpr int CB = (WTM / 16) / WGN;           // 16-row checksum blocks per wave
@@ -225,6 +227,63 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
         }
     };
 
+    // ---- loads through registers (kAnyA) ----------------------------------------------
+    // Same rows, same LDS image, but the 16-byte chunks of A come in with ordinary loads from any byte address
+    // and go to LDS from registers.  Nothing past the operand is read: a chunk at or past K - 16 is loaded from
+    // K - 16, and the one chunk that holds the end of the row is shifted down to its place when it is written
+    // (chunks past it, and bytes of it past K, meet zero rows of B).  A row shorter than a chunk (K < 16) is
+    // put together from bytes.
+    const uint8_t* a_row[A_LD];
+    int a_c16 = 0, a_c16_last = 0;
+    if constexpr (kAnyA != 0) {
+        a_c16 = (lane & 7) * 16;
+        a_c16_last = min(a_c16, p.K - 16 - (NS_all - 1) * BK);
+        const bool whole = p.K >= 16;   // (else the loads fetch sixteen bytes of B that nobody uses)
+        if (!whole) a_c16 = a_c16_last = 0;
+#pragma unroll
+        for (int i = 0; i < A_LD; ++i) {
+            const int r = (wave * A_LD + i) * 8 + (lane >> 3);
+            a_row[i] = whole ? p.A + (int64_t)min(row0 + r, p.M - 1) * p.lda : reinterpret_cast<const uint8_t*>(p.packed);
+        }
+    }
+    auto reg_load = [&](int s, v4i(&ra)[A_LD], v4i(&rb)[B_LD]) __attribute__((always_inline)) {
+        const int s_all = s_base + s;
+        const int64_t k = (int64_t)s_all * BK + (s_all == NS_all - 1 ? a_c16_last : a_c16);
+#pragma unroll
+        for (int i = 0; i < A_LD; ++i) ra[i] = *reinterpret_cast<const v4i_any*>(a_row[i] + k);
+        const int8_t* const base = b_wave + (int64_t)s * (2 * B_KB_STRIDE) + b_voff;
+#pragma unroll
+        for (int j = 0; j < B_LD; ++j) rb[j] = *reinterpret_cast<const v4i*>(base + j * 1024);
+    };
+    // column sums of the B bytes streamed (every wave keeps them for its own columns; with loads through registers for
+    // the columns it copies, which are the same, wm telling the two k-blocks of a stage apart)
+    uint32_t bsum[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) bsum[j] = 0;
+    static_assert(kAnyA == 0 || (B_LD == 2 * TN && WGM == 2 && WGN == 2), "two 1 KiB chunks, a 32-column unit of one k-block, per column sum");
+    auto reg_store = [&](int s, int buf, const v4i(&ra)[A_LD], const v4i(&rb)[B_LD]) __attribute__((always_inline)) {
+        if (s < NS) {   // (a stage past the end is a copy of the last one)
+#pragma unroll
+            for (int j = 0; j < B_LD; ++j)
+#pragma unroll
+                for (int d = 0; d < 4; ++d) bsum[j >> 1] = (uint32_t)__builtin_amdgcn_sdot4(rb[j][d], 0x01010101, (int)bsum[j >> 1], false);
+        }
+        const int over = (s_base + s >= NS_all - 1 && p.K >= 16) ? (16 - (p.K & 15)) & 15 : 0;  // bytes the end chunk moves down
+        const bool end_chunk = (NS_all - 1) * BK + a_c16 == (p.K & ~15);
+#pragma unroll
+        for (int i = 0; i < A_LD; ++i) {
+            const int r = (wave * A_LD + i) * 8 + (lane >> 3);
+            v4i v = ra[i];
+            if (over) {
+                const v4i m = shift_down(v, over);
+                v = end_chunk ? m : v;
+            }
+            *reinterpret_cast<v4i*>(smem + buf * A_STAGE + r * BK + ((lane & 7) ^ ((r >> 1) & 7)) * 16) = v;
+        }
+#pragma unroll
+        for (int j = 0; j < B_LD; ++j) *reinterpret_cast<v4i*>(smem + (b_lds - lds_base) + buf * B_STAGE + j * 1024 + b_voff) = rb[j];
+    };
+
     // ---- fragment reads -----------------------------------------------------------
     // A fragment (block i, k-step j): lane l holds row wm*WTM + i*32 + (l&31), chunk 2j + (l>>5)
     const int a_swz = (lane >> 1) & 7;
@@ -243,10 +302,6 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     v4i cacc[CB];
 #pragma unroll
     for (int i = 0; i < CB; ++i) cacc[i] = v4i{0, 0, 0, 0};
-    // column sums of the B bytes streamed (every wave keeps them for its own columns)
-    uint32_t bsum[TN];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) bsum[j] = 0;
 
     // Small wave tiles (at most four MFMAs per k-step) read their fragments two k-steps ahead: one
     // k-step of such a tile is shorter than the latency of an LDS read, so with one k-step of
@@ -430,7 +485,34 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     using frag_reads_c = std::integral_constant<int, TM + TN>;  // LDS reads of one k-step
     // (the digits of this tile column's share go out first: whatever wait publishes the first stage then
     // covers them as well, and their round trip to memory runs beside that of the stages)
-    if constexpr (kAhead2) {
+    constexpr int P = kAnyA ? kAnyA : 1;   // register sets: stages on their way to LDS
+    v4i ra[P][A_LD], rb[P][B_LD];
+    if constexpr (kAnyA != 0) {
+        // (loads return in order: a wavefront that has its first stage has its share of the digits too)
+        if (kCheck && ck_hi > ck_lo) stage_limbs(ck_lo);
+#pragma unroll
+        for (int st = 0; st < P; ++st) reg_load(min(st, NS - 1), ra[st], rb[st]);
+#pragma unroll
+        for (int st = 0; st < S; ++st) {
+            reg_store(st, st, ra[st % P], rb[st % P]);
+            reg_load(min(st + P, NS - 1), ra[st % P], rb[st % P]);
+        }
+        if (p.K < 16 && (lane & 7) == 0) {
+            // rows shorter than a chunk: the first chunk of the one stage, byte by byte
+            for (int i = 0; i < A_LD; ++i) {
+                const int r = (wave * A_LD + i) * 8 + (lane >> 3);
+                const uint8_t* const src = p.A + (int64_t)min(row0 + r, p.M - 1) * p.lda;
+                uint8_t* const dst = smem + r * BK + ((r >> 1) & 7) * 16;
+                for (int b = 0; b < p.K; ++b) dst[b] = src[b];
+            }
+        }
+        wait_lds();
+        __syncthreads();
+        read_frags(0, 0, 0);
+        read_frags(0, 1, 1);
+        wait_lds();
+        __builtin_amdgcn_sched_barrier(0);
+    } else if constexpr (kAhead2) {
         if (kCheck && ck_hi > ck_lo) stage_limbs(ck_lo);
 #pragma unroll
         for (int st = 0; st < S; ++st)
@@ -591,7 +673,50 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
             run(0, NS, std::false_type{}, ph_c);
         }
     };
-    if (WGM == 1) run_all(std::integral_constant<int, 2>{});
+    // The K loop of the register-staged loads: the k-steps of kAhead2 on a double buffer in LDS, stage s + 2 going to
+    // LDS from its register set once stage s is released, and the loads of stage s + 2 + P going out to that set.  A
+    // load has P stages of time, and the compiler, which sees all of them, waits for the set it needs and no more.
+    // One loop with a uniform branch around the digits: the sets are numbered by the stage, so the loop is unrolled
+    // over them and cannot start at an arbitrary stage.
+    auto run_any = [&]() __attribute__((always_inline)) {
+        for (int s0 = 0; s0 < NS; s0 += P) {
+#pragma unroll
+            for (int u = 0; u < P; ++u) {
+                const int s = s0 + u;
+                if (s >= NS) break;
+                const int buf = u & 1, nxt = buf ^ 1;
+                phase_small(0, 2, buf, 2, std::false_type{}, 0, 0, 0, 0);
+                if (kCheck && s >= ck_lo && s < ck_hi) {
+                    if (s - limb_base == kLimbStages) {
+                        // a further lot of digits (every wave has its last use of the previous lot behind it)
+                        __syncthreads();
+                        stage_limbs(s);
+                        wait_vmem();
+                        __syncthreads();
+                    }
+                    load_limbs(s);
+                    const uint8_t* const sA = smem + buf * A_STAGE;
+#pragma unroll
+                    for (int kbl = 0; kbl < 2; ++kbl)
+#pragma unroll
+                        for (int c = 0; c < CB; ++c)
+                            cacc[c] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+                                *reinterpret_cast<const v4i*>(sA + ck_off[kbl] + c * 16 * BK) ^ (int)0x80808080, limb[kbl], cacc[c], 0, 0, 0);
+                }
+                phase_small(1, 3, buf, 3, std::false_type{}, 0, 0, 0, 0);
+                wait_lds();   // every fragment of this stage is in registers, and what this wave wrote of the next one is in LDS
+                __syncthreads();
+                __builtin_amdgcn_sched_barrier(0);
+                reg_store(s + 2, buf, ra[(u + 2) % P], rb[(u + 2) % P]);
+                reg_load(min(s + 2 + P, NS - 1), ra[(u + 2) % P], rb[(u + 2) % P]);
+                phase_small(2, 0, nxt, 0, std::false_type{}, 0, 0, 0, 0);
+                phase_small(3, 1, nxt, 1, std::false_type{}, 0, 0, 0, 0);
+            }
+        }
+    };
+    if constexpr (kAnyA != 0) {
+        run_any();
+    } else if (WGM == 1) run_all(std::integral_constant<int, 2>{});
     else if ((wm & 1) == 0) run_all(std::integral_constant<int, 0>{});
     else run_all(std::integral_constant<int, 1>{});
     // (the last stage re-issued loads into a dead buffer; the epilogue keeps its scratch outside
@@ -972,7 +1097,7 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
 #endif
 }
 
-template <int BM, int BN, int WGM, int WGN, int kStages, int WGK = 1, bool kSplitK = false>
+template <int BM, int BN, int WGM, int WGN, int kStages, int WGK = 1, bool kSplitK = false, int kAnyA = 0>
 hipError_t launch_cfg(bool check, bool want_c, bool want_q, const GemmParams& p_in, hipStream_t s) {
     GemmParams p = p_in;
     const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
@@ -1013,7 +1138,7 @@ hipError_t launch_cfg(bool check, bool want_c, bool want_q, const GemmParams& p_
     } while (0)
 #define ABFT_LAUNCH_FORM(CK, OUT, BS)                                                                     \
     do {                                                                                                  \
-        auto kern = gemm_tile_async_kernel<BM, BN, WGM, WGN, kStages, CK, OUT, ((BS) || !(CK)), WGK, kSplitK>; \
+        auto kern = gemm_tile_async_kernel<BM, BN, WGM, WGN, kStages, CK, OUT, ((BS) || !(CK)), WGK, kSplitK, kAnyA>; \
         static std::atomic<uint64_t> lds_allowed{0};                                                      \
         const hipError_t e_attr = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed);\
         if (e_attr != hipSuccess) return e_attr;                                                          \

@@ -126,6 +126,30 @@ __global__ void gather_rows_kernel(const uint8_t* __restrict__ A, int64_t lda, c
     for (int k = threadIdx.x; k < (int)lda2; k += blockDim.x) dst[k] = k < K ? src[k] : (uint8_t)0;
 }
 
+// One thread per 16-byte chunk of the copy.  Loads at the byte address they have; the chunk that holds the end of a row is
+// loaded from K - 16 and shifted down, so that nothing past the operand is read.
+typedef int v4i_any __attribute__((ext_vector_type(4), aligned(1)));
+__global__ __launch_bounds__(256) void realign_kernel(const uint8_t* __restrict__ A, int64_t lda, int K, uint32_t chunks_per_row,
+                                                      uint32_t n_chunks, shift_v4i* __restrict__ A2) {
+    const uint32_t q = blockIdx.x * 256u + threadIdx.x;
+    if (q >= n_chunks) return;
+    const uint32_t r = q / chunks_per_row;
+    const int k = (int)(q - r * chunks_per_row) * 16;
+    const uint8_t* const src = A + (int64_t)r * lda;
+    shift_v4i v = shift_v4i{0, 0, 0, 0};
+    if (K >= 16) {
+        v = *reinterpret_cast<const v4i_any*>(src + min(k, K - 16));
+        if (k > K - 16) v = shift_down(v, k - (K - 16));   // 1..15 places, the same in every row
+    } else {
+        uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int b = 0; b < 16; ++b)
+            if (b < K) w[b >> 2] |= (uint32_t)src[b] << (8 * (b & 3));
+        v = shift_v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
+    }
+    A2[q] = v;
+}
+
 __global__ void scatter_rows_kernel(const int32_t* __restrict__ C2, const uint8_t* __restrict__ Cq2,
                                     const int32_t* __restrict__ flags2, const int32_t* __restrict__ idx, int N,
                                     int32_t* __restrict__ C, int64_t ldc, uint8_t* __restrict__ Cq, int64_t ldcq,
@@ -188,6 +212,12 @@ hipError_t launch_list_flagged(const int32_t* flags, int M, int32_t* idx, int32_
 hipError_t launch_gather_rows(const uint8_t* A, int64_t lda, const int32_t* idx, int n, int K, uint8_t* A2,
                               int64_t lda2, hipStream_t s) {
     gather_rows_kernel<<<dim3((unsigned)n), dim3(256), 0, s>>>(A, lda, idx, K, A2, lda2);
+    return hipGetLastError();
+}
+
+hipError_t launch_realign(const uint8_t* A, int64_t lda, int M, int K, uint8_t* A2, int64_t lda2, hipStream_t s) {
+    const uint32_t per_row = (uint32_t)(lda2 / 16), n = per_row * (uint32_t)M;
+    realign_kernel<<<dim3((n + 255) / 256), dim3(256), 0, s>>>(A, lda, K, per_row, n, reinterpret_cast<shift_v4i*>(A2));
     return hipGetLastError();
 }
 

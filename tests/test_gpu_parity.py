@@ -1078,3 +1078,65 @@ def test_k_split_across_workgroups(binding, gpu_util, oracle, M, N, K):
         assert np.array_equal(out["C"], Cw) and np.array_equal(out["flags"], fw) and out["err_count"] == nw
     out = run.gemm(A, ws=ws)
     assert out["err_count"] == 0 and not out["ws"][: base_bytes // 4].any()
+
+
+# (edges of the 16-byte chunk, of the 128-wide stage, of one and of several stages; streaming kernel, 64x64 kernel with loads
+# through registers, copy with padded rows - with a K split behind it too - and each of them where a smaller workspace has
+# no room for the copy)
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(5, 40, 3), (70, 70, 15), (2000, 1500, 13), (7, 100, 17), (33, 8200, 63), (64, 1100, 4001), (130, 70, 31), (65, 129, 127),
+                                   (100, 65, 129), (128, 64, 255), (129, 200, 257), (64, 64, 385), (200, 130, 2687), (70, 200, 5121),
+                                   (1000, 1300, 1249)])
+def test_rows_that_are_no_whole_chunks(binding, gpu_util, oracle, M, N, K):
+    """A whose rows start and end at any byte: clean, with C and B faults, requantized, contiguous and as a view one byte
+    into rows that are longer; nothing past the operand may count."""
+    import torch
+    say(f"rows of {K} bytes: {M}x{N}")
+    A, B = operands(M, N, K, M + N + K)
+    ref = oracle.checked_gemm(A, B)
+    run = gpu_util.GpuRun(binding, B)
+    inj = [(M - 1, N - 1, 1 << 31), (M // 2, N // 2, 1 << 3)]
+    refi = oracle.checked_gemm(A, B, flips_c=inj)
+    flip = (K - 1, N // 2, 6)
+    refb = oracle.checked_gemm(A, B, flips_b=[flip])
+    base_ints = 64 + max(2 * ((M + 63) // 64 * 64), 2 * (32 * 64 + 64))
+
+    class SmallWs:
+        tensor = torch.zeros(base_ints, dtype=torch.int32, device="cuda")
+    buf = torch.full((M * (K + 6) + 1,), 255, dtype=torch.uint8, device="cuda")
+    view = buf[1:].view(M, K + 6)[:, :K]
+    view.copy_(gpu_util.dev(A))
+    for ws in (None, SmallWs):
+        for operand in (A, view):
+            out = run.gemm(operand, ws=ws)
+            assert np.array_equal(out["C"], ref.C) and not out["flags"].any() and out["err_count"] == 0 and not out["ws"].any()
+        out = run.gemm(view, ws=ws, injections=inj, accumulate_from=1)
+        assert np.array_equal(out["C"], refi.C) and np.array_equal(out["flags"], refi.flags) and out["err_count"] == 1 + refi.err_count
+        binding.abft_packed_b_flip_bit(run.Bp, *flip)
+        out = run.gemm(A, ws=ws)
+        assert np.array_equal(out["C"], refb.C) and np.array_equal(out["flags"], refb.flags)
+        assert np.array_equal(run.gemm(view, ws=ws, check=False)["C"], refb.C)
+        binding.abft_packed_b_flip_bit(run.Bp, *flip)
+        mult = wlmod.draw_mult(np.random.default_rng(K), N, "channel")
+        out = run.gemm(A, ws=ws, requant=(128, 128, mult, None), want_c=False)
+        assert np.array_equal(out["Cq"], oracle.requantize(ref.C, ref.colsum, 128, 128, mult, precision="f32"))
+
+
+@pytest.mark.gpu
+def test_one_workspace_for_calls_of_different_sizes(binding, gpu_util, oracle):
+    """A K split's partial tiles and a padded copy of A are left behind in the workspace: the next call, of other sizes and
+    with words of its own where a smaller call's scratch could lie, starts from zeros all the same."""
+    import torch
+    shapes = [(128, 128, 16384), (5000, 96, 64), (300, 520, 1999), (5000, 96, 64), (256, 512, 8192), (16, 700, 320)]
+    runs, need = [], 0
+    for M, N, K in shapes:
+        A, B = operands(M, N, K, M + K)
+        run = gpu_util.GpuRun(binding, B)
+        need = max(need, binding.abft_gemm_workspace_bytes(M, run.Bp) // 4)
+        runs.append((A, oracle.checked_gemm(A, B, flips_c=[(M - 1, 1, 1 << 20)]), run))
+
+    class Shared:
+        tensor = torch.zeros(need, dtype=torch.int32, device="cuda")
+    for A, ref, run in runs:
+        out = run.gemm(A, ws=Shared, injections=[(A.shape[0] - 1, 1, 1 << 20)])
+        assert np.array_equal(out["C"], ref.C) and np.array_equal(out["flags"], ref.flags) and out["err_count"] == 1
