@@ -36,13 +36,7 @@ int hip_fail(hipError_t e, const char* what) {
 
 void free_handle(abft_packed_b* h) {
     if (!h) return;
-    (void)hipFree(h->packed);
-    (void)hipFree(h->limbs);
-    (void)hipFree(h->S_B);
-    (void)hipFree(h->colsum);
-    (void)hipFree(h->total);
-    (void)hipFree(h->limbs127);
-    (void)hipFree(h->S_B127);
+    (void)hipFree(h->packed);   // (one block holds everything)
     delete h;
 }
 
@@ -79,14 +73,21 @@ int abft_pack_b_checksum(const int8_t* B, int64_t ldb, int K, int N, int b_is_tr
     h->KB = ((K + 2 * abft::kUnitK - 1) / (2 * abft::kUnitK)) * 2;
     h->NT = (N + abft::kTileN - 1) / abft::kTileN;
     hipError_t e = hipGetDevice(&h->device);
-    const size_t packed_bytes = (size_t)h->NT * h->KB * abft::kUnitsPerTile * abft::kUnitBytes;
-    if (e == hipSuccess) e = hipMalloc(&h->packed, packed_bytes);
-    if (e == hipSuccess) e = hipMalloc(&h->limbs, (size_t)h->KB * abft::kUnitK * abft::kLimbs);
-    if (e == hipSuccess) e = hipMalloc(&h->S_B, (size_t)h->KB * abft::kUnitK * sizeof(int32_t));
-    if (e == hipSuccess) e = hipMalloc(&h->colsum, (size_t)h->NT * abft::kTileN * sizeof(int32_t));
-    if (e == hipSuccess) e = hipMalloc(&h->total, 64);
-    if (e == hipSuccess) e = hipMalloc(&h->limbs127, (size_t)h->KB * abft::kUnitK * abft::kLimbs);
-    if (e == hipSuccess) e = hipMalloc(&h->S_B127, (size_t)h->KB * abft::kUnitK * sizeof(int32_t));
+    // one block: the units, the digits, then S_B, colsum and total (cleared together before packing), S_B mod 127
+    const auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
+    const size_t units = (size_t)h->NT * h->KB * abft::kUnitsPerTile * abft::kUnitBytes, k_ints = (size_t)h->KB * abft::kUnitK * sizeof(int32_t);
+    const size_t digits = (size_t)h->KB * abft::kUnitK * abft::kLimbs, n_ints = (size_t)h->NT * abft::kTileN * sizeof(int32_t);
+    const size_t o_limbs = up(units), o_limbs127 = o_limbs + up(digits), o_sb = o_limbs127 + up(digits), o_colsum = o_sb + up(k_ints);
+    const size_t o_total = o_colsum + up(n_ints), o_sb127 = o_total + 256;
+    if (e == hipSuccess) e = hipMalloc(&h->packed, o_sb127 + k_ints);
+    if (e == hipSuccess) {
+        h->limbs = h->packed + o_limbs;
+        h->limbs127 = h->packed + o_limbs127;
+        h->S_B = reinterpret_cast<int32_t*>(h->packed + o_sb);
+        h->colsum = reinterpret_cast<int32_t*>(h->packed + o_colsum);
+        h->total = reinterpret_cast<int32_t*>(h->packed + o_total);
+        h->S_B127 = reinterpret_cast<int32_t*>(h->packed + o_sb127);
+    }
     if (e == hipSuccess) e = abft::launch_pack(B, ldb, b_is_transposed ? 1 : 0, h, (hipStream_t)stream);
     if (e != hipSuccess) {
         free_handle(h);

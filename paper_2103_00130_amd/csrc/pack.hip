@@ -6,103 +6,197 @@
 namespace abft {
 namespace {
 
-__device__ inline int8_t load_b(const int8_t* B, int64_t ldb, int transposed, int k, int j, int K, int N) {
-    if (k >= K || j >= N) return 0;
-    return transposed ? B[(int64_t)j * ldb + k] : B[(int64_t)k * ldb + j];
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v4i_any __attribute__((ext_vector_type(4), aligned(1)));
+
+// bytes at .. at + 15 of a row of len bytes, zeros past its end; nothing past the row is read
+__device__ inline v4i load16(const int8_t* row, int at, int len) {
+    if (at + 16 <= len) return *reinterpret_cast<const v4i_any*>(row + at);
+    if (at >= len) return v4i{0, 0, 0, 0};
+    if (len >= 16) return shift_down(*reinterpret_cast<const v4i_any*>(row + len - 16), at - (len - 16));
+    uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int b = 0; b < 16; ++b)
+        if (at + b < len) w[b >> 2] |= (uint32_t)(uint8_t)row[at + b] << (8 * (b & 3));
+    return v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
 }
 
-// One thread per 16-byte chunk of the packed layout (16 consecutive k of one column).
-__global__ void pack_units_kernel(const int8_t* __restrict__ B, int64_t ldb, int transposed, int K, int N,
-                                  int KB, int64_t n_chunks, int8_t* __restrict__ packed) {
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= n_chunks) return;
-    const int c = (int)(q % kUnitN);
-    const int kg = (int)((q / kUnitN) % 4);
-    const int unit = (int)((q / (kUnitN * 4)) % kUnitsPerTile);
-    const int kb = (int)((q / (kUnitN * 4 * kUnitsPerTile)) % KB);
-    const int ntile = (int)(q / ((int64_t)kUnitN * 4 * kUnitsPerTile * KB));
-    const int j = ntile * kTileN + unit * kUnitN + c;
-    const int k0 = kb * kUnitK + kg * 16;
-    uint32_t w[4];
+__device__ inline int32_t sum_bytes(v4i v, int32_t s) {
 #pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        uint32_t v = 0;
+    for (int d = 0; d < 4; ++d) s = __builtin_amdgcn_sdot4(v[d], 0x01010101, s, false);
+    return s;
+}
+
+// One pass over B: the packed units, and what the tile adds to the encoded column S_B (sums over the columns) and to the
+// column sums of Eq. 1 (sums over k).  A workgroup takes one packed n-tile of 256 columns by 128 k, 32 KiB, eight 16-byte
+// chunks per thread in flight at once; both sums are formed from the bytes in hand and leave with one integer atomic per
+// row and per column of the tile (S_B and colsum are cleared beforehand; integer addition makes the order irrelevant).
+// Bound by memory: 9.7 us at 4096 x 4096, 134 us (4.0 TB/s, a large copy reaches 4.8) at 16384 x 16384, as a torch Linear
+// holds it; 13 and 154 us with K along the rows.  Three passes, two of them strided, took 130 and 2900 us.
+constexpr int kPackK = 128;
+template <bool kTransposed>
+__global__ __launch_bounds__(256) void pack_kernel(const int8_t* __restrict__ B, int64_t ldb, int K, int N, int KB,
+                                                   v4i* __restrict__ packed, int32_t* __restrict__ S_B, int32_t* __restrict__ colsum) {
+    __shared__ __align__(16) int8_t s_tile[kTileN * kPackK];
+    __shared__ int32_t s_col[kTileN], s_row[kPackK];
+    const int tid = threadIdx.x;
+    const int ntile = blockIdx.y, k0 = blockIdx.x * kPackK, j0 = ntile * kTileN;
+    v4i* const out = packed + ((int64_t)ntile * KB + blockIdx.x * 2) * (kUnitsPerTile * kUnitBytes / 16);   // 2048 chunks in order
+    s_col[tid] = 0;
+    if (tid < kPackK) s_row[tid] = 0;
+    v4i v[8];
+    if constexpr (kTransposed) {
+        // rows of B are columns of the product: a chunk is sixteen consecutive bytes of one of them.  Chunk i*256 + tid
+        // of the packed order: k-block, unit, k-group, column
+        auto at = [&](int c, int& j, int& k) { j = ((c >> 7) & 7) * 32 + (c & 31); k = (c >> 10) * 64 + ((c >> 5) & 3) * 16; };
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
-            v |= (uint32_t)(uint8_t)load_b(B, ldb, transposed, k0 + 4 * d + b, j, K, N) << (8 * b);
-        w[d] = v;
+        for (int i = 0; i < 8; ++i) {
+            int j, k;
+            at(i * 256 + tid, j, k);
+            v[i] = j0 + j < N ? load16(B + (int64_t)(j0 + j) * ldb, k0 + k, K) : v4i{0, 0, 0, 0};
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            int j, k;
+            at(i * 256 + tid, j, k);
+            out[i * 256 + tid] = v[i];
+            // a column's 128 bytes, its chunks XOR-swizzled so that the writes of 32 columns spread over the banks
+            *reinterpret_cast<v4i*>(s_tile + j * kPackK + ((k >> 4) ^ (j & 7)) * 16) = v[i];
+            atomicAdd(&s_col[j], sum_bytes(v[i], 0));
+        }
+        __syncthreads();
+        // sums over the columns: four k per thread, 32 columns each
+        const int dk = tid & 31, g = tid >> 5;
+        int32_t s[4] = {0, 0, 0, 0};
+#pragma unroll 8
+        for (int j = g * 32; j < g * 32 + 32; ++j) {
+            const int w = *reinterpret_cast<const int*>(s_tile + j * kPackK + ((dk >> 2) ^ (j & 7)) * 16 + (dk & 3) * 4);
+#pragma unroll
+            for (int b = 0; b < 4; ++b) s[b] = __builtin_amdgcn_sdot4(w, 1 << (8 * b), s[b], false);
+        }
+#pragma unroll
+        for (int b = 0; b < 4; ++b) atomicAdd(&s_row[dk * 4 + b], s[b]);
+    } else {
+        // rows of B run along the columns of the product: the tile goes through LDS, and every thread turns blocks of
+        // four columns by sixteen k
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int r = i * 16 + (tid >> 4), c = (tid & 15) * 16;
+            v[i] = k0 + r < K ? load16(B + (int64_t)(k0 + r) * ldb, j0 + c, N) : v4i{0, 0, 0, 0};
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int r = i * 16 + (tid >> 4), c = (tid & 15) * 16;
+            *reinterpret_cast<v4i*>(s_tile + r * kTileN + c) = v[i];
+            // (the sixteen lanes of a DPP row hold one row of the tile)
+            int32_t rs = sum_bytes(v[i], 0);
+            rs += __builtin_amdgcn_update_dpp(0, rs, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
+            rs += __builtin_amdgcn_update_dpp(0, rs, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
+            rs += __builtin_amdgcn_update_dpp(0, rs, 0x141, 0xF, 0xF, true);  // row_half_mirror
+            rs += __builtin_amdgcn_update_dpp(0, rs, 0x140, 0xF, 0xF, true);  // row_mirror
+            if ((tid & 15) == 0) s_row[r] = rs;
+        }
+        __syncthreads();
+        const int cq = tid & 63;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int kg = i * 4 + (tid >> 6);   // k-group of the tile, 0..7
+            v4i q[4];                            // chunks of columns 4*cq .. + 3
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                uint32_t w[4];
+#pragma unroll
+                for (int b = 0; b < 4; ++b) w[b] = *reinterpret_cast<const uint32_t*>(s_tile + (kg * 16 + d * 4 + b) * kTileN + cq * 4);
+                // 4x4 bytes turned: first pairs of rows, then pairs of pairs
+                const uint32_t lo01 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400), hi01 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602);
+                const uint32_t lo23 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400), hi23 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602);
+                q[0][d] = (int)__builtin_amdgcn_perm(lo23, lo01, 0x05040100);
+                q[1][d] = (int)__builtin_amdgcn_perm(lo23, lo01, 0x07060302);
+                q[2][d] = (int)__builtin_amdgcn_perm(hi23, hi01, 0x05040100);
+                q[3][d] = (int)__builtin_amdgcn_perm(hi23, hi01, 0x07060302);
+            }
+            v4i* const o = out + (kg >> 2) * 1024 + (cq >> 3) * 128 + (kg & 3) * 32 + (cq & 7) * 4;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                o[c] = q[c];
+                atomicAdd(&s_col[cq * 4 + c], sum_bytes(q[c], 0));
+            }
+        }
     }
-    reinterpret_cast<uint4*>(packed)[q] = make_uint4(w[0], w[1], w[2], w[3]);
+    __syncthreads();
+    if (j0 + tid < N && s_col[tid] != 0) atomicAdd(&colsum[j0 + tid], s_col[tid]);
+    if (tid < kPackK && k0 + tid < K && s_row[tid] != 0) atomicAdd(&S_B[k0 + tid], s_row[tid]);
 }
 
-// S_B[k] = sum_j B[k][j] (the encoded column, exact int32), one wavefront per k.
-// Also emits the four signed base-256 digits of S_B[k]: d0 in [-128,127] with
-// s = d0 + 256*s1, and so on; the last digit is s3 reduced to 8 bits, which is exact
-// modulo 2^32.  Rows k >= K (padding) get zeros.
-__device__ inline void write_digits(int8_t* limbs, int k, int32_t s) {
+// Digit `digit` of s, the four signed base-256 digits: d0 in [-128,127] with s = d0 + 256*s1, and so on; the last digit
+// is s3 reduced to 8 bits, which is exact modulo 2^32.
+__device__ inline uint32_t digit_of(int32_t s, int digit) {
+    uint32_t out = 0;
 #pragma unroll
     for (int d = 0; d < kLimbs; ++d) {
         const int32_t dig = (int32_t)(((uint32_t)s + 128u) & 255u) - 128;
-        limbs[limb_offset(k, d)] = (int8_t)dig;
+        if (d == digit) out = (uint32_t)dig & 255u;
         s = (int32_t)((uint32_t)s - (uint32_t)dig) >> 8;
     }
+    return out;
+}
+__device__ inline void write_digits(int8_t* limbs, int k, int32_t s) {
+#pragma unroll
+    for (int d = 0; d < kLimbs; ++d) limbs[limb_offset(k, d)] = (int8_t)digit_of(s, d);
+}
+__device__ inline int32_t floor_mod127(int32_t s) {
+    const int32_t r = s % 127;
+    return r < 0 ? r + 127 : r;
 }
 
-// For Algorithm 1 as printed (Section IV-A-2) the same pass also emits rowSum[k] = S_B[k] mod 127
-// in [0,126]: as an int32 array and, in the digit layout, as a single live digit column.
-__global__ void checksum_rows_kernel(const int8_t* __restrict__ B, int64_t ldb, int transposed, int K, int N,
-                                     int Kpad, int32_t* __restrict__ S_B, int8_t* __restrict__ limbs,
-                                     int32_t* __restrict__ S_B127, int8_t* __restrict__ limbs127) {
-    const int k = blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64;
-    const int lane = threadIdx.x % 64;
-    if (k >= Kpad) return;
-    int32_t s = 0;
-    if (k < K)
-        for (int j = lane; j < N; j += 64) s += load_b(B, ldb, transposed, k, j, K, N);
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    if (lane == 0) {
-        S_B[k] = s;
-        write_digits(limbs, k, s);
-        int32_t r = s % 127;
-        if (r < 0) r += 127;
-        S_B127[k] = r;
-        write_digits(limbs127, k, r);
-    }
-}
-
-// colsum[j] = sum_k B[k][j] (rank-1 term e_k^T B_I of Eq. 1); zeros for padded columns.
-// Workgroup (column group of 64, K slice of 256): thread (c, q) sums 64 k-values of column c,
-// the four q are combined in LDS and added to colsum (zeroed beforehand) with one integer
-// atomic per column and slice; integer addition makes the order irrelevant.
-__global__ void colsum_kernel(const int8_t* __restrict__ B, int64_t ldb, int transposed, int K, int N,
-                              int32_t* __restrict__ colsum) {
-    __shared__ int32_t part[4][64];
-    const int c = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int j = blockIdx.x * 64 + c;
-    const int k0 = blockIdx.y * 256 + q * 64;
-    int32_t s = 0;
-    if (j < N)
-        for (int k = k0; k < min(k0 + 64, K); ++k) s += load_b(B, ldb, transposed, k, j, K, N);
-    part[q][c] = s;
+// What follows from the finished encoded column: its digits, and for Algorithm 1 as printed (Section IV-A-2) rowSum[k] =
+// S_B[k] mod 127 in [0,126], as an int32 array and, in the digit layout, as a single live digit column; the sums over k
+// of both (wrap-around) go to total[0] and total[1].  One thread per digit of sixteen k, the digit layout's 16 bytes.
+// Rows k >= K (padding) hold zeros.
+__global__ __launch_bounds__(256) void encode_kernel(const int32_t* __restrict__ S_B, int n_chunks, v4i* __restrict__ limbs,
+                                                     v4i* __restrict__ S_B127, v4i* __restrict__ limbs127, int32_t* __restrict__ total) {
+    __shared__ int32_t part[2];
+    if (threadIdx.x < 2) part[threadIdx.x] = 0;
     __syncthreads();
-    if (q == 0 && j < N) {
-        s = part[0][c] + part[1][c] + part[2][c] + part[3][c];
-        if (s != 0) atomicAdd(&colsum[j], s);
+    const int t = blockIdx.x * 256 + threadIdx.x, digit = t & (kLimbs - 1);
+    int32_t s = 0, r = 0;   // sums of this thread's quarter of the sixteen
+    if (t < n_chunks) {
+        const v4i* const src = reinterpret_cast<const v4i*>(S_B) + (t >> 2) * 4;
+        v4i out, out127 = v4i{0, 0, 0, 0};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const v4i v = src[q];
+            v4i m;
+            uint32_t w = 0, w127 = 0;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                w |= digit_of(v[b], digit) << (8 * b);
+                m[b] = floor_mod127(v[b]);
+                w127 |= (uint32_t)m[b] << (8 * b);
+            }
+            out[q] = (int)w;
+            if (digit == 0) out127[q] = (int)w127;
+            if (digit == q) {
+                S_B127[t] = m;   // (chunk t of the array: group t / 4, its quarter)
+                s = (int32_t)((uint32_t)v[0] + (uint32_t)v[1] + (uint32_t)v[2] + (uint32_t)v[3]);
+                r = m[0] + m[1] + m[2] + m[3];
+            }
+        }
+        limbs[t] = out;
+        limbs127[t] = out127;
     }
-}
-
-// total = sum_k S_B[k] (wrap-around), single workgroup so the result is a plain store.
-__global__ void total_kernel(const int32_t* __restrict__ S_B, int Kpad, int32_t* __restrict__ total) {
-    __shared__ uint32_t part[256];
-    uint32_t s = 0;
-    for (int k = threadIdx.x; k < Kpad; k += blockDim.x) s += (uint32_t)S_B[k];
-    part[threadIdx.x] = s;
+    for (int off = 32; off > 0; off >>= 1) {
+        s = (int32_t)((uint32_t)s + (uint32_t)__shfl_xor(s, off));
+        r += __shfl_xor(r, off);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicAdd(&part[0], s);
+        atomicAdd(&part[1], r);
+    }
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *total = (int32_t)part[0];
+    if (threadIdx.x < 2) atomicAdd(&total[threadIdx.x], part[threadIdx.x]);
 }
 
 __global__ void flip_bit_kernel(int8_t* packed, int64_t off, int bit) {
@@ -134,17 +228,18 @@ __global__ void fill_zero_kernel(int32_t* p, size_t n) {
 }  // namespace
 
 hipError_t launch_pack(const int8_t* B, int64_t ldb, int transposed, abft_packed_b* h, hipStream_t s) {
-    const int Kpad = h->KB * kUnitK, Npad = h->NT * kTileN;
-    const int64_t n_chunks = (int64_t)h->NT * h->KB * kUnitsPerTile * 4 * kUnitN;
-    pack_units_kernel<<<dim3((unsigned)((n_chunks + 255) / 256)), dim3(256), 0, s>>>(
-        B, ldb, transposed, h->K, h->N, h->KB, n_chunks, h->packed);
-    checksum_rows_kernel<<<dim3((Kpad + 3) / 4), dim3(256), 0, s>>>(B, ldb, transposed, h->K, h->N, Kpad, h->S_B,
-                                                                    h->limbs, h->S_B127, h->limbs127);
-    fill_zero_kernel<<<dim3((unsigned)((Npad + 255) / 256)), dim3(256), 0, s>>>(h->colsum, (size_t)Npad);
-    colsum_kernel<<<dim3((unsigned)(Npad / 64), (unsigned)((h->K + 255) / 256)), dim3(256), 0, s>>>(B, ldb, transposed, h->K, h->N,
-                                                                                                  h->colsum);
-    total_kernel<<<dim3(1), dim3(256), 0, s>>>(h->S_B, Kpad, h->total);
-    total_kernel<<<dim3(1), dim3(256), 0, s>>>(h->S_B127, Kpad, h->total + 1);
+    // S_B, colsum and total lie one after the other
+    const size_t n_zero = (size_t)(h->total - h->S_B) + 16;
+    hipError_t e = launch_fill_zero(h->S_B, n_zero, s);
+    if (e != hipSuccess) return e;
+    const dim3 grid((unsigned)(h->KB / 2), (unsigned)h->NT);
+    v4i* const out = reinterpret_cast<v4i*>(h->packed);
+    if (transposed) pack_kernel<true><<<grid, dim3(256), 0, s>>>(B, ldb, h->K, h->N, h->KB, out, h->S_B, h->colsum);
+    else pack_kernel<false><<<grid, dim3(256), 0, s>>>(B, ldb, h->K, h->N, h->KB, out, h->S_B, h->colsum);
+    const int n_chunks = h->KB * kUnitK / 16 * kLimbs;
+    encode_kernel<<<dim3((unsigned)((n_chunks + 255) / 256)), dim3(256), 0, s>>>(h->S_B, n_chunks, reinterpret_cast<v4i*>(h->limbs),
+                                                                                 reinterpret_cast<v4i*>(h->S_B127),
+                                                                                 reinterpret_cast<v4i*>(h->limbs127), h->total);
     return hipGetLastError();
 }
 

@@ -1140,3 +1140,32 @@ def test_one_workspace_for_calls_of_different_sizes(binding, gpu_util, oracle):
     for A, ref, run in runs:
         out = run.gemm(A, ws=Shared, injections=[(A.shape[0] - 1, 1, 1 << 20)])
         assert np.array_equal(out["C"], ref.C) and np.array_equal(out["flags"], ref.flags) and out["err_count"] == 1
+
+
+# (edges of the 16-byte chunk, of the 128 x 256 tile that a workgroup packs, rows shorter than a chunk)
+@pytest.mark.gpu
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("K,N", [(3, 300), (300, 3), (15, 17), (17, 255), (127, 256), (128, 257), (129, 15), (385, 530), (1000, 16)])
+def test_pack_of_strided_weights(binding, gpu_util, oracle, K, N, transposed):
+    """A weight that lies one byte into longer rows, either way round: its sums, its residues modulo 127, and the product
+    with it (every packed byte, the digits and their total take part in that)."""
+    import torch
+    A, B = operands(70, N, K, K * N)
+    src = B.T if transposed else B
+    rows, cols = src.shape
+    buf = torch.full((rows * (cols + 5) + 1,), 77, dtype=torch.int8, device="cuda")
+    view = buf[1:].view(rows, cols + 5)[:, :cols]
+    view.copy_(gpu_util.dev(src))
+    run = gpu_util.GpuRun(binding, B)
+    run.Bp = binding.abft_pack_b_checksum(view, b_is_transposed=transposed)
+    S_B = oracle.b_checksum(B)
+    assert np.array_equal(run.checksum(), S_B) and np.array_equal(run.colsum(), oracle.b_colsum(B))
+    r127 = torch.empty(K, dtype=torch.int32, device="cuda")
+    binding.abft_packed_b_get_checksum_mod127(run.Bp, r127)
+    assert np.array_equal(r127.cpu().numpy(), S_B % 127)
+    ref = oracle.checked_gemm(A, B)
+    out = run.gemm(A)
+    assert np.array_equal(out["C"], ref.C) and not out["flags"].any()
+    if K % 16 == 0:
+        out = run.gemm(A, mod127=True)
+        assert np.array_equal(out["C"], ref.C) and not out["flags"].any()
