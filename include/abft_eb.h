@@ -49,9 +49,9 @@ extern "C" {
 /* flags of abft_eb_u8_checked */
 #define ABFT_EB_CHECK 0u          /* default: Algorithm 2 for every lookup */
 #define ABFT_EB_NOCHECK 1u        /* same kernels with RSum, CSum and the comparison compiled out */
-#define ABFT_EB_VARIANT_MASK 0xF00u /* 0 = choose by batch size */
-#define ABFT_EB_VARIANT_BATCH 0x100u  /* a few lanes per lookup, rows straight into registers: large batches */
-#define ABFT_EB_VARIANT_GROUP 0x200u  /* one workgroup per lookup, rows staged in LDS: small batches */
+#define ABFT_EB_VARIANT_MASK 0xF00u /* 0 = choose by the number of lookups and of rows per lookup */
+#define ABFT_EB_VARIANT_BATCH 0x100u  /* a few lanes per lookup, rows straight into registers: very many short lookups */
+#define ABFT_EB_VARIANT_GROUP 0x200u  /* four wavefronts per lookup, rows staged in LDS: few lookups */
 
 /* flags of abft_eb_pack_rowsum */
 #define ABFT_EB_PACK_COMPACT 0u       /* default: records of d + 16 bytes back to back */

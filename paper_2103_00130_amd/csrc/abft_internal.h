@@ -264,12 +264,6 @@ hipError_t launch_mfma_peak_probe(unsigned long long* out, int iters, hipStream_
 hipError_t launch_row_checksum(const uint8_t* A, int64_t lda, int M, int K, const int32_t* S_B,
                                int32_t* row_chk, hipStream_t s);
 
-// EmbeddingBag: lookups from which the batch kernel is chosen over the group kernel, by the number of
-// 16-byte pieces of a row's codes
-constexpr int64_t eb_batch_min_lookups(int pieces) {
-    return pieces <= 1 ? 49152 : pieces == 2 ? 32768 : pieces == 4 ? 98304 : pieces == 8 ? 262144 : pieces == 16 ? 7168 : 16384;
-}
-
 // Lets `kern` use `bytes` of dynamic LDS on the current device: the attribute belongs to the device, so it
 // is set once per device and kernel (`done`: one bit per device ordinal, shared by the threads of the host)
 inline hipError_t allow_dynamic_lds(const void* kern, size_t bytes, std::atomic<uint64_t>& done) {

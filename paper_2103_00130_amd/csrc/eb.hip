@@ -9,12 +9,11 @@
 //  * The table is kept as fused records [codes][scale][bias][C_T][unused]: the row sum that
 //    Eq. 4 needs arrives in the same memory transaction as the scale and bias the lookup needs
 //    anyway, so the check adds no memory traffic at all.
-//  * Batch kernel (large batches): one lane per 16 code bytes of a row.  Every lane owns the columns
+//  * Batch kernel (very many lookups of a few rows): one lane per 16 code bytes of a row.  Every lane owns the columns
 //    of its bytes and reads them per pooled row straight into registers, eight rows in flight per
 //    lane; the chip is filled by lookups, and the lanes of a lookup walk its index list in order.
-//  * Group kernel (small batches): one workgroup per lookup.  All threads fetch different 16-byte
-//    pieces of the lookup's records into LDS (1024 or 2048 pieces in flight per workgroup), then
-//    the threads, now owning columns, walk the staged rows in index order.
+//  * Group kernel: one, two or four wavefronts per lookup.  Their threads fetch different 16-byte
+//    pieces of the lookup's records into LDS, then, owning columns, walk the staged rows in index order.
 //  * Every load is unconditional (clamped position, row 0 in place of a bad index): a load under
 //    `if (valid)` is followed by a wait, which would put the loads of a lookup one after the other.
 //  Both accumulate every output column in the same order (index order, one fused multiply-add
@@ -24,6 +23,7 @@
 #include <cmath>
 #include <cstring>
 #include <new>
+#include <type_traits>
 
 #include "../../include/abft_eb.h"
 #include "abft_internal.h"
@@ -267,32 +267,38 @@ __global__ __launch_bounds__(256) void eb_batch_kernel(const EbParams p) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Group kernel: one workgroup (four wavefronts) per lookup, rows staged through LDS.
-//  1. fetch: every thread loads different 16-byte pieces of the chunk's records (1024 pieces in
-//     flight per workgroup) and they are laid out in LDS record after record;
-//  2. per-row scalars, rows in parallel: the weighted scale and bias of every staged row, and
-//     the two exact binary64 products of its Eq. 4 term;
-//  3. pooling, rows in index order: threads own columns and do one LDS read, one convert and one
-//     fused multiply-add per row; meanwhile the last two wavefronts form the sums that do not
-//     depend on the column (the biases, in index order like the columns; the terms of CSum, lanes
-//     in parallel).
-template <int G, int BITS, bool kCheck, bool kWeighted>
-__global__ __launch_bounds__(256) void eb_group_kernel(const EbParams p) {
+// Group kernel: W wavefronts per lookup (a workgroup), rows staged through LDS.
+//  1. fetch: every thread loads different 16-byte pieces of the chunk's records (as many instructions as the chunk
+//     needs) and they are laid out in LDS record after record.  The thread that holds a record's tail piece forms the
+//     row's scalars on the way: the weighted scale and bias, each to an array of its own, and the row's term of Eq. 4,
+//     which is added up in that thread;
+//  2. pooling, rows in index order: threads own columns; eight rows at a time, the next eight on their way from LDS while
+//     the current ones are pooled, scales read four to an instruction.  The biases are added up in index order by a
+//     wavefront of its own (W = 1: by every lane beside its columns).
+//  The indices of the next chunk are on their way while a chunk is pooled.
+//  Many lookups of the same total: bound by memory, whole 128-byte lines for every record (16384 lookups of 100 rows of 80
+//  bytes: 59.0 us with four wavefronts each as it was before, 56.6 with two now; 272 bytes: 146 and 122).  Short lookups: by
+//  what a lookup costs beside its rows (9000 of 27 rows: 18.4 -> 12.3 us, 16384 of 10: 32 -> 10.8, 3000 of 5: 6.8 -> 3.5).
+template <int G, int BITS, int W, bool kCheck, bool kWeighted>
+__global__ __launch_bounds__(W * 64) void eb_group_kernel(const EbParams p) {
+    constexpr int NT = W * 64;
     constexpr int CB = 16 * G;                 // code bytes per row
     constexpr int D = CB * 8 / BITS, REC = CB + 16;   // REC: a record as staged in LDS (no padding there)
     constexpr int P = G + 1;                   // 16-byte pieces per record
-    constexpr int NL = G >= 16 ? 8 : 4;        // load instructions per thread and chunk
-    constexpr int PIECES = NL * 256;
-    constexpr int ROWS = PIECES / P;           // whole records per chunk
-    constexpr int NW = (ROWS + 255) / 256;     // rows per thread in the per-row pass
-    constexpr int BPT = CB > 256 ? CB / 256 : 1;  // code bytes per thread in the pooling phase
-    constexpr int CPL = BPT * 8 / BITS;           // columns per thread
-    // (the per-row scalars replace the tail piece of their staged record: no LDS beyond the records,
-    // so that eight workgroups - all the wavefront slots - fit a compute unit at every row width)
+    constexpr int NL = W >= 2 ? (G >= 16 ? 8 : 4) : (G >= 32 ? 16 : (G >= 4 ? 8 : 4));   // load instructions per thread and chunk
+    constexpr int PIECES = NL * NT;
+    constexpr int ROWS = PIECES / P / 8 * 8;   // whole records per chunk, in eights
+    static_assert(ROWS >= 8, "a chunk holds eight rows");
+    // with four wavefronts, which run few lookups at a time, the rows of the next chunk come in while a chunk is pooled; with
+    // one or two the registers that takes are worth more as further lookups under way
+    constexpr bool kPrefetch = W == 4;
+    constexpr int BPT = CB > NT ? CB / NT : 1; // code bytes per thread in the pooling phase
+    constexpr int CPL = BPT * 8 / BITS;        // columns per thread
     __shared__ v4u s_rec[PIECES];
-    __shared__ double s_rs[4], s_cs;
+    __shared__ __align__(16) float s_scale[ROWS], s_bias[ROWS];
+    __shared__ double s_rs[W], s_cs[W];
     __shared__ float s_beta;
-    __shared__ int s_flag;
+    __shared__ int s_bad[W];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t bag = blockIdx.x;
@@ -302,144 +308,258 @@ __global__ __launch_bounds__(256) void eb_group_kernel(const EbParams p) {
     float acc[CPL];
 #pragma unroll
     for (int k = 0; k < CPL; ++k) acc[k] = 0.0f;
-    float beta_sum = 0.0f;
-    double cs = 0.0;
+    float beta = 0.0f;
+    double cs = 0.0;   // this thread's terms of Eq. 4
+    bool bad_any = false;
     const bool col_thread = tid * BPT < CB;
-    // the chains that do not depend on the column run on wavefronts that own few or no columns
-    const bool beta_wave = wave == 2, cs_wave = wave == 3;
+    // the chain of the biases runs on a wavefront that owns few or no columns
+    const bool beta_wave = W == 1 || wave == W - 1;
     const uint8_t* const s_bytes = reinterpret_cast<const uint8_t*>(s_rec);
-    // staged tail of row r after the per-row pass: [weighted scale f32][weighted bias f32][Eq. 4 term f64]
-    auto row_scale = [&](int r) __attribute__((always_inline)) { return *reinterpret_cast<const float*>(s_bytes + r * REC + CB); };
-    auto row_bias = [&](int r) __attribute__((always_inline)) { return *reinterpret_cast<const float*>(s_bytes + r * REC + CB + 4); };
-    auto row_term = [&](int r) __attribute__((always_inline)) { return *reinterpret_cast<const double*>(s_bytes + r * REC + CB + 8); };
-    if (tid == 0) s_flag = 0;
+    auto meet = []() __attribute__((always_inline)) {
+        if constexpr (W > 1) {
+            __syncthreads();
+        } else {
+            // one wavefront: its LDS operations execute in order
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+    };
 
-    for (int64_t pos = beg; pos < end; pos += ROWS) {
-        const int n = (int)(end - pos < ROWS ? end - pos : ROWS);
-        // fetch: piece g = l*256 + tid of the chunk is piece g % P of row g / P.  All loads are
-        // unconditional (clamped row, row 0 in place of a bad index) so that they all go out together.
+    struct Indices {
         int64_t idx[NL];
-#pragma unroll
-        for (int l = 0; l < NL; ++l) {
-            const int r = (l * 256 + tid) / P;
-            idx[l] = p.indices[pos + (r < n ? r : n - 1)];
-        }
-        float wreg[NW];
-        if (kWeighted)
-#pragma unroll
-            for (int k = 0; k < NW; ++k) wreg[k] = p.weights[pos + (tid + 256 * k < n ? tid + 256 * k : n - 1)];
+        float w[NL];
+    };
+    struct Rows {
         v4u v[NL];
+        float w[NL];
+        bool ok[NL];
+    };
+    // Piece g = l*NT + tid of a chunk is piece g % P of row g / P.  All loads are unconditional (clamped row, row 0 in
+    // place of a bad index) so that they all go out together.
+    auto load_indices = [&](Indices& x, int64_t pos, int n, auto l_c) __attribute__((always_inline)) {
 #pragma unroll
-        for (int l = 0; l < NL; ++l) {
-            const int g = l * 256 + tid, r = g / P, pc = g - r * P;
-            const bool ok = (uint64_t)idx[l] < (uint64_t)p.rows;
-            v[l] = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(p.tab + (ok ? idx[l] : 0) * p.stride + pc * 16));
-            // the last word of a record's tail is unused in memory; staged, it marks a row that is not pooled
-            if (pc == G) v[l][3] = ok ? 0u : 1u;
+        for (int l = 0; l < decltype(l_c)::value; ++l) {
+            const int r = (l * NT + tid) / P;
+            const int64_t at = pos + (r < n ? r : n - 1);
+            x.idx[l] = p.indices[at];
+            if (kWeighted) x.w[l] = p.weights[at];
         }
-        __syncthreads();  // the previous chunk has been pooled
+    };
+    auto load_rows = [&](Rows& x, const Indices& ix, auto l_c) __attribute__((always_inline)) {
 #pragma unroll
-        for (int l = 0; l < NL; ++l) s_rec[l * 256 + tid] = v[l];
-        __syncthreads();
-        // per-row scalars.  A row that is not pooled gets scale, bias and row sum 0, which leaves every
-        // accumulator as it is, bit for bit.
-        int bad_any = 0;
+        for (int l = 0; l < decltype(l_c)::value; ++l) {
+            const int g = l * NT + tid, pc = g % P;
+            x.ok[l] = (uint64_t)ix.idx[l] < (uint64_t)p.rows;
+            if (kWeighted) x.w[l] = ix.w[l];
+            x.v[l] = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(p.tab + (x.ok[l] ? ix.idx[l] : 0) * p.stride + pc * 16));
+        }
+    };
+    auto stage = [&](const Rows& x, int n, auto l_c) __attribute__((always_inline)) {
 #pragma unroll
-        for (int k = 0; k < NW; ++k) {
-            const int r = tid + 256 * k;
-            if (r < n) {
-                const v4u tl = s_rec[r * P + G];
-                const bool bad = tl[3] != 0u;
-                bad_any |= bad ? ABFT_EB_BAD_INDEX : 0;
-                float a = as_f32(tl[0]), c = as_f32(tl[1]);
+        for (int l = 0; l < decltype(l_c)::value; ++l) {
+            const int g = l * NT + tid, r = g / P;
+            s_rec[g] = x.v[l];
+            if (g - r * P == G && r < ROWS) {
+                // A row that is not pooled - a bad index, the rows that fill up the last eight - gets scale, bias and row
+                // sum 0, which leaves every accumulator as it is, bit for bit.
+                const bool use = x.ok[l] && r < n;
+                if (!x.ok[l] && r < n) bad_any = true;
+                float a = as_f32(x.v[l][0]), c = as_f32(x.v[l][1]);
                 if (kWeighted) {
-                    a = wreg[k] * a;
-                    c = wreg[k] * c;
+                    a = x.w[l] * a;
+                    c = x.w[l] * c;
                 }
-                a = bad ? 0.0f : a;
-                c = bad ? 0.0f : c;
-                v4u out;
-                out[0] = __builtin_bit_cast(unsigned int, a);
-                out[1] = __builtin_bit_cast(unsigned int, c);
-                out[2] = out[3] = 0u;
-                if (kCheck) {
-                    // Eq. 4, the term of one pooled row: scale * C_T + d * bias, rounded once (both products
-                    // are exact in binary64)
-                    const double t = fma((double)a, (double)(bad ? 0 : (int32_t)tl[2]), (double)D * (double)c);
-                    const unsigned long long tb = __builtin_bit_cast(unsigned long long, t);
-                    out[2] = (unsigned int)tb;
-                    out[3] = (unsigned int)(tb >> 32);
-                }
-                s_rec[r * P + G] = out;
+                a = use ? a : 0.0f;
+                c = use ? c : 0.0f;
+                s_scale[r] = a;
+                s_bias[r] = c;
+                // Eq. 4, the term of one pooled row: scale * C_T + d * bias, rounded once (both products are exact in
+                // binary64).  The terms are exact to their one rounding; only the order of their sum differs from
+                // index order, by at most n * 2^-53 * sum |term|, eleven decimal orders below the bound of the comparison.
+                if (kCheck) cs = cs + fma((double)a, (double)(use ? (int32_t)x.v[l][2] : 0), (double)D * (double)c);
             }
         }
-        if (bad_any) atomicOr(&s_flag, bad_any);
-        __syncthreads();
-        // pooling, rows in index order
-        if (col_thread) {
-#pragma unroll 8
-            for (int r = 0; r < n; ++r) {
-                const float a = row_scale(r);
-                const uint8_t* codes = s_bytes + r * REC + tid * BPT;
-                unsigned int cw = BPT == 1 ? (unsigned int)*codes : (unsigned int)*reinterpret_cast<const uint16_t*>(codes);
+    };
+    struct Eight {
+        v4f a[2], c[2];
+        unsigned int code[8][BPT > 4 ? 2 : 1];
+    };
+    // (threads without columns, in narrow tables, repeat the last one's)
+    const int at = (col_thread ? tid : CB / BPT - 1) * BPT;
+    auto read_eight = [&](Eight& x, int r0, auto cols_c, auto beta_c) __attribute__((always_inline)) {
+        constexpr bool COLS = decltype(cols_c)::value, BETA = decltype(beta_c)::value;
 #pragma unroll
-                for (int k = 0; k < CPL; ++k) acc[k] = __builtin_fmaf(a, (float)((cw >> (BITS * k)) & ((1u << BITS) - 1u)), acc[k]);
+        for (int h = 0; h < 2; ++h) {
+            if (COLS) x.a[h] = *reinterpret_cast<const v4f*>(s_scale + r0 + 4 * h);
+            if (BETA) x.c[h] = *reinterpret_cast<const v4f*>(s_bias + r0 + 4 * h);
+        }
+        if (COLS)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const uint8_t* const codes = s_bytes + (r0 + i) * REC + at;
+                if constexpr (BPT == 1) x.code[i][0] = *codes;
+                else if constexpr (BPT == 2) x.code[i][0] = *reinterpret_cast<const uint16_t*>(codes);
+                else {
+#pragma unroll
+                    for (int h = 0; h < BPT / 4; ++h) x.code[i][h] = reinterpret_cast<const unsigned int*>(codes)[h];
+                }
             }
+    };
+    auto pool_eight = [&](const Eight& x, auto cols_c, auto beta_c) __attribute__((always_inline)) {
+        constexpr bool COLS = decltype(cols_c)::value, BETA = decltype(beta_c)::value;
+        constexpr int CPW = 32 / BITS;   // columns per word of codes
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (COLS)
+#pragma unroll
+                for (int k = 0; k < CPL; ++k)
+                    acc[k] = __builtin_fmaf(x.a[i >> 2][i & 3], (float)((x.code[i][k / CPW] >> (BITS * (k % CPW))) & ((1u << BITS) - 1u)), acc[k]);
+            if (BETA) beta = beta + x.c[i >> 2][i & 3];
         }
-        if (beta_wave) {
-#pragma unroll 8
-            for (int r = 0; r < n; ++r) beta_sum = beta_sum + row_bias(r);
+    };
+    auto pool_as = [&](int n, auto cols_c, auto beta_c) __attribute__((always_inline)) {
+        Eight x, y;
+        read_eight(x, 0, cols_c, beta_c);
+        for (int r = 0; r < n; r += 16) {
+            if (r + 8 < n) read_eight(y, r + 8, cols_c, beta_c);
+            pool_eight(x, cols_c, beta_c);
+            if (r + 8 >= n) break;
+            if (r + 16 < n) read_eight(x, r + 16, cols_c, beta_c);
+            pool_eight(y, cols_c, beta_c);
         }
-        if (kCheck && cs_wave) {
-            // CSum: the lanes of this wavefront take every 64th row each and are added up at the end.  (The
-            // terms are exact to their one rounding; only the order of their sum differs from index order,
-            // by at most n * 2^-53 * sum |term|, eleven decimal orders below the bound of the comparison.
-            // Walking them in index order is a chain of dependent binary64 additions that takes longer
-            // than the pooling it runs beside.)
-            for (int r = lane; r < n; r += 64) cs = cs + row_term(r);
+    };
+    auto pool = [&](int n) __attribute__((always_inline)) {
+        const bool cols = W == 1 || wave * 64 * BPT < CB;
+        if (W == 1) pool_as(n, std::true_type{}, std::true_type{});
+        else if (cols && beta_wave) pool_as(n, std::true_type{}, std::true_type{});
+        else if (cols) pool_as(n, std::true_type{}, std::false_type{});
+        else if (beta_wave) pool_as(n, std::false_type{}, std::true_type{});
+    };
+    auto short_lookup = [&](int n, auto l_c) __attribute__((always_inline)) {
+        Indices ix;
+        Rows x;
+        load_indices(ix, beg, n, l_c);
+        load_rows(x, ix, l_c);
+        stage(x, n, l_c);
+        meet();
+        pool(n);
+    };
+    using full_c = std::integral_constant<int, NL>;
+    const int64_t total = end - beg;
+    if (total <= ROWS) {
+        // the whole lookup in one chunk, with as many load instructions as it needs
+        const int n = (int)total, need = ((n + 7) / 8 * 8 * P + NT - 1) / NT;
+        if (n == 0) {
+        } else if (need <= 1) short_lookup(n, std::integral_constant<int, 1>{});
+        else if (need <= 2) short_lookup(n, std::integral_constant<int, 2>{});
+        else if (NL > 4 && need <= 4) short_lookup(n, std::integral_constant<int, 4>{});
+        else short_lookup(n, full_c{});
+    } else {
+        auto rows_at = [&](int64_t pos) { return (int)(end - pos < ROWS ? end - pos : ROWS); };
+        Indices ix;
+        Rows x;
+        load_indices(ix, beg, ROWS, full_c{});
+        load_rows(x, ix, full_c{});
+        load_indices(ix, beg + ROWS, rows_at(beg + ROWS), full_c{});
+        for (int64_t pos = beg;;) {
+            // here the rows of this chunk and the indices of the next are in flight
+            const int n = rows_at(pos);
+            stage(x, n, full_c{});
+            meet();
+            if (kPrefetch && pos + ROWS < end) load_rows(x, ix, full_c{});
+            if (kPrefetch && pos + 2 * ROWS < end) load_indices(ix, pos + 2 * ROWS, rows_at(pos + 2 * ROWS), full_c{});
+            pool(n);
+            pos += ROWS;
+            if (pos >= end) break;
+            if (!kPrefetch) {
+                load_rows(x, ix, full_c{});
+                if (pos + ROWS < end) load_indices(ix, pos + ROWS, rows_at(pos + ROWS), full_c{});
+            }
+            meet();   // this chunk has been pooled
         }
     }
 
-    if (beta_wave && lane == 0) s_beta = beta_sum;
-    if (kCheck && cs_wave) {
-        cs = wave_sum(cs);
-        if (lane == 0) s_cs = cs;
+    if (kCheck) cs = wave_sum(cs);
+    const bool bad_wave = __ballot(bad_any) != 0ull;
+    if constexpr (W > 1) {
+        if (beta_wave && lane == 0) s_beta = beta;
+        if (lane == 0) {
+            if (kCheck) s_cs[wave] = cs;
+            s_bad[wave] = bad_wave;
+        }
+        __syncthreads();
+        beta = s_beta;
     }
-    __syncthreads();
-    const float beta = s_beta;
     double rs = 0.0;
     if (col_thread) {
+        float* const out = p.R + bag * p.ldr + tid * CPL;
 #pragma unroll
         for (int k = 0; k < CPL; ++k) {
             const float v = acc[k] + beta;
-            p.R[bag * p.ldr + tid * CPL + k] = v;
+            out[k] = v;
             if (kCheck) rs += (double)v;
         }
     }
+    int flag = bad_wave ? ABFT_EB_BAD_INDEX : 0;
     if (kCheck) {
         rs = wave_sum(rs);
-        if (lane == 0) s_rs[wave] = rs;
-        __syncthreads();
+        if constexpr (W > 1) {
+            if (lane == 0) s_rs[wave] = rs;
+            __syncthreads();
+        }
         if (tid == 0) {
-            const double total = (s_rs[0] + s_rs[1]) + (s_rs[2] + s_rs[3]);
-            p.flags[bag] = s_flag | compare_sums(total, s_cs, p.bound);
-            if (p.rsum) p.rsum[bag] = total;
-            if (p.csum) p.csum[bag] = s_cs;
+            if constexpr (W > 1) {
+                rs = s_rs[0];
+                cs = s_cs[0];
+#pragma unroll
+                for (int w = 1; w < W; ++w) {
+                    rs += s_rs[w];
+                    cs += s_cs[w];
+                    if (s_bad[w]) flag = ABFT_EB_BAD_INDEX;
+                }
+            }
+            p.flags[bag] = flag | compare_sums(rs, cs, p.bound);
+            if (p.rsum) p.rsum[bag] = rs;
+            if (p.csum) p.csum[bag] = cs;
         }
     } else if (p.flags && tid == 0) {
-        p.flags[bag] = s_flag;
+        if constexpr (W > 1)
+#pragma unroll
+            for (int w = 1; w < W; ++w)
+                if (s_bad[w]) flag = ABFT_EB_BAD_INDEX;
+        p.flags[bag] = flag;
     }
 }
 
+// What runs a call: the batch kernel, or the group kernel with 1, 2 or 4 wavefronts per lookup.
+enum EbKernel { kEbBatch = 0, kEbGroup1 = 1, kEbGroup2 = 2, kEbGroup4 = 4 };
+
+// The choice by the number of lookups and of rows per lookup on average (us, all rows 80 bytes unless said otherwise:
+// batch / 4 / 2 / 1 wavefronts).  Few lookups: the latency of one counts and four wavefronts fetch more of it at once (300 of
+// 30 rows 10.7 / 3.5 / 3.5 / 3.6; 600 of 60: 24.4 / 4.8 / 5.0 / 5.2; 10 of 100: 25.7 / 4.6 / 5.1 / 5.9), except for narrow rows
+// of which there are hardly enough for one (300 of 5: 3.8 / 3.1 / 2.9 / 2.7).  Many lookups: what counts is how many are
+// under way, and one wavefront each, without barriers and idle threads, takes the short ones (4000 of 16: 10.5 / 10.0 / 6.3 /
+// 5.1; 9000 of 27: 18.4 / 22.0 / 12.4 / 12.3), two the long ones (3000 of 60, ragged: 78 / 14.2 / 12.3 / 13.2; records of 272
+// bytes, 1500 of 100: 40 / 19.9 / 16.4 / 18.3; 16384 of 100: 66 / 70 / 56.6 / 56.7).  Very many lookups of a handful of rows: a few
+// lanes per lookup (8000 of 4: 4.7 / 12.8 / 7.2 / 5.9; 16384 of 10: 10.8 / 32 / 15.8 / 14.1; 80000 of 20: 74 / 176 / 82 / 78).
+EbKernel pick_kernel(int64_t n_bags, int64_t n_indices, int pieces) {
+    const int64_t avg = n_indices / n_bags;
+    if (avg <= 5 ? n_bags >= 6000 : (avg <= 10 && n_bags >= 16000)) return kEbBatch;
+    if (n_bags < 1000) return avg <= 16 && pieces <= 4 ? kEbGroup1 : kEbGroup4;
+    return avg <= 45 && pieces <= 16 ? kEbGroup1 : kEbGroup2;
+}
+
 template <int G, int BITS>
-hipError_t launch_g(bool group, bool check, bool weighted, const EbParams& p, hipStream_t s) {
+hipError_t launch_g(EbKernel kernel, bool check, bool weighted, const EbParams& p, hipStream_t s) {
     // one set of rows per lane only where the rows are wide and the launch has at least four wavefronts
     // per SIMD (measured at 16384 and 65536 lookups of 256 columns: 2 and 4 % faster than two sets;
     // everywhere else two sets are faster, by up to 30 % at 4096 lookups)
     const bool two_sets = G < 16 || p.n_bags * G < (int64_t)4096 * 64;
 #define ABFT_EB_LAUNCH(CK, WT)                                                                                     \
     do {                                                                                                           \
-        if (group) eb_group_kernel<G, BITS, CK, WT><<<dim3((unsigned)p.n_bags), dim3(256), 0, s>>>(p);             \
+        if (kernel == kEbGroup1) eb_group_kernel<G, BITS, 1, CK, WT><<<dim3((unsigned)p.n_bags), dim3(64), 0, s>>>(p);      \
+        else if (kernel == kEbGroup2) eb_group_kernel<G, BITS, 2, CK, WT><<<dim3((unsigned)p.n_bags), dim3(128), 0, s>>>(p); \
+        else if (kernel == kEbGroup4) eb_group_kernel<G, BITS, 4, CK, WT><<<dim3((unsigned)p.n_bags), dim3(256), 0, s>>>(p); \
         else if (two_sets) eb_batch_kernel<G, BITS, CK, WT, true><<<dim3((unsigned)((p.n_bags * G + 255) / 256)), dim3(256), 0, s>>>(p); \
         else eb_batch_kernel<G, BITS, CK, WT, (G < 16)><<<dim3((unsigned)((p.n_bags * G + 255) / 256)), dim3(256), 0, s>>>(p); \
         return hipGetLastError();                                                                                  \
@@ -452,21 +572,21 @@ hipError_t launch_g(bool group, bool check, bool weighted, const EbParams& p, hi
 }
 
 template <int BITS>
-hipError_t launch_bits(int code_bytes, bool group, bool check, bool weighted, const EbParams& p, hipStream_t s) {
+hipError_t launch_bits(int code_bytes, EbKernel kernel, bool check, bool weighted, const EbParams& p, hipStream_t s) {
     switch (code_bytes) {
-        case 16: return launch_g<1, BITS>(group, check, weighted, p, s);
-        case 32: return launch_g<2, BITS>(group, check, weighted, p, s);
-        case 64: return launch_g<4, BITS>(group, check, weighted, p, s);
-        case 128: return launch_g<8, BITS>(group, check, weighted, p, s);
-        case 256: return launch_g<16, BITS>(group, check, weighted, p, s);
-        case 512: return launch_g<32, BITS>(group, check, weighted, p, s);
+        case 16: return launch_g<1, BITS>(kernel, check, weighted, p, s);
+        case 32: return launch_g<2, BITS>(kernel, check, weighted, p, s);
+        case 64: return launch_g<4, BITS>(kernel, check, weighted, p, s);
+        case 128: return launch_g<8, BITS>(kernel, check, weighted, p, s);
+        case 256: return launch_g<16, BITS>(kernel, check, weighted, p, s);
+        case 512: return launch_g<32, BITS>(kernel, check, weighted, p, s);
     }
     return hipErrorNotSupported;
 }
 
-hipError_t launch_eb(int code_bytes, int bits, bool group, bool check, bool weighted, const EbParams& p, hipStream_t s) {
-    return bits == 4 ? launch_bits<4>(code_bytes, group, check, weighted, p, s)
-                     : launch_bits<8>(code_bytes, group, check, weighted, p, s);
+hipError_t launch_eb(int code_bytes, int bits, EbKernel kernel, bool check, bool weighted, const EbParams& p, hipStream_t s) {
+    return bits == 4 ? launch_bits<4>(code_bytes, kernel, check, weighted, p, s)
+                     : launch_bits<8>(code_bytes, kernel, check, weighted, p, s);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -619,14 +739,9 @@ int abft_eb_u8_checked(const abft_eb_table* Tp, const int64_t* indices, int64_t 
     const int G = Tp->code_bytes / 16;
     if (n_bags > 0x7fffffffll || (n_bags * G + 255) / 256 > 0x7fffffffll)
         return abft::set_error(ABFT_EUNSUPPORTED, "%s: n_bags=%lld too large for one launch", fn, (long long)n_bags);
-    // The batch kernel needs enough lookups to fill the chip with lanes; below that one workgroup per lookup
-    // keeps more bytes in flight.  Crossovers measured with 100 rows per lookup on a 2 GiB table, checked
-    // (code bytes per row: lookups): 16: between 32768 and 65536; 32: 32768, within 2 % of each other
-    // beyond; 64 and 128: the group kernel still ahead by 1 % at 65536 and 131072; 256: between 6144 and
-    // 8192 (7 % either way); 512: group ahead by 4 % at 8192.
-    bool group = n_bags < abft::eb_batch_min_lookups(G);
-    if (variant == ABFT_EB_VARIANT_BATCH) group = false;
-    if (variant == ABFT_EB_VARIANT_GROUP) group = true;
+    abft::EbKernel kernel = abft::pick_kernel(n_bags, n_indices, G);
+    if (variant == ABFT_EB_VARIANT_BATCH) kernel = abft::kEbBatch;
+    if (variant == ABFT_EB_VARIANT_GROUP) kernel = abft::kEbGroup4;
     abft::EbParams p;
     p.tab = Tp->rec;
     p.stride = Tp->stride;
@@ -642,7 +757,7 @@ int abft_eb_u8_checked(const abft_eb_table* Tp, const int64_t* indices, int64_t 
     p.rsum = check ? rsum : nullptr;
     p.csum = check ? csum : nullptr;
     p.bound = rel_bound;
-    HIP_TRY(abft::launch_eb(Tp->code_bytes, Tp->bits, group, check, weights != nullptr, p, (hipStream_t)stream));
+    HIP_TRY(abft::launch_eb(Tp->code_bytes, Tp->bits, kernel, check, weights != nullptr, p, (hipStream_t)stream));
     return ABFT_OK;
 }
 

@@ -345,3 +345,40 @@ def test_table_beyond_4_gib(b):
     torch.cuda.synchronize()
     assert flags[0].item() == 1
     Tp.destroy()
+
+
+# (numbers of lookups and mean lengths on either side of every line of the choice; the lengths themselves sit at the edges
+# of the eight rows that are pooled at a time and of the chunks that are staged)
+@pytest.mark.parametrize("n_bags,mean", [(999, 10), (40, 30), (999, 17), (1000, 40), (1000, 60), (6000, 4), (16000, 9), (5999, 5)])
+@pytest.mark.parametrize("code_bytes,bits", [(16, 8), (32, 4), (64, 8), (64, 4), (128, 8), (256, 4), (512, 8)])
+def test_every_choice_by_size(b, code_bytes, bits, n_bags, mean):
+    """The kernel that the library picks by itself, with and without weights: every one within the round-off bound of the
+    definition, with the same bits as the documented order, bad indices reported and left out."""
+    d = code_bytes * 8 // bits
+    if n_bags * mean * d > 40_000_000:
+        n_bags, mean = 1200, mean     # (wide rows: the same side of the line with fewer lookups)
+    rng = w.rng_for(60 + code_bytes + bits, n_bags + mean)
+    rows = 4000
+    T, scale, bias = w.draw_table(rng, rows, d, "uniform", bits)
+    n = rng.integers(max(mean // 2, 0), mean + mean // 2 + 1, size=n_bags)
+    edge = np.array([0, 1, 7, 8, 9, 16, 17, 24, 31, 33, 56, 57, 96, 97, 104, 105, 120, 128, 129, 200, 201, 208, 700])
+    n[1:1 + len(edge)] = edge
+    offsets = np.concatenate([[0], np.cumsum(n)]).astype(np.int64)
+    indices = rng.integers(0, rows, size=int(offsets[-1]), dtype=np.int64)
+    g = GpuTable(b, T, scale, bias, aligned=bits == 4, bits=bits)
+    for weights in (None, w.draw_weights(rng, indices.size)):
+        ref = eb.checked_eb(T, scale, bias, indices, offsets, weights, bits=bits)
+        compare(g.run(indices, offsets, weights), ref, T, scale, bias, indices, offsets, weights, bits)
+        assert same_bits(g.run(indices, offsets, weights, check=False)["R"], ref.R)
+    # bad indices: at the start of a lookup, in its last row, and a lookup of nothing else
+    wrong = indices.copy()
+    wrong[[int(offsets[5]), int(offsets[24]) - 1, int(offsets[2])]] = [rows, -1, 2 ** 40]
+    out = g.run(wrong, offsets, weights)
+    flagged = np.zeros(n_bags, dtype=bool)
+    flagged[[5, 23, 2]] = True
+    assert np.array_equal((out["flags"] & b.ABFT_EB_BAD_INDEX) != 0, flagged)
+    keep = np.ones(indices.size, dtype=bool)
+    keep[[int(offsets[5]), int(offsets[24]) - 1, int(offsets[2])]] = False
+    left = np.concatenate([[0], np.cumsum(keep)])[offsets].astype(np.int64)
+    ref = eb.checked_eb(T, scale, bias, indices[keep], left, weights[keep], bits=bits)
+    assert same_bits(out["R"], ref.R)
