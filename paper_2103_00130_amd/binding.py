@@ -3,7 +3,10 @@
 Argument marshalling only.  torch tensors supply device memory and the current
 stream; every step of the method runs in the HIP kernels behind the C ABI.
 Importing this module fails loudly when the library has not been built
-(`python -m paper_2103_00130_amd.build`): there is no fallback path.
+(`python -m paper_2103_00130_amd.build`): there is no fallback path.  The two calls
+of a serving loop, the checked GEMM and the checked lookup, are marshalled natively
+(csrc/fastcall.cpp); operands that it does not take - and so every wrong one - go
+through the Python code that follows, which says what is wrong with them.
 """
 from __future__ import annotations
 
@@ -107,6 +110,13 @@ def _load() -> ctypes.CDLL:
 
 
 lib = _load()
+
+try:
+    from . import _fastcall
+except ImportError as e:
+    raise ImportError(f"{e}: build it with `python -m paper_2103_00130_amd.build`") from e
+_fastcall.bind(ctypes.cast(lib.abft_gemm_u8s8s32_checked, ctypes.c_void_p).value, ctypes.cast(lib.abft_eb_u8_checked, ctypes.c_void_p).value,
+               torch.cuda.current_device, torch._C._cuda_getCurrentRawStream)
 
 
 def _check(rc: int):
@@ -222,6 +232,12 @@ def make_injections(entries, device="cuda") -> torch.Tensor:
 
 def abft_gemm_u8s8s32_checked(A, Bp: PackedB, C, row_flags, err_count, rq=None, Cq=None, inj=None, n_inj=0,
                               flags=ABFT_CHECK, workspace=None, stream=None):
+    if rq is None or type(rq) is abft_requant_t:
+        rc = _fastcall.gemm(A, Bp.handle, Bp.K, Bp.N, C, row_flags, err_count, rq, Cq, inj, n_inj, flags, workspace, stream)
+        if rc is not None:
+            if rc != ABFT_OK:
+                _check(rc)
+            return
     M = A.shape[0]
     if A.shape[1] != Bp.K:
         raise ValueError(f"A is {tuple(A.shape)}, packed B has K={Bp.K}")
@@ -440,6 +456,11 @@ def abft_eb_u8_checked(Tp: EbTable, indices: torch.Tensor, offsets: torch.Tensor
                        rsum: torch.Tensor | None = None, csum: torch.Tensor | None = None,
                        rel_bound: float = 1e-5, flags: int = 0, stream=None):
     """Algorithm 2 for a batch: offsets has one entry more than there are lookups."""
+    rc = _fastcall.eb(Tp.handle, Tp.d, indices, offsets, R, bag_flags, weights, rsum, csum, rel_bound, flags, stream)
+    if rc is not None:
+        if rc != ABFT_OK:
+            _check(rc)
+        return
     n_bags = offsets.numel() - 1
     if n_bags < 0 or not offsets.is_contiguous() or not indices.is_contiguous():
         raise ValueError("indices and offsets must be contiguous; offsets needs n_bags + 1 entries")

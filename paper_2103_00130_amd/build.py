@@ -9,6 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libabftgemm.so")
+FASTCALL = os.path.join(HERE, "_fastcall.so")
 SOURCES = ["api.hip", "pack.hip", "gemm_tile.hip", "gemm_tile_a256.hip", "gemm_tile_a256w24.hip", "gemm_tile_a256w42.hip",
            "gemm_tile_a128.hip", "gemm_tile_a64.hip", "gemm_tile_a64r8.hip", "gemm_tile_a64r4.hip", "gemm_tile_a64s.hip", "gemm_tile_a64k2.hip", "gemm_tile_g64.hip", "gemm_smallm.hip",
            "rowops.hip", "locate.hip", "eb.hip"]
@@ -59,5 +60,24 @@ def _build(force, verbose, build_dir, lib, extra) -> str:
     return lib
 
 
+def build_fastcall(force: bool = True) -> str:
+    """_fastcall.so: the native marshalling that binding.py uses for the two calls of a serving loop (host code only)."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    src = os.path.join(CSRC, "fastcall.cpp")
+    deps = [src] + [os.path.join(HERE, "..", "include", h) for h in ("abft_gemm.h", "abft_eb.h")]
+    if not force and os.path.exists(FASTCALL) and os.path.getmtime(FASTCALL) >= max(os.path.getmtime(d) for d in deps):
+        return FASTCALL
+    lib_dir = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *(f"-isystem{d}" for d in cpp_extension.include_paths()), f"-I{sysconfig.get_paths()['include']}",
+           src, "-o", FASTCALL, f"-L{lib_dir}", "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    subprocess.run(cmd, check=True)
+    return FASTCALL
+
+
 if __name__ == "__main__":
+    print(build_fastcall(force="--force" in sys.argv))
     print(build_library(force="--force" in sys.argv, verbose=True, clock_trace="--clock-trace" in sys.argv))

@@ -1169,3 +1169,43 @@ def test_pack_of_strided_weights(binding, gpu_util, oracle, K, N, transposed):
     if K % 16 == 0:
         out = run.gemm(A, mod127=True)
         assert np.array_equal(out["C"], ref.C) and not out["flags"].any()
+
+
+@pytest.mark.gpu
+def test_operands_of_the_native_call(binding, gpu_util, oracle):
+    """The natively marshalled call takes what the Python code takes - views, single rows, an explicit stream, no errCount -
+    and leaves to it, errors and all, what it does not."""
+    import torch
+    M, N, K = 70, 65, 130
+    A, B = operands(M, N, K, 17)
+    ref = oracle.checked_gemm(A, B)
+    run = gpu_util.GpuRun(binding, B)
+    ws = binding.Workspace(M, run.Bp).tensor
+    wide = torch.zeros((M, K + 7), dtype=torch.uint8, device="cuda")
+    wide[:, 3:3 + K] = gpu_util.dev(A)
+    Cw = torch.zeros((M, N + 2), dtype=torch.int32, device="cuda")
+    flags = torch.full((M + 4,), 9, dtype=torch.int32, device="cuda")
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    call = binding.abft_gemm_u8s8s32_checked
+    call(wide[:, 3:3 + K], run.Bp, Cw[:, 1:1 + N], flags, None, workspace=ws, stream=side)
+    with torch.cuda.stream(side):
+        one = torch.zeros((1, N), dtype=torch.int32, device="cuda")
+        call(wide[5:6, 3:3 + K], run.Bp, one, flags[M:], None, workspace=ws)
+    side.synchronize()
+    assert np.array_equal(Cw[:, 1:1 + N].cpu().numpy(), ref.C) and not Cw[:, 0].any() and np.array_equal(one.cpu().numpy()[0], ref.C[5])
+    assert flags.cpu().tolist() == [0] * (M + 1) + [9] * 3
+    A_dev, C, cnt = gpu_util.dev(A), torch.zeros((M, N), dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    for bad, error in (((A_dev.cpu(), C, flags), TypeError), ((A_dev.int(), C, flags), TypeError), ((A_dev[:, :-1], C, flags), ValueError),
+                       ((A_dev, C[:, :-1], flags), ValueError), ((A_dev, C, flags[:M - 1]), ValueError), ((A_dev, C.float(), flags), TypeError),
+                       ((A_dev, None, flags), binding.AbftError), ((A_dev, C, None), binding.AbftError)):
+        with pytest.raises(error):
+            call(bad[0], run.Bp, bad[1], bad[2], cnt, workspace=ws)
+    with pytest.raises(ValueError):
+        call(A_dev, run.Bp, C, flags, cnt, inj=torch.zeros(2, dtype=torch.int32, device="cuda"), n_inj=1, workspace=ws)
+    with pytest.raises(binding.AbftError) as e:
+        call(A_dev, run.Bp, C, flags, cnt, workspace=ws[:64])
+    assert e.value.code == binding.ABFT_EINVAL and "workspace" in str(e.value)
+    call(A_dev, run.Bp, C, flags, cnt, flags=np.int64(0), workspace=ws)     # (a number that is no plain int)
+    torch.cuda.synchronize()
+    assert np.array_equal(C.cpu().numpy(), ref.C)
