@@ -119,6 +119,7 @@ struct GemmParams {
     const void* inj;           // abft_inject_t[n_inj]
     int n_inj;
     int ksplit;                // K slices across workgroups (split-K kernels; 1 elsewhere)
+    int split_q, split_r;      // stages of a slice, or of a K group inside the workgroup; the first split_r take one more
     int32_t* ws_tickets;       // split-K: one arrival counter per tile
     int32_t* ws_part;          // split-K: partial tiles, [tile][slice][value][thread]
     size_t ws_ints;            // ints the caller's workspace holds
@@ -152,7 +153,7 @@ constexpr size_t kWsScratchOff = kWsTicketsOff + kWsTickets;
 // Split-K across workgroups (64x64 tiles, grids that would leave most compute units idle): how many K slices,
 // and where the tile tickets and the partial tiles lie in the workspace behind the row words.  One place for
 // the rule, so that abft_gemm_workspace_bytes and the launcher agree.
-constexpr int kSplitKPartInts = 256 * 17;   // per workgroup: 256 threads x (16 accumulator values + 1 column sum)
+constexpr int kSplitKPartInts = 256 * 17 + 64;   // per workgroup: 256 threads x (16 accumulator values + 1 column sum), 64 rows' checksum shares
 struct SplitKPlan {
     int z;                                  // slices (1 = no split)
     size_t tickets_off, part_off, total_ints;
@@ -163,16 +164,16 @@ inline SplitKPlan splitk_plan(int M, int N, int stages) {
     pl.z = 1;
     // The slices of a tile meet through memory (the L2s are not coherent with each other): store the partial tile,
     // wait for the acknowledgement, take the ticket, fetch the others' partials - three dependent device-scope round
-    // trips, measured at 3.5-4 us.  A stage of the unsplit 64x64 loop takes about 0.25 us, so the split pays from
-    // about forty stages on (measured: 256x512x4096 8.1 us split against 8.5 unsplit, 256x1024x8192 10.5 against
-    // 14.0, 128x128x16384 9.8 against 33.9; 256x512x2048 7.6 against 5.9), and slices of fewer than four stages
-    // are all overhead.
-    if (stages >= 40 && M <= kWsRows)
-        for (int z = 16; z >= 2; z >>= 1)
-            if (tiles * z <= 256 && stages % z == 0 && stages / z >= 4) {
-                pl.z = z;
-                break;
-            }
+    // trips, about 3.5 us.  A stage of the unsplit 64x64 loop takes 0.2 us, so four slices pay from 24 stages on and two
+    // or three, where more tiles leave no room for four, from 40 (us, unsplit / split: 128x128x2048 7.5 / 7.1,
+    // 256x512x3072 8.9 / 8.4, 64x496x4096 10.5 / 8.3; with 128 tiles 512x1024x3072 9.7 / 10.2, 512x1024x4608 11.6 / 11.6,
+    // 512x1024x5200 15.3 / 12.4).  More slices shorten the loop but the last arrival fetches four partials at a time:
+    // eight from 60 stages on (64 stages 10.9 / 10.8 with four / eight, 125 stages 14.8 / 11.9), sixteen from 160.
+    const int most = tiles <= 128 ? (int)(256 / tiles) : 1;
+    if (most >= 2 && stages >= (most >= 4 ? 24 : 40) && M > 32 && M <= kWsRows) {   // (up to 32 rows: the streaming kernel)
+        const int z = stages >= 160 ? 16 : stages >= 60 ? 8 : 4;
+        pl.z = z < most ? z : most;
+    }
     pl.tickets_off = kWsTicketsOff;   // (at most 256 tiles are split)
     pl.part_off = kWsScratchOff;
     pl.total_ints = pl.z > 1 ? pl.part_off + (size_t)tiles * pl.z * kSplitKPartInts : ws_base_ints(M);

@@ -256,10 +256,13 @@ int abft_gemm_u8s8s32_checked(const uint8_t* A, int64_t lda, int M, const abft_p
         if (tiles(128) >= 136) return (int)abft::kTile128;  // (1024x2048x2048: 13.4 us on 64x64 tiles, 14.5 on 128x128)
         return (int)abft::kTile64;
     };
-    // The streaming kernel reads the weight once and wins wherever that dominates: up to 32 rows always,
-    // up to 64 rows when the weight is large (measured: 64x4096x2048 9.5 us against 10.1 us tiled, but
-    // 64x1024x1024 7.0 against 6.5 and 64x256x512 6.3 against 5.3).
-    const bool streaming = M <= 32 || (M <= 64 && (int64_t)Bp->N * Bp->K >= (int64_t)1 << 22);
+    // The streaming kernel reads the weight once and wins up to 32 rows; beyond, every row block costs it a pass over A per
+    // column block and the registers of a second workgroup per compute unit.  Up to 48 rows it still wins where its workgroups
+    // fit the compute units once and the tiles would be few, but neither a short K nor one that is worth a split (us,
+    // streaming / 64x64 tiles: 33x4096x1024 5.9 / 7.0, 48x4096x2048 8.0 / 8.6, 33x4096x4096 10.6 / 11.4, 48x4096x4096
+    // 12.2 / 11.4, 33x1000x512 5.7 / 5.3); with 64 rows nowhere (64x4096x2048 9.4 / 8.4, 64x8192x2048 18.1 / 10.3,
+    // 64x16384x4096 53 / 19).
+    const bool streaming = M <= 32 || (M <= 48 && Bp->N <= 4096 && Bp->K > 512 && Bp->K <= (M <= 40 ? 4096 : 2048));
     if (!chosen) variant = streaming ? (int)abft::kSmallM : pick_tile();
     hipError_t e;
     if (variant != abft::kSmallM && !mod127 && !(p.a_vec_ok && p.K % 16 == 0)) {

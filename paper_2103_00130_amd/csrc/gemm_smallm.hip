@@ -27,7 +27,7 @@ namespace {
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v4i_any __attribute__((ext_vector_type(4), aligned(1)));  // sixteen bytes at any address
 constexpr int kOutC = 1, kOutQ = 2;
-constexpr int kSmallMWideN = 8192;   // from this width on a workgroup owns 32 columns (M <= 32): at least 256 workgroups remain (with fewer, 16 x 4096 x 2048 runs in 5.6 us instead of 4.7)
+constexpr int kFlatN = 4096, kWideN = 8192;   // up to these widths workgroups of 16 and of 32 columns fit the compute units once
 
 // sum over the 16 lanes of a DPP row; every lane of the row ends up with the total
 __device__ inline uint32_t row_sum16(uint32_t s) {
@@ -48,8 +48,7 @@ __device__ inline int32_t floor_mod127(long long v) {
 // RB = 16-row blocks of A (M <= 16*RB); NCB = blocks of 16 columns per workgroup.  With NCB = 2 a workgroup owns a
 // whole 32-column unit of the packed weight, with NCB = 4 two neighbouring units: every k-block it reads is 2 or
 // 4 KiB of contiguous memory instead of every other 256 bytes of it, and one A operand serves two or four matrix
-// instructions (wide weights, where the column blocks alone fill the chip many times over; measured at M = 16 on
-// 16384 x 32768 int8: 0.49 of the HBM peak with NCB = 1, 0.64 with 2, 0.70 with 4).
+// instructions (wide weights, whose column blocks alone would come to several workgroups per compute unit).
 // kAny: A of any alignment, leading dimension and K >= 16.  The same chunks come in with loads from any byte address; the
 // one chunk that holds the end of a row, loaded from K - 16, is shifted down to its place before it is used.
 template <int RB, int NCB, bool kCheck, int kOut, bool kAny>
@@ -364,11 +363,18 @@ hipError_t launch_gemm_smallm(bool any_a, bool check, bool want_c, bool want_q, 
     if (p.M > 64) return hipErrorNotSupported;
     if (!p.a_vec_ok || p.K % 16 != 0)
         if (!any_a || p.mod127 || p.K < 16) return hipErrorNotSupported;
-    // whole 32-column units per workgroup once the 16-column blocks alone would fill the chip at least twice
-    const bool wide = p.N >= kSmallMWideN;
-    if (p.M <= 16 && p.N >= 2 * kSmallMWideN) return launch_rb<1, 4>(check, want_c, want_q, p, s);
-    if (p.M <= 16) return wide ? launch_rb<1, 2>(check, want_c, want_q, p, s) : launch_rb<1, 1>(check, want_c, want_q, p, s);
-    if (p.M <= 32) return wide ? launch_rb<2, 2>(check, want_c, want_q, p, s) : launch_rb<2, 1>(check, want_c, want_q, p, s);
+    // As few columns per workgroup as still give every compute unit one workgroup at most (us, NCB = 1 / 2 / 4):
+    // 16x4096x4096 7.0 / 8.5 / 11.4; 16x6000x4000 10.3 / 8.8 / 12.4; 16x8192x8192 19.1 / 15.1 / 21.1; 16x12000x12000 37.3 /
+    // 34.5 / 29.8; 16x16384x16384 62 / 58 / 43.7 (6.1 TB/s); 32x6000x4000 14.8 / 11.8 / 16.5; 32x16384x16384 90 / 65 / 49.4.
+    // (A handful of rows, whose A operands are next to nothing, stays with 32 columns up to 16384: 1x12000x12000 26.6 / 27.2.)
+    const int ncb = p.N <= kFlatN ? 1 : (p.N <= kWideN || (p.M <= 8 && p.N < 2 * kWideN)) ? 2 : 4;
+    if (p.M <= 16)
+        return ncb == 1 ? launch_rb<1, 1>(check, want_c, want_q, p, s)
+                        : ncb == 2 ? launch_rb<1, 2>(check, want_c, want_q, p, s) : launch_rb<1, 4>(check, want_c, want_q, p, s);
+    if (p.M <= 32)
+        return ncb == 1 ? launch_rb<2, 1>(check, want_c, want_q, p, s)
+                        : ncb == 2 ? launch_rb<2, 2>(check, want_c, want_q, p, s) : launch_rb<2, 4>(check, want_c, want_q, p, s);
+    if (p.M <= 48) return launch_rb<3, 1>(check, want_c, want_q, p, s);
     return launch_rb<4, 1>(check, want_c, want_q, p, s);
 }
 

@@ -34,9 +34,9 @@ hipError_t launch_gemm_tile(int variant, bool check, bool want_c, bool want_q, c
             // faster from K = 1536 on: 1024x1024x4096 unchecked 11.7 -> 10.4 us, 512x1024x4096 10.9 -> 8.9;
             // slower at K <= 1024, where the hand-over at the end costs more than the loop gains; four
             // groups, or four lone wavefronts of 64x64, are slower than two groups).  The launcher refuses
-            // a K that does not split evenly or whose checksum share per tile column is too long for the
-            // staged digits; then one group with a ring of eight stages takes a long K (it takes most of
-            // a unit's LDS, and filling it costs more than it saves below about sixteen stages).
+            // a K whose checksum share per tile column is too long for the staged digits; then one group with a
+            // ring of eight stages takes a long K (it takes most of a unit's LDS, and filling it costs more than
+            // it saves below about sixteen stages).
             const int64_t tiles = (int64_t)((p.M + 63) / 64) * ((p.N + 63) / 64);
             // few tiles and a long K: K is split across workgroups as well, so that the compute units that would sit
             // idle take slices of it (the launcher refuses when the caller's workspace has no room for the partial tiles)

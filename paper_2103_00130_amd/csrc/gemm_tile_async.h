@@ -108,11 +108,10 @@ constexpr size_t group_lds_bytes() {
 // barriers (same number of stages each, the launcher sees to it); at the end groups 1.. hand their
 // accumulators to group 0 through LDS and leave, and group 0 runs the epilogue.
 // kSplitK: K split across workgroups as well.  p.ksplit workgroups per tile take consecutive runs of stages; each
-// stores its partial tile (accumulators and column sums) in the workspace and takes a ticket on the tile's counter,
-// and the one that arrives last adds the others' partials to its own and runs the epilogue.  The checksum product
-// of every run of stages is dealt out to the tile columns as before, so every workgroup contributes its share
-// of it to the row words directly (the comparison of Eq. 2b is linear in the K slices) and only the last one
-// contributes row sums.  For grids of 64x64 tiles that would leave most compute units idle.
+// stores its partial tile (accumulators, column sums, and its share of the checksum product for the tile's rows) in the
+// workspace and takes a ticket on the tile's counter, and the one that arrives last adds the others' partials to its own
+// and runs the epilogue.  The checksum product of every run of stages is dealt out to the tile columns as before (the
+// comparison of Eq. 2b is linear in the K slices).  For grids of 64x64 tiles that would leave most compute units idle.
 template <int BM, int BN, int WGM, int WGN, int kStages, bool kCheck, int kOut, bool kBlockSums, int WGK, bool kSplitK = false, int kAnyA = 0>
 __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(const GemmParams p, const int tiles_m,
                                                                              const int tiles_n) {
@@ -158,8 +157,12 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     const int Z = kSplitK ? p.ksplit : 1;                                       // K slices across workgroups
     const int z = kSplitK ? (int)blockIdx.x / (tiles_m * tiles_n) : 0;
     const int NS_all = p.KB2;            // stages of 128 k-values
-    const int NS = NS_all / (WGK * Z);   // ... of this group (the launcher splits only what divides)
-    const int s_base = (z * WGK + grp) * NS;  // its first stage
+    // ... of this run of them (the slice of a K split across workgroups, the group of one inside the workgroup): as equal
+    // as they can be, the first split_r runs one stage longer
+    constexpr bool kRuns = kSplitK || WGK > 1;
+    const int run_no = kSplitK ? z : grp;
+    const int NS = kRuns ? p.split_q + (run_no < p.split_r ? 1 : 0) : NS_all;
+    const int s_base = kRuns ? share_begin(run_no, p.split_q, p.split_r) : 0;  // its first stage
 
     // ---- direct global->LDS loads ---------------------------------------------------
     // One instruction moves 16 bytes per lane to LDS address m0 + lane*16.  They are issued
@@ -335,12 +338,17 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     constexpr int kLimbStages = 32 / WGK;
     // (stage numbers of this group: every group's run of stages is dealt out to the tile columns in the same way, so
     // that the groups of a K-split workgroup carry the same number of checked stages between their common barriers)
-    const int ck_lo = kCheck ? share_begin(tile_n, p.share_q, p.share_r) : 0;
-    const int ck_hi = kCheck ? share_begin(tile_n + 1, p.share_q, p.share_r) : 0;
+    int share_q = p.share_q, share_r = p.share_r;   // (of a run of split_q stages: one stage more is one more to deal out)
+    if (kRuns && run_no < p.split_r && ++share_r == tiles_n) {
+        ++share_q;
+        share_r = 0;
+    }
+    const int ck_lo = kCheck ? share_begin(tile_n, share_q, share_r) : 0;
+    const int ck_hi = kCheck ? share_begin(tile_n + 1, share_q, share_r) : 0;
     uint8_t* const s_limb = smem + S * (A_STAGE + B_STAGE) + (4 * BN + WGN * BM + BM + 4) * sizeof(int32_t);
     // sum_k S_B[k], which the first tile column needs at the very end (the u8 -> s8 shift of A moves every
     // checksum product by 128 times it): fetched now, so that the epilogue does not wait for memory
-    int32_t total_sb = (kCheck && tile_n == 0 && z == 0) ? *p.total : 0;
+    int32_t total_sb = (kCheck && tile_n == 0) ? *p.total : 0;
     int limb_base = ck_lo;  // stage whose digits sit at the start of s_limb
     // (copied by the same direct global->LDS loads as the stages, 1 KiB per instruction: no trip through
     // registers, and no wait that the compiler would place - it does not see the direct loads and would
@@ -719,6 +727,8 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     } else if (WGM == 1) run_all(std::integral_constant<int, 2>{});
     else if ((wm & 1) == 0) run_all(std::integral_constant<int, 0>{});
     else run_all(std::integral_constant<int, 1>{});
+    // (the groups pass the same barriers: one per stage, and one more here for a group whose run is a stage shorter)
+    if (WGK > 1 && p.split_r > 0 && grp >= p.split_r) __syncthreads();
     // (the last stage re-issued loads into a dead buffer; the epilogue keeps its scratch outside
     // the stage buffers, so nobody waits for them before the very end of the kernel)
 
@@ -778,15 +788,35 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
         }
     }
 
+    // LDS scratch behind the stage buffers: [4][BN] column sums, [WGN][BM] row-sum parts,
+    // [BM] checksum parts, 4 control words
+    int32_t* const s_bs = reinterpret_cast<int32_t*>(smem + S * (A_STAGE + B_STAGE));
+    int32_t* const s_rs = s_bs + 4 * BN;
+    int32_t* const s_ck = s_rs + WGN * BM;
+    auto recombine_digits = [&]() __attribute__((always_inline)) {
+        // 16x16 accumulator: lane l, element e is row 4*(l/16) + e, column l%16; columns 0..3
+        // hold the four digit products
+#pragma unroll
+        for (int c = 0; c < CB; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int d = lane & 15;
+                uint32_t v = d < kLimbs ? ((uint32_t)cacc[c][e] << (8 * d)) : 0u;
+                v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);
+                v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);
+                if (d == 0) s_ck[wm * WTM + (wn * CB + c) * 16 + 4 * (lane >> 4) + e] = (int32_t)v;
+            }
+    };
+
     // ------------------------- K split across workgroups: partial tiles meet in the last arrival -------------------------
-    bool last = true;   // this workgroup holds the complete tile (always, without a split)
     if constexpr (kSplitK) {
         static_assert(WGK == 1 && TM * TN == 1 && NT == 256, "split-K is built for the 64x64 tile of four 32x32 wavefronts");
         __shared__ int s_ticket;
         constexpr int kVals = 16 * TM * TN + TN;
-        static_assert(kVals * NT == kSplitKPartInts, "layout of a partial tile");
+        static_assert(kVals * NT + BM == kSplitKPartInts, "layout of a partial tile");
         const int tile = tile_m * tiles_n + tile_n;
-        int32_t* const mine = p.ws_part + ((size_t)tile * Z + z) * kSplitKPartInts + tid;
+        int32_t* const part = p.ws_part + (size_t)tile * Z * kSplitKPartInts;
+        int32_t* const mine = part + (size_t)z * kSplitKPartInts + tid;
         {
             // device-scope stores (they pass through the L2, which is not coherent with the other seven): once this
             // wavefront's stores are acknowledged and the barrier is passed, the whole partial tile is in memory
@@ -795,33 +825,36 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
             for (int e = 0; e < 16; ++e) __hip_atomic_store(mine + (k++) * NT, acc[0][0][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(mine + (k++) * NT, (int32_t)bsum[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
+        if (kCheck) {
+            recombine_digits();
+            __syncthreads();
+            if (tid < BM) __hip_atomic_store(mine + kVals * NT, s_ck[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
         wait_vmem();   // (also the direct-to-LDS loads still in flight)
         __syncthreads();
         if (tid == 0) s_ticket = __hip_atomic_fetch_add(p.ws_tickets + tile, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
-        last = s_ticket == Z - 1;
-        if (last) {
-            if (tid == 0) __hip_atomic_store(p.ws_tickets + tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            // the other slices' partial tiles, four at a time so that their loads are in flight together (a slice
-            // number past the last one, or this workgroup's own, re-reads a valid partial and adds nothing)
-            for (int z0 = 0; z0 < Z; z0 += 4) {
-                int32_t v[4][kVals];
+        if (s_ticket != Z - 1) return;   // (nothing in flight: awaited above)
+        if (tid == 0) __hip_atomic_store(p.ws_tickets + tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // the other slices' partial tiles, four at a time so that their loads are in flight together (a slice
+        // number past the last one, or this workgroup's own, re-reads a valid partial and adds nothing)
+        for (int z0 = 0; z0 < Z; z0 += 4) {
+            int32_t v[4][kVals], ck[4] = {0, 0, 0, 0};
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int32_t* const theirs = p.ws_part + ((size_t)tile * Z + min(z0 + j, Z - 1)) * kSplitKPartInts + tid;
+            for (int j = 0; j < 4; ++j) {
+                const int32_t* const theirs = part + (size_t)min(z0 + j, Z - 1) * kSplitKPartInts + tid;
 #pragma unroll
-                    for (int k = 0; k < kVals; ++k) v[j][k] = __hip_atomic_load(theirs + k * NT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int32_t use = (z0 + j < Z && z0 + j != z) ? -1 : 0;   // all ones or zero
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) acc[0][0][e] += v[j][e] & use;
-                    bsum[0] += (uint32_t)(v[j][16] & use);
-                }
+                for (int k = 0; k < kVals; ++k) v[j][k] = __hip_atomic_load(theirs + k * NT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (kCheck && tid < BM) ck[j] = __hip_atomic_load(theirs + kVals * NT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
-        } else if (!kCheck) {
-            return;   // (nothing in flight: awaited above)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int32_t use = (z0 + j < Z && z0 + j != z) ? -1 : 0;   // all ones or zero
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[0][0][e] += v[j][e] & use;
+                bsum[0] += (uint32_t)(v[j][16] & use);
+                if (kCheck && tid < BM) s_ck[tid] = (int32_t)((uint32_t)s_ck[tid] + (uint32_t)(ck[j] & use));
+            }
         }
     }
 
@@ -829,14 +862,7 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     // accumulator layout of the 32x32 MFMA: lane l, element e of block (i, t) is
     // row 8*(e/4) + 4*(l/32) + e%4, column l%32 of that block.
     const int lcol = lane & 31, lhalf = lane >> 5;
-    // LDS scratch behind the stage buffers: [4][BN] column sums, [WGN][BM] row-sum parts,
-    // [BM] checksum parts, 4 control words
-    int32_t* const s_bs = reinterpret_cast<int32_t*>(smem + S * (A_STAGE + B_STAGE));
-    int32_t* const s_rs = s_bs + 4 * BN;
-    int32_t* const s_ck = s_rs + WGN * BM;
     const bool mod127 = kCheck && p.mod127 != 0;
-    // (split-K: only the workgroup that holds the complete tile stores it and forms its row sums)
-    if (last) {
     // column sums of the streamed B: lane halves hold the two k-groups, waves wm = 0 and 1 (or a
     // lone wave) hold alternate k-steps; every byte carried a bias of 128
     constexpr int SUM_WAVES = WGM == 1 ? 1 : 2;
@@ -1000,21 +1026,8 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
         }
     }
 
-    }  // if (last)
-
     if (kCheck) {
-        // 16x16 accumulator: lane l, element e is row 4*(l/16) + e, column l%16; columns 0..3
-        // hold the four digit products
-#pragma unroll
-        for (int c = 0; c < CB; ++c)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int d = lane & 15;
-                uint32_t v = d < kLimbs ? ((uint32_t)cacc[c][e] << (8 * d)) : 0u;
-                v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);
-                v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);
-                if (d == 0) s_ck[wm * WTM + (wn * CB + c) * 16 + 4 * (lane >> 4) + e] = (int32_t)v;
-            }
+        if (!kSplitK) recombine_digits();
         __syncthreads();
         // Row r of the product is spread over the tile columns; each of them adds its share of
         // (row sum - checksum) to the row's 64-bit workspace word with ONE returned atomic:
@@ -1029,12 +1042,10 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
         const int r = tid;
         if (r < BM && row0 + r < p.M) {
             uint32_t d = 0;
-            if (last) {
 #pragma unroll
-                for (int w = 0; w < WGN; ++w) d += (uint32_t)s_rs[w * BM + r];
-            }
-            const bool first = tile_n == 0 && z == 0;   // the workgroup that accounts for the u8 -> s8 shift of the checksum product
-            const int arrivals = tiles_n * Z;           // contributions a row's word receives
+            for (int w = 0; w < WGN; ++w) d += (uint32_t)s_rs[w * BM + r];
+            const bool first = tile_n == 0;   // the tile column that accounts for the u8 -> s8 shift of the checksum product
+            const int arrivals = tiles_n;     // contributions a row's word receives
             if (mod127) {
                 // residues: sums of at most 32 lanes x WGN waves of values below 127, minus the exact
                 // checksum share, as a residue again so that the workspace word cannot wrap
@@ -1111,15 +1122,17 @@ hipError_t launch_cfg(bool check, bool want_c, bool want_q, const GemmParams& p_
         p.ws_tickets = p.ws + pl.tickets_off;
         p.ws_part = p.ws + pl.part_off;
     }
-    p.share_q = (p.KB2 / (WGK * Z)) / tiles_n;   // stages of the checksum product per tile column (and K group / slice)
-    p.share_r = (p.KB2 / (WGK * Z)) % tiles_n;
+    p.split_q = p.KB2 / (WGK * Z);   // stages per K group / slice
+    p.split_r = p.KB2 % (WGK * Z);
+    p.share_q = p.split_q / tiles_n;   // ... and, of those, of the checksum product per tile column
+    p.share_r = p.split_q % tiles_n;
     const dim3 grid((unsigned)(tiles_m * tiles_n * Z)), block(WGM * WGN * WGK * 64);
     const size_t lds = WGK * ((group_lds_bytes<BM, BN, WGN, kStages, WGK>() + 1023) / 1024 * 1024);
     if (WGK > 1) {
-        // every group must pass the same barriers: equal runs of stages, and a share of the checksum
-        // product that its staged digits hold without a refill (32 / WGK stages)
-        const int ns = p.KB2;
-        if (ns % WGK != 0 || ns / WGK < 2 || (ns / WGK + tiles_n - 1) / tiles_n > 32 / WGK) return hipErrorNotSupported;
+        // a share of the checksum product must be one that a group's staged digits hold without a refill (which would be a
+        // barrier that the other group does not pass)
+        const int longest = p.split_q + (p.split_r ? 1 : 0);
+        if (p.split_q < 2 || (longest + tiles_n - 1) / tiles_n > 32 / WGK) return hipErrorNotSupported;
     }
     // Row sums in block form or per row.  Small wave tiles: always the block form, which halves the
     // vector work of an epilogue that is short anyway.  The 128x128 wave tile: per row when the grid

@@ -1209,3 +1209,46 @@ def test_operands_of_the_native_call(binding, gpu_util, oracle):
     call(A_dev, run.Bp, C, flags, cnt, flags=np.int64(0), workspace=ws)     # (a number that is no plain int)
     torch.cuda.synchronize()
     assert np.array_equal(C.cpu().numpy(), ref.C)
+
+
+# (K slices across workgroups that are not all equally long: 24, 25, 41, 61, 105 and 161 stages in 4, 2 or 3, 8 and 16 slices;
+# two K groups of unequal length inside a workgroup: 13 and 25 stages; three row blocks and 64 columns per workgroup on the
+# streaming kernel)
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(100, 64, 3072), (100, 200, 3200), (700, 500, 5136), (130, 70, 7696), (61, 496, 13440), (65, 64, 20496),
+                                   (700, 900, 1664), (500, 1300, 3200), (33, 1000, 1040), (48, 333, 2048), (40, 4096, 784), (20, 8250, 96),
+                                   (32, 16390, 64), (9, 12330, 160), (64, 4200, 1024)])
+def test_unequal_runs_and_wide_blocks(binding, gpu_util, oracle, M, N, K):
+    """Bit for bit against the oracle: clean, faults in C, in B and in the checksum column, requantized, modulo 127."""
+    say(f"unequal runs: {M}x{N}x{K}")
+    A, B = operands(M, N, K, M + N + K)
+    ref = oracle.checked_gemm(A, B)
+    run = gpu_util.GpuRun(binding, B)
+    ws = binding.Workspace(M, run.Bp)
+    out = run.gemm(A, ws=ws)
+    assert np.array_equal(out["C"], ref.C) and not out["flags"].any() and out["err_count"] == 0 and not out["ws"].any()
+    assert np.array_equal(run.gemm(A, ws=ws, check=False)["C"], ref.C)
+    inj = [(0, 0, 1 << 31), (M - 1, N - 1, 1), (M // 2, N // 3, 1 << 9), (M // 2, N // 2, 1 << 3)]
+    refi = oracle.checked_gemm(A, B, flips_c=inj)
+    out = run.gemm(A, ws=ws, injections=inj, accumulate_from=3)
+    assert np.array_equal(out["C"], refi.C) and np.array_equal(out["flags"], refi.flags) and out["err_count"] == 3 + refi.err_count
+    for (k, j, bit) in [(0, 0, 7), (K - 1, N - 1, 0), (K // 2 + 3, N // 2, 6)]:
+        refb = oracle.checked_gemm(A, B, flips_b=[(k, j, bit)])
+        binding.abft_packed_b_flip_bit(run.Bp, k, j, bit)
+        out = run.gemm(A, ws=ws)
+        binding.abft_packed_b_flip_bit(run.Bp, k, j, bit)
+        assert np.array_equal(out["C"], refb.C) and np.array_equal(out["flags"], refb.flags) and out["err_count"] == refb.err_count
+    for k in (1, K // 3, K - 2):     # a fault in the checksum column, in the share of different runs and tile columns
+        S2 = ref.S_B.copy()
+        S2.view(np.uint32)[k] ^= np.uint32(1 << 9)
+        want, n = oracle.compare(ref.rsum, oracle.row_checksum(A, S2))
+        binding.abft_packed_b_flip_checksum_bit(run.Bp, k, 9)
+        out = run.gemm(A, ws=ws)
+        binding.abft_packed_b_flip_checksum_bit(run.Bp, k, 9)
+        assert np.array_equal(out["flags"], want) and out["err_count"] == n
+    mult = wlmod.draw_mult(np.random.default_rng(K), N, "channel")
+    out = run.gemm(A, ws=ws, requant=(128, 128, mult, None), want_c=False)
+    assert np.array_equal(out["Cq"], oracle.requantize(ref.C, ref.colsum, 128, 128, mult, precision="f32"))
+    Cw, fw, nw = oracle.checked_gemm_mod127(A, B, flips_c=inj[:3])
+    out = run.gemm(A, ws=ws, mod127=True, injections=inj[:3])
+    assert np.array_equal(out["C"], Cw) and np.array_equal(out["flags"], fw) and out["err_count"] == nw and not out["ws"].any()
