@@ -15,9 +15,9 @@
 //  * The four partial accumulators meet in LDS; wavefront 0 adds them, forms the row sums with
 //    DPP row reductions, stores C, and then adds (row sum - checksum) per row into 64-bit
 //    workspace words that also count arrivals (returned integer atomics, a few dozen arrivals
-//    per word at most): whoever completes a row's word writes its flag, whoever completes the
-//    count of finished rows writes errCount, and each clears what it completed.  No workgroup
-//    waits for another and there is no closing pass.
+//    per word at most): whoever completes a word clears it, and a row's word writes its flag.
+//    errCount is cleared at the start and added to.  No workgroup waits for another and there is
+//    no closing pass.
 #include "../../include/abft_gemm.h"
 #include "abft_internal.h"
 
@@ -28,6 +28,11 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v4i_any __attribute__((ext_vector_type(4), aligned(1)));  // sixteen bytes at any address
 constexpr int kOutC = 1, kOutQ = 2;
 constexpr int kFlatN = 4096, kWideN = 8192;   // up to these widths workgroups of 16 and of 32 columns fit the compute units once
+
+// Up to so many column blocks arrive at a row's word directly; beyond, the blocks of a slot meet at a word of their own first (us,
+// directly / by slots: 50 blocks, 1x800x3200, 5.0 / 5.1; 63 4.7 / 4.75; 100 5.1 / 4.7; 256 7.1 / 4.8: arrivals at one word follow
+// each other at about 10 ns).
+constexpr int kFlatBlocks = 64;
 
 // sum over the 16 lanes of a DPP row; every lane of the row ends up with the total
 __device__ inline uint32_t row_sum16(uint32_t s) {
@@ -78,6 +83,12 @@ __global__ __launch_bounds__(256) void gemm_smallm_kernel(const GemmParams p, co
 
     // sum_k S_B[k] for the first column block's share of the check, fetched ahead of its use at the very end
     const int32_t total_sb = (kCheck && cb == 0) ? *p.total : 0;
+
+    // errCount is overwritten: the first column block clears it here and whoever finds corrupted rows adds to it.  No row is
+    // complete, and so nothing added, before that block has arrived at the row's word, which it does once this store has
+    // been acknowledged.
+    const bool clears = kCheck && cb == 0 && p.err_count != nullptr && !p.err_accumulate;
+    if (clears && tid == 0) __hip_atomic_store(p.err_count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
     v4i acc[NCB][RB], cacc[RB];
 #pragma unroll
@@ -173,6 +184,7 @@ __global__ __launch_bounds__(256) void gemm_smallm_kernel(const GemmParams p, co
     }
     __syncthreads();
     if (wave == 0) {
+        if (clears) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
 #pragma unroll
         for (int w = 0; w < 3; ++w) {
 #pragma unroll
@@ -263,14 +275,13 @@ __global__ __launch_bounds__(256) void gemm_smallm_kernel(const GemmParams p, co
                                           : rs - ck - total128;
                 }
             // One row per lane.  The row's difference climbs workspace words, each a 64-bit
-            // (value << 32 | arrivals) taken with one returned atomic.  With more than 32 column
+            // (value << 32 | arrivals) taken with one returned atomic.  With more than kFlatBlocks column
             // blocks the first word is that of (slot, row), shared by the blocks of one slot, whose
             // last arrival carries the slot's sum on; the next is the word of the row, where the last
-            // arrival has the complete difference and writes the flag.  The rows a wavefront finishes
-            // are counted with one atomic on the word of finished rows, whose last arrival writes
-            // errCount.  Every word is cleared by the arrival that completes it.  No word sees more
-            // than a few dozen arrivals, and nobody waits for anybody.
-            bool fin = false, bad = false;
+            // arrival has the complete difference and writes the flag.  Every word is cleared by the
+            // arrival that completes it.  No word sees more than a few dozen arrivals, and nobody
+            // waits for anybody.
+            bool bad = false;
             if (lane < 16 * RB && lane < p.M) {
                 unsigned long long* const w_slot =
                     reinterpret_cast<unsigned long long*>(p.ws + kWsHeaderInts) + slot * kSmallMRows + lane;
@@ -278,7 +289,7 @@ __global__ __launch_bounds__(256) void gemm_smallm_kernel(const GemmParams p, co
                     reinterpret_cast<unsigned long long*>(p.ws + kWsHeaderInts) + kSmallMSlots * kSmallMRows + lane;
                 uint32_t t = s_d[lane], n_row = (uint32_t)n_blocks;
                 bool go = true;
-                if (n_blocks > kSmallMSlots) {
+                if (n_blocks > kFlatBlocks) {
                     const uint32_t n_slot = ((uint32_t)n_blocks - (uint32_t)slot + kSmallMSlots - 1) / kSmallMSlots;
                     const unsigned long long old = __hip_atomic_fetch_add(w_slot, ((unsigned long long)t << 32) | 1ull,
                                                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -293,7 +304,6 @@ __global__ __launch_bounds__(256) void gemm_smallm_kernel(const GemmParams p, co
                     // a single column block holds the whole row: nothing crosses workgroups
                     bad = mod127 ? (t % 127u != 0u) : (t != 0u);
                     p.row_flags[lane] = (int32_t)bad;
-                    fin = true;
                 } else if (go) {
                     const unsigned long long old = __hip_atomic_fetch_add(w_row, ((unsigned long long)t << 32) | 1ull,
                                                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -302,27 +312,13 @@ __global__ __launch_bounds__(256) void gemm_smallm_kernel(const GemmParams p, co
                         bad = mod127 ? (diff % 127u != 0u) : (diff != 0u);
                         __hip_atomic_store(w_row, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         p.row_flags[lane] = (int32_t)bad;
-                        fin = true;
                     }
                 }
             }
-            // errCount: not asked for / added to by the wavefronts that found corrupted rows (no return value,
-            // nobody waits) / overwritten by the report that brings the count of finished rows to M
-            const unsigned long long fin_mask = __ballot(fin), bad_mask = __ballot(fin && bad);
-            if (p.err_count == nullptr) {
-            } else if (p.err_accumulate) {
-                if (bad_mask != 0ull && lane == __builtin_ctzll(bad_mask))
-                    __hip_atomic_fetch_add(p.err_count, (int32_t)__builtin_popcountll(bad_mask), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            } else if (fin_mask != 0ull && lane == __builtin_ctzll(fin_mask)) {
-                unsigned long long* const w_done = reinterpret_cast<unsigned long long*>(p.ws + kWsDoneWord);
-                const uint32_t n_fin = (uint32_t)__builtin_popcountll(fin_mask), n_bad = (uint32_t)__builtin_popcountll(bad_mask);
-                const unsigned long long old = __hip_atomic_fetch_add(w_done, ((unsigned long long)n_bad << 32) | n_fin,
-                                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if ((uint32_t)old + n_fin == (uint32_t)p.M) {
-                    *p.err_count = (int32_t)((uint32_t)(old >> 32) + n_bad);
-                    __hip_atomic_store(w_done, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-            }
+            // errCount is added to by the wavefronts that found corrupted rows (no return value, nobody waits)
+            const unsigned long long bad_mask = __ballot(bad);
+            if (p.err_count != nullptr && bad_mask != 0ull && lane == __builtin_ctzll(bad_mask))
+                __hip_atomic_fetch_add(p.err_count, (int32_t)__builtin_popcountll(bad_mask), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 }

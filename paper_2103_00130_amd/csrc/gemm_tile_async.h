@@ -350,6 +350,16 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     // checksum product by 128 times it): fetched now, so that the epilogue does not wait for memory
     int32_t total_sb = (kCheck && tile_n == 0) ? *p.total : 0;
     int limb_base = ck_lo;  // stage whose digits sit at the start of s_limb
+    // (behind the load of the total, which the compiler can only make a scalar one ahead of any store)
+    // errCount is overwritten on a grid of one row of tiles: the first workgroup clears it here and whoever finds corrupted
+    // rows adds to it.  No row is complete, and so nothing added, before that workgroup has arrived at the row's word (its
+    // slice at the tile's ticket), which it does once this store has been acknowledged.  (On other grids the rows of other
+    // tile rows do not wait for it: there the last report of finished rows writes the count, one more round trip.)
+    // (64x64 tiles only: the larger ones have one row of tiles on the widest weights alone)
+    constexpr bool kClearsFirst = kCheck && BM == 64;
+    const bool count_added = kClearsFirst && tiles_m == 1 ? true : p.err_accumulate != 0;
+    const bool clears = kClearsFirst && tiles_m == 1 && !p.err_accumulate && p.err_count != nullptr && tile_n == 0 && z == 0;
+    if (kClearsFirst && clears && threadIdx.x == 0) __hip_atomic_store(p.err_count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // (copied by the same direct global->LDS loads as the stages, 1 KiB per instruction: no trip through
     // registers, and no wait that the compiler would place - it does not see the direct loads and would
     // wait for every one of them.  A lot that ends in half an instruction re-reads its last chunk into
@@ -863,6 +873,7 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     // row 8*(e/4) + 4*(l/32) + e%4, column l%32 of that block.
     const int lcol = lane & 31, lhalf = lane >> 5;
     const bool mod127 = kCheck && p.mod127 != 0;
+    if (kClearsFirst && clears) wait_vmem();
     // column sums of the streamed B: lane halves hold the two k-groups, waves wm = 0 and 1 (or a
     // lone wave) hold alternate k-steps; every byte carried a bias of 128
     constexpr int SUM_WAVES = WGM == 1 ? 1 : 2;
@@ -1078,12 +1089,12 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
         // half, corrupted ones in the high half); the report that brings the count to M has the total,
         // writes errCount and clears the word.  Workgroups that completed nothing are done here, and no
         // barrier stands between the two atomics.
-        // With p.err_accumulate the count is a counter that is added to: only wavefronts that found corrupted
+        // Where the count is added to (p.err_accumulate, or cleared at the start), only wavefronts that found corrupted
         // rows touch it (one atomic without a return value), and nobody waits for anything.
         const unsigned long long fin_mask = __ballot(fin), bad_mask = __ballot(fin && bad);
         if (p.err_count == nullptr) {
             // no count was asked for
-        } else if (p.err_accumulate) {
+        } else if (count_added) {
             if (bad_mask != 0ull && lane == __builtin_ctzll(bad_mask))
                 __hip_atomic_fetch_add(p.err_count, (int32_t)__builtin_popcountll(bad_mask), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else if (fin_mask != 0ull && lane == __builtin_ctzll(fin_mask)) {
