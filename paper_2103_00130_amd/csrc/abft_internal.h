@@ -82,12 +82,36 @@ __device__ inline RequantCol requant_col(int32_t cs, int col, const RequantDev& 
     c.mult = rq.mult[rq.per_channel ? col : 0];
     return c;
 }
-__device__ inline uint8_t requant_with(int32_t v, const RequantCol& c, int32_t zC) {
+// the rounded and clamped value, a whole number in [0, 255]
+__device__ inline float requant_float(int32_t v, const RequantCol& c, int32_t zC) {
     const uint32_t t = (uint32_t)v - c.sub;
     const float p = __fmul_rn((float)(int32_t)t, c.mult);
-    float y = __builtin_rintf(p) + (float)zC;
-    y = fminf(fmaxf(y, 0.0f), 255.0f);
-    return (uint8_t)y;
+    const float y = __builtin_rintf(p) + (float)zC;
+    return __builtin_amdgcn_fmed3f(y, 0.0f, 255.0f);   // (clamped; a NaN gives 0, as min(max(y, 0), 255) does)
+}
+__device__ inline uint8_t requant_with(int32_t v, const RequantCol& c, int32_t zC) { return (uint8_t)requant_float(v, c, zC); }
+// ... as byte `row` of w
+__device__ inline uint32_t requant_into(uint32_t w, int row, int32_t v, const RequantCol& c, int32_t zC) {
+    return __builtin_amdgcn_cvt_pk_u8_f32(requant_float(v, c, zC), row, w);
+}
+// The matrix cores leave four rows of one column in a lane and neighbouring columns in neighbouring lanes, so that bytes would
+// go to memory one at a time.  Here the four lanes of a quad turn their 4x4 bytes: byte r of lane c becomes byte c of lane r,
+// and one store writes four columns of the row that the lane now holds.
+__device__ inline uint32_t turn_quad(uint32_t w, int lane) {
+    const uint32_t p1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0xB1, 0xF, 0xF, true);   // lane ^ 1
+    const uint32_t x = __builtin_amdgcn_perm(p1, w, (lane & 1) ? 0x03070105u : 0x06020400u);      // rows 0 and 2 / 1 and 3, two columns
+    const uint32_t p2 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, true);   // lane ^ 2
+    return __builtin_amdgcn_perm(p2, x, (lane & 2) ? 0x03020706u : 0x05040100u);
+}
+typedef uint32_t u32_any __attribute__((aligned(1)));
+__device__ inline void store_quad_nt(uint8_t* p, uint32_t w) { __builtin_nontemporal_store(w, reinterpret_cast<u32_any*>(p)); }
+// four bytes of a row at any address, of which the first n (at least one, at most four) exist
+__device__ inline void store_quad(uint8_t* p, uint32_t w, int n) {
+    if (n >= 4) {
+        *reinterpret_cast<u32_any*>(p) = w;
+    } else {
+        for (int b = 0; b < n; ++b) p[b] = (uint8_t)(w >> (8 * b));
+    }
 }
 __device__ inline uint8_t requant_one(int32_t v, int32_t cs, int col, const RequantDev& rq) {
     return requant_with(v, requant_col(cs, col, rq), rq.zC);

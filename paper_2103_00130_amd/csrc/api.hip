@@ -253,7 +253,11 @@ int abft_gemm_u8s8s32_checked(const uint8_t* A, int64_t lda, int M, const abft_p
         // three tile shapes on shapes between 128x2048 and 4096x4096.
         auto tiles = [&](int b) { return (int64_t)((M + b - 1) / b) * ((Bp->N + b - 1) / b); };
         if (tiles(256) >= 128) return (int)abft::kTile256;
-        if (tiles(128) >= 136) return (int)abft::kTile128;  // (1024x2048x2048: 13.4 us on 64x64 tiles, 14.5 on 128x128)
+        // (1024x2048x2048: 13.4 us on 64x64 tiles, 14.5 on 128x128; a short K that leaves a third of the last round of
+        // 128x128 tiles without one: 1536x1536x512, 144 tiles, 7.5 / 8.5, 2300x2300x1024, 324 tiles, 18.2 / 20.3; with three
+        // quarters of it taken 4096x768x1024, 192 tiles, 11.2 / 11.1, or a longer K, 1536x1536x2048 14.0 / 14.1, it is even)
+        const int64_t t128 = tiles(128), rounds = (t128 + 255) / 256;
+        if (t128 >= 136 && (Bp->K > 1024 || 3 * t128 >= 2 * 256 * rounds)) return (int)abft::kTile128;
         return (int)abft::kTile64;
     };
     // The streaming kernel reads the weight once and wins up to 32 rows; beyond, every row block costs it a pass over A per

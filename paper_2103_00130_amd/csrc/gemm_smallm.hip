@@ -241,15 +241,20 @@ __global__ __launch_bounds__(256) void gemm_smallm_kernel(const GemmParams p, co
             rqc.mult = 0.0f;
             if (kWantQ && col < p.N) rqc = requant_col(p.colsum[col], col, p.rq);
 #pragma unroll
-            for (int rb = 0; rb < RB; ++rb)
+            for (int rb = 0; rb < RB; ++rb) {
+                uint32_t qw = 0;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int row = rb * 16 + 4 * lkg + e;
-                    if (row < p.M && col < p.N) {
-                        if (kWantC) p.C[(int64_t)row * p.ldc + col] = acc[c][rb][e];
-                        if (kWantQ) p.Cq[(int64_t)row * p.ldcq + col] = requant_with(acc[c][rb][e], rqc, p.rq.zC);
-                    }
+                    if (kWantC && row < p.M && col < p.N) p.C[(int64_t)row * p.ldc + col] = acc[c][rb][e];
+                    if (kWantQ) qw = requant_into(qw, e, acc[c][rb][e], rqc, p.rq.zC);
                 }
+                if (kWantQ) {
+                    qw = turn_quad(qw, lane);
+                    const int row = rb * 16 + 4 * lkg + (lane & 3), first = col & ~3;
+                    if (row < p.M && first < p.N) store_quad(p.Cq + (int64_t)row * p.ldcq + first, qw, p.N - first);
+                }
+            }
         }
         if (kCheck) {
             const bool mod127 = p.mod127 != 0;

@@ -161,8 +161,8 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     // as they can be, the first split_r runs one stage longer
     constexpr bool kRuns = kSplitK || WGK > 1;
     const int run_no = kSplitK ? z : grp;
-    const int NS = kRuns ? p.split_q + (run_no < p.split_r ? 1 : 0) : NS_all;
-    const int s_base = kRuns ? share_begin(run_no, p.split_q, p.split_r) : 0;  // its first stage
+    const int NS = kRuns ? p.split_q + (run_no < p.split_r ? 1 : 0) : NS_all / (WGK * Z);
+    const int s_base = kRuns ? share_begin(run_no, p.split_q, p.split_r) : (z * WGK + grp) * NS;  // its first stage
 
     // ---- direct global->LDS loads ---------------------------------------------------
     // One instruction moves 16 bytes per lane to LDS address m0 + lane*16.  They are issued
@@ -357,7 +357,6 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     // tile rows do not wait for it: there the last report of finished rows writes the count, one more round trip.)
     // (64x64 tiles only: the larger ones have one row of tiles on the widest weights alone)
     constexpr bool kClearsFirst = kCheck && BM == 64;
-    const bool count_added = kClearsFirst && tiles_m == 1 ? true : p.err_accumulate != 0;
     const bool clears = kClearsFirst && tiles_m == 1 && !p.err_accumulate && p.err_count != nullptr && tile_n == 0 && z == 0;
     if (kClearsFirst && clears && threadIdx.x == 0) __hip_atomic_store(p.err_count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // (copied by the same direct global->LDS loads as the stages, 1 KiB per instruction: no trip through
@@ -919,11 +918,20 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
         if (kWantQ) {
             const int col = col0 + c_lane + t * 32;
             rqc[t] = requant_col(p.colsum[col], col < p.N ? col : 0, p.rq);
+            rqc[t].sub -= (uint32_t)cs[t];   // (taken off the accumulator as it is: one addition less per element)
         }
     }
     const int32_t rq_zC = kWantQ ? p.rq.zC : 0;
     int32_t* cptr = kWantC ? p.C + (int64_t)(row0 + r_lane) * p.ldc + col0 + c_lane : nullptr;
-    uint8_t* qptr = kWantQ ? p.Cq + (int64_t)(row0 + r_lane) * p.ldcq + col0 + c_lane : nullptr;
+    // Cq: four columns of one row per lane (turn_quad), this lane's row among four being lane & 3: 2000x1000x480 8.0 -> 6.4 us
+    // without C, 9.2 -> 7.9 with it, 4096x2048x512 18.6 -> 16.9.  The 128x128 wave tile that stores C as well goes byte by
+    // byte between the stores of C, which take the time anyway and leave no registers for four rows (4096x4096x1024
+    // 33.4 us, 34.9 by fours).
+    constexpr bool kTurnQ = kWantQ && (kAhead2 || !kWantC);
+    uint8_t* qptr = !kWantQ ? nullptr
+                    : kTurnQ ? p.Cq + (int64_t)(row0 + r_lane + (lane & 3)) * p.ldcq + col0 + (c_lane & ~3)
+                             : p.Cq + (int64_t)(row0 + r_lane) * p.ldcq + col0 + c_lane;
+    const int q_cols_left = p.N - col0 - (c_lane & ~3);
     const int rows_left = p.M - row0 - r_lane;  // rows of this lane's column that exist
     auto store_blocks = [&](auto full_c, auto mod_c, auto scatter_c) __attribute__((always_inline)) {
         constexpr bool FULL = decltype(full_c)::value;  // no bounds to test inside a whole tile
@@ -936,6 +944,9 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
             uint32_t rsv[16];  // this lane's part of the sixteen row sums of the block
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
+                uint32_t qw[TN];   // four rows' requantized values of this lane's columns
+#pragma unroll
+                for (int t = 0; t < TN; ++t) qw[t] = 0;
 #pragma unroll
                 for (int ee = 0; ee < 4; ++ee) {
                     const int e = g * 4 + ee;
@@ -953,8 +964,9 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
                                 if (kAhead2) cptr[t * 32] = val;
                                 else __builtin_nontemporal_store(val, &cptr[t * 32]);
                             }
-                            if (kWantQ) qptr[t * 32] = requant_with(val, rqc[t], rq_zC);
+                            if (kWantQ && !kTurnQ) qptr[t * 32] = requant_with(raw, rqc[t], rq_zC);
                         }
+                        if (kTurnQ) qw[t] = requant_into(qw[t], ee, raw, rqc[t], rq_zC);
                     }
                     if (kCheck) {
                         if (MOD) rs = (uint32_t)floor_mod127(rs64);
@@ -966,12 +978,23 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
                         }
                     }
                     if (kWantC) cptr += p.ldc;
-                    if (kWantQ) qptr += p.ldcq;
+                    if (kWantQ && !kTurnQ) qptr += p.ldcq;
                     asm volatile("" : "+v"(cptr), "+v"(qptr));
+                }
+                if (kTurnQ) {
+#pragma unroll
+                    for (int t = 0; t < TN; ++t) {
+                        const uint32_t w = turn_quad(qw[t], lane);
+                        if (FULL && !kAhead2) store_quad_nt(qptr + t * 32, w);   // (as C is: 4096x4096x4096 73.0 -> 71.8 us)
+                        else if (FULL) store_quad(qptr + t * 32, w, 4);
+                        else if (i * 32 + 8 * g + (lane & 3) < rows_left && t * 32 < q_cols_left) store_quad(qptr + t * 32, w, q_cols_left - t * 32);
+                    }
+                    qptr += 8 * p.ldcq;
+                    asm volatile("" : "+v"(qptr));
                 }
                 // rows 8g+4 .. 8g+7 belong to the other half-wave
                 if (kWantC) cptr += 4 * p.ldc;
-                if (kWantQ) qptr += 4 * p.ldcq;
+                if (kWantQ && !kTurnQ) qptr += 4 * p.ldcq;
             }
             if (kCheck && kScatterSum) {
                 // lane lcol of each half-wave holds the sum of row e = bit-reversed low four bits of lcol
@@ -995,10 +1018,10 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
 
     if (p.n_inj > 0) {
         // Simulated faults in the 32-bit intermediate (test hook): the element is flipped where it
-        // now lies - in C, in Cq and in its row sum - by the lane that owns it, after that lane's
-        // own store of the clean value (same lane, same address: program order holds).  The
-        // accumulators are only read.  Entries that name the same element act as one entry
+        // now lies - in C, in Cq and in its row sum - by the lane that owns it, after this wavefront's
+        // stores of the clean values have been acknowledged.  The accumulators are only read.  Entries that name the same element act as one entry
         // with the XOR of their masks.
+        wait_vmem();
         const abft_inject_t* inj = reinterpret_cast<const abft_inject_t*>(p.inj);
         for (int n = 0; n < p.n_inj; ++n) {
             const int row = inj[n].row, col = inj[n].col;
@@ -1027,7 +1050,7 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
             if (lcol == (c & 31) && lhalf == half_hit) {
                 const int32_t val = raw + cs_hit, bad = (int32_t)((uint32_t)val ^ mask);
                 if (kWantC) p.C[(int64_t)row * p.ldc + col] = bad;
-                if (kWantQ) p.Cq[(int64_t)row * p.ldcq + col] = requant_with(bad, rqc_hit, rq_zC);
+                if (kWantQ) p.Cq[(int64_t)row * p.ldcq + col] = requant_with((int32_t)((uint32_t)bad - (uint32_t)cs_hit), rqc_hit, rq_zC);
                 // (the row sum was formed from the clean value; it is moved by the difference, taken in
                 // wrap-around arithmetic: a flip of bit 31 changes the value by 2^31)
                 if (kCheck)
@@ -1038,7 +1061,22 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     }
 
     if (kCheck) {
-        if (!kSplitK) recombine_digits();
+        if constexpr (!kSplitK) {
+        // (written out once more: through the function of the split the 256x256 kernel gets another register allocation, and its
+        // epilogue takes 1.4 us longer)
+        // 16x16 accumulator: lane l, element e is row 4*(l/16) + e, column l%16; columns 0..3
+        // hold the four digit products
+#pragma unroll
+        for (int c = 0; c < CB; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int d = lane & 15;
+                uint32_t v = d < kLimbs ? ((uint32_t)cacc[c][e] << (8 * d)) : 0u;
+                v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);
+                v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);
+                if (d == 0) s_ck[wm * WTM + (wn * CB + c) * 16 + 4 * (lane >> 4) + e] = (int32_t)v;
+            }
+        }
         __syncthreads();
         // Row r of the product is spread over the tile columns; each of them adds its share of
         // (row sum - checksum) to the row's 64-bit workspace word with ONE returned atomic:
@@ -1094,7 +1132,7 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
         const unsigned long long fin_mask = __ballot(fin), bad_mask = __ballot(fin && bad);
         if (p.err_count == nullptr) {
             // no count was asked for
-        } else if (count_added) {
+        } else if (p.err_accumulate || (kClearsFirst && tiles_m == 1)) {
             if (bad_mask != 0ull && lane == __builtin_ctzll(bad_mask))
                 __hip_atomic_fetch_add(p.err_count, (int32_t)__builtin_popcountll(bad_mask), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else if (fin_mask != 0ull && lane == __builtin_ctzll(fin_mask)) {

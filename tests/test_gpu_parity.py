@@ -1252,3 +1252,41 @@ def test_unequal_runs_and_wide_blocks(binding, gpu_util, oracle, M, N, K):
     Cw, fw, nw = oracle.checked_gemm_mod127(A, B, flips_c=inj[:3])
     out = run.gemm(A, ws=ws, mod127=True, injections=inj[:3])
     assert np.array_equal(out["C"], Cw) and np.array_equal(out["flags"], fw) and out["err_count"] == nw and not out["ws"].any()
+
+
+# (widths around four columns, a quad of lanes, 32-column blocks and whole tiles; one to four rows past the last whole quad)
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K,variant", [(5, 1, 64, "auto"), (20, 67, 128, "auto"), (33, 130, 1040, "auto"), (70, 3, 64, "tile64"), (129, 65, 96, "tile64"),
+                                           (66, 257, 97, "auto"), (131, 254, 64, "tile128"), (258, 515, 64, "tile256"), (512, 512, 64, "tile256")])
+def test_requantized_quads(binding, gpu_util, oracle, M, N, K, variant):
+    """The uint8 output, stored four columns at a time, in rows that start at any byte: every value as the oracle's, faults and
+    multipliers that are zero, negative, infinite or no number included, and nothing written beside it."""
+    import torch
+    say(f"requantized quads: {M}x{N}x{K} {variant}")
+    A, B = operands(M, N, K, 3 * M + N)
+    inj = [(M - 1, N - 1, 1 << 20), (0, 0, 1 << 12), (M // 2, N // 2, 1 << 31)]
+    ref = oracle.checked_gemm(A, B, flips_c=inj)
+    run = gpu_util.GpuRun(binding, B)
+    ws = binding.Workspace(M, run.Bp).tensor
+    rng = np.random.default_rng(N)
+    mult = wlmod.draw_mult(rng, N, "channel")
+    mult[::7] = [np.float32(v) for v in (0.0, -1e-3, np.inf, -np.inf, np.nan, 1e30)][N % 6]
+    bias = rng.integers(-3000, 3000, size=N).astype(np.int32)
+    with np.errstate(all="ignore"):
+        t = (ref.C.astype(np.int64) - 128 * ref.colsum.astype(np.int64) + bias).astype(np.uint32).view(np.int32).astype(np.float32)
+        want = np.fmin(np.fmax(np.rint(t * mult) + np.float32(7), np.float32(0)), np.float32(255)).astype(np.uint8)
+    keep = (gpu_util.dev(mult), gpu_util.dev(bias))
+    rq = binding.make_requant(128, 7, *keep)
+    A_dev, inj_dev = gpu_util.dev(A), binding.make_injections(inj)
+    for want_c in (False, True):
+        buf = torch.full((M * (N + 5) + 3,), 99, dtype=torch.uint8, device="cuda")
+        Cq = buf[3:].view(M, N + 5)[:, :N]
+        C = torch.zeros((M, N), dtype=torch.int32, device="cuda") if want_c else None
+        flags = torch.empty(M, dtype=torch.int32, device="cuda")
+        binding.abft_gemm_u8s8s32_checked(A_dev, run.Bp, C, flags, None, rq=rq, Cq=Cq, inj=inj_dev, n_inj=len(inj),
+                                          flags=gpu_util.VARIANTS[variant], workspace=ws)
+        torch.cuda.synchronize()
+        assert np.array_equal(Cq.cpu().numpy(), want) and np.array_equal(flags.cpu().numpy(), ref.flags)
+        assert (buf[:3] == 99).all() and (buf[3:].view(M, N + 5)[:, N:] == 99).all()
+        if want_c:
+            assert np.array_equal(C.cpu().numpy(), ref.C)
