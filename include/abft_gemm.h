@@ -147,14 +147,14 @@ typedef struct {
  * with Bp given, also room for the partial tiles of a K split across
  * workgroups on the shapes where the library uses one (few tiles, K of about
  * 5000 and more), and for a copy of A with padded rows where K is no multiple
- * of 16 and the product is large enough for the copy to pay (Bp == NULL, or a
- * smaller workspace of at least the size this call returns for Bp == NULL,
- * runs every shape without them).
+ * of 16 and the product is large enough for the copy to pay.  Such room is used
+ * wherever the workspace holds it, whatever it was sized for; a smaller one, of
+ * at least the size that this call returns for Bp == NULL, runs without it, with
+ * the same results.
  * The memory must be zero before its first use (abft_workspace_init) and every
  * call leaves its words zero again, so one workspace serves any number of calls
- * that are ordered on one stream, of different sizes too (one that has served
- * calls with such room must not be used for more than 131072 rows afterwards
- * without being zeroed).  Calls that may overlap need one workspace each. */
+ * that are ordered on one stream, of different sizes too.  Calls that may
+ * overlap need one workspace each. */
 size_t abft_gemm_workspace_bytes(int M, const abft_packed_b* Bp);
 int abft_workspace_init(void* workspace, size_t bytes, void* stream);
 

@@ -168,7 +168,8 @@ inline size_t ws_base_ints(int M) {
 
 // What some calls need beyond those words - the tile tickets and partial tiles of a K split, a copy of A with padded rows -
 // lies behind the words of any call of up to kWsRows rows, so that one workspace can serve calls of different sizes: the
-// words (tickets among them) are zero between calls, the scratch behind them holds whatever the last call left.
+// words (tickets among them) are zero between calls, the scratch behind them holds whatever the last call left (a call of more
+// rows, whose words reach into it, zeroes that part first: launch_gemm_tile).
 constexpr int kWsRows = 131072;
 constexpr size_t kWsTicketsOff = (size_t)kWsHeaderInts + 2 * (size_t)kWsRows;
 constexpr size_t kWsTickets = 1024;

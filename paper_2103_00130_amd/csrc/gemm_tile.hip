@@ -19,10 +19,14 @@ hipError_t launch_gemm_tile(int variant, bool check, bool want_c, bool want_q, c
     // direct-to-LDS kernels need whole, aligned 16-byte chunks of A
     // (and 32-bit byte offsets into A)
     const bool fast_a = p.a_vec_ok && (p.K % 16 == 0) && ((int64_t)(p.M - 1) * p.lda + p.K <= 0x7fffffffll);
-    if (!fast_a) {
-        if (p.mod127) return hipErrorNotSupported;
-        return launch_gemm_tile_g64(check, want_c, want_q, p, s);   // (whichever tile was asked for: the results are the same)
+    if (!fast_a && p.mod127) return hipErrorNotSupported;
+    // The row words of more than about kWsRows rows reach into the scratch that earlier calls on this workspace may have left
+    // a K split's partial tiles or a padded copy of A in, so that part of them is zeroed first (one small launch, 2 us).
+    if (check && ws_base_ints(p.M) > kWsScratchOff) {
+        const hipError_t e = launch_fill_zero(p.ws + kWsScratchOff, ws_base_ints(p.M) - kWsScratchOff, s);
+        if (e != hipSuccess) return e;
     }
+    if (!fast_a) return launch_gemm_tile_g64(check, want_c, want_q, p, s);   // (whichever tile was asked for: the results are the same)
     switch (variant) {
         case kTile256: return launch_gemm_tile_a256(check, want_c, want_q, p, s);
         case kTile128: return launch_gemm_tile_a128(check, want_c, want_q, p, s);

@@ -1142,6 +1142,34 @@ def test_one_workspace_for_calls_of_different_sizes(binding, gpu_util, oracle):
         assert np.array_equal(out["C"], ref.C) and np.array_equal(out["flags"], ref.flags) and out["err_count"] == 1
 
 
+@pytest.mark.gpu
+def test_many_rows_after_calls_that_left_scratch(binding, gpu_util, oracle):
+    """Row words beyond 131072 rows lie where a K split's partial tiles and a padded copy of A are left: a call of that many
+    rows starts from zeros all the same, overwriting and adding to errCount, and leaves zeros."""
+    import torch
+    M, N, K = 150000, 258, 32
+    A, B = operands(M, N, K, 5)
+    inj = [(M - 1, 1, 1 << 20), (131600, N - 1, 1 << 3), (7, 0, 1 << 31)]
+    ref, refi = oracle.checked_gemm(A, B), oracle.checked_gemm(A, B, flips_c=inj)
+    run, A_dev = gpu_util.GpuRun(binding, B), gpu_util.dev(A)
+
+    class Shared:
+        tensor = torch.zeros(400064, dtype=torch.int32, device="cuda")   # what 200000 rows need without a weight
+    for m, n, k in ((128, 64, 3072), (500, 4160, 1001)):
+        a, b = operands(m, n, k, m)
+        small = gpu_util.GpuRun(binding, b)
+        want = oracle.checked_gemm(a, b)
+        out = small.gemm(a, ws=Shared)
+        assert np.array_equal(out["C"], want.C) and not out["flags"].any() and out["err_count"] == 0
+        assert Shared.tensor[263232:].any(), "the call left no scratch: this test has lost its point"
+        out = run.gemm(A_dev, ws=Shared)
+        assert np.array_equal(out["C"], ref.C) and not out["flags"].any() and out["err_count"] == 0
+        assert not Shared.tensor[:64 + 2 * M].any()
+        out = small.gemm(a, ws=Shared)
+        out = run.gemm(A_dev, ws=Shared, injections=inj, accumulate_from=4)
+        assert np.array_equal(out["flags"], refi.flags) and out["err_count"] == 4 + refi.err_count
+
+
 # (edges of the 16-byte chunk, of the 128 x 256 tile that a workgroup packs, rows shorter than a chunk)
 @pytest.mark.gpu
 @pytest.mark.parametrize("transposed", [False, True])
