@@ -27,6 +27,7 @@
 
 #include "../../include/abft_eb.h"
 #include "abft_internal.h"
+#include "eb_choice.h"
 
 struct abft_eb_table {
     uint8_t* rec;    // rows * stride bytes: [codes][scale f32][bias f32][C_T i32][unused]
@@ -531,24 +532,6 @@ __global__ __launch_bounds__(W * 64) void eb_group_kernel(const EbParams p) {
     }
 }
 
-// What runs a call: the batch kernel, or the group kernel with 1, 2 or 4 wavefronts per lookup.
-enum EbKernel { kEbBatch = 0, kEbGroup1 = 1, kEbGroup2 = 2, kEbGroup4 = 4 };
-
-// The choice by the number of lookups and of rows per lookup on average (us, all rows 80 bytes unless said otherwise:
-// batch / 4 / 2 / 1 wavefronts).  Few lookups: the latency of one counts and four wavefronts fetch more of it at once (300 of
-// 30 rows 10.7 / 3.5 / 3.5 / 3.6; 600 of 60: 24.4 / 4.8 / 5.0 / 5.2; 10 of 100: 25.7 / 4.6 / 5.1 / 5.9), except for narrow rows
-// of which there are hardly enough for one (300 of 5: 3.8 / 3.1 / 2.9 / 2.7).  Many lookups: what counts is how many are
-// under way, and one wavefront each, without barriers and idle threads, takes the short ones (4000 of 16: 10.5 / 10.0 / 6.3 /
-// 5.1; 9000 of 27: 18.4 / 22.0 / 12.4 / 12.3), two the long ones (3000 of 60, ragged: 78 / 14.2 / 12.3 / 13.2; records of 272
-// bytes, 1500 of 100: 40 / 19.9 / 16.4 / 18.3; 16384 of 100: 66 / 70 / 56.6 / 56.7).  Very many lookups of a handful of rows: a few
-// lanes per lookup (8000 of 4: 4.7 / 12.8 / 7.2 / 5.9; 16384 of 10: 10.8 / 32 / 15.8 / 14.1; 80000 of 20: 74 / 176 / 82 / 78).
-EbKernel pick_kernel(int64_t n_bags, int64_t n_indices, int pieces) {
-    const int64_t avg = n_indices / n_bags;
-    if (avg <= 5 ? n_bags >= 6000 : (avg <= 10 && n_bags >= 16000)) return kEbBatch;
-    if (n_bags < 1000) return avg <= 16 && pieces <= 4 ? kEbGroup1 : kEbGroup4;
-    return avg <= 45 && pieces <= 16 ? kEbGroup1 : kEbGroup2;
-}
-
 template <int G, int BITS>
 hipError_t launch_g(EbKernel kernel, bool check, bool weighted, const EbParams& p, hipStream_t s) {
     // one set of rows per lane only where the rows are wide and the launch has at least four wavefronts
@@ -737,11 +720,11 @@ int abft_eb_u8_checked(const abft_eb_table* Tp, const int64_t* indices, int64_t 
     if (variant != 0 && variant != ABFT_EB_VARIANT_BATCH && variant != ABFT_EB_VARIANT_GROUP)
         return abft::set_error(ABFT_EINVAL, "%s: unknown variant %#x", fn, variant);
     const int G = Tp->code_bytes / 16;
-    if (n_bags > 0x7fffffffll || (n_bags * G + 255) / 256 > 0x7fffffffll)
+    const bool few = n_bags <= 0x7fffffffll;
+    const abft::EbKernel kernel = variant == ABFT_EB_VARIANT_GROUP ? abft::kEbGroup4
+                                  : variant == ABFT_EB_VARIANT_BATCH || !few ? abft::kEbBatch : abft::eb_pick_kernel(n_bags, n_indices, G);
+    if (!few || abft::eb_work_items(kernel, n_bags, G) > abft::kEbMaxWorkItems)
         return abft::set_error(ABFT_EUNSUPPORTED, "%s: n_bags=%lld too large for one launch", fn, (long long)n_bags);
-    abft::EbKernel kernel = abft::pick_kernel(n_bags, n_indices, G);
-    if (variant == ABFT_EB_VARIANT_BATCH) kernel = abft::kEbBatch;
-    if (variant == ABFT_EB_VARIANT_GROUP) kernel = abft::kEbGroup4;
     abft::EbParams p;
     p.tab = Tp->rec;
     p.stride = Tp->stride;

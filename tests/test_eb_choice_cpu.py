@@ -1,0 +1,33 @@
+"""The rule that chooses the kernel of a checked EmbeddingBag call (csrc/eb_choice.h, host code only), built here on its own."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2103_00130_amd", "csrc")
+BATCH, GROUP1, GROUP2, GROUP4 = 0, 1, 2, 4
+MOST = 2 ** 32 - 1      # work-items of one launch
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("rule") / "rule.so")
+    src = ('#include "eb_choice.h"\nextern "C" int pick(long long n, long long i, int p) { return abft::eb_pick_kernel(n, i, p); }\n'
+           'extern "C" long long items(int k, long long n, int p) { return abft::eb_work_items((abft::EbKernel)k, n, p); }\n')
+    subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", f"-I{CSRC}", "-x", "c++", "-", "-o", lib],
+                   input=src, text=True, check=True)
+    so = ctypes.CDLL(lib)
+    so.pick.argtypes, so.items.argtypes, so.items.restype = [ctypes.c_longlong] * 2 + [ctypes.c_int], [ctypes.c_int, ctypes.c_longlong, ctypes.c_int], ctypes.c_longlong
+    return so
+
+
+@pytest.mark.parametrize("pieces", [1, 2, 4, 8, 16, 32])
+def test_no_launch_is_too_large(rule, pieces):
+    """Whatever the batch kernel can run is run: never a kernel whose launch would have 2^32 work-items or more."""
+    for n in [1, 999, 16000] + [2 ** e + o for e in range(20, 31) for o in (-1, 0, 1)]:
+        for mean in (0, 1, 5, 6, 10, 11, 12, 16, 20, 30, 45, 46, 100, 1000):
+            chosen = rule.pick(n, n * mean, pieces)
+            assert chosen in (BATCH, GROUP1, GROUP2, GROUP4)
+            if rule.items(BATCH, n, pieces) <= MOST:
+                assert rule.items(chosen, n, pieces) <= MOST, (n, mean)

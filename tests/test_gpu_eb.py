@@ -347,6 +347,31 @@ def test_table_beyond_4_gib(b):
     Tp.destroy()
 
 
+@pytest.mark.parametrize("n_bags,mean", [(2 ** 25 + 3, 47), (2 ** 26 + 3, 30)])
+def test_more_lookups_than_wavefronts_in_a_launch(b, n_bags, mean):
+    """So many lookups that one or two wavefronts each would be more work-items than a launch takes: the call runs all the same,
+    and the variant that asks for four each is refused.  (The index array has `mean` entries per lookup, one of them pooled.)"""
+    rows, d = 1000, 16
+    g = torch.Generator("cuda").manual_seed(n_bags)
+    T = torch.randint(0, 256, (rows, d), dtype=torch.uint8, device="cuda", generator=g)
+    scale, bias = torch.rand(rows, device="cuda", generator=g), torch.rand(rows, device="cuda", generator=g) - 0.5
+    Tp = b.abft_eb_pack_rowsum(T, scale, bias)
+    indices = torch.zeros(n_bags * mean, dtype=torch.int64, device="cuda")
+    indices[:n_bags] = torch.randint(0, rows, (n_bags,), device="cuda", generator=g)
+    offsets = torch.arange(n_bags + 1, device="cuda")
+    R, flags = torch.empty(n_bags, d, device="cuda"), torch.empty(n_bags, dtype=torch.int32, device="cuda")
+    with pytest.raises(b.AbftError) as e:
+        b.abft_eb_u8_checked(Tp, indices, offsets, R, flags, flags=VARIANTS["group"])
+    assert e.value.code == b.ABFT_EUNSUPPORTED
+    b.abft_eb_u8_checked(Tp, indices, offsets, R, flags)
+    torch.cuda.synchronize()
+    assert not flags.any()
+    rows_f32 = scale[:, None] * T.float() + bias[:, None]      # (one row: a product and a sum, each rounded once)
+    for at in range(0, n_bags, 1 << 22):
+        assert torch.equal(R[at:at + (1 << 22)], rows_f32[indices[at:min(at + (1 << 22), n_bags)]])
+    Tp.destroy()
+
+
 # (numbers of lookups and mean lengths on either side of every line of the choice; the lengths themselves sit at the edges
 # of the eight rows that are pooled at a time and of the chunks that are staged)
 @pytest.mark.parametrize("n_bags,mean", [(999, 10), (40, 30), (999, 17), (1000, 40), (1000, 60), (6000, 4), (16000, 9), (5999, 5)])
