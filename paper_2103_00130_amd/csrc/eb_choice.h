@@ -20,10 +20,26 @@ constexpr int64_t kEbMaxWorkItems = 0xffffffffll;
 // under way, and one wavefront each, without barriers and idle threads, takes the short ones (4000 of 16: 10.5 / 10.0 / 6.3 /
 // 5.1; 9000 of 27: 18.4 / 22.0 / 12.4 / 12.3), two the long ones (3000 of 60, ragged: 78 / 14.2 / 12.3 / 13.2; records of 272
 // bytes, 1500 of 100: 40 / 19.9 / 16.4 / 18.3; 16384 of 100: 66 / 70 / 56.6 / 56.7).  Very many lookups of a handful of rows: a few
-// lanes per lookup (8000 of 4: 4.7 / 12.8 / 7.2 / 5.9; 16384 of 10: 10.8 / 32 / 15.8 / 14.1; 80000 of 20: 74 / 176 / 82 / 78).
+// lanes per lookup (8000 of 4: 4.7 / 12.8 / 7.2 / 5.9; 16384 of 10: 10.8 / 32 / 15.8 / 14.1).
+// With more lookups yet that holds for longer ones too: kEbBatchLines, by the width of a row (us, batch / 1 / 2 wavefronts,
+// lengths between half and one and a half times the mean: 16 bytes of codes, 49152 lookups of 13 25.6 / 27.6 / 40, of 16 30.5 /
+// 29.2 / 41, 196608 of 16 101 / 109 / 160, of 20 128 / 119 / 167; 32 bytes, 32768 of 13 18.6 / 20.4 / 29, of 20 25.5 / 25.2 / 32;
+// 64 bytes, 65536 of 20 61 / 65 / 68, 98304 of 13 63 / 80 / 89, of 20 91 / 96 / 100, of 25 108 / 108 / 110; 128 bytes, 262144 of 16
+// 262 / 270 / 323, of 20 320 / 311 / 361; 512 bytes, 16384 of 13 41.6 / 44.5 / 41.9, 65536 of 20 206 / 213 / 210, of 25 246 / 249 / 244).
+// Lengths all alike gain more from it (64 bytes, 98304 of 12: 55 / 80), very different ones lose (128 bytes, 262144 of 14,
+// geometric: 289 / 232), and the host does not know which they are.  Rows of 256 bytes have no line: 16384 of 12, 22.0 / 23.3 at
+// best, 13 24.6 / 23.2, geometric 34 / 25.
+struct EbBatchLine {
+    int pieces;        // rows of so many pieces: ...
+    int64_t lookups;   // from so many lookups on ...
+    int mean;          // ... up to such a mean length
+};
+constexpr EbBatchLine kEbBatchLines[] = {{1, 49152, 15}, {1, 196608, 17}, {2, 32768, 17}, {4, 65536, 22}, {8, 262144, 17}, {32, 16384, 13}, {32, 65536, 22}};
 inline EbKernel eb_pick_kernel(int64_t n_bags, int64_t n_indices, int pieces) {
     const int64_t avg = n_indices / n_bags;
     if (avg <= 5 ? n_bags >= 6000 : (avg <= 10 && n_bags >= 16000)) return kEbBatch;
+    for (const EbBatchLine& l : kEbBatchLines)
+        if (pieces == l.pieces && n_bags >= l.lookups && avg <= l.mean) return kEbBatch;
     if (n_bags < 1000) return avg <= 16 && pieces <= 4 ? kEbGroup1 : kEbGroup4;
     // fewer wavefronts where that many lookups make more work-items than a launch takes, a few lanes where one is too many too
     EbKernel kernel = avg <= 45 && pieces <= 16 ? kEbGroup1 : kEbGroup2;

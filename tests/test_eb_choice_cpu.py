@@ -31,3 +31,12 @@ def test_no_launch_is_too_large(rule, pieces):
             assert chosen in (BATCH, GROUP1, GROUP2, GROUP4)
             if rule.items(BATCH, n, pieces) <= MOST:
                 assert rule.items(chosen, n, pieces) <= MOST, (n, mean)
+
+
+# (rows of 16, 32, 64, 128 and 512 bytes where a few lanes per lookup measured faster than a wavefront, and where they did not)
+@pytest.mark.parametrize("pieces,n,mean,batch", [(1, 49152, 13, True), (1, 49152, 16, False), (1, 196608, 16, True), (1, 196608, 20, False), (2, 32768, 16, True),
+                                                 (2, 32768, 25, False), (4, 80000, 20, True), (4, 98304, 12, True), (4, 98304, 25, False), (4, 16384, 12, False),
+                                                 (8, 262144, 16, True), (8, 65536, 20, False), (16, 16384, 13, False), (32, 16384, 12, True),
+                                                 (32, 16384, 16, False), (32, 65536, 20, True), (32, 65536, 32, False)])
+def test_large_batches_of_longer_lookups(rule, pieces, n, mean, batch):
+    assert (rule.pick(n, n * mean, pieces) == BATCH) == batch
