@@ -247,6 +247,7 @@ int abft_gemm_u8s8s32_checked(const uint8_t* A, int64_t lda, int M, const abft_p
 
     int variant = (int)((flags & ABFT_VARIANT_MASK) >> 8);
     const bool chosen = variant != 0;
+    if (variant >= abft::kVariantEnd) return fail(ABFT_EINVAL, "%s: unknown variant %d", fn, variant);
     auto pick_tile = [&]() {
         // The larger the tile the better the matrix cores are fed, but a grid that leaves most of the
         // 256 compute units without a workgroup loses more than that: thresholds from timing the
@@ -286,10 +287,8 @@ int abft_gemm_u8s8s32_checked(const uint8_t* A, int64_t lda, int M, const abft_p
         e = abft::launch_gemm_smallm(!chosen, check, want_c, want_q, p, (hipStream_t)stream);
         if (e == hipErrorNotSupported && !chosen)  // rows shorter than a 16-byte chunk: the tiled path takes them
             e = abft::launch_gemm_tile(pick_tile(), check, want_c, want_q, p, (hipStream_t)stream);
-    } else if (variant >= abft::kTile256 && variant < abft::kVariantEnd) {
-        e = abft::launch_gemm_tile(variant, check, want_c, want_q, p, (hipStream_t)stream);
     } else {
-        return fail(ABFT_EINVAL, "%s: unknown variant %d", fn, variant);
+        e = abft::launch_gemm_tile(variant, check, want_c, want_q, p, (hipStream_t)stream);
     }
     if (e == hipErrorNotSupported) return fail(ABFT_EUNSUPPORTED, "%s: variant %d is not available", fn, variant);
     if (e != hipSuccess) return hip_fail(e, fn);

@@ -1200,6 +1200,21 @@ def test_pack_of_strided_weights(binding, gpu_util, oracle, K, N, transposed):
 
 
 @pytest.mark.gpu
+def test_refused_variant_enqueues_nothing(binding, gpu_util):
+    """An unknown variant on rows that a copy would be made of: refused, and the workspace stays as it was."""
+    import torch
+    A, B = operands(500, 4160, 1001, 3)
+    run = gpu_util.GpuRun(binding, B)
+    ws = binding.Workspace(500, run.Bp).tensor
+    C, flags = torch.zeros((500, 4160), dtype=torch.int32, device="cuda"), torch.zeros(500, dtype=torch.int32, device="cuda")
+    with pytest.raises(binding.AbftError) as e:
+        binding.abft_gemm_u8s8s32_checked(gpu_util.dev(A), run.Bp, C, flags, None, flags=0x700, workspace=ws)
+    assert e.value.code == binding.ABFT_EINVAL
+    torch.cuda.synchronize()
+    assert ws.numel() > 263232 and not ws.any() and not C.any()
+
+
+@pytest.mark.gpu
 def test_operands_of_the_native_call(binding, gpu_util, oracle):
     """The natively marshalled call takes what the Python code takes - views, single rows, an explicit stream, no errCount -
     and leaves to it, errors and all, what it does not."""
