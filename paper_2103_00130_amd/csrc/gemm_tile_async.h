@@ -258,8 +258,29 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
 #pragma unroll
         for (int j = 0; j < B_LD; ++j) rb[j] = *reinterpret_cast<const v4i*>(base + j * 1024);
     };
+
+    // ---- fragment reads -----------------------------------------------------------
+    // A fragment (block i, k-step j): lane l holds row wm*WTM + i*32 + (l&31), chunk 2j + (l>>5)
+    const int a_swz = (lane >> 1) & 7;
+    int a_off[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) a_off[j] = (wm * WTM + (lane & 31)) * BK + (((2 * j + (lane >> 5)) ^ a_swz) << 4);
+    const int b_off = S * A_STAGE + wn * TN * 2048 + lane * 16;
+
+    v16i acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0;
+    v4i cacc[CB];
+#pragma unroll
+    for (int i = 0; i < CB; ++i) cacc[i] = v4i{0, 0, 0, 0};
     // column sums of the B bytes streamed (every wave keeps them for its own columns; with loads through registers for
     // the columns it copies, which are the same, wm telling the two k-blocks of a stage apart)
+    // (declared behind the accumulators: ahead of them the compiler allocates registers in another order, which cost the
+    // 256x256 kernel 1 us at its end - 4096x4096x4096 67.5 us checked, 66.5 this way, 4096x4096x1024 29.3 and 28.3)
     uint32_t bsum[TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j) bsum[j] = 0;
@@ -287,24 +308,6 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
         for (int j = 0; j < B_LD; ++j) *reinterpret_cast<v4i*>(smem + (b_lds - lds_base) + buf * B_STAGE + j * 1024 + b_voff) = rb[j];
     };
 
-    // ---- fragment reads -----------------------------------------------------------
-    // A fragment (block i, k-step j): lane l holds row wm*WTM + i*32 + (l&31), chunk 2j + (l>>5)
-    const int a_swz = (lane >> 1) & 7;
-    int a_off[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) a_off[j] = (wm * WTM + (lane & 31)) * BK + (((2 * j + (lane >> 5)) ^ a_swz) << 4);
-    const int b_off = S * A_STAGE + wn * TN * 2048 + lane * 16;
-
-    v16i acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0;
-    v4i cacc[CB];
-#pragma unroll
-    for (int i = 0; i < CB; ++i) cacc[i] = v4i{0, 0, 0, 0};
 
     // Small wave tiles (at most four MFMAs per k-step) read their fragments two k-steps ahead: one
     // k-step of such a tile is shorter than the latency of an LDS read, so with one k-step of
@@ -1021,7 +1024,7 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
         // now lies - in C, in Cq and in its row sum - by the lane that owns it, after this wavefront's
         // stores of the clean values have been acknowledged.  The accumulators are only read.  Entries that name the same element act as one entry
         // with the XOR of their masks.
-        wait_vmem();
+        if (kTurnQ) wait_vmem();   // (else the lane that owns the element stored it itself)
         const abft_inject_t* inj = reinterpret_cast<const abft_inject_t*>(p.inj);
         for (int n = 0; n < p.n_inj; ++n) {
             const int row = inj[n].row, col = inj[n].col;
