@@ -926,22 +926,26 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     }
     const int32_t rq_zC = kWantQ ? p.rq.zC : 0;
     int32_t* cptr = kWantC ? p.C + (int64_t)(row0 + r_lane) * p.ldc + col0 + c_lane : nullptr;
-    // Cq: four columns of one row per lane (turn_quad), this lane's row among four being lane & 3: 2000x1000x480 8.0 -> 6.4 us
-    // without C, 9.2 -> 7.9 with it, 4096x2048x512 18.6 -> 16.9.  The 128x128 wave tile that stores C as well goes byte by
-    // byte between the stores of C, which take the time anyway and leave no registers for four rows (4096x4096x1024
-    // 33.4 us, 34.9 by fours).
-    constexpr bool kTurnQ = kWantQ && (kAhead2 || !kWantC);
-    uint8_t* qptr = !kWantQ ? nullptr
-                    : kTurnQ ? p.Cq + (int64_t)(row0 + r_lane + (lane & 3)) * p.ldcq + col0 + (c_lane & ~3)
-                             : p.Cq + (int64_t)(row0 + r_lane) * p.ldcq + col0 + c_lane;
+    uint8_t* qptr = kWantQ ? p.Cq + (int64_t)(row0 + r_lane) * p.ldcq + col0 + c_lane : nullptr;
     const int q_cols_left = p.N - col0 - (c_lane & ~3);
     const int rows_left = p.M - row0 - r_lane;  // rows of this lane's column that exist
+    // Cq by fours: four columns of one row per lane (turn_quad), this lane's row among four being lane & 3.  The small wave tiles
+    // store that way always (2000x1000x480 8.0 -> 6.4 us without C, 9.2 -> 7.9 with it).  The 128x128 wave tile that stores Cq
+    // alone does where a tile is cut off, whose single bytes under a mask take long (4096x4093x512 43.0 us, 29.2 by fours), and
+    // in block form, where the grid does not fill the chip (3072x3072x3072 42.1 / 40.1); whole tiles of a full grid and unchecked
+    // ones go byte by byte, neighbouring lanes to neighbouring bytes, which memory takes faster than 32 bytes of eight rows at
+    // once (4096x4096x4096 71.3 us, 76.5 by fours; x1024 31.0 / 35.1; unchecked 23.6 / 27.3).  The one that stores C as well goes
+    // byte by byte between the stores of C, which take the time anyway and leave no registers for four rows (4096x4096x1024
+    // 33.4 / 34.9).
+    constexpr auto turn_q = [](bool full_tile) { return kWantQ && (kAhead2 || (!kWantC && (!full_tile || (kCheck && kBlockSums)))); };
     auto store_blocks = [&](auto full_c, auto mod_c, auto scatter_c) __attribute__((always_inline)) {
         constexpr bool FULL = decltype(full_c)::value;  // no bounds to test inside a whole tile
         constexpr bool MOD = decltype(mod_c)::value;    // row sums as residues modulo 127 (Algorithm 1 as printed)
         // Cross-lane part of the row sums: the sixteen rows of a block together (sum32_of16), or one
         // reduction per row between the stores (see where the choice is made).
         constexpr bool kScatterSum = decltype(scatter_c)::value;
+        constexpr bool kTurnQ = turn_q(FULL);
+        if (kTurnQ) qptr += (int64_t)(lane & 3) * p.ldcq - (lane & 3);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             uint32_t rsv[16];  // this lane's part of the sixteen row sums of the block
@@ -988,7 +992,7 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
 #pragma unroll
                     for (int t = 0; t < TN; ++t) {
                         const uint32_t w = turn_quad(qw[t], lane);
-                        if (FULL && !kAhead2) store_quad_nt(qptr + t * 32, w);   // (as C is: 4096x4096x4096 73.0 -> 71.8 us)
+                        if (FULL && !kAhead2) store_quad_nt(qptr + t * 32, w);   // (as C is: 3072x3072x3072 41.0 -> 40.4 us)
                         else if (FULL) store_quad(qptr + t * 32, w, 4);
                         else if (i * 32 + 8 * g + (lane & 3) < rows_left && t * 32 < q_cols_left) store_quad(qptr + t * 32, w, q_cols_left - t * 32);
                     }
@@ -1024,7 +1028,7 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
         // now lies - in C, in Cq and in its row sum - by the lane that owns it, after this wavefront's
         // stores of the clean values have been acknowledged.  The accumulators are only read.  Entries that name the same element act as one entry
         // with the XOR of their masks.
-        if (kTurnQ) wait_vmem();   // (else the lane that owns the element stored it itself)
+        if (turn_q(false)) wait_vmem();   // (else the lane that owns the element stored it itself)
         const abft_inject_t* inj = reinterpret_cast<const abft_inject_t*>(p.inj);
         for (int n = 0; n < p.n_inj; ++n) {
             const int row = inj[n].row, col = inj[n].col;

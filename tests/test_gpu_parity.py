@@ -1333,3 +1333,30 @@ def test_requantized_quads(binding, gpu_util, oracle, M, N, K, variant):
         assert (buf[:3] == 99).all() and (buf[3:].view(M, N + 5)[:, N:] == 99).all()
         if want_c:
             assert np.array_equal(C.cpu().numpy(), ref.C)
+
+
+@pytest.mark.gpu
+def test_requantized_full_grid(binding, gpu_util, oracle):
+    """The uint8 output alone on a grid of 256 tiles of 256x256, whole ones (byte by byte) beside cut ones (by fours): checked with
+    faults in both, and unchecked, whose faults move Cq all the same; rows that start at any byte, nothing written beside them."""
+    import torch
+    M, N, K = 4094, 4093, 64
+    A, B = operands(M, N, K, 9)
+    inj = [(M - 1, N - 1, 1 << 20), (0, 0, 1 << 12), (M // 2, N // 2, 1 << 31), (700, 4092, 1 << 15), (4093, 900, 1 << 14)]
+    ref = oracle.checked_gemm(A, B, flips_c=inj)
+    mult = wlmod.draw_mult(np.random.default_rng(N), N, "channel")
+    want = oracle.requantize(ref.C, ref.colsum, 128, 7, mult, precision="f32")
+    run = gpu_util.GpuRun(binding, B)
+    ws = binding.Workspace(M, run.Bp).tensor
+    keep = gpu_util.dev(mult)
+    rq = binding.make_requant(128, 7, keep)
+    A_dev, inj_dev = gpu_util.dev(A), binding.make_injections(inj)
+    for how in (binding.ABFT_CHECK, binding.ABFT_NOCHECK):
+        buf = torch.full((M * (N + 5) + 3,), 99, dtype=torch.uint8, device="cuda")
+        Cq = buf[3:].view(M, N + 5)[:, :N]
+        flags = torch.zeros(M, dtype=torch.int32, device="cuda")
+        binding.abft_gemm_u8s8s32_checked(A_dev, run.Bp, None, flags, None, rq=rq, Cq=Cq, inj=inj_dev, n_inj=len(inj), flags=how, workspace=ws)
+        torch.cuda.synchronize()
+        assert np.array_equal(Cq.cpu().numpy(), want)
+        assert (buf[:3] == 99).all() and (buf[3:].view(M, N + 5)[:, N:] == 99).all()
+        assert np.array_equal(flags.cpu().numpy(), ref.flags if how == binding.ABFT_CHECK else np.zeros(M, np.int32))
