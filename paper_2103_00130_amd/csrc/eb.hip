@@ -270,9 +270,11 @@ __global__ __launch_bounds__(256) void eb_batch_kernel(const EbParams p) {
 // ---------------------------------------------------------------------------------------------
 // Group kernel: W wavefronts per lookup (a workgroup), rows staged through LDS.
 //  1. fetch: every thread loads different 16-byte pieces of the chunk's records (as many instructions as the chunk
-//     needs) and they are laid out in LDS record after record.  The thread that holds a record's tail piece forms the
-//     row's scalars on the way: the weighted scale and bias, each to an array of its own, and the row's term of Eq. 4,
-//     which is added up in that thread;
+//     needs) and they are laid out in LDS record after record.  The row's scalars - the weighted scale and bias, each to an
+//     array of its own, and the row's term of Eq. 4, which is added up in a thread - are formed by the thread that holds a
+//     record's tail piece where a chunk is one or two load instructions, and else by a thread per row from the staged tails:
+//     the few lanes that hold tails would go through the same forty instructions once per load instruction (W = 4, 512-byte
+//     rows, one lookup of 112: 8.0 us, 7.0 by rows; 100 of 240 rows of 256 bytes 10.4 / 9.3);
 //  2. pooling, rows in index order: threads own columns; eight rows at a time, the next eight on their way from LDS while
 //     the current ones are pooled, scales read four to an instruction.  The biases are added up in index order by a
 //     wavefront of its own (W = 1: by every lane beside its columns).
@@ -288,15 +290,23 @@ __global__ __launch_bounds__(W * 64) void eb_group_kernel(const EbParams p) {
     constexpr int P = G + 1;                   // 16-byte pieces per record
     constexpr int NL = W >= 2 ? (G >= 16 ? 8 : 4) : (G >= 32 ? 16 : (G >= 4 ? 8 : 4));   // load instructions per thread and chunk
     constexpr int PIECES = NL * NT;
-    constexpr int ROWS = PIECES / P / 8 * 8;   // whole records per chunk, in eights
+    // Whole records per chunk: with one or two wavefronts in eights, as they are pooled; with four, where a lookup's time is
+    // that of its chunks one after the other, as many as the loads fetch (512-byte rows, one lookup of 58 rows: 4.9 us in one
+    // chunk of 62, 6.6 with chunks of 56; 128 bytes, 113 rows: 4.6 / 5.7).  The rows that fill up its last eight are whatever
+    // lies there, pooled with scale 0.
+    constexpr int ROWS = W == 4 ? PIECES / P : PIECES / P / 8 * 8, ROWS8 = (ROWS + 7) / 8 * 8;
     static_assert(ROWS >= 8, "a chunk holds eight rows");
     // with four wavefronts, which run few lookups at a time, the rows of the next chunk come in while a chunk is pooled; with
-    // one or two the registers that takes are worth more as further lookups under way
-    constexpr bool kPrefetch = W == 4;
+    // one or two, and with rows of 256 bytes and more, whose chunks are eight load instructions, the registers that takes are
+    // worth more as further lookups under way (512-byte rows, 4-bit codes, 1024 lookups of 210: 46.2 us, 39.1 without; 500 of
+    // 210 28.7 / 25.9; 100 of 210 20.7 / 21.5)
+    constexpr bool kPrefetch = W == 4 && G < 16;
+    constexpr int kByRowsFrom = W >= 2 || G >= 4 ? 4 : NL + 1;   // (narrow rows in one wavefront have their tails in most lanes)
+    static_assert(ROWS8 == ROWS || kByRowsFrom <= NL, "the rows that fill up a full chunk need their zeros");
     constexpr int BPT = CB > NT ? CB / NT : 1; // code bytes per thread in the pooling phase
     constexpr int CPL = BPT * 8 / BITS;        // columns per thread
-    __shared__ v4u s_rec[PIECES];
-    __shared__ __align__(16) float s_scale[ROWS], s_bias[ROWS];
+    __shared__ v4u s_rec[ROWS8 * P > PIECES ? ROWS8 * P : PIECES];
+    __shared__ __align__(16) float s_scale[ROWS8], s_bias[ROWS8];
     __shared__ double s_rs[W], s_cs[W];
     __shared__ float s_beta;
     __shared__ int s_bad[W];
@@ -355,29 +365,51 @@ __global__ __launch_bounds__(W * 64) void eb_group_kernel(const EbParams p) {
             x.v[l] = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(p.tab + (x.ok[l] ? ix.idx[l] : 0) * p.stride + pc * 16));
         }
     };
-    auto stage = [&](const Rows& x, int n, auto l_c) __attribute__((always_inline)) {
+    // A row's scalars go to arrays of their own: the weighted scale and bias, and its term of Eq. 4 to a sum.  A row that is not
+    // pooled - a bad index, the rows that fill up the last eight - gets scale, bias and row sum 0, which leaves every accumulator
+    // as it is, bit for bit.
+    auto scalars = [&](int r, int n, bool ok, float a, float c, unsigned int c_t) __attribute__((always_inline)) {
+        const bool use = ok && r < n;
+        if (!ok && r < n) bad_any = true;
+        a = use ? a : 0.0f;
+        c = use ? c : 0.0f;
+        s_scale[r] = a;
+        s_bias[r] = c;
+        // Eq. 4, the term of one pooled row: scale * C_T + d * bias, rounded once (both products are exact in
+        // binary64).  The terms are exact to their one rounding; only the order of their sum differs from
+        // index order, by at most n * 2^-53 * sum |term|, eleven decimal orders below the bound of the comparison.
+        if (kCheck) cs = cs + fma((double)a, (double)(use ? (int32_t)c_t : 0), (double)D * (double)c);
+    };
+    auto stage = [&](const Rows& x, int n, auto l_c, auto chunk_c) __attribute__((always_inline)) {
+        const int rows8 = (n + 7) / 8 * 8;
+        constexpr bool kByRows = decltype(l_c)::value >= kByRowsFrom;
 #pragma unroll
         for (int l = 0; l < decltype(l_c)::value; ++l) {
+            if (decltype(chunk_c)::value && l > 0 && l * NT >= rows8 * P) break;   // (what a short last chunk does not need is left where it is)
             const int g = l * NT + tid, r = g / P;
-            s_rec[g] = x.v[l];
-            if (g - r * P == G && r < ROWS) {
-                // A row that is not pooled - a bad index, the rows that fill up the last eight - gets scale, bias and row
-                // sum 0, which leaves every accumulator as it is, bit for bit.
-                const bool use = x.ok[l] && r < n;
-                if (!x.ok[l] && r < n) bad_any = true;
-                float a = as_f32(x.v[l][0]), c = as_f32(x.v[l][1]);
+            const bool tail = g - r * P == G;
+            v4u v = x.v[l];
+            if constexpr (kByRows) {
                 if (kWeighted) {
-                    a = x.w[l] * a;
-                    c = x.w[l] * c;
+                    v[0] = tail ? __builtin_bit_cast(unsigned int, x.w[l] * as_f32(v[0])) : v[0];
+                    v[1] = tail ? __builtin_bit_cast(unsigned int, x.w[l] * as_f32(v[1])) : v[1];
                 }
-                a = use ? a : 0.0f;
-                c = use ? c : 0.0f;
-                s_scale[r] = a;
-                s_bias[r] = c;
-                // Eq. 4, the term of one pooled row: scale * C_T + d * bias, rounded once (both products are exact in
-                // binary64).  The terms are exact to their one rounding; only the order of their sum differs from
-                // index order, by at most n * 2^-53 * sum |term|, eleven decimal orders below the bound of the comparison.
-                if (kCheck) cs = cs + fma((double)a, (double)(use ? (int32_t)x.v[l][2] : 0), (double)D * (double)c);
+                v[3] = tail ? (unsigned int)x.ok[l] : v[3];   // (unused in memory)
+                s_rec[g] = v;
+            } else {
+                s_rec[g] = v;
+                if (tail && r < ROWS) scalars(r, n, x.ok[l], kWeighted ? x.w[l] * as_f32(v[0]) : as_f32(v[0]), kWeighted ? x.w[l] * as_f32(v[1]) : as_f32(v[1]), v[2]);
+            }
+        }
+        if constexpr (kByRows) {
+            meet();
+#pragma unroll
+            for (int k = 0; k < (ROWS8 + NT - 1) / NT; ++k) {
+                const int r = k * NT + tid;
+                if (r < rows8) {
+                    const v4u t = s_rec[r * P + G];
+                    scalars(r, n, t[3] != 0u, as_f32(t[0]), as_f32(t[1]), t[2]);
+                }
             }
         }
     };
@@ -441,7 +473,7 @@ __global__ __launch_bounds__(W * 64) void eb_group_kernel(const EbParams p) {
         Rows x;
         load_indices(ix, beg, n, l_c);
         load_rows(x, ix, l_c);
-        stage(x, n, l_c);
+        stage(x, n, l_c, std::false_type{});
         meet();
         pool(n);
     };
@@ -465,7 +497,7 @@ __global__ __launch_bounds__(W * 64) void eb_group_kernel(const EbParams p) {
         for (int64_t pos = beg;;) {
             // here the rows of this chunk and the indices of the next are in flight
             const int n = rows_at(pos);
-            stage(x, n, full_c{});
+            stage(x, n, full_c{}, std::true_type{});
             meet();
             if (kPrefetch && pos + ROWS < end) load_rows(x, ix, full_c{});
             if (kPrefetch && pos + 2 * ROWS < end) load_indices(ix, pos + 2 * ROWS, rows_at(pos + 2 * ROWS), full_c{});

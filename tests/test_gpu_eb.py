@@ -407,3 +407,40 @@ def test_every_choice_by_size(b, code_bytes, bits, n_bags, mean):
     left = np.concatenate([[0], np.cumsum(keep)])[offsets].astype(np.int64)
     ref = eb.checked_eb(T, scale, bias, indices[keep], left, weights[keep], bits=bits)
     assert same_bits(out["R"], ref.R)
+
+
+# (a chunk of four wavefronts holds 512, 341, 204, 113, 120 and 62 rows of 16, 32, .. 512 bytes, one of two wavefronts 256, 168, 96, 56,
+# 56 and 24, one of one 128, 80, 96, 56, 24 and 24: lookups of one row less and more than one and two of them; four wavefronts are
+# asked for, one and two are chosen for many lookups, short ones and long ones)
+@pytest.mark.parametrize("code_bytes,bits", [(16, 8), (32, 4), (64, 8), (64, 4), (128, 8), (256, 4), (256, 8), (512, 8), (512, 4)])
+@pytest.mark.parametrize("fill,variant", [(None, "group"), (20, "auto"), (48, "auto")])
+def test_chunk_edges(b, code_bytes, bits, fill, variant):
+    """R with the same bits as the documented order, bad indices in the first and last rows of chunks reported and left out."""
+    d = code_bytes * 8 // bits
+    G = code_bytes // 16
+    four = (8 if G >= 16 else 4) * 256 // (G + 1)
+    two = (8 if G >= 16 else 4) * 128 // (G + 1) // 8 * 8
+    one = (16 if G >= 32 else 8 if G >= 4 else 4) * 64 // (G + 1) // 8 * 8
+    n = sorted({max(m * c + o, 1) for c in (four, two, one) for m in (1, 2) for o in (-1, 0, 1, 2)})
+    if fill is not None:
+        n += [fill] * (1700 if G < 32 else 4100)
+    rng = w.rng_for(90 + code_bytes + bits, len(n))
+    rows = 3000
+    T, scale, bias = w.draw_table(rng, rows, d, "uniform", bits)
+    offsets = np.concatenate([[0], np.cumsum(n)]).astype(np.int64)
+    indices = rng.integers(0, rows, size=int(offsets[-1]), dtype=np.int64)
+    g = GpuTable(b, T, scale, bias, bits=bits)
+    for weights in (None, w.draw_weights(rng, indices.size)):
+        ref = eb.checked_eb(T, scale, bias, indices, offsets, weights, bits=bits)
+        compare(g.run(indices, offsets, weights, variant), ref, T, scale, bias, indices, offsets, weights, bits)
+    wrong = indices.copy()
+    hit = [int(offsets[3]), int(offsets[6]) - 1, int(offsets[8]) + min(four, n[8]) - 1]
+    wrong[hit] = [rows, -1, 2 ** 40]
+    out = g.run(wrong, offsets, weights, variant)
+    flagged = np.zeros(len(n), dtype=bool)
+    flagged[[3, 5, 8]] = True
+    assert np.array_equal((out["flags"] & b.ABFT_EB_BAD_INDEX) != 0, flagged)
+    keep = np.ones(indices.size, dtype=bool)
+    keep[hit] = False
+    left = np.concatenate([[0], np.cumsum(keep)])[offsets].astype(np.int64)
+    assert same_bits(out["R"], eb.checked_eb(T, scale, bias, indices[keep], left, weights[keep], bits=bits).R)
