@@ -110,7 +110,9 @@ __device__ inline void store_quad(uint8_t* p, uint32_t w, int n) {
     if (n >= 4) {
         *reinterpret_cast<u32_any*>(p) = w;
     } else {
-        for (int b = 0; b < n; ++b) p[b] = (uint8_t)(w >> (8 * b));
+#pragma unroll
+        for (int b = 0; b < 3; ++b)
+            if (b < n) p[b] = (uint8_t)(w >> (8 * b));
     }
 }
 __device__ inline uint8_t requant_one(int32_t v, int32_t cs, int col, const RequantDev& rq) {
