@@ -168,6 +168,14 @@ inline size_t ws_base_ints(int M) {
     return (size_t)kWsHeaderInts + (rows > streaming ? rows : streaming);
 }
 
+// The streaming kernel reads the weight once and wins up to 32 rows; beyond, every row block costs it a pass over A per
+// column block and the registers of a second workgroup per compute unit.  Up to 48 rows it still wins where its workgroups
+// fit the compute units once and the tiles would be few, but neither a short K nor one that is worth a split (us,
+// streaming / 64x64 tiles: 33x4096x1024 5.9 / 7.0, 48x4096x2048 8.0 / 8.6, 33x4096x4096 10.6 / 11.4, 48x4096x4096
+// 12.2 / 11.4, 33x1000x512 5.7 / 5.3); with 64 rows nowhere (64x4096x2048 9.4 / 8.4, 64x8192x2048 18.1 / 10.3,
+// 64x16384x4096 53 / 19).
+inline bool streaming_wins(int M, int N, int K) { return M <= 32 || (M <= 48 && N <= 4096 && K > 512 && K <= (M <= 40 ? 4096 : 2048)); }
+
 // What some calls need beyond those words - the tile tickets and partial tiles of a K split, a copy of A with padded rows -
 // lies behind the words of any call of up to kWsRows rows, so that one workspace can serve calls of different sizes: the
 // words (tickets among them) are zero between calls, the scratch behind them holds whatever the last call left (a call of more

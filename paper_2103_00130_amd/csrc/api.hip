@@ -154,7 +154,8 @@ size_t abft_gemm_workspace_bytes(int M, const abft_packed_b* Bp) {
     if (M < 1) return 0;
     // with the weight known: room for the partial tiles of a K split across workgroups, where one would be used
     // and, where rows of Bp->K bytes are no whole chunks, for the copy with padded rows
-    if (Bp) {
+    // (the streaming kernel needs neither)
+    if (Bp && !abft::streaming_wins(M, Bp->N, Bp->K)) {
         const abft::RealignPlan ra = abft::realign_plan(M, Bp->N, Bp->K, Bp->KB / 2);
         if (Bp->K % 16 != 0 && ra.copy) return ra.total_ints * sizeof(int32_t);
         return abft::splitk_plan(M, Bp->N, Bp->KB / 2).total_ints * sizeof(int32_t);
@@ -261,13 +262,7 @@ int abft_gemm_u8s8s32_checked(const uint8_t* A, int64_t lda, int M, const abft_p
         if (t128 >= 136 && (Bp->K > 1024 || 3 * t128 >= 2 * 256 * rounds)) return (int)abft::kTile128;
         return (int)abft::kTile64;
     };
-    // The streaming kernel reads the weight once and wins up to 32 rows; beyond, every row block costs it a pass over A per
-    // column block and the registers of a second workgroup per compute unit.  Up to 48 rows it still wins where its workgroups
-    // fit the compute units once and the tiles would be few, but neither a short K nor one that is worth a split (us,
-    // streaming / 64x64 tiles: 33x4096x1024 5.9 / 7.0, 48x4096x2048 8.0 / 8.6, 33x4096x4096 10.6 / 11.4, 48x4096x4096
-    // 12.2 / 11.4, 33x1000x512 5.7 / 5.3); with 64 rows nowhere (64x4096x2048 9.4 / 8.4, 64x8192x2048 18.1 / 10.3,
-    // 64x16384x4096 53 / 19).
-    const bool streaming = M <= 32 || (M <= 48 && Bp->N <= 4096 && Bp->K > 512 && Bp->K <= (M <= 40 ? 4096 : 2048));
+    const bool streaming = abft::streaming_wins(M, Bp->N, Bp->K);
     if (!chosen) variant = streaming ? (int)abft::kSmallM : pick_tile();
     hipError_t e;
     if (variant != abft::kSmallM && !mod127 && !(p.a_vec_ok && p.K % 16 == 0)) {

@@ -1200,6 +1200,19 @@ def test_pack_of_strided_weights(binding, gpu_util, oracle, K, N, transposed):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K,words_only", [(1, 800, 4095, True), (32, 300, 2049, True), (40, 1000, 3071, True), (48, 4096, 2048, True), (33, 8192, 4095, False),
+                                              (41, 1000, 3071, False), (64, 512, 4096, False)])
+def test_workspace_holds_what_calls_use(binding, gpu_util, M, N, K, words_only):
+    """Shapes that go to the streaming kernel are asked for the row and counting words alone, others for scratch as well; either way
+    the call runs on what was asked for and leaves the words zero."""
+    A, B = operands(M, N, K, M)
+    run = gpu_util.GpuRun(binding, B)
+    assert (binding.abft_gemm_workspace_bytes(M, run.Bp) == (64 + 2 * (32 * 64 + 64)) * 4) == words_only
+    out = run.gemm(A)
+    assert np.array_equal(out["C"], A.astype(np.int32) @ B.astype(np.int32)) and not out["flags"].any() and not out["ws"].any()
+
+
+@pytest.mark.gpu
 def test_refused_variant_enqueues_nothing(binding, gpu_util):
     """An unknown variant on rows that a copy would be made of: refused, and the workspace stays as it was."""
     import torch
