@@ -381,7 +381,7 @@ def test_every_choice_by_size(b, code_bytes, bits, n_bags, mean):
     definition, with the same bits as the documented order, bad indices reported and left out."""
     d = code_bytes * 8 // bits
     if n_bags * mean * d > 40_000_000:
-        n_bags, mean = 1200, mean     # (wide rows: the same side of the line with fewer lookups)
+        mean = 6     # (wide rows: the same side of the line with shorter lookups)
     rng = w.rng_for(60 + code_bytes + bits, n_bags + mean)
     rows = 4000
     T, scale, bias = w.draw_table(rng, rows, d, "uniform", bits)
@@ -444,3 +444,53 @@ def test_chunk_edges(b, code_bytes, bits, fill, variant):
     keep[hit] = False
     left = np.concatenate([[0], np.cumsum(keep)])[offsets].astype(np.int64)
     assert same_bits(out["R"], eb.checked_eb(T, scale, bias, indices[keep], left, weights[keep], bits=bits).R)
+
+
+def test_operands_of_the_native_call(b, monkeypatch):
+    """The natively marshalled lookup takes what the Python code takes and leaves to it, errors and all, what it does not: the
+    native function says which (a return code, or None)."""
+    native, said = b._fastcall.eb, []
+
+    def watched(*args):
+        said.append(native(*args))
+        return said[-1]
+    monkeypatch.setattr(b._fastcall, "eb", watched)
+    rows, d, n = 500, 64, 20
+    rng = w.rng_for(7, 1)
+    T, scale, bias = w.draw_table(rng, rows, d, "uniform", 8)
+    offsets = np.arange(n + 1, dtype=np.int64) * 5
+    indices = rng.integers(0, rows, size=5 * n, dtype=np.int64)
+    weights = w.draw_weights(rng, indices.size)
+    g = GpuTable(b, T, scale, bias)
+    i, o, wt = dev(indices), dev(offsets), dev(weights)
+    R, flags = torch.zeros(n, d, device="cuda"), torch.zeros(n, dtype=torch.int32, device="cuda")
+    sums = torch.zeros(n, dtype=torch.float64, device="cuda")
+    wide = torch.zeros(n + 1, d + 4, device="cuda")
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    call = b.abft_eb_u8_checked
+    for weighted, out, stream in ((None, R, None), (wt, R, side), (wt, wide[:, :d], None)):
+        call(g.Tp, i, o, out, flags, weighted, sums, sums.clone(), stream=stream)
+        assert said.pop() == b.ABFT_OK
+        torch.cuda.synchronize()
+        want = eb.checked_eb(T, scale, bias, indices, offsets, None if weighted is None else weights)
+        assert same_bits(out[:n].cpu().numpy(), want.R) and np.array_equal(flags.cpu().numpy(), want.flags)
+    call(g.Tp, i, o, R, None, flags=b.ABFT_EB_NOCHECK)
+    assert said.pop() == b.ABFT_OK
+    for args, kw, error in (((i.int(), o, R, flags), {}, TypeError), ((i.cpu(), o, R, flags), {}, TypeError), ((i, o[::2], R, flags), {}, ValueError),
+                            ((i, o, R[:, :-1], flags), {}, ValueError), ((i, o, R[:-1], flags), {}, ValueError), ((i, o, R.double(), flags), {}, TypeError),
+                            ((i, o, R, flags[:-1]), {}, ValueError), ((i, o, R, flags.float()), {}, TypeError), ((i, o, R, flags, wt[:-1]), {}, ValueError),
+                            ((i, o, R, flags, wt.double()), {}, TypeError), ((i, o, R, flags), {"rsum": sums.float()}, TypeError),
+                            ((i, o, R, flags), {"csum": sums[:-1]}, ValueError)):
+        with pytest.raises(error):
+            call(g.Tp, *args, **kw)
+        assert said.pop() is None
+    for args, kw in (((i, o, R, None), {}), ((i, o, R, flags), {"flags": 0x300}), ((i, o, R, flags), {"rel_bound": -1.0}), ((i, o, wide[:, 1:1 + d], flags), {})):
+        with pytest.raises(b.AbftError) as e:
+            call(g.Tp, *args, **kw)
+        assert e.value.code == b.ABFT_EINVAL and said.pop() == b.ABFT_EINVAL
+    call(g.Tp, i, o, R, flags, flags=np.int64(0))     # (a number that is no plain int)
+    call(g.Tp, i, o, R, flags, rel_bound=np.float32(1e-5))
+    assert said == [None, None]
+    torch.cuda.synchronize()
+    assert same_bits(R.cpu().numpy(), eb.checked_eb(T, scale, bias, indices, offsets, None).R)

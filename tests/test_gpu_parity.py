@@ -1228,10 +1228,16 @@ def test_refused_variant_enqueues_nothing(binding, gpu_util):
 
 
 @pytest.mark.gpu
-def test_operands_of_the_native_call(binding, gpu_util, oracle):
+def test_operands_of_the_native_call(binding, gpu_util, oracle, monkeypatch):
     """The natively marshalled call takes what the Python code takes - views, single rows, an explicit stream, no errCount -
-    and leaves to it, errors and all, what it does not."""
+    and leaves to it, errors and all, what it does not: the native function says which (a return code, or None)."""
     import torch
+    native, said = binding._fastcall.gemm, []
+
+    def watched(*args):
+        said.append(native(*args))
+        return said[-1]
+    monkeypatch.setattr(binding._fastcall, "gemm", watched)
     M, N, K = 70, 65, 130
     A, B = operands(M, N, K, 17)
     ref = oracle.checked_gemm(A, B)
@@ -1249,6 +1255,7 @@ def test_operands_of_the_native_call(binding, gpu_util, oracle):
         one = torch.zeros((1, N), dtype=torch.int32, device="cuda")
         call(wide[5:6, 3:3 + K], run.Bp, one, flags[M:], None, workspace=ws)
     side.synchronize()
+    assert said == [binding.ABFT_OK] * 2
     assert np.array_equal(Cw[:, 1:1 + N].cpu().numpy(), ref.C) and not Cw[:, 0].any() and np.array_equal(one.cpu().numpy()[0], ref.C[5])
     assert flags.cpu().tolist() == [0] * (M + 1) + [9] * 3
     A_dev, C, cnt = gpu_util.dev(A), torch.zeros((M, N), dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
@@ -1257,12 +1264,20 @@ def test_operands_of_the_native_call(binding, gpu_util, oracle):
                        ((A_dev, None, flags), binding.AbftError), ((A_dev, C, None), binding.AbftError)):
         with pytest.raises(error):
             call(bad[0], run.Bp, bad[1], bad[2], cnt, workspace=ws)
+        assert said.pop() == (binding.ABFT_EINVAL if error is binding.AbftError else None)
     with pytest.raises(ValueError):
         call(A_dev, run.Bp, C, flags, cnt, inj=torch.zeros(2, dtype=torch.int32, device="cuda"), n_inj=1, workspace=ws)
+    assert said.pop() is None
     with pytest.raises(binding.AbftError) as e:
         call(A_dev, run.Bp, C, flags, cnt, workspace=ws[:64])
     assert e.value.code == binding.ABFT_EINVAL and "workspace" in str(e.value)
+    assert said.pop() == binding.ABFT_EINVAL
     call(A_dev, run.Bp, C, flags, cnt, flags=np.int64(0), workspace=ws)     # (a number that is no plain int)
+    assert said.pop() is None
+    mult = torch.full((N,), 1e-3, device="cuda")
+    Cq = torch.zeros((M, N), dtype=torch.uint8, device="cuda")
+    call(A_dev, run.Bp, None, flags, cnt, rq=binding.make_requant(0, 0, mult), Cq=Cq, inj=binding.make_injections([(0, 0, 1)]), n_inj=1, workspace=ws)
+    assert said.pop() == binding.ABFT_OK
     torch.cuda.synchronize()
     assert np.array_equal(C.cpu().numpy(), ref.C)
 
