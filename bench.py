@@ -756,8 +756,8 @@ def main():
         torch.cuda.empty_cache()
         out["smallm_sweep"] = smallm_sweep(b, torch, args.steps, args.warmup, 0 if args.overwrite_count else b.ABFT_ERRCOUNT_ACCUMULATE)
         out["splitk"] = splitk_points(b, torch, args.steps, 0 if args.overwrite_count else b.ABFT_ERRCOUNT_ACCUMULATE)
-        out["splitk_note"] = ("few 64x64 tiles, long K: K split across workgroups (chosen from about forty 128-k stages on) against the same "
-                              "launch unsplit (a workspace without room for the partial tiles); the third shape sits below the threshold")
+        out["splitk_note"] = ("few 64x64 tiles, long K: K split across workgroups (four slices and more from 24 128-k stages on, two or three from 40) "
+                              "against the same launch unsplit (a workspace without room for the partial tiles)")
         out["smallm_sweep_note"] = ("streaming kernel, M = 16, weights of growing size rotated through >= 768 MiB of packed "
                                     "copies (nothing served from cache): algorithmic bytes / time against 8 TB/s")
     if not args.no_eb:

@@ -209,7 +209,7 @@ inline SplitKPlan splitk_plan(int M, int N, int stages) {
         const int z = stages >= 160 ? 16 : stages >= 60 ? 8 : 4;
         pl.z = z < most ? z : most;
     }
-    pl.tickets_off = kWsTicketsOff;   // (at most 256 tiles are split)
+    pl.tickets_off = kWsTicketsOff;   // (at most 128 tiles are split)
     pl.part_off = kWsScratchOff;
     pl.total_ints = pl.z > 1 ? pl.part_off + (size_t)tiles * pl.z * kSplitKPartInts : ws_base_ints(M);
     return pl;

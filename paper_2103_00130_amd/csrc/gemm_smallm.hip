@@ -14,8 +14,8 @@
 //    column blocks split its K range between them.
 //  * The four partial accumulators meet in LDS; wavefront 0 adds them, forms the row sums with
 //    DPP row reductions, stores C, and then adds (row sum - checksum) per row into 64-bit
-//    workspace words that also count arrivals (returned integer atomics, a few dozen arrivals
-//    per word at most): whoever completes a word clears it, and a row's word writes its flag.
+//    workspace words that also count arrivals (returned integer atomics, at most 64 arrivals at a
+//    word up to 2048 column blocks, a 32nd of the blocks beyond): whoever completes a word clears it, and a row's word writes its flag.
 //    errCount is cleared at the start and added to.  No workgroup waits for another and there is
 //    no closing pass.
 #include "../../include/abft_gemm.h"
@@ -284,8 +284,7 @@ __global__ __launch_bounds__(256) void gemm_smallm_kernel(const GemmParams p, co
             // blocks the first word is that of (slot, row), shared by the blocks of one slot, whose
             // last arrival carries the slot's sum on; the next is the word of the row, where the last
             // arrival has the complete difference and writes the flag.  Every word is cleared by the
-            // arrival that completes it.  No word sees more than a few dozen arrivals, and nobody
-            // waits for anybody.
+            // arrival that completes it.  Nobody waits for anybody.
             bool bad = false;
             if (lane < 16 * RB && lane < p.M) {
                 unsigned long long* const w_slot =
