@@ -43,9 +43,10 @@ inline EbKernel eb_pick_kernel(int64_t n_bags, int64_t n_indices, int pieces) {
     if (n_bags < 1000) return avg <= 16 && pieces <= 4 ? kEbGroup1 : kEbGroup4;
     // Four wavefronts for long lookups of wide rows a little further (us, four / two): rows of 256 bytes while all lookups are
     // under way at once, four to a compute unit (4-bit, 1024 of 210 25.2 / 28.1, 1100 of 110 16.6 / 17.3 but 8-bit 14.7 / 13.8);
-    // of 512 bytes longer (4-bit, 1400 of 110 30.1 / 34.2, 2600 of 210 81.8 / 89.8; 8-bit, 1400 of 50 14.7 / 14.7, 2600 of 80
-    // 29.8 / 31.8); of 128 bytes where a lookup is one chunk with four and two with two (1100 of 50 6.8 / 7.4, of 110 10.9 / 10.6)
-    const int64_t most4 = pieces == 32 && avg > 45 ? 3999 : pieces >= 16 || (pieces == 8 && avg > 80) ? 1024 : pieces == 8 && avg > 45 ? 1279 : 0;
+    // of 512 bytes longer (4-bit, 1400 of 110 30.1 / 34.2, 2600 of 210 81.8 / 89.8, 7000 of 110 115.6 / 118.0, 16000 of 110 251.8 /
+    // 252.6; 8-bit, 1400 of 50 14.7 / 14.7, 2600 of 80 29.8 / 31.8, 4200 of 50 33.3 / 32.5, of 200 105.7 / 110.0); of 128
+    // bytes where a lookup is one chunk with four and two with two (1100 of 50 6.8 / 7.4, of 110 10.9 / 10.6)
+    const int64_t most4 = pieces == 32 && avg > 45 ? (avg > 80 ? 9999 : 3999) : pieces >= 16 || (pieces == 8 && avg > 80) ? 1024 : pieces == 8 && avg > 45 ? 1279 : 0;
     if (n_bags <= most4) return kEbGroup4;
     // fewer wavefronts where that many lookups make more work-items than a launch takes, a few lanes where one is too many too
     EbKernel kernel = avg <= 45 && pieces <= 16 ? kEbGroup1 : kEbGroup2;

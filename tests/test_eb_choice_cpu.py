@@ -43,7 +43,7 @@ def test_large_batches_of_longer_lookups(rule, pieces, n, mean, batch):
 
 
 @pytest.mark.parametrize("pieces,n,mean,kernel", [(4, 999, 60, GROUP4), (4, 1000, 60, GROUP2), (16, 1024, 30, GROUP4), (16, 1025, 30, GROUP1), (16, 1100, 60, GROUP2),
-                                                  (32, 3999, 60, GROUP4), (32, 4000, 60, GROUP2), (32, 1100, 30, GROUP2), (8, 1279, 60, GROUP4),
+                                                  (32, 3999, 60, GROUP4), (32, 4000, 60, GROUP2), (32, 9999, 110, GROUP4), (32, 10000, 110, GROUP2), (32, 1100, 30, GROUP2), (8, 1279, 60, GROUP4),
                                                   (8, 1280, 60, GROUP2), (8, 1024, 110, GROUP4), (8, 1025, 110, GROUP2), (8, 1000, 30, GROUP1)])
 def test_four_wavefronts_for_long_lookups_of_wide_rows(rule, pieces, n, mean, kernel):
     assert rule.pick(n, n * mean, pieces) == kernel
