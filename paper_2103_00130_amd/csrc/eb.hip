@@ -14,6 +14,8 @@
 //    lane; the chip is filled by lookups, and the lanes of a lookup walk its index list in order.
 //  * Group kernel: one, two or four wavefronts per lookup.  Their threads fetch different 16-byte
 //    pieces of the lookup's records into LDS, then, owning columns, walk the staged rows in index order.
+//  * The loads are ordinary ones: marked as streaming, a record that straddles two lines has the second fetched anew (16384 lookups
+//    of 100 rows of 80 bytes 56.9 us, 50.4 without the mark; 16987 of 36 rows of 272 bytes 49.7 / 39.9; 65536 of 4 rows of 80 18.7 / 15.6).
 //  * Every load is unconditional (clamped position, row 0 in place of a bad index): a load under
 //    `if (valid)` is followed by a wait, which would put the loads of a lookup one after the other.
 //  Both accumulate every output column in the same order (index order, one fused multiply-add
@@ -185,8 +187,8 @@ __global__ __launch_bounds__(256) void eb_batch_kernel(const EbParams p) {
             if (in && !r.ok[u]) flag |= ABFT_EB_BAD_INDEX;
             if (kWeighted) r.wv[u] = ix.wv[u];
             const uint8_t* rec = base + (r.ok[u] ? ix.idx[u] : 0) * p.stride;
-            r.q[u] = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(rec));
-            r.tl[u] = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(rec + (CB - piece * 16)));
+            r.q[u] = *reinterpret_cast<const v4u*>(rec);
+            r.tl[u] = *reinterpret_cast<const v4u*>(rec + (CB - piece * 16));
         }
     };
     auto pool = [&](const RowSet& r) __attribute__((always_inline)) {
@@ -280,7 +282,7 @@ __global__ __launch_bounds__(256) void eb_batch_kernel(const EbParams p) {
 //     wavefront of its own (W = 1: by every lane beside its columns).
 //  The indices of the next chunk are on their way while a chunk is pooled.
 //  Many lookups of the same total: bound by memory, whole 128-byte lines for every record (16384 lookups of 100 rows of 80
-//  bytes: 59.0 us with four wavefronts each as it was before, 56.6 with two now; 272 bytes: 146 and 122).  Short lookups: by
+//  bytes: 59.0 us with four wavefronts each as it was before, 50.4 with two now; 272 bytes: 146 and 100).  Short lookups: by
 //  what a lookup costs beside its rows (9000 of 27 rows: 18.4 -> 12.3 us, 16384 of 10: 32 -> 10.8, 3000 of 5: 6.8 -> 3.5).
 template <int G, int BITS, int W, bool kCheck, bool kWeighted>
 __global__ __launch_bounds__(W * 64) void eb_group_kernel(const EbParams p) {
@@ -362,7 +364,7 @@ __global__ __launch_bounds__(W * 64) void eb_group_kernel(const EbParams p) {
             const int g = l * NT + tid, pc = g % P;
             x.ok[l] = (uint64_t)ix.idx[l] < (uint64_t)p.rows;
             if (kWeighted) x.w[l] = ix.w[l];
-            x.v[l] = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(p.tab + (x.ok[l] ? ix.idx[l] : 0) * p.stride + pc * 16));
+            x.v[l] = *reinterpret_cast<const v4u*>(p.tab + (x.ok[l] ? ix.idx[l] : 0) * p.stride + pc * 16);
         }
     };
     // A row's scalars go to arrays of their own: the weighted scale and bias, and its term of Eq. 4 to a sum.  A row that is not
