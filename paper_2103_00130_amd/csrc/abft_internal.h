@@ -146,8 +146,10 @@ struct GemmParams {
     int n_inj;
     int ksplit;                // K slices across workgroups (split-K kernels; 1 elsewhere)
     int split_q, split_r;      // stages of a slice, or of a K group inside the workgroup; the first split_r take one more
-    int32_t* ws_tickets;       // split-K: one arrival counter per tile
-    int32_t* ws_part;          // split-K: partial tiles, [tile][slice][value][thread]
+    int32_t* ws_tickets;       // split-K: one arrival counter per tile and finishing wavefront
+    int32_t* ws_part;          // split-K: parts, [tile][finishing wavefront][slice][value][lane]
+    int wk_stages;             // K split among wavefronts: stages of the wavefronts with fewest; those with one more deal out
+    int wk_share_q1, wk_share_r1;  // their k-steps of the checksum product by these instead of share_q, share_r
     size_t ws_ints;            // ints the caller's workspace holds
     unsigned long long* clock_trace;  // diagnostic builds (ABFT_CLOCK_TRACE): 6 words per workgroup, else NULL
     int32_t* ws;               // workspace: counting words in the first kWsHeaderInts ints, then the per-row words
@@ -168,13 +170,8 @@ inline size_t ws_base_ints(int M) {
     return (size_t)kWsHeaderInts + (rows > streaming ? rows : streaming);
 }
 
-// The streaming kernel reads the weight once and wins up to 32 rows; beyond, every row block costs it a pass over A per
-// column block and the registers of a second workgroup per compute unit.  Up to 48 rows it still wins where its workgroups
-// fit the compute units once and the tiles would be few, but neither a short K nor one that is worth a split (us,
-// streaming / 64x64 tiles: 33x4096x1024 5.9 / 7.0, 48x4096x2048 8.0 / 8.6, 33x4096x4096 10.6 / 11.4, 48x4096x4096
-// 12.2 / 11.4, 33x1000x512 5.7 / 5.3); with 64 rows nowhere (64x4096x2048 9.4 / 8.4, 64x8192x2048 18.1 / 10.3,
-// 64x16384x4096 53 / 19).
-inline bool streaming_wins(int M, int N, int K) { return M <= 32 || (M <= 48 && N <= 4096 && K > 512 && K <= (M <= 40 ? 4096 : 2048)); }
+// Calls of so few rows that no copy of A with padded rows is ever made for them: abft_gemm_workspace_bytes leaves its room out.
+inline bool words_suffice(int M, int N, int K) { return M <= 32 || (M <= 48 && N <= 4096 && K > 512 && K <= (M <= 40 ? 4096 : 2048)); }
 
 // What some calls need beyond those words - the tile tickets and partial tiles of a K split, a copy of A with padded rows -
 // lies behind the words of any call of up to kWsRows rows, so that one workspace can serve calls of different sizes: the
@@ -185,33 +182,36 @@ constexpr size_t kWsTicketsOff = (size_t)kWsHeaderInts + 2 * (size_t)kWsRows;
 constexpr size_t kWsTickets = 1024;
 constexpr size_t kWsScratchOff = kWsTicketsOff + kWsTickets;
 
-// Split-K across workgroups (64x64 tiles, grids that would leave most compute units idle): how many K slices,
-// and where the tile tickets and the partial tiles lie in the workspace behind the row words.  One place for
-// the rule, so that abft_gemm_workspace_bytes and the launcher agree.
-constexpr int kSplitKPartInts = 256 * 17 + 64;   // per workgroup: 256 threads x (16 accumulator values + 1 column sum), 64 rows' checksum shares
+// Split-K across workgroups (32x32 tiles of gemm_tile_wk.h, grids that would leave most compute units idle): how many K slices,
+// and where the tickets and the parts lie in the workspace behind the row words.  One place for the rule, so that
+// abft_gemm_workspace_bytes and the launcher agree.
+constexpr int kWkPartInts = 4 * 64 * 5;   // per workgroup: four finishing wavefronts x 64 lanes x (four sums and a checksum share)
 struct SplitKPlan {
     int z;                                  // slices (1 = no split)
     size_t tickets_off, part_off, total_ints;
+    size_t room_ints;                       // for any way the rows of A may lie
 };
-inline SplitKPlan splitk_plan(int M, int N, int stages) {
+inline SplitKPlan splitk_plan(int M, int N, int stages, bool whole_a) {
     SplitKPlan pl;
-    const long tiles = (long)((M + 63) / 64) * ((N + 63) / 64);
+    const int64_t tiles = (int64_t)((M + 31) / 32) * ((N + 31) / 32);
     pl.z = 1;
-    // The slices of a tile meet through memory (the L2s are not coherent with each other): store the partial tile,
-    // wait for the acknowledgement, take the ticket, fetch the others' partials - three dependent device-scope round
-    // trips, about 3.5 us.  A stage of the unsplit 64x64 loop takes 0.2 us, so four slices pay from 24 stages on and two
-    // or three, where more tiles leave no room for four, from 40 (us, unsplit / split: 128x128x2048 7.5 / 7.1,
-    // 256x512x3072 8.9 / 8.4, 64x496x4096 10.5 / 8.3; with 128 tiles 512x1024x3072 9.7 / 10.2, 512x1024x4608 11.6 / 11.6,
-    // 512x1024x5200 15.3 / 12.4).  More slices shorten the loop but the last arrival fetches four partials at a time:
-    // eight from 60 stages on (64 stages 10.9 / 10.8 with four / eight, 125 stages 14.8 / 11.9), sixteen from 160.
-    const int most = tiles <= 128 ? (int)(256 / tiles) : 1;
-    if (most >= 2 && stages >= (most >= 4 ? 24 : 40) && M > 32 && M <= kWsRows) {   // (up to 32 rows: the streaming kernel)
-        const int z = stages >= 160 ? 16 : stages >= 60 ? 8 : 4;
-        pl.z = z < most ? z : most;
+    // The parts meet through memory (the L2s are not coherent with each other): store them, wait for the acknowledgement, take the
+    // ticket, fetch the others' - three dependent device-scope round trips, about 2 us.  A workgroup of eight wavefronts takes
+    // eight stages in 0.4 us, 0.85 us where rows are no whole chunks, so slices of sixteen stages pay from 64 stages on, or 36 (us,
+    // unsplit / split: 46x128x13504 10.6 / 8.1, 64x64x16384 11.9 / 8.2, 96x96x10000 9.0 / 7.8, 100x1000x8192 in two 8.2 / 9.5;
+    // rows that are no whole chunks, 32x240x12600 11.2 / 7.7, 45x1000x5001 8.9 / 7.8, 41x1000x3071 in two slower), and where there
+    // are eight tiles at most from 24 (65x64x6144 7.0 / 6.8, 128x64x3072 5.6 / 6.4).  How the rows lie is known when the call comes;
+    // there is room in the workspace for either.
+    const bool room = M <= kWsRows && tiles <= 128 && stages >= (M > 40 ? 24 : 40);
+    if (room && (whole_a ? (tiles <= 64 && stages >= 64) || (tiles <= 8 && M > 40) : stages >= 36)) {
+        const int64_t most = (stages + 15) / 16, fit = 256 / tiles;
+        pl.z = (int)(most < fit ? most : fit);
+        if (pl.z > 16) pl.z = 16;
     }
     pl.tickets_off = kWsTicketsOff;   // (at most 128 tiles are split)
     pl.part_off = kWsScratchOff;
-    pl.total_ints = pl.z > 1 ? pl.part_off + (size_t)tiles * pl.z * kSplitKPartInts : ws_base_ints(M);
+    pl.total_ints = pl.z > 1 ? pl.part_off + (size_t)tiles * pl.z * kWkPartInts : ws_base_ints(M);
+    pl.room_ints = room ? pl.part_off + (size_t)(tiles * (256 / tiles < 16 ? 256 / tiles : 16)) * kWkPartInts : ws_base_ints(M);
     return pl;
 }
 
@@ -231,11 +231,10 @@ struct RealignPlan {
 };
 inline RealignPlan realign_plan(int M, int N, int K, int stages) {
     RealignPlan pl;
-    const SplitKPlan sk = splitk_plan(M, N, stages);
     const int64_t tiles = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
     pl.lda = ((int64_t)K + 15) / 16 * 16;
     pl.copy = (tiles + 255) / 256 * stages >= 20 && M <= kWsRows && pl.lda * M <= (512ll << 20);
-    pl.off = sk.z > 1 ? sk.total_ints : kWsScratchOff;
+    pl.off = kWsScratchOff;
     pl.total_ints = pl.off + (size_t)(pl.lda * M / 4) + 4;
     return pl;
 }
@@ -261,6 +260,30 @@ __device__ inline shift_v4i shift_down(shift_v4i v, int n) {
 }
 #endif
 
+// Which form of gemm_tile_wk.h (K split among the wavefronts of a workgroup) takes a call, if any: rows x columns of the tile, wavefronts.
+enum WkForm { kWkNone = 0, kWk32x32w4, kWk32x32w8, kWk32x64w4, kWk32x64w8, kWk64x64w4 };
+// By the number of tiles and of stages of 128 k (us, the 64x64 tiles of gemm_tile_async.h or up to 32 rows the streaming kernel / this form):
+//  * as long as no compute unit has two: 32x32 tiles, eight wavefronts from nine stages on (441x479x1255 8.7 / 5.2, with four 5.3;
+//    322x306x80 4.8 / 4.3, with four 4.2);
+//  * then 32x64 tiles (674x480x2048 7.8 / 5.7; 1246x204x3856 10.5 / 7.4 with eight wavefronts, 7.6 with four);
+//  * then 64x64 tiles where the loop is long enough to pay for the sums at the end (1000x1000x3200 10.1 / 9.6, but 1024x1024x1024
+//    6.9 / 7.4);
+//  * up to two 32x64 tiles per compute unit for a short K where 64 rows a tile are partly padding or the rows are no whole chunks
+//    (78x6549x96 7.4 / 6.7, 65x9664x688 9.2 / 6.6, 2042x336x146 6.0 / 4.8; but 773x928x240 5.4 / 5.5);
+//  * not for up to 16 rows of a middling K, where half the tile is padding and the streaming kernel has all its loads under way
+//    at once (16x4096x2048 4.8 / 5.1, 7x660x3872 5.0 / 5.5; but 8x4096x4096 6.7 / 6.0, 12x8368x3424 11.0 / 7.3, 4x864x96 4.4 / 3.4,
+//    13x144x11067 16.6 / 7.8 split across workgroups).
+inline WkForm wk_form(int M, int N, int stages, bool whole_a) {
+    const int64_t t32 = (int64_t)((M + 31) / 32) * ((N + 31) / 32), t3264 = (int64_t)((M + 31) / 32) * ((N + 63) / 64),
+                  t64 = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
+    if (M <= 16 && N <= 4096 && stages > 8 && stages < 32) return kWkNone;
+    if (t32 <= 256) return stages >= 9 ? kWk32x32w8 : kWk32x32w4;
+    if (t3264 <= 256) return stages >= 24 ? kWk32x64w8 : kWk32x64w4;
+    if (t64 <= 256 && stages >= 10) return kWk64x64w4;
+    if (t3264 <= 512 && stages < 10 && (!whole_a || M <= 128)) return kWk32x64w4;
+    return kWkNone;
+}
+
 enum Variant { kTile256 = 1, kTile128 = 2, kTile64 = 3, kSmallM = 4, kTile256w24 = 5, kTile256w42 = 6, kVariantEnd = 7 };
 
 // launchers (each returns the hipError_t of its launch)
@@ -269,6 +292,8 @@ hipError_t launch_flip_bit(abft_packed_b* h, int k, int j, int bit, hipStream_t 
 hipError_t launch_flip_checksum_bit(abft_packed_b* h, int k, int bit, hipStream_t s);
 hipError_t launch_flip_checksum127_bit(abft_packed_b* h, int k, int bit, hipStream_t s);
 hipError_t launch_fill_zero(int32_t* p, size_t n_ints, hipStream_t s);
+// (refuses what it does not take: a form of kWkNone, K below 16 with rows that are no whole chunks, the printed modulus on such rows)
+hipError_t launch_gemm_wk(WkForm form, bool check, bool want_c, bool want_q, const GemmParams& p, hipStream_t s);
 hipError_t launch_gemm_tile(int variant, bool check, bool want_c, bool want_q, const GemmParams& p, hipStream_t s);
 // any_a: A of any alignment and K >= 16 is taken too (else only whole, aligned 16-byte chunks)
 hipError_t launch_gemm_smallm(bool any_a, bool check, bool want_c, bool want_q, const GemmParams& p, hipStream_t s);

@@ -152,13 +152,13 @@ void abft_packed_b_destroy(abft_packed_b* Bp) { free_handle(Bp); }
 
 size_t abft_gemm_workspace_bytes(int M, const abft_packed_b* Bp) {
     if (M < 1) return 0;
-    // with the weight known: room for the partial tiles of a K split across workgroups, where one would be used
-    // and, where rows of Bp->K bytes are no whole chunks, for the copy with padded rows
-    // (the streaming kernel needs neither)
-    if (Bp && !abft::streaming_wins(M, Bp->N, Bp->K)) {
+    // with the weight known: room for the parts of a K split across workgroups, where one would be used, and, where rows of
+    // Bp->K bytes are no whole chunks, for the copy with padded rows
+    if (Bp) {
+        const size_t split = abft::splitk_plan(M, Bp->N, Bp->KB / 2, false).room_ints;
         const abft::RealignPlan ra = abft::realign_plan(M, Bp->N, Bp->K, Bp->KB / 2);
-        if (Bp->K % 16 != 0 && ra.copy) return ra.total_ints * sizeof(int32_t);
-        return abft::splitk_plan(M, Bp->N, Bp->KB / 2).total_ints * sizeof(int32_t);
+        const bool copy = Bp->K % 16 != 0 && ra.copy && !abft::words_suffice(M, Bp->N, Bp->K);
+        return (copy && ra.total_ints > split ? ra.total_ints : split) * sizeof(int32_t);
     }
     return ws_ints(M) * sizeof(int32_t);
 }
@@ -262,9 +262,13 @@ int abft_gemm_u8s8s32_checked(const uint8_t* A, int64_t lda, int M, const abft_p
         if (t128 >= 136 && (Bp->K > 1024 || 3 * t128 >= 2 * 256 * rounds)) return (int)abft::kTile128;
         return (int)abft::kTile64;
     };
-    const bool streaming = abft::streaming_wins(M, Bp->N, Bp->K);
-    if (!chosen) variant = streaming ? (int)abft::kSmallM : pick_tile();
     hipError_t e;
+    if (!chosen) {
+        e = abft::launch_gemm_wk(abft::wk_form(M, Bp->N, p.KB2, p.a_vec_ok && p.K % 16 == 0), check, want_c, want_q, p, (hipStream_t)stream);
+        if (e == hipSuccess) return ABFT_OK;
+        if (e != hipErrorNotSupported) return hip_fail(e, fn);
+        variant = M <= 32 ? (int)abft::kSmallM : pick_tile();
+    }
     if (variant != abft::kSmallM && !mod127 && !(p.a_vec_ok && p.K % 16 == 0)) {
         const abft::RealignPlan ra = abft::realign_plan(M, Bp->N, Bp->K, p.KB2);
         if (ra.copy && workspace && p.ws_ints >= ra.total_ints) {

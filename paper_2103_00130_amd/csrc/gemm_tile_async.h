@@ -94,34 +94,24 @@ __device__ inline int32_t floor_mod127(long long v) {
 
 // kBlockSums: the cross-lane part of the row sums is done for the sixteen rows of a block together
 // (sum32_of16) instead of row by row between the stores; the launcher says when.
-// LDS bytes of one group of WGM x WGN wavefronts: the stage ring, the scratch of the epilogue, the staged
+// LDS bytes of a workgroup of WGM x WGN wavefronts: the stage ring, the scratch of the epilogue, the staged
 // checksum digits (kLimbStages stages of 512 bytes)
-template <int BM, int BN, int WGN, int kStages, int WGK>
-constexpr size_t group_lds_bytes() {
-    return kStages * (size_t)(BM + BN) * BK + (4 * BN + WGN * BM + BM + 4) * sizeof(int32_t) + (32 / WGK) * 512;
+constexpr int kLimbStages = 32;
+template <int BM, int BN, int WGN, int kStages>
+constexpr size_t lds_bytes() {
+    return kStages * (size_t)(BM + BN) * BK + (4 * BN + WGN * BM + BM + 4) * sizeof(int32_t) + kLimbStages * 512;
 }
 
-// WGK > 1: K split inside the workgroup.  WGK groups of WGM x WGN wavefronts work on the same tile; group g
-// takes the g-th run of stages with a stage ring of its own, so that a SIMD has WGK wavefronts to issue
-// from (a tile of 64x64 keeps one wavefront per SIMD busy with about a hundred instructions per stage,
-// and one wavefront issues at most one instruction every four cycles).  The groups pass the same
-// barriers (same number of stages each, the launcher sees to it); at the end groups 1.. hand their
-// accumulators to group 0 through LDS and leave, and group 0 runs the epilogue.
-// kSplitK: K split across workgroups as well.  p.ksplit workgroups per tile take consecutive runs of stages; each
-// stores its partial tile (accumulators, column sums, and its share of the checksum product for the tile's rows) in the
-// workspace and takes a ticket on the tile's counter, and the one that arrives last adds the others' partials to its own
-// and runs the epilogue.  The checksum product of every run of stages is dealt out to the tile columns as before (the
-// comparison of Eq. 2b is linear in the K slices).  For grids of 64x64 tiles that would leave most compute units idle.
-template <int BM, int BN, int WGM, int WGN, int kStages, bool kCheck, int kOut, bool kBlockSums, int WGK, bool kSplitK = false, int kAnyA = 0>
-__global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(const GemmParams p, const int tiles_m,
+template <int BM, int BN, int WGM, int WGN, int kStages, bool kCheck, int kOut, bool kBlockSums, int kAnyA = 0>
+__global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const GemmParams p, const int tiles_m,
                                                                              const int tiles_n) {
-    constexpr int NW = WGM * WGN, NT = NW * 64;    // wavefronts and threads of one group
+    constexpr int NW = WGM * WGN, NT = NW * 64;    // wavefronts and threads
     constexpr int WTM = BM / WGM, WTN = BN / WGN;  // wave tile
     constexpr int TM = WTM / 32, TN = WTN / 32;    // 32x32 blocks per wave
     constexpr int A_STAGE = BM * BK, B_STAGE = BN * BK;
     constexpr int S = kStages;                     // stages resident in LDS
     static_assert(S >= 2, "at least a double buffer");
-    static_assert(kAnyA == 0 || (S == 2 && WGK == 1 && kAnyA % 2 == 0), "register-staged loads: a double buffer in LDS");
+    static_assert(kAnyA == 0 || (S == 2 && kAnyA % 2 == 0), "register-staged loads: a double buffer in LDS");
     constexpr int A_LD = (BM / 8) / NW;            // async A loads per wave per stage (8 rows each)
     constexpr int B_LD = (BN / 8) / NW;            // async B loads per wave per stage (1 KiB each)
     constexpr int CB = (WTM / 16) / WGN;           // 16-row checksum blocks per wave
@@ -129,14 +119,11 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     static_assert(A_LD >= 1 && B_LD >= 1 && CB >= 1 && (WTM / 16) % WGN == 0, "tile too small for the workgroup");
     static_assert(BN >= 64 && NT <= 4 * BN, "epilogue scratch layout");
 
-    // LDS of a group: [S][A_STAGE] then [S][B_STAGE], then the scratch of the epilogue, then the digits
-    extern __shared__ __align__(1024) uint8_t smem_all[];
-    constexpr size_t GROUP_LDS = (group_lds_bytes<BM, BN, WGN, kStages, WGK>() + 1023) / 1024 * 1024;
-    const int grp = WGK > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT) : 0;
-    uint8_t* const smem = smem_all + grp * GROUP_LDS;
+    // LDS: [S][A_STAGE] then [S][B_STAGE], then the scratch of the epilogue, then the digits
+    extern __shared__ __align__(1024) uint8_t smem[];
     const uint32_t lds_base = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) uint8_t*)smem);
 
-    const int tid = (int)threadIdx.x - grp * NT, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WGN, wn = wave % WGN;
     // Workgroups go round-robin over the 8 XCDs; give every XCD a compact block of tiles
     // (consecutive ids inside an XCD walk down a strip of 4 tile rows) so that its L2 sees
@@ -144,8 +131,8 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     int tile_m, tile_n;
     {
         const int n_tiles = tiles_m * tiles_n;
-        int t = kSplitK ? (int)blockIdx.x % n_tiles : (int)blockIdx.x;   // (split-K: slice z = blockIdx.x / n_tiles)
-        if (!kSplitK && n_tiles % 8 == 0) t = (blockIdx.x & 7) * (n_tiles >> 3) + (blockIdx.x >> 3);
+        int t = (int)blockIdx.x;
+        if (n_tiles % 8 == 0) t = (blockIdx.x & 7) * (n_tiles >> 3) + (blockIdx.x >> 3);
         const int strip_h = tiles_m >= 4 ? 4 : tiles_m;
         const int per_strip = strip_h * tiles_n;
         const int strip = t / per_strip, r = t - strip * per_strip;
@@ -154,18 +141,7 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
         tile_m = strip * strip_h + r - tile_n * h;
     }
     const int row0 = tile_m * BM, col0 = tile_n * BN;
-    const int Z = kSplitK ? p.ksplit : 1;                                       // K slices across workgroups
-    const int z = kSplitK ? (int)blockIdx.x / (tiles_m * tiles_n) : 0;
-    const int NS_all = p.KB2;            // stages of 128 k-values
-    // ... of this run of them (the slice of a K split across workgroups, the group of one inside the workgroup): as equal
-    // as they can be, the first split_r runs one stage longer
-    constexpr bool kRuns = kSplitK || WGK > 1;
-    const int run_no = kSplitK ? z : grp;
-    // (Without such runs WGK and Z are one, z and grp zero, and this is NS_all and 0.  Written so, the compiler allocates registers
-    // in another way: 4096x4096x4096 66.6 us against 66.9 and 64.5 against 65.5 on two devices, but 3072x3072x3072, whose grid does
-    // not fill the chip, 39.7 against 39.4.)
-    const int NS = kRuns ? p.split_q + (run_no < p.split_r ? 1 : 0) : NS_all / (WGK * Z);
-    const int s_base = kRuns ? share_begin(run_no, p.split_q, p.split_r) : (z * WGK + grp) * NS;  // its first stage
+    const int NS = p.KB2;            // stages of 128 k-values
 
     // ---- direct global->LDS loads ---------------------------------------------------
     // One instruction moves 16 bytes per lane to LDS address m0 + lane*16.  They are issued
@@ -186,14 +162,14 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     // of B), hence the second set of offsets.
     uint32_t a_voff[A_LD], a_voff_last[A_LD], a_lds[A_LD];
     {
-        const int c16_max = p.K - 16 - (NS_all - 1) * BK;
+        const int c16_max = p.K - 16 - (NS - 1) * BK;
 #pragma unroll
         for (int i = 0; i < A_LD; ++i) {
             const int r = (wave * A_LD + i) * 8 + (lane >> 3);
             const int c16 = ((lane & 7) ^ ((r >> 1) & 7)) * 16;
             const uint32_t rowoff = (uint32_t)min(row0 + r, p.M - 1) * (uint32_t)p.lda;
             a_voff[i] = rowoff + (uint32_t)c16;
-            a_voff_last[i] = rowoff + (uint32_t)((grp == WGK - 1 && z == Z - 1) ? min(c16, c16_max) : c16);  // only the last group meets K's end
+            a_voff_last[i] = rowoff + (uint32_t)min(c16, c16_max);
             a_lds[i] = lds_base + (wave * A_LD + i) * 1024;
         }
     }
@@ -209,7 +185,7 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     {
         const int bc0 = wave * B_LD, kbl = bc0 / B_CHUNKS_PER_KB, cc0 = bc0 % B_CHUNKS_PER_KB;
         b_wave = p.packed + packed_unit_offset(tile_n / TILES_PER_NT, 0, (tile_n % TILES_PER_NT) * (BN / 32), p.KB2 * 2) +
-                 (int64_t)kbl * B_KB_STRIDE + cc0 * 1024 + (int64_t)s_base * (2 * B_KB_STRIDE);
+                 (int64_t)kbl * B_KB_STRIDE + cc0 * 1024;
         b_lds = lds_base + S * A_STAGE + kbl * (BN * 64) + cc0 * 1024;
     }
 
@@ -219,7 +195,7 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     auto issue_load = [&](int s, int buf, int n) __attribute__((always_inline)) {
         if (n < A_LD) {
             const uint32_t voff = (s == NS - 1) ? a_voff_last[n] : a_voff[n];
-            dma(a_lds[n] + buf * A_STAGE, voff, p.A + (int64_t)(s_base + s) * BK, std::integral_constant<int, 0>{});
+            dma(a_lds[n] + buf * A_STAGE, voff, p.A + (int64_t)s * BK, std::integral_constant<int, 0>{});
         } else {
             const int j = n - A_LD, g = j >> 2;
             const int8_t* const base = b_wave + (int64_t)s * (2 * B_KB_STRIDE) + g * 4096;
@@ -243,7 +219,7 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     int a_c16 = 0, a_c16_last = 0;
     if constexpr (kAnyA != 0) {
         a_c16 = (lane & 7) * 16;
-        a_c16_last = min(a_c16, p.K - 16 - (NS_all - 1) * BK);
+        a_c16_last = min(a_c16, p.K - 16 - (NS - 1) * BK);
         const bool whole = p.K >= 16;   // (else the loads fetch sixteen bytes of B that nobody uses)
         if (!whole) a_c16 = a_c16_last = 0;
 #pragma unroll
@@ -253,8 +229,7 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
         }
     }
     auto reg_load = [&](int s, v4i(&ra)[A_LD], v4i(&rb)[B_LD]) __attribute__((always_inline)) {
-        const int s_all = s_base + s;
-        const int64_t k = (int64_t)s_all * BK + (s_all == NS_all - 1 ? a_c16_last : a_c16);
+        const int64_t k = (int64_t)s * BK + (s == NS - 1 ? a_c16_last : a_c16);
 #pragma unroll
         for (int i = 0; i < A_LD; ++i) ra[i] = *reinterpret_cast<const v4i_any*>(a_row[i] + k);
         const int8_t* const base = b_wave + (int64_t)s * (2 * B_KB_STRIDE) + b_voff;
@@ -295,8 +270,8 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
 #pragma unroll
                 for (int d = 0; d < 4; ++d) bsum[j >> 1] = (uint32_t)__builtin_amdgcn_sdot4(rb[j][d], 0x01010101, (int)bsum[j >> 1], false);
         }
-        const int over = (s_base + s >= NS_all - 1 && p.K >= 16) ? (16 - (p.K & 15)) & 15 : 0;  // bytes the end chunk moves down
-        const bool end_chunk = (NS_all - 1) * BK + a_c16 == (p.K & ~15);
+        const int over = (s >= NS - 1 && p.K >= 16) ? (16 - (p.K & 15)) & 15 : 0;  // bytes the end chunk moves down
+        const bool end_chunk = (NS - 1) * BK + a_c16 == (p.K & ~15);
 #pragma unroll
         for (int i = 0; i < A_LD; ++i) {
             const int r = (wave * A_LD + i) * 8 + (lane >> 3);
@@ -341,16 +316,8 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     // that the loop holds no global load the compiler knows of: it would put a wait for *all*
     // vector-memory traffic, the direct-to-LDS loads of the next stage included, in front of the
     // digit MFMAs.
-    constexpr int kLimbStages = 32 / WGK;
-    // (stage numbers of this group: every group's run of stages is dealt out to the tile columns in the same way, so
-    // that the groups of a K-split workgroup carry the same number of checked stages between their common barriers)
-    int share_q = p.share_q, share_r = p.share_r;   // (of a run of split_q stages: one stage more is one more to deal out)
-    if (kRuns && run_no < p.split_r && ++share_r == tiles_n) {
-        ++share_q;
-        share_r = 0;
-    }
-    const int ck_lo = kCheck ? share_begin(tile_n, share_q, share_r) : 0;
-    const int ck_hi = kCheck ? share_begin(tile_n + 1, share_q, share_r) : 0;
+    const int ck_lo = kCheck ? share_begin(tile_n, p.share_q, p.share_r) : 0;
+    const int ck_hi = kCheck ? share_begin(tile_n + 1, p.share_q, p.share_r) : 0;
     uint8_t* const s_limb = smem + S * (A_STAGE + B_STAGE) + (4 * BN + WGN * BM + BM + 4) * sizeof(int32_t);
     // sum_k S_B[k], which the first tile column needs at the very end (the u8 -> s8 shift of A moves every
     // checksum product by 128 times it): fetched now, so that the epilogue does not wait for memory
@@ -358,12 +325,11 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     int limb_base = ck_lo;  // stage whose digits sit at the start of s_limb
     // (behind the load of the total, which the compiler can only make a scalar one ahead of any store)
     // errCount is overwritten on a grid of one row of tiles: the first workgroup clears it here and whoever finds corrupted
-    // rows adds to it.  No row is complete, and so nothing added, before that workgroup has arrived at the row's word (its
-    // slice at the tile's ticket), which it does once this store has been acknowledged.  (On other grids the rows of other
+    // rows adds to it.  No row is complete, and so nothing added, before that workgroup has arrived at the row's word, which it does once this store has been acknowledged.  (On other grids the rows of other
     // tile rows do not wait for it: there the last report of finished rows writes the count, one more round trip.)
     // (64x64 tiles only: the larger ones have one row of tiles on the widest weights alone)
     constexpr bool kClearsFirst = kCheck && BM == 64;
-    const bool clears = kClearsFirst && tiles_m == 1 && !p.err_accumulate && p.err_count != nullptr && tile_n == 0 && z == 0;
+    const bool clears = kClearsFirst && tiles_m == 1 && !p.err_accumulate && p.err_count != nullptr && tile_n == 0;
     if (kClearsFirst && clears && threadIdx.x == 0) __hip_atomic_store(p.err_count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // (copied by the same direct global->LDS loads as the stages, 1 KiB per instruction: no trip through
     // registers, and no wait that the compiler would place - it does not see the direct loads and would
@@ -372,7 +338,7 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     const uint32_t lds_limb = lds_base + (uint32_t)(S * (A_STAGE + B_STAGE) + (4 * BN + WGN * BM + BM + 4) * sizeof(int32_t));
     auto stage_limbs = [&](int s0) __attribute__((always_inline)) {
         const int n = min(ck_hi - s0, kLimbStages);
-        const int8_t* const src = p.limbs + (int64_t)(s_base + s0) * 512;
+        const int8_t* const src = p.limbs + (int64_t)s0 * 512;
         for (int i = wave; i * 2 < n; i += NW)
             dma(lds_limb + i * 1024, (uint32_t)min(i * 1024 + lane * 16, n * 512 - 16), src, std::integral_constant<int, 0>{});
         limb_base = s0;
@@ -742,8 +708,6 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     } else if (WGM == 1) run_all(std::integral_constant<int, 2>{});
     else if ((wm & 1) == 0) run_all(std::integral_constant<int, 0>{});
     else run_all(std::integral_constant<int, 1>{});
-    // (the groups pass the same barriers: one per stage, and one more here for a group whose run is a stage shorter)
-    if (WGK > 1 && p.split_r > 0 && grp >= p.split_r) __syncthreads();
     // (the last stage re-issued loads into a dead buffer; the epilogue keeps its scratch outside
     // the stage buffers, so nobody waits for them before the very end of the kernel)
 
@@ -756,122 +720,11 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
         o[3] = wall_clock64();
     }
 #endif
-    // ------------------------- K split: the groups' results come together -------------------------
-    if constexpr (WGK > 1) {
-        static_assert(TM * TN <= 4, "the K split is for small wave tiles");
-        constexpr int kVals = 16 * TM * TN + TN + 4 * CB;  // accumulators, column sums, digit accumulators per lane
-        static_assert((size_t)kVals * NT * sizeof(int32_t) <= GROUP_LDS, "a group's values fit its own LDS");
-        // every direct-to-LDS load of every group has landed and every wavefront has left the loop: the
-        // LDS of groups 1.. is free (that of group 0 holds the scratch its epilogue is about to use)
-        wait_vmem();
-        __syncthreads();
-        int32_t* const xch = reinterpret_cast<int32_t*>(smem_all + GROUP_LDS);
-        if (grp > 0) {
-            int32_t* const mine = xch + (size_t)(grp - 1) * kVals * NT + tid;
-            int k = 0;
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int t = 0; t < TN; ++t)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) mine[(k++) * NT] = acc[i][t][e];
-#pragma unroll
-            for (int t = 0; t < TN; ++t) mine[(k++) * NT] = (int32_t)bsum[t];
-#pragma unroll
-            for (int c = 0; c < CB; ++c)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) mine[(k++) * NT] = cacc[c][e];
-        }
-        __syncthreads();
-        if (grp > 0) return;  // (nothing of this group is in flight: its loads were awaited above)
-#pragma unroll
-        for (int g = 1; g < WGK; ++g) {
-            const int32_t* const theirs = xch + (size_t)(g - 1) * kVals * NT + tid;
-            int k = 0;
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int t = 0; t < TN; ++t)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) acc[i][t][e] += theirs[(k++) * NT];
-#pragma unroll
-            for (int t = 0; t < TN; ++t) bsum[t] += (uint32_t)theirs[(k++) * NT];
-#pragma unroll
-            for (int c = 0; c < CB; ++c)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) cacc[c][e] += theirs[(k++) * NT];
-        }
-    }
-
     // LDS scratch behind the stage buffers: [4][BN] column sums, [WGN][BM] row-sum parts,
     // [BM] checksum parts, 4 control words
     int32_t* const s_bs = reinterpret_cast<int32_t*>(smem + S * (A_STAGE + B_STAGE));
     int32_t* const s_rs = s_bs + 4 * BN;
     int32_t* const s_ck = s_rs + WGN * BM;
-    auto recombine_digits = [&]() __attribute__((always_inline)) {
-        // 16x16 accumulator: lane l, element e is row 4*(l/16) + e, column l%16; columns 0..3
-        // hold the four digit products
-#pragma unroll
-        for (int c = 0; c < CB; ++c)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int d = lane & 15;
-                uint32_t v = d < kLimbs ? ((uint32_t)cacc[c][e] << (8 * d)) : 0u;
-                v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);
-                v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);
-                if (d == 0) s_ck[wm * WTM + (wn * CB + c) * 16 + 4 * (lane >> 4) + e] = (int32_t)v;
-            }
-    };
-
-    // ------------------------- K split across workgroups: partial tiles meet in the last arrival -------------------------
-    if constexpr (kSplitK) {
-        static_assert(WGK == 1 && TM * TN == 1 && NT == 256, "split-K is built for the 64x64 tile of four 32x32 wavefronts");
-        __shared__ int s_ticket;
-        constexpr int kVals = 16 * TM * TN + TN;
-        static_assert(kVals * NT + BM == kSplitKPartInts, "layout of a partial tile");
-        const int tile = tile_m * tiles_n + tile_n;
-        int32_t* const part = p.ws_part + (size_t)tile * Z * kSplitKPartInts;
-        int32_t* const mine = part + (size_t)z * kSplitKPartInts + tid;
-        {
-            // device-scope stores (they pass through the L2, which is not coherent with the other seven): once this
-            // wavefront's stores are acknowledged and the barrier is passed, the whole partial tile is in memory
-            int k = 0;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) __hip_atomic_store(mine + (k++) * NT, acc[0][0][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(mine + (k++) * NT, (int32_t)bsum[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        if (kCheck) {
-            recombine_digits();
-            __syncthreads();
-            if (tid < BM) __hip_atomic_store(mine + kVals * NT, s_ck[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        wait_vmem();   // (also the direct-to-LDS loads still in flight)
-        __syncthreads();
-        if (tid == 0) s_ticket = __hip_atomic_fetch_add(p.ws_tickets + tile, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        if (s_ticket != Z - 1) return;   // (nothing in flight: awaited above)
-        if (tid == 0) __hip_atomic_store(p.ws_tickets + tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // the other slices' partial tiles, four at a time so that their loads are in flight together (a slice
-        // number past the last one, or this workgroup's own, re-reads a valid partial and adds nothing)
-        for (int z0 = 0; z0 < Z; z0 += 4) {
-            int32_t v[4][kVals], ck[4] = {0, 0, 0, 0};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int32_t* const theirs = part + (size_t)min(z0 + j, Z - 1) * kSplitKPartInts + tid;
-#pragma unroll
-                for (int k = 0; k < kVals; ++k) v[j][k] = __hip_atomic_load(theirs + k * NT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (kCheck && tid < BM) ck[j] = __hip_atomic_load(theirs + kVals * NT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int32_t use = (z0 + j < Z && z0 + j != z) ? -1 : 0;   // all ones or zero
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[0][0][e] += v[j][e] & use;
-                bsum[0] += (uint32_t)(v[j][16] & use);
-                if (kCheck && tid < BM) s_ck[tid] = (int32_t)((uint32_t)s_ck[tid] + (uint32_t)(ck[j] & use));
-            }
-        }
-    }
 
     // ---------------------------------- epilogue ----------------------------------
     // accumulator layout of the 32x32 MFMA: lane l, element e of block (i, t) is
@@ -895,7 +748,7 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
         uint32_t v = (uint32_t)s_bs[wn * WTN + t * 32 + lcol];
         if (SUM_WAVES == 2) v += (uint32_t)s_bs[BN + wn * WTN + t * 32 + lcol];
         // (the k-steps of small wave tiles sum signed bytes directly, the others carry a bias of 128 per byte)
-        cs[t] = 128 * (int32_t)(kAhead2 ? v : v - 128u * (uint32_t)(NS_all * BK));
+        cs[t] = 128 * (int32_t)(kAhead2 ? v : v - 128u * (uint32_t)(NS * BK));
     }
     // C_temp = accumulator + cs (undoing the a - 128 shift); the sum is formed on the way to
     // memory, the accumulators stay as they are
@@ -1071,9 +924,6 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
     }
 
     if (kCheck) {
-        if constexpr (!kSplitK) {
-        // (recombine_digits, written out: called here it gives the 256x256 kernel another register allocation and a longer epilogue,
-        // 4096x4096x4096 66.2 us against 65.7, 4096x4096x1024 26.5 against 26.0)
         // 16x16 accumulator: lane l, element e is row 4*(l/16) + e, column l%16; columns 0..3
         // hold the four digit products
 #pragma unroll
@@ -1086,7 +936,6 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
                 v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);
                 if (d == 0) s_ck[wm * WTM + (wn * CB + c) * 16 + 4 * (lane >> 4) + e] = (int32_t)v;
             }
-        }
         __syncthreads();
         // Row r of the product is spread over the tile columns; each of them adds its share of
         // (row sum - checksum) to the row's 64-bit workspace word with ONE returned atomic:
@@ -1167,32 +1016,14 @@ __global__ __launch_bounds__(WGM* WGN* WGK * 64) void gemm_tile_async_kernel(con
 #endif
 }
 
-template <int BM, int BN, int WGM, int WGN, int kStages, int WGK = 1, bool kSplitK = false, int kAnyA = 0>
+template <int BM, int BN, int WGM, int WGN, int kStages, int kAnyA = 0>
 hipError_t launch_cfg(bool check, bool want_c, bool want_q, const GemmParams& p_in, hipStream_t s) {
     GemmParams p = p_in;
     const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
-    int Z = 1;
-    if (kSplitK) {
-        // slices, tickets and partial tiles as splitk_plan lays them out; refused when the workspace does not hold them
-        const SplitKPlan pl = splitk_plan(p.M, p.N, p.KB2);
-        if (pl.z < 2 || p.ws == nullptr || p.ws_ints < pl.total_ints) return hipErrorNotSupported;
-        Z = pl.z;
-        p.ksplit = Z;
-        p.ws_tickets = p.ws + pl.tickets_off;
-        p.ws_part = p.ws + pl.part_off;
-    }
-    p.split_q = p.KB2 / (WGK * Z);   // stages per K group / slice
-    p.split_r = p.KB2 % (WGK * Z);
-    p.share_q = p.split_q / tiles_n;   // ... and, of those, of the checksum product per tile column
-    p.share_r = p.split_q % tiles_n;
-    const dim3 grid((unsigned)(tiles_m * tiles_n * Z)), block(WGM * WGN * WGK * 64);
-    const size_t lds = WGK * ((group_lds_bytes<BM, BN, WGN, kStages, WGK>() + 1023) / 1024 * 1024);
-    if (WGK > 1) {
-        // a share of the checksum product must be one that a group's staged digits hold without a refill (which would be a
-        // barrier that the other group does not pass)
-        const int longest = p.split_q + (p.split_r ? 1 : 0);
-        if (p.split_q < 2 || (longest + tiles_n - 1) / tiles_n > 32 / WGK) return hipErrorNotSupported;
-    }
+    p.share_q = p.KB2 / tiles_n;   // stages of the checksum product per tile column
+    p.share_r = p.KB2 % tiles_n;
+    const dim3 grid((unsigned)(tiles_m * tiles_n)), block(WGM * WGN * 64);
+    const size_t lds = (lds_bytes<BM, BN, WGN, kStages>() + 1023) / 1024 * 1024;
     // Row sums in block form or per row.  Small wave tiles: always the block form, which halves the
     // vector work of an epilogue that is short anyway.  The 128x128 wave tile: per row when the grid
     // fills the chip - the stores then take the time memory needs and the arithmetic between them is
@@ -1210,7 +1041,7 @@ hipError_t launch_cfg(bool check, bool want_c, bool want_q, const GemmParams& p_
     } while (0)
 #define ABFT_LAUNCH_FORM(CK, OUT, BS)                                                                     \
     do {                                                                                                  \
-        auto kern = gemm_tile_async_kernel<BM, BN, WGM, WGN, kStages, CK, OUT, ((BS) || !(CK)), WGK, kSplitK, kAnyA>; \
+        auto kern = gemm_tile_async_kernel<BM, BN, WGM, WGN, kStages, CK, OUT, ((BS) || !(CK)), kAnyA>; \
         static std::atomic<uint64_t> lds_allowed{0};                                                      \
         const hipError_t e_attr = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed);\
         if (e_attr != hipSuccess) return e_attr;                                                          \

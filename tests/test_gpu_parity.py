@@ -1388,3 +1388,43 @@ def test_requantized_full_grid(binding, gpu_util, oracle):
         assert np.array_equal(Cq.cpu().numpy(), want)
         assert (buf[:3] == 99).all() and (buf[3:].view(M, N + 5)[:, N:] == 99).all()
         assert np.array_equal(flags.cpu().numpy(), ref.flags if how == binding.ABFT_CHECK else np.zeros(M, np.int32))
+
+
+# (each tile form with one stage, stages that no wavefront, some or all wavefronts have, tiles and stages cut off, rows of whole chunks
+# and of any length; slots for 64, 128 and 256 rows; K split across workgroups)
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(1, 1, 16), (17, 33, 17), (31, 31, 128), (33, 65, 1008), (100, 129, 1153), (257, 95, 2049), (65, 200, 4111),
+                                   (300, 900, 304), (320, 1000, 1553), (257, 1025, 3090), (1000, 1000, 1296), (1023, 963, 1290), (130, 3500, 70),
+                                   (16, 1600, 80), (5, 8000, 200), (64, 1537, 1201), (65, 3200, 250), (128, 3105, 1040), (129, 1700, 144), (256, 1569, 90),
+                                   (40, 70, 8192), (129, 40, 3000), (33, 200, 5001), (3, 100, 9000)])
+def test_k_split_among_wavefronts(binding, gpu_util, oracle, M, N, K):
+    """Grids that do not fill the chip: clean, C and B faults early and late in K and in the last row and column, both outputs,
+    unchecked, errCount overwritten, added to and absent, the printed modulus where rows are whole chunks."""
+    say(f"K split among wavefronts {M}x{N}x{K}")
+    A, B = operands(M, N, K, 3 * M + N + K)
+    run = gpu_util.GpuRun(binding, B)
+    clean = oracle.checked_gemm(A, B)
+    mult = wlmod.draw_mult(np.random.default_rng(K), N, "channel")
+    bias = np.random.default_rng(M).integers(-9000, 9000, size=N).astype(np.int32)
+    out = run.gemm(A, requant=(128, 128, mult, bias))
+    assert np.array_equal(out["C"], clean.C) and not out["flags"].any() and out["err_count"] == 0 and not out["ws"].any()
+    assert np.array_equal(out["Cq"], oracle.requantize(clean.C, clean.colsum, 128, 128, mult, bias, precision="f32"))
+    out = run.gemm(A, requant=(128, 128, mult, bias), want_c=False, want_count=False)
+    assert np.array_equal(out["Cq"], oracle.requantize(clean.C, clean.colsum, 128, 128, mult, bias, precision="f32")) and not out["flags"].any()
+    assert np.array_equal(run.gemm(A, check=False)["C"], clean.C)
+    inj = [(M - 1, N - 1, 1 << 31), (0, 0, 1 << 3), (M // 2, N // 3, 0x00400000)]
+    ref = oracle.checked_gemm(A, B, flips_c=inj)
+    for accumulate in (None, 5):
+        out = run.gemm(A, injections=inj, accumulate_from=accumulate)
+        assert np.array_equal(out["C"], ref.C) and np.array_equal(out["flags"], ref.flags) and out["err_count"] == (accumulate or 0) + ref.err_count
+    for flip in ((0, N - 1, 6), (K - 1, N // 2, 7), (K // 2, 0, 2)):
+        binding.abft_packed_b_flip_bit(run.Bp, *flip)
+        ref = oracle.checked_gemm(A, B, flips_b=[flip])
+        out = run.gemm(A)
+        assert np.array_equal(out["C"], ref.C) and np.array_equal(out["flags"], ref.flags) and out["err_count"] == ref.err_count
+        binding.abft_packed_b_flip_bit(run.Bp, *flip)
+    if K % 16 == 0:
+        C127, flags127, count127 = oracle.checked_gemm_mod127(A, B, flips_c=inj)
+        out = run.gemm(A, injections=inj, mod127=True)
+        assert np.array_equal(out["C"], C127) and np.array_equal(out["flags"], flags127) and out["err_count"] == count127
+    assert not run.gemm(A)["flags"].any()
