@@ -116,7 +116,7 @@ try:
 except ImportError as e:
     raise ImportError(f"{e}: build it with `python -m paper_2103_00130_amd.build`") from e
 _fastcall.bind(ctypes.cast(lib.abft_gemm_u8s8s32_checked, ctypes.c_void_p).value, ctypes.cast(lib.abft_eb_u8_checked, ctypes.c_void_p).value,
-               torch.cuda.current_device, torch._C._cuda_getCurrentRawStream)
+               torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
 
 
 def _check(rc: int):

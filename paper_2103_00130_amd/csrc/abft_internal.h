@@ -149,6 +149,7 @@ struct GemmParams {
     int32_t* ws_tickets;       // split-K: one arrival counter per tile and finishing wavefront
     int32_t* ws_part;          // split-K: parts, [tile][finishing wavefront][slice][value][lane]
     int wk_stages;             // K split among wavefronts: stages of the wavefronts with fewest; those with one more deal out
+    int wk_stream;             // ... the weight is larger than the memory-side cache
     int wk_share_q1, wk_share_r1;  // their k-steps of the checksum product by these instead of share_q, share_r
     size_t ws_ints;            // ints the caller's workspace holds
     unsigned long long* clock_trace;  // diagnostic builds (ABFT_CLOCK_TRACE): 6 words per workgroup, else NULL
@@ -156,6 +157,7 @@ struct GemmParams {
 };
 
 constexpr int kWsHeaderInts = 64;
+constexpr int kWsDoneSlots = 16;    // 64-bit words at the start of the header where many reports of finished rows meet first
 constexpr int kWsDoneWord = 48;     // int offset, inside the header, of the 64-bit word that counts finished rows (low half)
                                     // and corrupted ones among them (high half)
 // the streaming kernel spreads its per-row sums over kSmallMSlots slots of kSmallMRows rows
@@ -266,21 +268,25 @@ enum WkForm { kWkNone = 0, kWk32x32w4, kWk32x32w8, kWk32x64w4, kWk32x64w8, kWk64
 //  * as long as no compute unit has two: 32x32 tiles, eight wavefronts from nine stages on (441x479x1255 8.7 / 5.2, with four 5.3;
 //    322x306x80 4.8 / 4.3, with four 4.2);
 //  * then 32x64 tiles (674x480x2048 7.8 / 5.7; 1246x204x3856 10.5 / 7.4 with eight wavefronts, 7.6 with four);
-//  * then 64x64 tiles where the loop is long enough to pay for the sums at the end (1000x1000x3200 10.1 / 9.6, but 1024x1024x1024
-//    6.9 / 7.4);
+//  * then 64x64 tiles where the loop is long enough to pay for the sums at the end (1000x1000x3200 10.1 / 9.6, but 2537x352x1200
+//    8.4 / 8.9);
 //  * up to two 32x64 tiles per compute unit for a short K where 64 rows a tile are partly padding or the rows are no whole chunks
 //    (78x6549x96 7.4 / 6.7, 65x9664x688 9.2 / 6.6, 2042x336x146 6.0 / 4.8; but 773x928x240 5.4 / 5.5);
-//  * not for up to 16 rows of a middling K, where half the tile is padding and the streaming kernel has all its loads under way
-//    at once (16x4096x2048 4.8 / 5.1, 7x660x3872 5.0 / 5.5; but 8x4096x4096 6.7 / 6.0, 12x8368x3424 11.0 / 7.3, 4x864x96 4.4 / 3.4,
-//    13x144x11067 16.6 / 7.8 split across workgroups).
+//  * up to two 64x64 tiles for such rows (2000x1000x479 both outputs 10.9 / 9.4, 900x2000x777 11.1 / 9.9, 600x3000x250 8.9 / 8.1;
+//    576 tiles, 1500x1500x700 12.2 / 14.3);
+//  * not for up to 16 rows of a middling K where the streaming kernel's 16 columns a workgroup give more of them: few columns
+//    (1x240x1696 4.0 / 4.5, 10x464x4064 4.9 / 5.4, 1x145x6128 6.0 / 6.4; but 8x748x2656 5.2 / 4.9, 1x800x3200 5.0 / 4.8, 4x864x96 4.4 / 3.4,
+//    13x144x11067 16.6 / 7.8) and, where arrivals go by slots there, many (7x3696x2000 4.6 / 4.8, 16x4096x2048 4.8 / 5.0; but 8x4096x4096
+//    5.4 / 5.4, with another weight at every call less).
 inline WkForm wk_form(int M, int N, int stages, bool whole_a) {
     const int64_t t32 = (int64_t)((M + 31) / 32) * ((N + 31) / 32), t3264 = (int64_t)((M + 31) / 32) * ((N + 63) / 64),
                   t64 = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
-    if (M <= 16 && N <= 4096 && stages > 8 && stages < 32) return kWkNone;
+    if (M <= 16 && whole_a && stages > 8 && (N <= 640 ? stages < 64 : N > 1500 && N <= 4096 && stages <= 20)) return kWkNone;
     if (t32 <= 256) return stages >= 9 ? kWk32x32w8 : kWk32x32w4;
     if (t3264 <= 256) return stages >= 24 ? kWk32x64w8 : kWk32x64w4;
-    if (t64 <= 256 && stages >= 10) return kWk64x64w4;
-    if (t3264 <= 512 && stages < 10 && (!whole_a || M <= 128)) return kWk32x64w4;
+    if (t64 <= 256 && stages >= 12) return kWk64x64w4;
+    if (t3264 <= 512 && stages < 12 && (!whole_a || M <= 128)) return kWk32x64w4;
+    if (!whole_a && t64 <= 512 && stages <= 10) return kWk64x64w4;
     return kWkNone;
 }
 

@@ -48,10 +48,14 @@ constexpr int xch_bytes() { return TM * TN * 4096 + TN * 256 + TM * 512; }
 template <int TM, int TN>
 constexpr int wave_bytes() { return ((slot_bytes<TM, TN>() > xch_bytes<TM, TN>() ? slot_bytes<TM, TN>() : xch_bytes<TM, TN>()) + 1023) / 1024 * 1024; }
 
-// sixteen bytes per lane from sbase + voff + OFF to LDS address lds + LDS + OFF + lane * 16 (see gemm_tile_async.h)
-template <int LDS, int OFF>
+// sixteen bytes per lane from sbase + voff + OFF to LDS address lds + LDS + OFF + lane * 16 (see gemm_tile_async.h); kStream: not kept
+// in the caches
+template <int LDS, int OFF, bool kStream>
 __device__ __attribute__((always_inline)) inline void load_to_lds(uint32_t lds, uint32_t voff, const void* sbase) {
-    asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" ::"s"(lds), "v"(voff), "s"(sbase), "n"(OFF), "n"(LDS) : "m0", "scc", "memory");
+    if constexpr (kStream)
+        asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3 nt" ::"s"(lds), "v"(voff), "s"(sbase), "n"(OFF), "n"(LDS) : "m0", "scc", "memory");
+    else
+        asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" ::"s"(lds), "v"(voff), "s"(sbase), "n"(OFF), "n"(LDS) : "m0", "scc", "memory");
 }
 // The digit MFMA with its accumulator in ordinary vector registers: left to the compiler, which gives the MFMAs of a function one
 // class of registers for their results, the digit accumulators move to accumulation registers and back around every one of them.
@@ -149,7 +153,9 @@ __global__ __launch_bounds__(W * 64) void gemm_tile_wk_kernel(const GemmParams p
     }
     uint32_t a_voff[A_LD];
     const uint8_t* a_row[A_LD];
-    v4i ra[A_LD];
+    v4i ra[A_LD] = {};
+    // loads whose rows all lie past the last one are left out: what LDS holds there goes into sums that nobody stores or reports
+    const int a_loads = min((p.M - row0 + 7) / 8, A_LD);
 #pragma unroll
     for (int i = 0; i < A_LD; ++i) {
         const int r = i * 8 + (lane >> 3);
@@ -159,6 +165,7 @@ __global__ __launch_bounds__(W * 64) void gemm_tile_wk_kernel(const GemmParams p
     constexpr int64_t B_KB_STRIDE = (int64_t)kUnitsPerTile * kUnitBytes;
     const int8_t* const b_base = p.packed + packed_unit_offset(col0 / kTileN, 0, (col0 % kTileN) / kUnitN, p.KB2 * 2);
     const uint32_t b_voff = lane * 16;
+    const bool stream = p.wk_stream != 0;
 
     const bool cut = p.K < p.KB2 * BK;   // the last stage is cut off: a chunk at or past K is re-read from the last whole chunk (it meets zero rows of B)
     const int c16_over = ((lane & 7) ^ ((lane >> 4) & 7)) * 16 - (p.K - 16 - (p.KB2 - 1) * BK);           // of loads of even number ...
@@ -167,26 +174,31 @@ __global__ __launch_bounds__(W * 64) void gemm_tile_wk_kernel(const GemmParams p
     auto issue_stage = [&](int i) __attribute__((always_inline)) {
         const int s = s_base + wave + i * W;
         if (kCheck && u_lo < 4 * i + 4 && u_hi > 4 * i)
-            load_to_lds<(BM + BN) * BK, 0>(lds_mine, (uint32_t)min(lane * 16, 512 - 16), p.limbs + (int64_t)s * 512);
+            load_to_lds<(BM + BN) * BK, 0, false>(lds_mine, (uint32_t)min(lane * 16, 512 - 16), p.limbs + (int64_t)s * 512);
         if constexpr (!kAny) {
             const uint8_t* const a = p.A + (int64_t)s * BK;
             const bool last = cut && s == p.KB2 - 1;
             const uint32_t over0 = last ? (uint32_t)max(c16_over, 0) : 0u, over1 = last ? (uint32_t)max(c16_over1, 0) : 0u;
             for_each<A_LD>([&](auto n) __attribute__((always_inline)) {
                 constexpr int at = n.value;
-                load_to_lds<at * 1024, 0>(lds_mine, a_voff[at] - (at & 1 ? over1 : over0), a);
+                if (at < a_loads) load_to_lds<at * 1024, 0, false>(lds_mine, a_voff[at] - (at & 1 ? over1 : over0), a);
             });
         }
-        for_each<B_LD>([&](auto n) __attribute__((always_inline)) {
-            constexpr int kbl = n.value / (B_LD / 2), c = n.value % (B_LD / 2);
-            load_to_lds<BM * BK + kbl * (BN * 64), c * 1024>(lds_mine, b_voff, b_base + (int64_t)(2 * s + kbl) * B_KB_STRIDE);
-        });
+        auto load_b = [&](auto stream_c) __attribute__((always_inline)) {
+            for_each<B_LD>([&](auto n) __attribute__((always_inline)) {
+                constexpr int kbl = n.value / (B_LD / 2), c = n.value % (B_LD / 2);
+                load_to_lds<BM * BK + kbl * (BN * 64), c * 1024, decltype(stream_c)::value>(lds_mine, b_voff, b_base + (int64_t)(2 * s + kbl) * B_KB_STRIDE);
+            });
+        };
+        if (TN == 2 && stream) load_b(std::true_type{});
+        else load_b(std::false_type{});
         if constexpr (kAny) {
             // rows of any alignment come in through registers (behind the loads of B: the wait for them covers those); nothing
             // past the operand is read: a chunk at or past K - 16 is loaded from K - 16
             const int k = min(s * BK + (lane & 7) * 16, p.K - 16);
 #pragma unroll
-            for (int n = 0; n < A_LD; ++n) ra[n] = *reinterpret_cast<const v4i_any*>(a_row[n] + k);
+            for (int n = 0; n < A_LD; ++n)
+                if (n < a_loads) ra[n] = *reinterpret_cast<const v4i_any*>(a_row[n] + k);
         }
     };
     if (wave < NS) issue_stage(0);
@@ -520,16 +532,44 @@ __global__ __launch_bounds__(W * 64) void gemm_tile_wk_kernel(const GemmParams p
         }
         const unsigned long long fin_mask = __ballot(fin), bad_mask = __ballot(fin && bad);
         if (err_count == nullptr) {
+            // no count was asked for
         } else if (p.err_accumulate || tiles_m == 1) {
             if (bad_mask != 0ull && lane == __builtin_ctzll(bad_mask))
                 __hip_atomic_fetch_add(err_count, (int32_t)__builtin_popcountll(bad_mask), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else if (fin_mask != 0ull && lane == __builtin_ctzll(fin_mask)) {
-            unsigned long long* const w_done = reinterpret_cast<unsigned long long*>(ws + kWsDoneWord);
-            const uint32_t n_fin = (uint32_t)__builtin_popcountll(fin_mask), n_bad = (uint32_t)__builtin_popcountll(bad_mask);
-            const unsigned long long old = __hip_atomic_fetch_add(w_done, ((unsigned long long)n_bad << 32) | n_fin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if ((uint32_t)old + n_fin == (uint32_t)p.M) {
-                *err_count = (int32_t)((uint32_t)(old >> 32) + n_bad);
-                __hip_atomic_store(w_done, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+            // Finished rows are reported, the corrupted ones among them in the high half; the report that brings the count to M writes
+            // errCount.  The wavefronts of a workgroup report together (a K split's finish apart), and where there are many
+            // tile rows the reports of every sixteenth meet at a word of their own first (2739x80x112, 86 tile rows of 32:
+            // 8.4 us with a report per wavefront at one word).
+            unsigned long long report = ((unsigned long long)__builtin_popcountll(bad_mask) << 32) | (uint32_t)__builtin_popcountll(fin_mask);
+            if constexpr (!kSplit && F > 1) {
+                unsigned long long* const s_report = reinterpret_cast<unsigned long long*>(smem + W * WAVE);
+                if (lane == 0) s_report[wave] = report;
+                __syncthreads();
+                report = 0;
+#pragma unroll
+                for (int w = 0; w < F; ++w) report += s_report[w];
+                if (wave != 0) return;
+            }
+            if (lane == 0 && (uint32_t)report != 0u) {
+                unsigned long long* const head = reinterpret_cast<unsigned long long*>(ws);
+                bool go = true;
+                if (tiles_m > 2 * kWsDoneSlots) {
+                    const int slot_m = tile_m & (kWsDoneSlots - 1), last = tiles_m - 1;
+                    const int rows = ((last - slot_m) / kWsDoneSlots + 1) * BM - ((last & (kWsDoneSlots - 1)) == slot_m ? tiles_m * BM - p.M : 0);
+                    const unsigned long long before = __hip_atomic_fetch_add(head + slot_m, report, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    report += before;
+                    go = (uint32_t)report == (uint32_t)rows;
+                    if (go) __hip_atomic_store(head + slot_m, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                if (go) {
+                    unsigned long long* const w_done = reinterpret_cast<unsigned long long*>(ws + kWsDoneWord);
+                    report += __hip_atomic_fetch_add(w_done, report, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if ((uint32_t)report == (uint32_t)p.M) {
+                        *err_count = (int32_t)(uint32_t)(report >> 32);
+                        __hip_atomic_store(w_done, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                }
             }
         }
     }
@@ -557,6 +597,9 @@ hipError_t launch_any(bool check, bool want_c, bool want_q, const GemmParams& p_
     p.share_r = 4 * p.wk_stages % tiles_n;
     p.wk_share_q1 = 4 * (p.wk_stages + 1) / tiles_n;
     p.wk_share_r1 = 4 * (p.wk_stages + 1) % tiles_n;
+    // A weight larger than the 256 MiB memory-side cache passes through without being kept there (16x16384x16384, another weight at every
+    // call: 52.1 us, 46.2 this way); a smaller one may still be there at the next call (16x8192x8192, three weights in turn: 13.9, 18.7 this way).
+    p.wk_stream = (int64_t)p.N * p.K >= (int64_t)224 << 20;
     const uint32_t per_strip = (uint32_t)(tiles_m < 4 ? tiles_m : 4) * (uint32_t)tiles_n;
     const uint32_t strip_rcp = per_strip == 1 ? 0u : (uint32_t)((0x100000000ull + per_strip - 1) / per_strip);
     // Arrivals at one word follow each other at 10 to 20 ns.  From 49 tile columns on (never fewer than slots), and as long as the
@@ -568,7 +611,7 @@ hipError_t launch_any(bool check, bool want_c, bool want_q, const GemmParams& p_
     static_assert((32 + 1) * 64 <= kSmallMSlots * kSmallMRows + kSmallMRows && (8 + 1) * 128 <= kSmallMSlots * kSmallMRows && (4 + 1) * 256 <= kSmallMSlots * kSmallMRows,
                   "the slots fit the words of every call");
     const dim3 grid((unsigned)(tiles_m * tiles_n * (kSplit ? p.ksplit : 1))), block(W * 64);
-    const size_t lds = (size_t)W * wave_bytes<TM, TN>();
+    const size_t lds = (size_t)W * wave_bytes<TM, TN>() + 64;   // (the wavefronts' parts, and their reports)
 #define ABFT_LAUNCH(CK, OUT)                                                                              \
     do {                                                                                                  \
         auto kern = gemm_tile_wk_kernel<TM, TN, W, CK, OUT, kAny, kSplit>;                                \
