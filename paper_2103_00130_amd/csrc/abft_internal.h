@@ -149,7 +149,7 @@ struct GemmParams {
     int32_t* ws_tickets;       // split-K: one arrival counter per tile and finishing wavefront
     int32_t* ws_part;          // split-K: parts, [tile][finishing wavefront][slice][value][lane]
     int wk_stages;             // K split among wavefronts: stages of the wavefronts with fewest; those with one more deal out
-    int wk_stream;             // ... the weight is larger than the memory-side cache
+    int wk_stream;             // ... the weight is not kept in the caches
     int wk_share_q1, wk_share_r1;  // their k-steps of the checksum product by these instead of share_q, share_r
     size_t ws_ints;            // ints the caller's workspace holds
     unsigned long long* clock_trace;  // diagnostic builds (ABFT_CLOCK_TRACE): 6 words per workgroup, else NULL

@@ -597,9 +597,12 @@ hipError_t launch_any(bool check, bool want_c, bool want_q, const GemmParams& p_
     p.share_r = 4 * p.wk_stages % tiles_n;
     p.wk_share_q1 = 4 * (p.wk_stages + 1) / tiles_n;
     p.wk_share_r1 = 4 * (p.wk_stages + 1) % tiles_n;
-    // A weight larger than the 256 MiB memory-side cache passes through without being kept there (16x16384x16384, another weight at every
-    // call: 52.1 us, 46.2 this way); a smaller one may still be there at the next call (16x8192x8192, three weights in turn: 13.9, 18.7 this way).
-    p.wk_stream = (int64_t)p.N * p.K >= (int64_t)224 << 20;
+    // A weight of a good part of the 256 MiB memory-side cache, read once, passes through without being kept there: with others of its size
+    // in the program it would not be there at the next call (three weights in turn, us, kept / passed through: 16x16384x16384 52.1 / 46.2,
+    // 12000x12000 and 8 rows 30.2 / 27.1, 16384x6400 and 32 rows 22.1 / 20.6; but 16x8192x8192 13.9 / 18.7; read by two rows of tiles,
+    // 33x8192x12000, 24.6 / 36.4).  Up to 32 rows, which were always read that way; beyond, only what the cache cannot hold at all
+    // (60 rows of 12000x12000 alone in a loop 28.6 / 38.3).
+    p.wk_stream = tiles_m == 1 && (int64_t)p.N * p.K >= (int64_t)(p.M <= 32 ? 96 : 224) << 20;
     const uint32_t per_strip = (uint32_t)(tiles_m < 4 ? tiles_m : 4) * (uint32_t)tiles_n;
     const uint32_t strip_rcp = per_strip == 1 ? 0u : (uint32_t)((0x100000000ull + per_strip - 1) / per_strip);
     // Arrivals at one word follow each other at 10 to 20 ns.  From 49 tile columns on (never fewer than slots), and as long as the
