@@ -229,7 +229,7 @@ def cpu_baseline(job, target_s=12.0):
 
 def smallm_sweep(b, torch, steps, warmup, count_flag=0, M=16,
                  shapes=((4096, 2048), (4096, 4096), (8192, 8192), (16384, 16384), (16384, 32768))):
-    """The streaming kernel on weights from 8 MiB to 512 MiB (N x K int8), M = 16: how close to the HBM
+    """Sixteen rows on weights from 8 MiB to 512 MiB (N x K int8), by the kernel the library picks: how close to the HBM
     roofline it gets once the weight is large enough to amortise the launch.  Operands are seeded draws on
     the device (timing only; parity of these kernels is the tests' business)."""
     out = []
@@ -362,7 +362,7 @@ def clock_trace(b, torch, args):
 
 
 def splitk_points(b, torch, steps, count_flag, shapes=((256, 1024, 8192), (128, 128, 16384), (256, 512, 4096))):
-    """Few 64x64 tiles and a long K: the library splits K across workgroups when the workspace has room for the
+    """Few tiles and a long K: the library splits K across workgroups when the workspace has room for the
     partial tiles; the same launch on a workspace of the row words alone runs unsplit.  Seeded draws on the device."""
     out = []
     gen = torch.Generator(device="cuda")
@@ -756,9 +756,9 @@ def main():
         torch.cuda.empty_cache()
         out["smallm_sweep"] = smallm_sweep(b, torch, args.steps, args.warmup, 0 if args.overwrite_count else b.ABFT_ERRCOUNT_ACCUMULATE)
         out["splitk"] = splitk_points(b, torch, args.steps, 0 if args.overwrite_count else b.ABFT_ERRCOUNT_ACCUMULATE)
-        out["splitk_note"] = ("few 64x64 tiles, long K: K split across workgroups (four slices and more from 24 128-k stages on, two or three from 40) "
-                              "against the same launch unsplit (a workspace without room for the partial tiles)")
-        out["smallm_sweep_note"] = ("streaming kernel, M = 16, weights of growing size rotated through >= 768 MiB of packed "
+        out["splitk_note"] = ("few 32x32 tiles, long K: K split across workgroups (up to 64 tiles from 64 128-k stages on, up to eight from 24) "
+                              "against the same launch unsplit (a workspace without room for the parts)")
+        out["smallm_sweep_note"] = ("M = 16, weights of growing size rotated through >= 768 MiB of packed "
                                     "copies (nothing served from cache): algorithmic bytes / time against 8 TB/s")
     if not args.no_eb:
         # second operator (Algorithm 2): Table I at d = 64 and the same table under a large batch; with

@@ -144,10 +144,9 @@ typedef struct {
 /* Scratch the checked GEMM needs for a problem with M rows against Bp: one
  * 64-bit word per row (partial row sum - checksum, and how many column blocks
  * have contributed) and a few counting words (rows finished, rows corrupted);
- * with Bp given, also room for the partial tiles of a K split across
- * workgroups on the shapes where the library uses one (few tiles, K of about
- * 3000 and more), and for a copy of A with padded rows where K is no multiple
- * of 16 and the product is large enough for the copy to pay.  Such room is used
+ * with Bp given, also room for the parts of a K split across workgroups on the
+ * shapes where the library may use one (few tiles, K of about 3000 and more),
+ * and for a copy of A with padded rows where K is no multiple of 16 and the product is large enough for the copy to pay.  Such room is used
  * wherever the workspace holds it, whatever it was sized for; a smaller one, of
  * at least the size that this call returns for Bp == NULL, runs without it, with
  * the same results.

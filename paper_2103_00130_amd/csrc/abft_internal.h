@@ -145,7 +145,7 @@ struct GemmParams {
     const void* inj;           // abft_inject_t[n_inj]
     int n_inj;
     int ksplit;                // K slices across workgroups (split-K kernels; 1 elsewhere)
-    int split_q, split_r;      // stages of a slice, or of a K group inside the workgroup; the first split_r take one more
+    int split_q, split_r;      // stages of a slice; the first split_r take one more
     int32_t* ws_tickets;       // split-K: one arrival counter per tile and finishing wavefront
     int32_t* ws_part;          // split-K: parts, [tile][finishing wavefront][slice][value][lane]
     int wk_stages;             // K split among wavefronts: stages of the wavefronts with fewest; those with one more deal out
@@ -219,9 +219,10 @@ inline SplitKPlan splitk_plan(int M, int N, int stages, bool whole_a) {
 
 // Rows of A that are no whole, aligned 16-byte chunks (K no multiple of 16, or such a base or leading dimension): either the
 // 64x64 kernel with loads through registers takes them as they lie, or a copy with padded rows is made first, in the
-// workspace, for the direct-to-LDS kernels.  The copy costs about 3 us (a launch and a pass over A); the loads through
-// registers cost 0.2-0.3 us more for every stage that a compute unit works through, and the large tiles and K splits are
-// out of reach, so the copy pays from about twenty stages per unit on (measured in us, loads through registers / copy:
+// workspace, for the direct-to-LDS kernels (grids that gemm_tile_wk.h does not take).  The copy costs
+// about 3 us (a launch and a pass over A); the loads through registers cost 0.2-0.3 us more for every stage that a compute
+// unit works through, and the large tiles are out of reach, so the copy pays from about twenty stages per unit on
+// (measured in us, loads through registers / copy:
 // 2000x1000x1001, 16 stages per unit, 11.5 / 11.8; 256x512x2049, 17, 10.8 / 11.4; 1111x3333x777, 28, 16.5 / 14.9;
 // 1000x1000x4097, 33, 20.3 / 16.9; 4096x2048x1023, 64, 30.2 / 23.1; 4096x4096x4095, 512, 148 / 74).
 // abft_gemm_workspace_bytes includes the room when K is no multiple of 16 and the copy would be made (copies above 512 MiB
@@ -245,7 +246,8 @@ inline RealignPlan realign_plan(int M, int N, int K, int stages) {
 __host__ __device__ inline int share_begin(int c, int q, int r) { return c * q + (c < r ? c : r); }
 
 #ifdef __HIPCC__
-// The sixteen bytes of v (four 32-bit words) moved down by n places, zeros coming in; n is 1..15.  For the end of a row whose length is no multiple of 16: its last sixteen bytes, loaded as they lie,
+// The sixteen bytes of v (four 32-bit words) moved down by n places, zeros coming in; n is 1..15.  For the end
+// of a row whose length is no multiple of 16: its last sixteen bytes, loaded as they lie,
 // become the last chunk.
 typedef int shift_v4i __attribute__((ext_vector_type(4)));
 __device__ inline shift_v4i shift_down(shift_v4i v, int n) {
