@@ -14,8 +14,12 @@
 //    lane; the chip is filled by lookups, and the lanes of a lookup walk its index list in order.
 //  * Group kernel: one, two or four wavefronts per lookup.  Their threads fetch different 16-byte
 //    pieces of the lookup's records into LDS, then, owning columns, walk the staged rows in index order.
-//  * The loads are ordinary ones: marked as streaming, a record that straddles two lines has the second fetched anew (16384 lookups
-//    of 100 rows of 80 bytes 56.9 us, 50.4 without the mark; 16987 of 36 rows of 272 bytes 49.7 / 39.9; 65536 of 4 rows of 80 18.7 / 15.6).
+//  * The loads of the records are ordinary ones where lookups are many: rows that come back, in the same batch or a later one, are
+//    then found in the caches (the same 16384 lookups of 100 rows of 80 bytes again and again: 50.4 us, 56.9 marked as streaming;
+//    16987 of 36 rows of 272 bytes 39.9 / 49.7; 65536 of 4 rows of 80 15.6 / 18.7), which costs something where no row comes back
+//    (eight such batches in turn, 2.5 GB of lines: 60.6 / 58.5, rows of whole lines 46.2 / 44.0).  Four wavefronts per lookup, the
+//    form for few lookups, whose time is latency, mark them (10 lookups of 100 rows never read before: 5.0 us, 5.55 without;
+//    read before: 4.5 either way).
 //  * Every load is unconditional (clamped position, row 0 in place of a bad index): a load under
 //    `if (valid)` is followed by a wait, which would put the loads of a lookup one after the other.
 //  Both accumulate every output column in the same order (index order, one fused multiply-add
@@ -395,7 +399,8 @@ __global__ __launch_bounds__(W * 64) void eb_group_kernel(const EbParams p) {
             const int g = l * NT + tid, pc = g % P;
             x.ok[l] = (uint64_t)ix.idx[l] < (uint64_t)p.rows;
             if (kWeighted) x.w[l] = ix.w[l];
-            x.v[l] = *reinterpret_cast<const v4u*>(p.tab + (x.ok[l] ? ix.idx[l] : 0) * p.stride + pc * 16);
+            const v4u* rec = reinterpret_cast<const v4u*>(p.tab + (x.ok[l] ? ix.idx[l] : 0) * p.stride + pc * 16);
+            x.v[l] = W == 4 ? __builtin_nontemporal_load(rec) : *rec;
         }
     };
     // A row's scalars go to arrays of their own: the weighted scale and bias, and its term of Eq. 4 to a sum.  A row that is not
