@@ -237,7 +237,10 @@ inline RealignPlan realign_plan(int M, int N, int K, int stages) {
     const int64_t tiles = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
     pl.lda = ((int64_t)K + 15) / 16 * 16;
     pl.copy = (tiles + 255) / 256 * stages >= 20 && M <= kWsRows && pl.lda * M <= (512ll << 20);
-    pl.off = kWsScratchOff;
+    // (behind the parts of a K split: with 64x64 tiles asked for, the padded rows may be multiplied in slices that store their
+    // parts while others still read the copy)
+    const SplitKPlan sk = splitk_plan(M, N, stages, true);
+    pl.off = sk.z > 1 ? sk.total_ints : kWsScratchOff;
     pl.total_ints = pl.off + (size_t)(pl.lda * M / 4) + 4;
     return pl;
 }

@@ -1,0 +1,63 @@
+"""The rules by which a checked product is laid out in its workspace (csrc/abft_internal.h, host code), built here on their own."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2103_00130_amd", "csrc")
+SRC = """
+#include "abft_internal.h"
+extern "C" void plan(int M, int N, int K, int stages, int whole, long long* out) {
+    const abft::SplitKPlan s = abft::splitk_plan(M, N, stages, whole != 0);
+    const abft::RealignPlan r = abft::realign_plan(M, N, K, stages);
+    const long long v[] = {s.z, (long long)s.tickets_off, (long long)s.part_off, (long long)s.total_ints, (long long)s.room_ints, r.copy, (long long)r.off,
+                           (long long)r.total_ints, (long long)abft::ws_base_ints(M)};
+    for (int i = 0; i < 9; ++i) out[i] = v[i];
+}
+"""
+
+
+class Plan:
+    def __init__(self, v):
+        self.z, self.tickets_off, self.part_off, self.split_ints, self.room_ints, self.copy, self.copy_off, self.copy_ints, self.words = v
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("plan") / "plan.so")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-shared", "-fPIC", f"-I{CSRC}", f"-I{rocm}/include", "-x", "c++", "-",
+                    "-o", lib], input=SRC, text=True, check=True)
+    so = ctypes.CDLL(lib)
+
+    def call(M, N, K, whole):
+        out = (ctypes.c_longlong * 9)()
+        so.plan(M, N, K, ((K + 63) // 64 + 1) // 2, whole, out)
+        return Plan(out)
+    return call
+
+
+SIZES = [1, 16, 32, 33, 40, 41, 48, 64, 65, 128, 129, 200, 256, 500, 512, 1000, 4097]
+WIDTHS = [1, 32, 33, 64, 100, 200, 256, 500, 1000, 4096, 9000]
+DEPTHS = [17, 385, 2049, 2999, 3071, 3073, 4609, 5001, 6145, 8191, 9001, 16383, 40001]
+
+
+def test_copy_and_parts_lie_apart(plan):
+    """Wherever a call may both copy the rows of A and split K (its copy has whole rows), neither area reaches into the other, nor
+    into the words, and a workspace that holds the copy holds the parts too."""
+    both = 0
+    for M in SIZES:
+        for N in WIDTHS:
+            for K in DEPTHS:
+                p = plan(M, N, K, 1)
+                assert p.words <= p.tickets_off < p.part_off
+                if p.copy:
+                    assert p.copy_off >= p.part_off and p.copy_ints >= p.copy_off + M * ((K + 15) // 16 * 16) // 4
+                if p.copy and p.z > 1:
+                    both += 1
+                    assert p.copy_off >= p.split_ints, (M, N, K, p.z)
+                for whole in (0, 1):
+                    s = plan(M, N, K, whole)
+                    assert s.z == 1 or s.split_ints <= s.room_ints, (M, N, K)
+    assert both > 50

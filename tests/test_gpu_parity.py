@@ -1122,6 +1122,37 @@ def test_rows_that_are_no_whole_chunks(binding, gpu_util, oracle, M, N, K):
         assert np.array_equal(out["Cq"], oracle.requantize(ref.C, ref.colsum, 128, 128, mult, precision="f32"))
 
 
+# (one and several tile columns; two to sixteen slices)
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(65, 64, 3001), (64, 32, 32001), (129, 40, 9001), (64, 64, 16383), (256, 200, 9001), (512, 100, 9001)])
+def test_padded_copy_and_k_split_in_one_call(binding, gpu_util, oracle, M, N, K):
+    """64x64 tiles asked for, rows that are no whole chunks, few tiles and a long K: the rows are copied into the workspace and K is
+    split across workgroups, whose parts go there too, beside the copy.  One workspace for all calls, tickets left zero."""
+    import torch
+    say(f"copy and K split: {M}x{N}x{K}")
+    A, B = operands(M, N, K, M + N + K)
+    run = gpu_util.GpuRun(binding, B)
+    ws = binding.Workspace(M, run.Bp)
+    tickets, scratch = 64 + 2 * 131072, 64 + 2 * 131072 + 1024     # ints into the workspace
+    clean = oracle.checked_gemm(A, B)
+    inj = [(M - 1, N - 1, 1 << 31), (M // 2, N // 3, 1 << 7)]
+    refi = oracle.checked_gemm(A, B, flips_c=inj)
+    flip = (K - 1, N // 2, 6)
+    refb = oracle.checked_gemm(A, B, flips_b=[flip])
+    for _ in range(4):
+        ws.tensor[scratch:].zero_()
+        out = run.gemm(A, variant="tile64", ws=ws)
+        assert np.array_equal(out["C"], clean.C) and not out["flags"].any() and out["err_count"] == 0
+        assert not ws.tensor[:scratch].any() and ws.tensor[scratch:scratch + 1280].any(), "the parts of a split come first"
+        assert np.array_equal(run.gemm(A, variant="tile64", ws=ws, check=False)["C"], clean.C)
+        out = run.gemm(A, variant="tile64", ws=ws, injections=inj, accumulate_from=3)
+        assert np.array_equal(out["C"], refi.C) and np.array_equal(out["flags"], refi.flags) and out["err_count"] == 3 + refi.err_count
+    binding.abft_packed_b_flip_bit(run.Bp, *flip)
+    out = run.gemm(A, variant="tile64", ws=ws)
+    assert np.array_equal(out["C"], refb.C) and np.array_equal(out["flags"], refb.flags) and out["err_count"] == refb.err_count
+    assert not ws.tensor[tickets:scratch].any()
+
+
 @pytest.mark.gpu
 def test_one_workspace_for_calls_of_different_sizes(binding, gpu_util, oracle):
     """A K split's partial tiles and a padded copy of A are left behind in the workspace: the next call, of other sizes and
