@@ -97,14 +97,24 @@ __global__ __launch_bounds__(W * 64) void gemm_tile_wk_kernel(const GemmParams p
     if (kWantQ) asm volatile("" : "+s"(Cq), "+s"(ldcq), "+s"(rq_zA), "+s"(rq_zC));
     int tile_m, tile_n, z = 0;
     {
-        // an XCD gets a compact block of tiles, walked in strips of four tile rows (see gemm_tile_async.h); quotients by
-        // multiplication with rounded-up reciprocals, exact for the at most 65535 tiles of a launch
+        // An XCD gets a compact block of tiles, walked in strips of four tile rows (see gemm_tile_async.h), whatever their number: with
+        // the tiles of a column spread over the XCDs every L2 fetches it (us, spread / in blocks: 64x5000x12000 23.1 / 18.5,
+        // 128x3000x9008 21.9 / 14.9, 100x3000x9001 21.8 / 16.6, 600x3000x250 8.1 / 7.3).  Quotients by multiplication with rounded-up
+        // reciprocals, exact for the at most 65535 tiles of a launch.
         const int n_tiles = tiles_m * tiles_n;
         int t = (int)blockIdx.x;
         if (kSplit) {   // slice z, then the tile
             for (; t >= n_tiles; t -= n_tiles) ++z;
-        } else if (n_tiles % 8 == 0) {
-            t = (t & 7) * (n_tiles >> 3) + (t >> 3);
+        } else {
+            const int x = t & 7;
+            t = x * (n_tiles >> 3) + (t >> 3);
+            // The first n_tiles % 8 XCDs have a tile more.  (The empty asm keeps this a branch of its own: as part of the sum above it moves
+            // the loads of the launch parameters apart, 0.1 us a call.)
+            if (n_tiles % 8 != 0) {
+                int more = min(x, n_tiles & 7);
+                asm volatile("" : "+s"(more));
+                t += more;
+            }
         }
         const int strip = (int)__umulhi((uint32_t)t, strip_rcp), r = t - strip * min(tiles_m, 4) * tiles_n;
         const int h = min(4, tiles_m - strip * 4);

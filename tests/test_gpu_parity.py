@@ -1356,6 +1356,20 @@ def test_unequal_runs_and_wide_blocks(binding, gpu_util, oracle, M, N, K):
     assert np.array_equal(out["C"], Cw) and np.array_equal(out["flags"], fw) and out["err_count"] == nw and not out["ws"].any()
 
 
+# (one to fifteen tile columns, eight and more with every remainder by eight; one tile row, two, and a strip of four and one more; each form)
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,width,K", [(20, 32, 144), (20, 32, 1168), (150, 32, 144), (150, 32, 2321), (2500, 32, 144), (1300, 64, 1296), (40, 480, 144)])
+def test_grids_of_any_number_of_tiles(binding, gpu_util, oracle, M, width, K):
+    """Every tile is computed once, whatever their number: the XCDs' blocks of tiles are of two lengths where it is no multiple of eight."""
+    A, B = operands(M, 15 * width, K, M + K)
+    ref = oracle.checked_gemm(A, B)
+    for n in range(1, 16):
+        N = n * width - (n % 3)
+        run = gpu_util.GpuRun(binding, np.ascontiguousarray(B[:, :N]))
+        out = run.gemm(A)
+        assert np.array_equal(out["C"], ref.C[:, :N]) and not out["flags"].any() and out["err_count"] == 0 and not out["ws"].any(), N
+
+
 # (widths around four columns, a quad of lanes, 32-column blocks and whole tiles; one to four rows past the last whole quad)
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,N,K,variant", [(5, 1, 64, "auto"), (20, 67, 128, "auto"), (33, 130, 1040, "auto"), (70, 3, 64, "tile64"), (129, 65, 96, "tile64"),
