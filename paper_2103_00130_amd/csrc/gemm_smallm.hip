@@ -110,13 +110,10 @@ __global__ __launch_bounds__(256) void gemm_smallm_kernel(const GemmParams p, co
             const int kbc = min(kb, KB - 1);
             // a k-block past the end is fetched from the last one and zeroed below
 #pragma unroll
-            for (int c = 0; c < NCB; ++c) {   // the next 16 columns of a unit lie 256 bytes further on, the next unit 2 KiB
-                const v4i* const at = reinterpret_cast<const v4i*>(b_src + (int64_t)kbc * B_KB_STRIDE + (c >> 1) * kUnitBytes + (c & 1) * 256);
-                // (a wide weight passes through without being kept in the caches; a small one may still be there at the next call: 7x660x3872,
-                // seven weights in turn, 6.0 us with the mark, 5.3 without)
-                if constexpr (NCB == 1) fb[s][u][c] = *at;
-                else fb[s][u][c] = __builtin_nontemporal_load(at);
-            }
+            for (int c = 0; c < NCB; ++c)   // the next 16 columns of a unit lie 256 bytes further on, the next unit 2 KiB
+                // (The weight passes through without being kept in the caches.  Kept, of one column block per workgroup: 16x4096x2048 4.76 us
+                // against 4.81 with one weight again and again and 5.23 / 5.42 with eight in turn, but 5.82 / 5.53 with fresh ones.)
+                fb[s][u][c] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(b_src + (int64_t)kbc * B_KB_STRIDE + (c >> 1) * kUnitBytes + (c & 1) * 256));
             const int k = min(kbc * 64 + lkg * 16, p.K - 16);
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
