@@ -267,6 +267,34 @@ __device__ inline shift_v4i shift_down(shift_v4i v, int n) {
 }
 #endif
 
+// Up to 16 rows (one block of the streaming kernel) where that kernel is the better one for a weight that the program has not just used.
+// It has a batch of 2048 k of its 16 or 32 columns in flight at once; the wavefronts of gemm_tile_wk.h have 512 or 1024 k of 32 or 64
+// columns, and wait once per round for what the caches do not hold.  So the lines lie by the stages of 128 k, where the mean of three
+// states favours it: one weight again and again, eight in turn, fresh ones (us each, streaming / gemm_tile_wk.h):
+//  * whole chunks: 1x800x2048 4.2 4.3 4.2 / 4.4 4.5 5.3, 1x800x3200 5.0 5.1 5.0 / 4.8 5.0 6.1, 4x4096x4096 5.5 6.7 6.7 / 5.7 6.3 7.7,
+//    8x2048x4096 5.4 6.3 6.2 / 5.6 6.1 7.3, 1x3000x12000 10.0 10.6 10.6 / 9.5 13.6 13.6, 8x12000x1024 4.9 5.9 6.0 / 4.9 6.1 6.9, 1x15000x3008
+//    9.9 10.7 10.7 / 10.4 11.8 12.1; but 3x3000x9008 9.1 9.5 9.6 / 7.5 8.8 11.6, 1x800x2560 5.0 5.3 5.2 / 4.4 4.7 5.9, 8x3000x6400 8.4 8.9 8.8 / 6.4 7.3 9.4, 8x800x6400
+//    6.9 8.1 7.9 / 6.0 6.8 8.6, 16x4096x4096 6.5 7.5 7.6 / 5.7 6.3 8.0, 4x12000x1152 6.2 / 5.1, 8x15000x5008 15.5 / 14.3
+//  * 9 to 16 rows, few or middling columns: 10x464x4064 4.9 / 5.4, 1x145x6128 6.0 / 6.4, 16x4096x2048 4.8 / 5.0; but 16x1200x2048 even,
+//    13x144x11067 16.6 / 7.8
+//  * rows that are no whole chunks, which the streaming kernel loads row by row: one row 1x300x2001 4.4 / 5.0, 1x800x3201 5.6 5.8 5.8 /
+//    5.6 6.0 7.9, 1x800x1001 4.5 4.6 4.4 / 4.3 4.3 5.2, 1x6001x9001 13.0 / 13.4 and fresh 13.4 / 15.8; up to 8 rows of one batch 4x300x2001
+//    4.7 / 5.0 and fresh 4.7 / 5.5, 8x8192x1001 4.8 5.6 5.5 / 4.7 5.9 6.4; but 4x800x3201 7.2 / 5.7, 8x3000x2049 8.6 / 5.4, 1x800x2561 and
+//    1x8192x16383 even, 1x800x500 4.6 / 3.7
+inline bool few_rows_stream(int M, int N, int stages, bool whole_a) {
+    if (M > 16 || N >= 16384) return false;
+    if (M <= 8 && N > 4096 && (stages == 7 || stages == 8)) return true;
+    if (!whole_a) {
+        if (N <= 4096 && M <= 8 && stages <= 16) return stages >= (M == 1 ? 8 : 13);
+        return M == 1 && (N <= 4096 ? stages <= 32 || (N > 2048 && stages >= 70) : stages >= 48 && stages < 96);
+    }
+    if (N > 4096) return M <= 8 && N > 12288 && stages >= 24 && stages <= (M <= 4 ? 48 : 32);
+    if (stages <= 8) return false;
+    if (N <= 640) return stages < 64;
+    if (N <= 1500) return M <= 8 && (stages <= 16 || (stages > 24 && stages <= 32));   // (the last batch at least half full)
+    return stages <= 20 || (M <= 8 && (stages <= 32 || (N > 2048 && stages >= 72)));
+}
+
 // Which form of gemm_tile_wk.h (K split among the wavefronts of a workgroup) takes a call, if any: rows x columns of the tile, wavefronts.
 enum WkForm { kWkNone = 0, kWk32x32w4, kWk32x32w8, kWk32x64w4, kWk32x64w8, kWk64x64w4 };
 // By the number of tiles and of stages of 128 k (us, the 64x64 tiles of gemm_tile_async.h or up to 32 rows the streaming kernel / this form):
@@ -278,15 +306,11 @@ enum WkForm { kWkNone = 0, kWk32x32w4, kWk32x32w8, kWk32x64w4, kWk32x64w8, kWk64
 //  * up to two 32x64 tiles per compute unit for a short K where 64 rows a tile are partly padding or the rows are no whole chunks
 //    (78x6549x96 7.4 / 6.7, 65x9664x688 9.2 / 6.6, 2042x336x146 6.0 / 4.8; but 773x928x240 5.4 / 5.5);
 //  * up to two 64x64 tiles for such rows (2000x1000x479 both outputs 10.9 / 9.4, 900x2000x777 11.1 / 9.9, 600x3000x250 8.9 / 8.1;
-//    576 tiles, 1500x1500x700 12.2 / 14.3);
-//  * not for up to 16 rows of a middling K where the streaming kernel's 16 columns a workgroup give more of them: few columns
-//    (1x240x1696 4.0 / 4.5, 10x464x4064 4.9 / 5.4, 1x145x6128 6.0 / 6.4; but 8x748x2656 5.2 / 4.9, 1x800x3200 5.0 / 4.8, 4x864x96 4.4 / 3.4,
-//    13x144x11067 16.6 / 7.8) and, where arrivals go by slots there, many (7x3696x2000 4.6 / 4.8, 16x4096x2048 4.8 / 5.0; but 8x4096x4096
-//    5.4 / 5.4, with another weight at every call less).
+//    576 tiles, 1500x1500x700 12.2 / 14.3).
 inline WkForm wk_form(int M, int N, int stages, bool whole_a) {
     const int64_t t32 = (int64_t)((M + 31) / 32) * ((N + 31) / 32), t3264 = (int64_t)((M + 31) / 32) * ((N + 63) / 64),
                   t64 = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
-    if (M <= 16 && whole_a && stages > 8 && (N <= 640 ? stages < 64 : N > 1500 && N <= 4096 && stages <= 20)) return kWkNone;
+    if (few_rows_stream(M, N, stages, whole_a)) return kWkNone;
     if (t32 <= 256) return stages >= 9 ? kWk32x32w8 : kWk32x32w4;
     if (t3264 <= 256) return stages >= 24 ? kWk32x64w8 : kWk32x64w4;
     if (t64 <= 256 && stages >= 12) return kWk64x64w4;

@@ -15,7 +15,9 @@ extern "C" void plan(int M, int N, int K, int stages, int whole, long long* out)
                            (long long)r.total_ints, (long long)abft::ws_base_ints(M)};
     for (int i = 0; i < 9; ++i) out[i] = v[i];
 }
+extern "C" int form(int M, int N, int stages, int whole) { return abft::wk_form(M, N, stages, whole != 0); }
 """
+NONE, T32X32W4, T32X32W8, T32X64W4, T32X64W8, T64X64W4 = range(6)
 
 
 class Plan:
@@ -35,6 +37,7 @@ def plan(tmp_path_factory):
         out = (ctypes.c_longlong * 9)()
         so.plan(M, N, K, ((K + 63) // 64 + 1) // 2, whole, out)
         return Plan(out)
+    call.form = lambda M, N, K: so.form(M, N, ((K + 63) // 64 + 1) // 2, K % 16 == 0)
     return call
 
 
@@ -61,3 +64,14 @@ def test_copy_and_parts_lie_apart(plan):
                     s = plan(M, N, K, whole)
                     assert s.z == 1 or s.split_ints <= s.room_ints, (M, N, K)
     assert both > 50
+
+
+# (shapes where the streaming kernel measured faster for weights that have not just been used, and neighbours where it did not)
+@pytest.mark.parametrize("M,N,K,streams", [(1, 800, 2048, True), (1, 800, 3200, True), (4, 4096, 4096, True), (8, 2048, 4096, True), (1, 3000, 12000, True), (8, 3000, 16384, True),
+                                           (8, 12000, 1024, True), (1, 15000, 3008, True), (16, 4096, 2048, True), (10, 464, 4064, True), (1, 800, 2560, False),
+                                           (8, 3000, 6400, False), (8, 800, 6400, False), (16, 4096, 4096, False), (16, 1200, 2048, False), (4, 12000, 1152, False),
+                                           (8, 15000, 3008, True), (8, 15000, 5008, False), (4, 15000, 5008, True), (8, 8192, 1001, True), (1, 4096, 9001, True), (3, 3000, 9008, False), (1, 16384, 3008, False), (24, 800, 2048, False), (8, 4096, 512, False), (1, 800, 3201, True),
+                                           (1, 300, 2001, True), (1, 800, 1001, True), (4, 300, 2001, True), (1, 6001, 9001, True), (4, 800, 3201, False), (8, 3000, 2049, False),
+                                           (1, 800, 500, False), (1, 8192, 16383, False), (2, 800, 1001, False), (16, 300, 2001, False)])
+def test_few_rows(plan, M, N, K, streams):
+    assert (plan.form(M, N, K) == NONE) == streams
