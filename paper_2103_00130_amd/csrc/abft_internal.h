@@ -273,8 +273,9 @@ __device__ inline shift_v4i shift_down(shift_v4i v, int n) {
 // states favours it: one weight again and again, eight in turn, fresh ones (us each, streaming / gemm_tile_wk.h):
 //  * whole chunks: 1x800x2048 4.2 4.3 4.2 / 4.4 4.5 5.3, 1x800x3200 5.0 5.1 5.0 / 4.8 5.0 6.1, 4x4096x4096 5.5 6.7 6.7 / 5.7 6.3 7.7,
 //    8x2048x4096 5.4 6.3 6.2 / 5.6 6.1 7.3, 1x3000x12000 10.0 10.6 10.6 / 9.5 13.6 13.6, 8x12000x1024 4.9 5.9 6.0 / 4.9 6.1 6.9, 1x15000x3008
-//    9.9 10.7 10.7 / 10.4 11.8 12.1; but 3x3000x9008 9.1 9.5 9.6 / 7.5 8.8 11.6, 1x800x2560 5.0 5.3 5.2 / 4.4 4.7 5.9, 8x3000x6400 8.4 8.9 8.8 / 6.4 7.3 9.4, 8x800x6400
-//    6.9 8.1 7.9 / 6.0 6.8 8.6, 16x4096x4096 6.5 7.5 7.6 / 5.7 6.3 8.0, 4x12000x1152 6.2 / 5.1, 8x15000x5008 15.5 / 14.3
+//    9.9 10.7 10.7 / 10.4 11.8 12.1; but 3x3000x9008 9.1 9.5 9.6 / 7.5 8.8 11.6, 1x800x2560 5.0 5.3 5.2 / 4.4 4.7 5.9, 8x3000x6400
+//    8.4 8.9 8.8 / 6.4 7.3 9.4, 8x800x6400 6.9 8.1 7.9 / 6.0 6.8 8.6, 16x4096x4096 6.5 7.5 7.6 / 5.7 6.3 8.0, 4x12000x1152 6.2 / 5.1,
+//    8x15000x5008 15.5 / 14.3
 //  * 9 to 16 rows, few or middling columns: 10x464x4064 4.9 / 5.4, 1x145x6128 6.0 / 6.4, 16x4096x2048 4.8 / 5.0; but 16x1200x2048 even,
 //    13x144x11067 16.6 / 7.8
 //  * rows that are no whole chunks, which the streaming kernel loads row by row: one row 1x300x2001 4.4 / 5.0, 1x800x3201 5.6 5.8 5.8 /
@@ -306,11 +307,15 @@ enum WkForm { kWkNone = 0, kWk32x32w4, kWk32x32w8, kWk32x64w4, kWk32x64w8, kWk64
 //  * up to two 32x64 tiles per compute unit for a short K where 64 rows a tile are partly padding or the rows are no whole chunks
 //    (78x6549x96 7.4 / 6.7, 65x9664x688 9.2 / 6.6, 2042x336x146 6.0 / 4.8; but 773x928x240 5.4 / 5.5);
 //  * up to two 64x64 tiles for such rows (2000x1000x479 both outputs 10.9 / 9.4, 900x2000x777 11.1 / 9.9, 600x3000x250 8.9 / 8.1;
-//    576 tiles, 1500x1500x700 12.2 / 14.3).
+//    576 tiles, 1500x1500x700 12.2 / 14.3);
+//  * not for one stage (two from 2560 rows on) of more than 1024 rows where the tiles of 64x64 are half as many: their rows are reported in one
+//    step instead of two, and of up to 64 columns without meeting other columns (3000x64x128 4.6 / 5.0, 2739x80x112 5.0 / 5.4, 3000x128x256
+//    5.2 / 5.5, 1056x300x128 4.8 / 5.0; but 1500x128x112 4.8 / 4.8, 2100x100x256 5.3 / 5.3, 1056x64x256 4.8 / 4.7).
 inline WkForm wk_form(int M, int N, int stages, bool whole_a) {
     const int64_t t32 = (int64_t)((M + 31) / 32) * ((N + 31) / 32), t3264 = (int64_t)((M + 31) / 32) * ((N + 63) / 64),
                   t64 = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
     if (few_rows_stream(M, N, stages, whole_a)) return kWkNone;
+    if (whole_a && M > 1024 && stages <= (M > 2560 ? 2 : 1) && (t32 > 256 || (N > 32 && N <= 64))) return kWkNone;
     if (t32 <= 256) return stages >= 9 ? kWk32x32w8 : kWk32x32w4;
     if (t3264 <= 256) return stages >= 24 ? kWk32x64w8 : kWk32x64w4;
     if (t64 <= 256 && stages >= 12) return kWk64x64w4;

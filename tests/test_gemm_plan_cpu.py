@@ -75,3 +75,11 @@ def test_copy_and_parts_lie_apart(plan):
                                            (1, 800, 500, False), (1, 8192, 16383, False), (2, 800, 1001, False), (16, 300, 2001, False)])
 def test_few_rows(plan, M, N, K, streams):
     assert (plan.form(M, N, K) == NONE) == streams
+
+
+# (one or two stages of many rows, where the 64x64 tiles measured faster, and neighbours where they did not)
+@pytest.mark.parametrize("M,N,K,form", [(3000, 64, 128, NONE), (2739, 80, 112, NONE), (3000, 128, 256, NONE), (1056, 300, 128, NONE), (1500, 64, 112, NONE),
+                                        (1500, 128, 112, T32X32W4), (2100, 100, 256, T32X64W4), (1056, 64, 256, T32X32W4), (3000, 32, 112, T32X32W4),
+                                        (3000, 128, 384, T32X64W4), (2739, 80, 115, T32X64W4), (1000, 64, 128, T32X32W4)])
+def test_many_rows_of_a_short_k(plan, M, N, K, form):
+    assert plan.form(M, N, K) == form
