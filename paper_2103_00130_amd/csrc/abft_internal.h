@@ -324,6 +324,11 @@ inline WkForm wk_form(int M, int N, int stages, bool whole_a) {
     return kWkNone;
 }
 
+// Rows that are no whole chunks, where the form is the one of 64x64 tiles and the loop is long: with room in the workspace the copy with padded
+// rows is made first and multiplied (us, through registers / copied first: 100x5000x3001 12.5 / 12.0, 64x12000x5001 20.0 / 17.9,
+// 256x3000x5001 17.9 / 16.9, 128x6500x9001 30.4 / 24.6, 200x4096x9001 30.8 / 24.7; but 256x4096x3001 13.1 / 13.5, 100x5000x2001 10.4 / 12.8).
+inline bool copy_first(WkForm form, int stages) { return form == kWk64x64w4 && stages >= 32; }
+
 enum Variant { kTile256 = 1, kTile128 = 2, kTile64 = 3, kSmallM = 4, kTile256w24 = 5, kTile256w42 = 6, kVariantEnd = 7 };
 
 // launchers (each returns the hipError_t of its launch)

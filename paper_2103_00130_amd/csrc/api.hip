@@ -263,23 +263,26 @@ int abft_gemm_u8s8s32_checked(const uint8_t* A, int64_t lda, int M, const abft_p
         return (int)abft::kTile64;
     };
     hipError_t e;
+    const bool whole_a = p.a_vec_ok && p.K % 16 == 0;
+    const abft::RealignPlan ra = abft::realign_plan(M, Bp->N, Bp->K, p.KB2);
+    const bool can_copy = !whole_a && !mod127 && ra.copy && workspace && p.ws_ints >= ra.total_ints;
     if (!chosen) {
-        e = abft::launch_gemm_wk(abft::wk_form(M, Bp->N, p.KB2, p.a_vec_ok && p.K % 16 == 0), check, want_c, want_q, p, (hipStream_t)stream);
-        if (e == hipSuccess) return ABFT_OK;
-        if (e != hipErrorNotSupported) return hip_fail(e, fn);
+        const abft::WkForm form = abft::wk_form(M, Bp->N, p.KB2, whole_a);
+        if (!(can_copy && abft::copy_first(form, p.KB2))) {
+            e = abft::launch_gemm_wk(form, check, want_c, want_q, p, (hipStream_t)stream);
+            if (e == hipSuccess) return ABFT_OK;
+            if (e != hipErrorNotSupported) return hip_fail(e, fn);
+        }
         variant = M <= 32 ? (int)abft::kSmallM : pick_tile();
     }
-    if (variant != abft::kSmallM && !mod127 && !(p.a_vec_ok && p.K % 16 == 0)) {
-        const abft::RealignPlan ra = abft::realign_plan(M, Bp->N, Bp->K, p.KB2);
-        if (ra.copy && workspace && p.ws_ints >= ra.total_ints) {
-            uint8_t* const A2 = (uint8_t*)(((uintptr_t)(p.ws + ra.off) + 15) & ~(uintptr_t)15);
-            e = abft::launch_realign(A, lda, M, p.K, A2, ra.lda, (hipStream_t)stream);
-            if (e != hipSuccess) return hip_fail(e, fn);
-            p.A = A2;
-            p.lda = ra.lda;
-            p.a_vec_ok = 1;
-            p.K = (int)ra.lda;    // (the padding meets rows of zeros in the packed weight)
-        }
+    if (variant != abft::kSmallM && can_copy) {
+        uint8_t* const A2 = (uint8_t*)(((uintptr_t)(p.ws + ra.off) + 15) & ~(uintptr_t)15);
+        e = abft::launch_realign(A, lda, M, p.K, A2, ra.lda, (hipStream_t)stream);
+        if (e != hipSuccess) return hip_fail(e, fn);
+        p.A = A2;
+        p.lda = ra.lda;
+        p.a_vec_ok = 1;
+        p.K = (int)ra.lda;    // (the padding meets rows of zeros in the packed weight)
     }
     if (variant == abft::kSmallM) {
         if (M > 64) return fail(ABFT_EUNSUPPORTED, "%s: the streaming variant takes M <= 64, got %d", fn, M);

@@ -16,6 +16,7 @@ extern "C" void plan(int M, int N, int K, int stages, int whole, long long* out)
     for (int i = 0; i < 9; ++i) out[i] = v[i];
 }
 extern "C" int form(int M, int N, int stages, int whole) { return abft::wk_form(M, N, stages, whole != 0); }
+extern "C" int copy_first(int form, int stages) { return abft::copy_first((abft::WkForm)form, stages); }
 """
 NONE, T32X32W4, T32X32W8, T32X64W4, T32X64W8, T64X64W4 = range(6)
 
@@ -37,6 +38,7 @@ def plan(tmp_path_factory):
         out = (ctypes.c_longlong * 9)()
         so.plan(M, N, K, ((K + 63) // 64 + 1) // 2, whole, out)
         return Plan(out)
+    call.copy_first = lambda form, K: bool(so.copy_first(form, ((K + 63) // 64 + 1) // 2))
     call.form = lambda M, N, K: so.form(M, N, ((K + 63) // 64 + 1) // 2, K % 16 == 0)
     return call
 
@@ -83,3 +85,13 @@ def test_few_rows(plan, M, N, K, streams):
                                         (3000, 128, 384, T32X64W4), (2739, 80, 115, T32X64W4), (1000, 64, 128, T32X32W4)])
 def test_many_rows_of_a_short_k(plan, M, N, K, form):
     assert plan.form(M, N, K) == form
+
+
+# (rows that are no whole chunks: a copy first for the 64x64 form and a long K, with a workspace that has the room)
+@pytest.mark.parametrize("M,N,K,copied", [(64, 12000, 5001, True), (128, 6500, 9001, True), (256, 3000, 5001, True), (100, 5000, 2001, False), (64, 5000, 9001, False),
+                                          (33, 8192, 9001, False), (2000, 1000, 479, False)])
+def test_copy_ahead_of_the_large_form(plan, M, N, K, copied):
+    form = plan.form(M, N, K)
+    assert form != NONE and plan.copy_first(form, K) == copied
+    if copied:      # the copy is one that is made, the whole rows then run on 64x64 tiles of the same kernel, and M > 32 leaves room for it
+        assert plan(M, N, K, 0).copy and plan.form(M, N, (K + 15) // 16 * 16) == T64X64W4 and M > 32

@@ -1086,7 +1086,7 @@ def test_k_split_across_workgroups(binding, gpu_util, oracle, M, N, K):
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,N,K", [(5, 40, 3), (70, 70, 15), (2000, 1500, 13), (7, 100, 17), (33, 8200, 63), (64, 1100, 4001), (130, 70, 31), (65, 129, 127),
                                    (100, 65, 129), (128, 64, 255), (129, 200, 257), (64, 64, 385), (200, 130, 2687), (70, 200, 5121),
-                                   (1000, 1300, 1249), (1, 300, 2001), (8, 700, 1999), (1, 4203, 6205), (7, 4999, 1021)])
+                                   (1000, 1300, 1249), (1, 300, 2001), (8, 700, 1999), (1, 4203, 6205), (7, 4999, 1021), (65, 5505, 4111)])
 def test_rows_that_are_no_whole_chunks(binding, gpu_util, oracle, M, N, K):
     """A whose rows start and end at any byte: clean, with C and B faults, requantized, contiguous and as a view one byte
     into rows that are longer; nothing past the operand may count."""
