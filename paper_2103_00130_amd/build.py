@@ -11,9 +11,9 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libabftgemm.so")
 FASTCALL = os.path.join(HERE, "_fastcall.so")
 SOURCES = ["api.hip", "pack.hip", "gemm_tile.hip", "gemm_tile_a256.hip", "gemm_tile_a256w24.hip", "gemm_tile_a256w42.hip",
-           "gemm_tile_a128.hip", "gemm_tile_a64.hip", "gemm_tile_a64r4.hip", "gemm_tile_g64.hip", "gemm_smallm.hip",
+           "gemm_tile_a128.hip", "gemm_tile_a64.hip", "gemm_tile_a64r4.hip", "gemm_tile_a64s.hip", "gemm_tile_g64.hip", "gemm_smallm.hip",
            "gemm_tile_wk32x32w4.hip", "gemm_tile_wk32x32w8.hip", "gemm_tile_wk32x32w8s.hip", "gemm_tile_wk32x64w4.hip", "gemm_tile_wk32x64w8.hip", "gemm_tile_wk64x64w4.hip",
-           "rowops.hip","locate.hip", "eb.hip"]
+           "rowops.hip", "locate.hip", "eb.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function", "-Wno-inline-asm",

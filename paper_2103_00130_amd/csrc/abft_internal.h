@@ -146,8 +146,8 @@ struct GemmParams {
     int n_inj;
     int ksplit;                // K slices across workgroups (split-K kernels; 1 elsewhere)
     int split_q, split_r;      // stages of a slice; the first split_r take one more
-    int32_t* ws_tickets;       // split-K: one arrival counter per tile and finishing wavefront
-    int32_t* ws_part;          // split-K: parts, [tile][finishing wavefront][slice][value][lane]
+    int32_t* ws_tickets;       // split-K: one arrival counter per tile (and finishing wavefront)
+    int32_t* ws_part;          // split-K: parts, [tile][slice][value][thread] or [tile][finishing wavefront][slice][value][lane]
     int wk_stages;             // K split among wavefronts: stages of the wavefronts with fewest; those with one more deal out
     int wk_stream;             // ... the weight is not kept in the caches
     int wk_share_q1, wk_share_r1;  // their k-steps of the checksum product by these instead of share_q, share_r
@@ -217,6 +217,31 @@ inline SplitKPlan splitk_plan(int M, int N, int stages, bool whole_a) {
     return pl;
 }
 
+// The split of 64x64 tiles (gemm_tile_async.h): 33 to 64 rows, whose weight these tiles read once, and a K so long that the slices'
+// meeting is paid for.  Its 256 workgroups keep more of a weight in flight than the fewer ones of gemm_tile_wk.h with 32 or 64 columns,
+// which counts where the weight is not in the caches; where the line lies depends on how many of those there are (us, one weight again
+// and again / fresh ones; gemm_tile_wk.h, then this split): 64x4200x9008 15.4 22.0 / 14.5 17.5, 64x5000x16000 21.0 30.5 / 19.8 22.7, 33x5000x9008
+// 14.5 17.8 / 16.7 16.2, 33x4200x12000 17.8 21.0 / 16.3 17.4, 64x3000x12000 14.3 19.3 / 14.6 16.4, 64x2000x16000 15.1 19.4 / 14.5 14.5,
+// 64x6500x16000 22.4 32.5 / 24.2 28.3; but 64x5000x6000 11.4 16.6 / 12.7 14.5, 33x3000x12000 13.3 15.4 / 14.3 16.5, 64x2000x9008 9.1 16.0 /
+// 11.5 12.8, 64x6500x9008 16.4 22.9 / 17.7 22.6, 64x1000x16000 10.7 12.5 / 12.5 14.5; 128 rows 128x3000x12000 17.9 24 / 20.0 24.6.
+constexpr int kSplit64PartInts = 256 * 17 + 64;   // per workgroup: 256 threads x (16 accumulator values + 1 column sum), 64 rows' checksum shares
+struct Split64Plan {
+    int z;                // slices (1 = no split)
+    size_t total_ints;    // tickets from kWsTicketsOff on, parts from kWsScratchOff on
+};
+inline Split64Plan split64_plan(int M, int N, int stages) {
+    Split64Plan pl;
+    const int64_t tiles = ((int64_t)N + 63) / 64;
+    const int line = tiles <= 20 || tiles > 128 ? 1 << 30 : tiles <= 32 ? 120 : tiles <= 64 ? (M > 48 ? 90 : 120) : tiles <= 85 ? 60 : 120;
+    pl.z = 1;
+    if (M > 32 && M <= 64 && stages >= line) {
+        const int most = (int)(256 / tiles), z = stages >= 160 ? 16 : 8;
+        pl.z = z < most ? z : most;
+    }
+    pl.total_ints = pl.z > 1 ? kWsScratchOff + (size_t)tiles * pl.z * kSplit64PartInts : ws_base_ints(M);
+    return pl;
+}
+
 // Rows of A that are no whole, aligned 16-byte chunks (K no multiple of 16, or such a base or leading dimension): either the
 // 64x64 kernel with loads through registers takes them as they lie, or a copy with padded rows is made first, in the
 // workspace, for the direct-to-LDS kernels (grids that gemm_tile_wk.h does not take).  The copy costs
@@ -240,7 +265,9 @@ inline RealignPlan realign_plan(int M, int N, int K, int stages) {
     // (behind the parts of a K split: with 64x64 tiles asked for, the padded rows may be multiplied in slices that store their
     // parts while others still read the copy)
     const SplitKPlan sk = splitk_plan(M, N, stages, true);
-    pl.off = sk.z > 1 ? sk.total_ints : kWsScratchOff;
+    const Split64Plan s64 = split64_plan(M, N, stages);
+    pl.off = s64.z > 1 ? s64.total_ints : kWsScratchOff;
+    if (sk.z > 1 && sk.total_ints > pl.off) pl.off = sk.total_ints;
     pl.total_ints = pl.off + (size_t)(pl.lda * M / 4) + 4;
     return pl;
 }
@@ -339,6 +366,8 @@ hipError_t launch_flip_checksum127_bit(abft_packed_b* h, int k, int bit, hipStre
 hipError_t launch_fill_zero(int32_t* p, size_t n_ints, hipStream_t s);
 // (refuses what it does not take: a form of kWkNone, K below 16 with rows that are no whole chunks, the printed modulus on such rows)
 hipError_t launch_gemm_wk(WkForm form, bool check, bool want_c, bool want_q, const GemmParams& p, hipStream_t s);
+// (refuses where split64_plan has none, the workspace has no room for it, or A is not in whole, aligned chunks)
+hipError_t launch_gemm_split64(bool check, bool want_c, bool want_q, const GemmParams& p, hipStream_t s);
 hipError_t launch_gemm_tile(int variant, bool check, bool want_c, bool want_q, const GemmParams& p, hipStream_t s);
 // any_a: A of any alignment and K >= 16 is taken too (else only whole, aligned 16-byte chunks)
 hipError_t launch_gemm_smallm(bool any_a, bool check, bool want_c, bool want_q, const GemmParams& p, hipStream_t s);

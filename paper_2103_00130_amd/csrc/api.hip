@@ -155,7 +155,8 @@ size_t abft_gemm_workspace_bytes(int M, const abft_packed_b* Bp) {
     // with the weight known: room for the parts of a K split across workgroups, where one would be used, and, where rows of
     // Bp->K bytes are no whole chunks, for the copy with padded rows
     if (Bp) {
-        const size_t split = abft::splitk_plan(M, Bp->N, Bp->KB / 2, false).room_ints;
+        const size_t small = abft::splitk_plan(M, Bp->N, Bp->KB / 2, false).room_ints, large = abft::split64_plan(M, Bp->N, Bp->KB / 2).total_ints;
+        const size_t split = small > large ? small : large;
         const abft::RealignPlan ra = abft::realign_plan(M, Bp->N, Bp->K, Bp->KB / 2);
         const bool copy = Bp->K % 16 != 0 && ra.copy && !abft::words_suffice(M, Bp->N, Bp->K);
         return (copy && ra.total_ints > split ? ra.total_ints : split) * sizeof(int32_t);
@@ -267,8 +268,13 @@ int abft_gemm_u8s8s32_checked(const uint8_t* A, int64_t lda, int M, const abft_p
     const abft::RealignPlan ra = abft::realign_plan(M, Bp->N, Bp->K, p.KB2);
     const bool can_copy = !whole_a && !mod127 && ra.copy && workspace && p.ws_ints >= ra.total_ints;
     if (!chosen) {
+        if (whole_a) {
+            e = abft::launch_gemm_split64(check, want_c, want_q, p, (hipStream_t)stream);
+            if (e == hipSuccess) return ABFT_OK;
+            if (e != hipErrorNotSupported) return hip_fail(e, fn);
+        }
         const abft::WkForm form = abft::wk_form(M, Bp->N, p.KB2, whole_a);
-        if (!(can_copy && abft::copy_first(form, p.KB2))) {
+        if (!(can_copy && (abft::copy_first(form, p.KB2) || abft::split64_plan(M, Bp->N, p.KB2).z > 1))) {
             e = abft::launch_gemm_wk(form, check, want_c, want_q, p, (hipStream_t)stream);
             if (e == hipSuccess) return ABFT_OK;
             if (e != hipErrorNotSupported) return hip_fail(e, fn);

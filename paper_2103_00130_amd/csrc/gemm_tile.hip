@@ -9,6 +9,7 @@ ABFT_DECL(a256w42);
 ABFT_DECL(a128);
 ABFT_DECL(a64);
 ABFT_DECL(a64r4);
+ABFT_DECL(a64s);
 ABFT_DECL(g64);
 #undef ABFT_DECL
 #define ABFT_DECL(name) hipError_t launch_gemm_##name(bool, bool, bool, bool, const GemmParams&, hipStream_t)
@@ -43,6 +44,11 @@ hipError_t launch_gemm_wk(WkForm form, bool check, bool want_c, bool want_q, con
     }
 }
 
+hipError_t launch_gemm_split64(bool check, bool want_c, bool want_q, const GemmParams& p, hipStream_t s) {
+    if (!whole_chunks(p)) return hipErrorNotSupported;
+    return launch_gemm_tile_a64s(check, want_c, want_q, p, s);
+}
+
 hipError_t launch_gemm_tile(int variant, bool check, bool want_c, bool want_q, const GemmParams& p, hipStream_t s) {
     const bool fast_a = whole_chunks(p);
     if (!fast_a && p.mod127) return hipErrorNotSupported;
@@ -58,9 +64,11 @@ hipError_t launch_gemm_tile(int variant, bool check, bool want_c, bool want_q, c
         case kTile128: return launch_gemm_tile_a128(check, want_c, want_q, p, s);
         case kTile64: {
             // The 64x64 kernels are bound by instruction issue and the LDS reads of a wavefront, not by the matrix cores, so they
-            // run as four wavefronts of 32x32 on four SIMDs (5-10 % faster than two of 32x64).  Where it is the faster one the
-            // kernel that splits K among wavefronts takes the call.
-            const hipError_t e = launch_gemm_wk(wk_form(p.M, p.N, p.KB2, true), check, want_c, want_q, p, s);
+            // run as four wavefronts of 32x32 on four SIMDs (5-10 % faster than two of 32x64).  Where they are the faster ones their
+            // split across workgroups or the kernel that splits K among wavefronts takes the call.
+            hipError_t e = launch_gemm_split64(check, want_c, want_q, p, s);
+            if (e != hipErrorNotSupported) return e;
+            e = launch_gemm_wk(wk_form(p.M, p.N, p.KB2, true), check, want_c, want_q, p, s);
             if (e != hipErrorNotSupported) return e;
             const int64_t tiles = (int64_t)((p.M + 63) / 64) * ((p.N + 63) / 64);
             // short K on such a grid: a ring of four stages, all in flight before the first k-step, instead of the

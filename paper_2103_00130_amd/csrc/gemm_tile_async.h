@@ -102,7 +102,11 @@ constexpr size_t lds_bytes() {
     return kStages * (size_t)(BM + BN) * BK + (4 * BN + WGN * BM + BM + 4) * sizeof(int32_t) + kLimbStages * 512;
 }
 
-template <int BM, int BN, int WGM, int WGN, int kStages, bool kCheck, int kOut, bool kBlockSums, int kAnyA = 0>
+// kSplitK: K split across workgroups.  p.ksplit workgroups per tile take consecutive runs of stages; each stores its partial tile
+// (accumulators, column sums, and its share of the checksum product for the tile's rows) in the workspace and takes a ticket on the
+// tile's counter, and the one that arrives last adds the others' partials to its own and runs the epilogue.  The checksum product of
+// every run of stages is dealt out to the tile columns as before (the comparison of Eq. 2b is linear in the K slices).
+template <int BM, int BN, int WGM, int WGN, int kStages, bool kCheck, int kOut, bool kBlockSums, int kAnyA = 0, bool kSplitK = false>
 __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const GemmParams p, const int tiles_m,
                                                                              const int tiles_n) {
     constexpr int NW = WGM * WGN, NT = NW * 64;    // wavefronts and threads
@@ -111,7 +115,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     constexpr int A_STAGE = BM * BK, B_STAGE = BN * BK;
     constexpr int S = kStages;                     // stages resident in LDS
     static_assert(S >= 2, "at least a double buffer");
-    static_assert(kAnyA == 0 || (S == 2 && kAnyA % 2 == 0), "register-staged loads: a double buffer in LDS");
+    static_assert(kAnyA == 0 || (S == 2 && kAnyA % 2 == 0 && !kSplitK), "register-staged loads: a double buffer in LDS");
     constexpr int A_LD = (BM / 8) / NW;            // async A loads per wave per stage (8 rows each)
     constexpr int B_LD = (BN / 8) / NW;            // async B loads per wave per stage (1 KiB each)
     constexpr int CB = (WTM / 16) / WGN;           // 16-row checksum blocks per wave
@@ -131,8 +135,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     int tile_m, tile_n;
     {
         const int n_tiles = tiles_m * tiles_n;
-        int t = (int)blockIdx.x;
-        if (n_tiles % 8 == 0) t = (blockIdx.x & 7) * (n_tiles >> 3) + (blockIdx.x >> 3);
+        int t = kSplitK ? (int)blockIdx.x % n_tiles : (int)blockIdx.x;   // (split: slice blockIdx.x / n_tiles)
+        if (!kSplitK && n_tiles % 8 == 0) t = (blockIdx.x & 7) * (n_tiles >> 3) + (blockIdx.x >> 3);
         const int strip_h = tiles_m >= 4 ? 4 : tiles_m;
         const int per_strip = strip_h * tiles_n;
         const int strip = t / per_strip, r = t - strip * per_strip;
@@ -141,7 +145,11 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
         tile_m = strip * strip_h + r - tile_n * h;
     }
     const int row0 = tile_m * BM, col0 = tile_n * BN;
-    const int NS = p.KB2;            // stages of 128 k-values
+    const int NS_all = p.KB2;        // stages of 128 k-values
+    // ... of this slice of them: as equal as they can be, the first split_r are one stage longer
+    const int Z = kSplitK ? p.ksplit : 1, z = kSplitK ? (int)blockIdx.x / (tiles_m * tiles_n) : 0;
+    const int NS = kSplitK ? p.split_q + (z < p.split_r ? 1 : 0) : NS_all;
+    const int s_base = kSplitK ? share_begin(z, p.split_q, p.split_r) : 0;   // its first stage
 
     // ---- direct global->LDS loads ---------------------------------------------------
     // One instruction moves 16 bytes per lane to LDS address m0 + lane*16.  They are issued
@@ -162,14 +170,14 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     // of B), hence the second set of offsets.
     uint32_t a_voff[A_LD], a_voff_last[A_LD], a_lds[A_LD];
     {
-        const int c16_max = p.K - 16 - (NS - 1) * BK;
+        const int c16_max = p.K - 16 - (NS_all - 1) * BK;
 #pragma unroll
         for (int i = 0; i < A_LD; ++i) {
             const int r = (wave * A_LD + i) * 8 + (lane >> 3);
             const int c16 = ((lane & 7) ^ ((r >> 1) & 7)) * 16;
             const uint32_t rowoff = (uint32_t)min(row0 + r, p.M - 1) * (uint32_t)p.lda;
             a_voff[i] = rowoff + (uint32_t)c16;
-            a_voff_last[i] = rowoff + (uint32_t)min(c16, c16_max);
+            a_voff_last[i] = rowoff + (uint32_t)(z == Z - 1 ? min(c16, c16_max) : c16);   // only the last slice meets K's end
             a_lds[i] = lds_base + (wave * A_LD + i) * 1024;
         }
     }
@@ -185,7 +193,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     {
         const int bc0 = wave * B_LD, kbl = bc0 / B_CHUNKS_PER_KB, cc0 = bc0 % B_CHUNKS_PER_KB;
         b_wave = p.packed + packed_unit_offset(tile_n / TILES_PER_NT, 0, (tile_n % TILES_PER_NT) * (BN / 32), p.KB2 * 2) +
-                 (int64_t)kbl * B_KB_STRIDE + cc0 * 1024;
+                 (int64_t)kbl * B_KB_STRIDE + cc0 * 1024 + (int64_t)s_base * (2 * B_KB_STRIDE);
         b_lds = lds_base + S * A_STAGE + kbl * (BN * 64) + cc0 * 1024;
     }
 
@@ -195,7 +203,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     auto issue_load = [&](int s, int buf, int n) __attribute__((always_inline)) {
         if (n < A_LD) {
             const uint32_t voff = (s == NS - 1) ? a_voff_last[n] : a_voff[n];
-            dma(a_lds[n] + buf * A_STAGE, voff, p.A + (int64_t)s * BK, std::integral_constant<int, 0>{});
+            dma(a_lds[n] + buf * A_STAGE, voff, p.A + (int64_t)(s_base + s) * BK, std::integral_constant<int, 0>{});
         } else {
             const int j = n - A_LD, g = j >> 2;
             const int8_t* const base = b_wave + (int64_t)s * (2 * B_KB_STRIDE) + g * 4096;
@@ -316,8 +324,14 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     // that the loop holds no global load the compiler knows of: it would put a wait for *all*
     // vector-memory traffic, the direct-to-LDS loads of the next stage included, in front of the
     // digit MFMAs.
-    const int ck_lo = kCheck ? share_begin(tile_n, p.share_q, p.share_r) : 0;
-    const int ck_hi = kCheck ? share_begin(tile_n + 1, p.share_q, p.share_r) : 0;
+    // (stage numbers of this slice: every slice's run of stages is dealt out to the tile columns in the same way)
+    int share_q = p.share_q, share_r = p.share_r;   // (of a run of split_q stages: one stage more is one more to deal out)
+    if (kSplitK && z < p.split_r && ++share_r == tiles_n) {
+        ++share_q;
+        share_r = 0;
+    }
+    const int ck_lo = kCheck ? share_begin(tile_n, share_q, share_r) : 0;
+    const int ck_hi = kCheck ? share_begin(tile_n + 1, share_q, share_r) : 0;
     uint8_t* const s_limb = smem + S * (A_STAGE + B_STAGE) + (4 * BN + WGN * BM + BM + 4) * sizeof(int32_t);
     // sum_k S_B[k], which the first tile column needs at the very end (the u8 -> s8 shift of A moves every
     // checksum product by 128 times it): fetched now, so that the epilogue does not wait for memory
@@ -325,11 +339,12 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     int limb_base = ck_lo;  // stage whose digits sit at the start of s_limb
     // (behind the load of the total, which the compiler can only make a scalar one ahead of any store)
     // errCount is overwritten on a grid of one row of tiles: the first workgroup clears it here and whoever finds corrupted
-    // rows adds to it.  No row is complete, and so nothing added, before that workgroup has arrived at the row's word, which it does once this store has been acknowledged.  (On other grids the rows of other
+    // rows adds to it.  No row is complete, and so nothing added, before that workgroup has arrived at the row's word (its
+    // slice at the tile's ticket), which it does once this store has been acknowledged.  (On other grids the rows of other
     // tile rows do not wait for it: there the last report of finished rows writes the count, one more round trip.)
     // (64x64 tiles only: the larger ones have one row of tiles on the widest weights alone)
     constexpr bool kClearsFirst = kCheck && BM == 64;
-    const bool clears = kClearsFirst && tiles_m == 1 && !p.err_accumulate && p.err_count != nullptr && tile_n == 0;
+    const bool clears = kClearsFirst && tiles_m == 1 && !p.err_accumulate && p.err_count != nullptr && tile_n == 0 && z == 0;
     if (kClearsFirst && clears && threadIdx.x == 0) __hip_atomic_store(p.err_count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // (copied by the same direct global->LDS loads as the stages, 1 KiB per instruction: no trip through
     // registers, and no wait that the compiler would place - it does not see the direct loads and would
@@ -338,7 +353,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     const uint32_t lds_limb = lds_base + (uint32_t)(S * (A_STAGE + B_STAGE) + (4 * BN + WGN * BM + BM + 4) * sizeof(int32_t));
     auto stage_limbs = [&](int s0) __attribute__((always_inline)) {
         const int n = min(ck_hi - s0, kLimbStages);
-        const int8_t* const src = p.limbs + (int64_t)s0 * 512;
+        const int8_t* const src = p.limbs + (int64_t)(s_base + s0) * 512;
         for (int i = wave; i * 2 < n; i += NW)
             dma(lds_limb + i * 1024, (uint32_t)min(i * 1024 + lane * 16, n * 512 - 16), src, std::integral_constant<int, 0>{});
         limb_base = s0;
@@ -725,6 +740,70 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     int32_t* const s_bs = reinterpret_cast<int32_t*>(smem + S * (A_STAGE + B_STAGE));
     int32_t* const s_rs = s_bs + 4 * BN;
     int32_t* const s_ck = s_rs + WGN * BM;
+    // Checksum shares of the rows from the digit products: 16x16 accumulator, lane l, element e is row 4*(l/16) + e, column l%16;
+    // columns 0..3 hold the four digits
+    auto recombine_digits = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < CB; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int d = lane & 15;
+                uint32_t v = d < kLimbs ? ((uint32_t)cacc[c][e] << (8 * d)) : 0u;
+                v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);
+                v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);
+                if (d == 0) s_ck[wm * WTM + (wn * CB + c) * 16 + 4 * (lane >> 4) + e] = (int32_t)v;
+            }
+    };
+
+    // ------------------------- K split across workgroups: partial tiles meet in the last arrival -------------------------
+    if constexpr (kSplitK) {
+        static_assert(TM * TN == 1 && NT == 256, "the split is built for the 64x64 tile of four 32x32 wavefronts");
+        __shared__ int s_ticket;
+        constexpr int kVals = 16 * TM * TN + TN;
+        static_assert(kVals * NT + BM == kSplit64PartInts, "layout of a partial tile");
+        const int tile = tile_m * tiles_n + tile_n;
+        int32_t* const part = p.ws_part + (size_t)tile * Z * kSplit64PartInts;
+        int32_t* const mine = part + (size_t)z * kSplit64PartInts + tid;
+        {
+            // device-scope stores (they pass through the L2, which is not coherent with the other seven): once this
+            // wavefront's stores are acknowledged and the barrier is passed, the whole partial tile is in memory
+            int k = 0;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) __hip_atomic_store(mine + (k++) * NT, acc[0][0][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(mine + (k++) * NT, (int32_t)bsum[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (kCheck) {
+            recombine_digits();
+            __syncthreads();
+            if (tid < BM) __hip_atomic_store(mine + kVals * NT, s_ck[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        wait_vmem();   // (also the direct-to-LDS loads still in flight)
+        __syncthreads();
+        if (tid == 0) s_ticket = __hip_atomic_fetch_add(p.ws_tickets + tile, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (s_ticket != Z - 1) return;   // (nothing in flight: awaited above)
+        if (tid == 0) __hip_atomic_store(p.ws_tickets + tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // the other slices' partial tiles, four at a time so that their loads are in flight together (a slice
+        // number past the last one, or this workgroup's own, re-reads a valid partial and adds nothing)
+        for (int z0 = 0; z0 < Z; z0 += 4) {
+            int32_t v[4][kVals], ck[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int32_t* const theirs = part + (size_t)min(z0 + j, Z - 1) * kSplit64PartInts + tid;
+#pragma unroll
+                for (int k = 0; k < kVals; ++k) v[j][k] = __hip_atomic_load(theirs + k * NT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (kCheck && tid < BM) ck[j] = __hip_atomic_load(theirs + kVals * NT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int32_t use = (z0 + j < Z && z0 + j != z) ? -1 : 0;   // all ones or zero
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[0][0][e] += v[j][e] & use;
+                bsum[0] += (uint32_t)(v[j][16] & use);
+                if (kCheck && tid < BM) s_ck[tid] = (int32_t)((uint32_t)s_ck[tid] + (uint32_t)(ck[j] & use));
+            }
+        }
+    }
 
     // ---------------------------------- epilogue ----------------------------------
     // accumulator layout of the 32x32 MFMA: lane l, element e of block (i, t) is
@@ -748,7 +827,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
         uint32_t v = (uint32_t)s_bs[wn * WTN + t * 32 + lcol];
         if (SUM_WAVES == 2) v += (uint32_t)s_bs[BN + wn * WTN + t * 32 + lcol];
         // (the k-steps of small wave tiles sum signed bytes directly, the others carry a bias of 128 per byte)
-        cs[t] = 128 * (int32_t)(kAhead2 ? v : v - 128u * (uint32_t)(NS * BK));
+        cs[t] = 128 * (int32_t)(kAhead2 ? v : v - 128u * (uint32_t)(NS_all * BK));
     }
     // C_temp = accumulator + cs (undoing the a - 128 shift); the sum is formed on the way to
     // memory, the accumulators stay as they are
@@ -924,6 +1003,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     }
 
     if (kCheck) {
+        if constexpr (!kSplitK) {
+        // (recombine_digits, written out: called here it gives the 256x256 kernel another register allocation and a longer epilogue,
+        // 4096x4096x4096 66.2 us against 65.7, 4096x4096x1024 26.5 against 26.0)
         // 16x16 accumulator: lane l, element e is row 4*(l/16) + e, column l%16; columns 0..3
         // hold the four digit products
 #pragma unroll
@@ -936,6 +1018,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
                 v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);
                 if (d == 0) s_ck[wm * WTM + (wn * CB + c) * 16 + 4 * (lane >> 4) + e] = (int32_t)v;
             }
+        }
         __syncthreads();
         // Row r of the product is spread over the tile columns; each of them adds its share of
         // (row sum - checksum) to the row's 64-bit workspace word with ONE returned atomic:
@@ -1016,13 +1099,25 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
 #endif
 }
 
-template <int BM, int BN, int WGM, int WGN, int kStages, int kAnyA = 0>
+template <int BM, int BN, int WGM, int WGN, int kStages, int kAnyA = 0, bool kSplitK = false>
 hipError_t launch_cfg(bool check, bool want_c, bool want_q, const GemmParams& p_in, hipStream_t s) {
     GemmParams p = p_in;
     const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
-    p.share_q = p.KB2 / tiles_n;   // stages of the checksum product per tile column
-    p.share_r = p.KB2 % tiles_n;
-    const dim3 grid((unsigned)(tiles_m * tiles_n)), block(WGM * WGN * 64);
+    int shortest = p.KB2;   // stages of the shortest slice
+    if (kSplitK) {
+        // slices, tickets and partial tiles as split64_plan lays them out; refused when the workspace does not hold them
+        const Split64Plan pl = split64_plan(p.M, p.N, p.KB2);
+        if (pl.z < 2 || p.ws == nullptr || p.ws_ints < pl.total_ints) return hipErrorNotSupported;
+        p.ksplit = pl.z;
+        p.ws_tickets = p.ws + kWsTicketsOff;
+        p.ws_part = p.ws + kWsScratchOff;
+        p.split_q = p.KB2 / pl.z;
+        p.split_r = p.KB2 % pl.z;
+        shortest = p.split_q;
+    }
+    p.share_q = shortest / tiles_n;   // ... and, of those, of the checksum product per tile column
+    p.share_r = shortest % tiles_n;
+    const dim3 grid((unsigned)(tiles_m * tiles_n * (kSplitK ? p.ksplit : 1))), block(WGM * WGN * 64);
     const size_t lds = (lds_bytes<BM, BN, WGN, kStages>() + 1023) / 1024 * 1024;
     // Row sums in block form or per row.  Small wave tiles: always the block form, which halves the
     // vector work of an epilogue that is short anyway.  The 128x128 wave tile: per row when the grid
@@ -1041,7 +1136,7 @@ hipError_t launch_cfg(bool check, bool want_c, bool want_q, const GemmParams& p_
     } while (0)
 #define ABFT_LAUNCH_FORM(CK, OUT, BS)                                                                     \
     do {                                                                                                  \
-        auto kern = gemm_tile_async_kernel<BM, BN, WGM, WGN, kStages, CK, OUT, ((BS) || !(CK)), kAnyA>; \
+        auto kern = gemm_tile_async_kernel<BM, BN, WGM, WGN, kStages, CK, OUT, ((BS) || !(CK)), kAnyA, kSplitK>; \
         static std::atomic<uint64_t> lds_allowed{0};                                                      \
         const hipError_t e_attr = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed);\
         if (e_attr != hipSuccess) return e_attr;                                                          \

@@ -5,6 +5,8 @@ from __future__ import annotations
 import numpy as np
 import torch
 
+# ints into a workspace where the scratch of K splits and padded copies begins: behind the counting words, the words of 131072 rows and the tickets
+WS_SCRATCH = 64 + 2 * 131072 + 1024
 VARIANTS = {"auto": 0, "tile256": 0x100, "tile128": 0x200, "tile64": 0x300, "smallm": 0x400,
             "tile256w2x4": 0x500, "tile256w4x2": 0x600}
 
@@ -21,13 +23,6 @@ class GpuRun:
         self.B_dev = dev(B.T if transposed else B)
         self.Bp = binding.abft_pack_b_checksum(self.B_dev, b_is_transposed=transposed)
         self.K, self.N = self.Bp.K, self.Bp.N
-
-    def _zero_ints(self, M, numel):
-        base = 64 + max(2 * ((M + 63) // 64 * 64), 2 * (32 * 64 + 64))
-        if numel <= base:
-            return numel
-        tiles = ((M + 63) // 64) * ((self.N + 63) // 64)
-        return base + (tiles + 63) // 64 * 64
 
     def checksum(self) -> np.ndarray:
         out = torch.empty(self.K, dtype=torch.int32, device="cuda")
@@ -73,7 +68,7 @@ class GpuRun:
             "flags": flags.cpu().numpy(),
             "err_count": int(cnt.item()),
             "Cq": None if Cq is None else Cq.cpu().numpy(),
-            # the words every call must leave at zero: row and counting words, and (when the workspace also has room for
-            # the partial tiles of a K split across workgroups, whose contents are irrelevant) the tile tickets behind them
-            "ws": ws.tensor.cpu().numpy()[: self._zero_ints(M, ws.tensor.numel())],
+            # the words every call must leave at zero: counting words, row words and tickets (what lies in the scratch behind
+            # them is irrelevant, unless there are so many rows that their words reach into it)
+            "ws": ws.tensor.cpu().numpy()[: max(WS_SCRATCH, 64 + 2 * M)],
         }

@@ -11,9 +11,10 @@ SRC = """
 extern "C" void plan(int M, int N, int K, int stages, int whole, long long* out) {
     const abft::SplitKPlan s = abft::splitk_plan(M, N, stages, whole != 0);
     const abft::RealignPlan r = abft::realign_plan(M, N, K, stages);
+    const abft::Split64Plan l = abft::split64_plan(M, N, stages);
     const long long v[] = {s.z, (long long)s.tickets_off, (long long)s.part_off, (long long)s.total_ints, (long long)s.room_ints, r.copy, (long long)r.off,
-                           (long long)r.total_ints, (long long)abft::ws_base_ints(M)};
-    for (int i = 0; i < 9; ++i) out[i] = v[i];
+                           (long long)r.total_ints, (long long)abft::ws_base_ints(M), l.z, (long long)l.total_ints};
+    for (int i = 0; i < 11; ++i) out[i] = v[i];
 }
 extern "C" int form(int M, int N, int stages, int whole) { return abft::wk_form(M, N, stages, whole != 0); }
 extern "C" int copy_first(int form, int stages) { return abft::copy_first((abft::WkForm)form, stages); }
@@ -23,7 +24,7 @@ NONE, T32X32W4, T32X32W8, T32X64W4, T32X64W8, T64X64W4 = range(6)
 
 class Plan:
     def __init__(self, v):
-        self.z, self.tickets_off, self.part_off, self.split_ints, self.room_ints, self.copy, self.copy_off, self.copy_ints, self.words = v
+        self.z, self.tickets_off, self.part_off, self.split_ints, self.room_ints, self.copy, self.copy_off, self.copy_ints, self.words, self.z64, self.split64_ints = v
 
 
 @pytest.fixture(scope="module")
@@ -35,7 +36,7 @@ def plan(tmp_path_factory):
     so = ctypes.CDLL(lib)
 
     def call(M, N, K, whole):
-        out = (ctypes.c_longlong * 9)()
+        out = (ctypes.c_longlong * 11)()
         so.plan(M, N, K, ((K + 63) // 64 + 1) // 2, whole, out)
         return Plan(out)
     call.copy_first = lambda form, K: bool(so.copy_first(form, ((K + 63) // 64 + 1) // 2))
@@ -44,14 +45,14 @@ def plan(tmp_path_factory):
 
 
 SIZES = [1, 16, 32, 33, 40, 41, 48, 64, 65, 128, 129, 200, 256, 500, 512, 1000, 4097]
-WIDTHS = [1, 32, 33, 64, 100, 200, 256, 500, 1000, 4096, 9000]
+WIDTHS = [1, 32, 33, 64, 100, 200, 256, 500, 1000, 1500, 4096, 4200, 6500, 9000]
 DEPTHS = [17, 385, 2049, 2999, 3071, 3073, 4609, 5001, 6145, 8191, 9001, 16383, 40001]
 
 
 def test_copy_and_parts_lie_apart(plan):
     """Wherever a call may both copy the rows of A and split K (its copy has whole rows), neither area reaches into the other, nor
     into the words, and a workspace that holds the copy holds the parts too."""
-    both = 0
+    both = both64 = 0
     for M in SIZES:
         for N in WIDTHS:
             for K in DEPTHS:
@@ -62,10 +63,13 @@ def test_copy_and_parts_lie_apart(plan):
                 if p.copy and p.z > 1:
                     both += 1
                     assert p.copy_off >= p.split_ints, (M, N, K, p.z)
+                if p.copy and p.z64 > 1:
+                    both64 += 1
+                    assert p.copy_off >= p.split64_ints, (M, N, K, p.z64)
                 for whole in (0, 1):
                     s = plan(M, N, K, whole)
                     assert s.z == 1 or s.split_ints <= s.room_ints, (M, N, K)
-    assert both > 50
+    assert both > 50 and both64 > 5
 
 
 # (shapes where the streaming kernel measured faster for weights that have not just been used, and neighbours where it did not)
@@ -95,3 +99,15 @@ def test_copy_ahead_of_the_large_form(plan, M, N, K, copied):
     assert form != NONE and plan.copy_first(form, K) == copied
     if copied:      # the copy is one that is made, the whole rows then run on 64x64 tiles of the same kernel, and M > 32 leaves room for it
         assert plan(M, N, K, 0).copy and plan.form(M, N, (K + 15) // 16 * 16) == T64X64W4 and M > 32
+
+
+# (33 to 64 rows where the 64x64 tiles with a split K measured faster, by slices, and neighbours where they did not)
+@pytest.mark.parametrize("M,N,K,z", [(64, 4200, 9008, 3), (64, 5000, 16000, 3), (33, 5000, 9008, 3), (64, 3000, 12000, 5), (64, 2000, 16000, 8), (64, 6500, 16000, 2),
+                                     (40, 1360, 20496, 11), (64, 5000, 6000, 1), (33, 3000, 12000, 1), (64, 2000, 9008, 1), (64, 6500, 9008, 1), (64, 1000, 16000, 1),
+                                     (65, 4200, 9008, 1), (32, 4200, 9008, 1), (64, 9000, 16000, 1)])
+def test_split_of_the_large_tiles(plan, M, N, K, z):
+    p = plan(M, N, K, 1)
+    assert p.z64 == z
+    if z > 1:
+        tiles = (N + 63) // 64
+        assert 128 < tiles * z <= 256 and tiles <= p.part_off - p.tickets_off and p.split64_ints == p.part_off + tiles * z * (256 * 17 + 64)

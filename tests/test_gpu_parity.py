@@ -610,12 +610,13 @@ def test_long_and_wide_ragged_shapes(binding, gpu_util, oracle, M, N, K):
     assert out["err_count"] == ref.err_count == 3 and not out["ws"].any()
 
 
+# (grids that do not fill the chip, on the tiles of gemm_tile_wk.h either way; 64x64 tiles with four stages in flight, in whole rounds of them and with
+# one and three left over; 289 of them with two)
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,N,K", [(200, 300, 2304), (1000, 1000, 4096), (65, 64, 2048)])
+@pytest.mark.parametrize("M,N,K", [(200, 300, 2304), (1000, 1000, 4096), (65, 64, 2048), (1000, 1000, 1024), (1000, 1000, 640), (1000, 990, 1408), (1040, 1088, 2064)])
 @pytest.mark.parametrize("variant", ["auto", "tile64"])
 def test_small_grid_long_k(binding, gpu_util, oracle, M, N, K, variant):
-    """At most 256 tiles of 64x64 and K of sixteen stages or more: the 64x64 kernel with the deep ring
-    of stages, with injections, in the exact check and modulo 127."""
+    """Grids of a few hundred tiles and several stages of K, with injections, in the exact check and modulo 127."""
     say(f"small grid, long K {M}x{N}x{K} {variant}")
     A, B = operands(M, N, K, 3 * M + N + K)
     inj = [(M - 1, N - 1, 1 << 30), (0, 0, 1), (M // 2, N // 3, 0x00020000)]
@@ -633,11 +634,10 @@ def test_small_grid_long_k(binding, gpu_util, oracle, M, N, K, variant):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,N,K", [(200, 130, 2000), (192, 64, 1792), (130, 200, 3008), (300, 520, 1536)])
-def test_k_split_between_wavefront_groups(binding, gpu_util, oracle, M, N, K):
-    """The 64x64 kernel that splits K between two groups of wavefronts (few tiles, K of twelve stages or
-    more, an even number of them): a K that ends inside the last stage (the second group meets it), one
-    tile column whose whole checksum share straddles the two groups, ragged M and N, injections, faults in
-    the weight early and late in K (one per group), requantized output, and the check modulo 127."""
+def test_k_split_between_wavefronts(binding, gpu_util, oracle, M, N, K):
+    """Few tiles and a K of twelve stages and more, in rounds among the wavefronts of a workgroup: a K that ends inside
+    the last stage, tile columns whose checksum shares lie in every wavefront's stages, ragged M and N, injections, faults in
+    the weight early and late in K, requantized output, and the check modulo 127."""
     say(f"K split {M}x{N}x{K}")
     A, B = operands(M, N, K, 7 * M + N + K, full_range_b=False)
     inj = [(M - 1, N - 1, 1 << 29), (0, 0, 1 << 3), (M // 2, N // 2, 0x00400000)]
@@ -667,13 +667,14 @@ def test_k_split_between_wavefront_groups(binding, gpu_util, oracle, M, N, K):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,N,K", [(200, 130, 2064), (64, 64, 2048), (130, 200, 3008), (320, 1000, 4096), (1000, 1024, 2176), (70, 190, 4112)])
+@pytest.mark.parametrize("M,N,K", [(200, 130, 2064), (64, 64, 2048), (130, 200, 3008), (320, 1000, 4096), (1000, 1024, 2176), (70, 190, 4112),
+                                   (1000, 1000, 1296), (1024, 1150, 1424)])
 def test_small_grid_long_k_every_feature(binding, gpu_util, oracle, M, N, K):
-    """At most 256 tiles of 64x64 and K of sixteen stages or more (the kernels with deep stage rings and K split
-    inside the workgroup): odd and even numbers of stages, a K that ends inside the last stage, shares of the checksum
-    product of one and two stages and empty ones, ragged M and N, injections in every quadrant of a tile, faults in the
-    weight early, late and in the middle of K and in the checksum column, both outputs with requantization, the
-    unchecked launch, the check modulo 127."""
+    """Grids of up to 288 tiles of 64x64 with every feature, on gemm_tile_wk.h and, where its forms do not take the grid, on the
+    64x64 tiles with four stages in flight (1000x1000x1296) and with two (1024x1150x1424): odd and even numbers of stages, a K that
+    ends inside the last stage, shares of the checksum product of one and two stages and empty ones, ragged M and N, injections in
+    every quadrant of a tile, faults in the weight early, late and in the middle of K and in the checksum column, both outputs with
+    requantization, the unchecked launch, the check modulo 127."""
     say(f"small grid, long K, every feature {M}x{N}x{K}")
     A, B = operands(M, N, K, 11 * M + N + K, full_range_b=False)
     inj = [(M - 1, N - 1, 1 << 29), (0, 0, 1 << 3), (M // 2, N // 2, 0x00400000), (40, 10, 1 << 31), (5, 50, 1 << 12)]
@@ -715,10 +716,11 @@ def test_small_grid_long_k_every_feature(binding, gpu_util, oracle, M, N, K):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,N,K,variant", [(100, 64, 8320, "tile64"), (300, 256, 12288, "tile256"), (130, 128, 4224, "tile128")])
+@pytest.mark.parametrize("M,N,K,variant", [(100, 64, 8320, "tile64"), (16450, 33, 4240, "tile64"), (300, 256, 12288, "tile256"), (130, 128, 4224, "tile128")])
 def test_long_checksum_share(binding, gpu_util, oracle, M, N, K, variant):
     """One tile column and a long K: its share of the checksum product is longer than one lot of
-    digits in LDS (32 stages of 128), so the digits are staged in several lots."""
+    digits in LDS (32 stages of 128), so the digits are staged in several lots (64x64 tiles: from 257 of them on; fewer
+    run on gemm_tile_wk.h, which fetches a stage's digits with it)."""
     say(f"long checksum share {M}x{N}x{K} {variant}")
     A, B = operands(M, N, K, 5 * M + N + K)
     inj = [(M - 1, N - 1, 1 << 31), (0, 0, 1 << 5)]
@@ -1007,11 +1009,14 @@ def test_recompute_flagged_rows_without_a_host_round_trip(binding, gpu_util, ora
     b.abft_packed_b_flip_bit(run.Bp, 100, 200, 6)
 
 
+# (32x32 tiles in two, three, four, seven, eight and sixteen slices, rows of whole chunks and of any length; 64x64 tiles in three, eight and
+# eleven; shapes next to them that run unsplit)
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,N,K", [(256, 512, 8192), (200, 300, 5120), (65, 64, 6144), (130, 70, 5264), (100, 1000, 8192),
-                                   (128, 128, 16384)])
-def test_k_split_across_workgroups(binding, gpu_util, oracle, M, N, K):
-    """Few 64x64 tiles and a long K: the library splits K across workgroups, the slices of a tile meet through the
+@pytest.mark.parametrize("M,N,K,split", [(65, 64, 3072, True), (65, 64, 6144, True), (46, 128, 13504, True), (100, 500, 8208, True), (128, 128, 16384, True), (40, 32, 32000, True),
+                                         (45, 1000, 5001, True), (32, 240, 12600, True), (33, 4161, 7712, True), (64, 1345, 15376, True), (49, 1345, 20496, True),
+                                         (256, 512, 8192, False), (200, 300, 5120, False), (130, 70, 5264, False), (100, 1000, 8192, False)])
+def test_k_split_across_workgroups(binding, gpu_util, oracle, M, N, K, split):
+    """Few tiles and a long K: the library splits K across workgroups, the slices of a tile meet through the
     workspace, and every slice contributes its share of the checksum product on its own.  Bit-exact against the
     oracle: clean, C faults in several tiles, B faults early and late in K (different slices), A faults, the
     requantization epilogue, the printed modulus, errCount as a counter - and the same shapes unsplit, which is
@@ -1021,22 +1026,19 @@ def test_k_split_across_workgroups(binding, gpu_util, oracle, M, N, K):
     A, B = operands(M, N, K, M + 2 * N + K, relu_like=(K % 256 == 0))
     run = gpu_util.GpuRun(binding, B)
     ws = binding.Workspace(M, run.Bp)
-    base_bytes = (64 + max(2 * ((M + 63) // 64 * 64), 2 * (32 * 64 + 64))) * 4
-    assert ws.tensor.numel() * 4 > base_bytes, "this shape is meant to be split"
-    small = torch.zeros(base_bytes // 4, dtype=torch.int32, device="cuda")
+    scratch = gpu_util.WS_SCRATCH
 
     class SmallWs:
-        tensor = small
+        tensor = torch.zeros(binding.lib.abft_gemm_workspace_bytes(M, None) // 4, dtype=torch.int32, device="cuda")
     ref = oracle.checked_gemm(A, B)
     for w in (ws, SmallWs):
         out = run.gemm(A, ws=w)
         assert np.array_equal(out["C"], ref.C) and not out["flags"].any() and out["err_count"] == 0
-        assert not out["ws"][: base_bytes // 4].any(), "row words and counting words must be left zero"
-        if w is ws:
-            tiles = ((M + 63) // 64) * ((N + 63) // 64)
-            assert not out["ws"][base_bytes // 4: base_bytes // 4 + tiles].any(), "tile tickets must be left zero"
+        assert not out["ws"].any(), "row words, counting words and tickets must be left zero"
+        if w is ws:     # the parts of the slices stay behind in the scratch, in whose first ints nothing else lies
+            assert ws.tensor[scratch:scratch + 1280].any().item() == split
         out = run.gemm(A, ws=w, check=False)
-        assert np.array_equal(out["C"], ref.C)
+        assert np.array_equal(out["C"], ref.C) and not out["ws"].any()
     rng = np.random.default_rng(K + M)
     inj = [(0, 0, 1 << 31), (M - 1, N - 1, 1), (M // 2, N // 2, 1 << 17), (M // 2, N // 3, 1 << 5), (1, N - 1, 0xFFFF0000)]
     refi = oracle.checked_gemm(A, B, flips_c=inj)
@@ -1077,7 +1079,7 @@ def test_k_split_across_workgroups(binding, gpu_util, oracle, M, N, K):
         out = run.gemm(A, ws=ws, mod127=True, injections=inj[:3])
         assert np.array_equal(out["C"], Cw) and np.array_equal(out["flags"], fw) and out["err_count"] == nw
     out = run.gemm(A, ws=ws)
-    assert out["err_count"] == 0 and not out["ws"][: base_bytes // 4].any()
+    assert out["err_count"] == 0 and not out["ws"].any()
 
 
 # (edges of the 16-byte chunk, of the 128-wide stage, of one and of several stages; streaming kernel, 64x64 kernel with loads
@@ -1124,7 +1126,8 @@ def test_rows_that_are_no_whole_chunks(binding, gpu_util, oracle, M, N, K):
 
 # (one and several tile columns; two to sixteen slices)
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,N,K", [(65, 64, 3001), (64, 32, 32001), (129, 40, 9001), (64, 64, 16383), (256, 200, 9001), (512, 100, 9001)])
+@pytest.mark.parametrize("M,N,K", [(65, 64, 3001), (64, 32, 32001), (129, 40, 9001), (64, 64, 16383), (256, 200, 9001), (512, 100, 9001),
+                                   (64, 4161, 7690)])
 def test_padded_copy_and_k_split_in_one_call(binding, gpu_util, oracle, M, N, K):
     """64x64 tiles asked for, rows that are no whole chunks, few tiles and a long K: the rows are copied into the workspace and K is
     split across workgroups, whose parts go there too, beside the copy.  One workspace for all calls, tickets left zero."""
@@ -1133,7 +1136,7 @@ def test_padded_copy_and_k_split_in_one_call(binding, gpu_util, oracle, M, N, K)
     A, B = operands(M, N, K, M + N + K)
     run = gpu_util.GpuRun(binding, B)
     ws = binding.Workspace(M, run.Bp)
-    tickets, scratch = 64 + 2 * 131072, 64 + 2 * 131072 + 1024     # ints into the workspace
+    scratch = gpu_util.WS_SCRATCH
     clean = oracle.checked_gemm(A, B)
     inj = [(M - 1, N - 1, 1 << 31), (M // 2, N // 3, 1 << 7)]
     refi = oracle.checked_gemm(A, B, flips_c=inj)
@@ -1143,14 +1146,14 @@ def test_padded_copy_and_k_split_in_one_call(binding, gpu_util, oracle, M, N, K)
         ws.tensor[scratch:].zero_()
         out = run.gemm(A, variant="tile64", ws=ws)
         assert np.array_equal(out["C"], clean.C) and not out["flags"].any() and out["err_count"] == 0
-        assert not ws.tensor[:scratch].any() and ws.tensor[scratch:scratch + 1280].any(), "the parts of a split come first"
+        assert not out["ws"].any() and ws.tensor[scratch:scratch + 1280].any(), "the parts of a split come first"
         assert np.array_equal(run.gemm(A, variant="tile64", ws=ws, check=False)["C"], clean.C)
         out = run.gemm(A, variant="tile64", ws=ws, injections=inj, accumulate_from=3)
         assert np.array_equal(out["C"], refi.C) and np.array_equal(out["flags"], refi.flags) and out["err_count"] == 3 + refi.err_count
     binding.abft_packed_b_flip_bit(run.Bp, *flip)
     out = run.gemm(A, variant="tile64", ws=ws)
     assert np.array_equal(out["C"], refb.C) and np.array_equal(out["flags"], refb.flags) and out["err_count"] == refb.err_count
-    assert not ws.tensor[tickets:scratch].any()
+    assert not out["ws"].any()
 
 
 @pytest.mark.gpu
@@ -1192,7 +1195,7 @@ def test_many_rows_after_calls_that_left_scratch(binding, gpu_util, oracle):
         want = oracle.checked_gemm(a, b)
         out = small.gemm(a, ws=Shared)
         assert np.array_equal(out["C"], want.C) and not out["flags"].any() and out["err_count"] == 0
-        assert Shared.tensor[263232:].any(), "the call left no scratch: this test has lost its point"
+        assert Shared.tensor[gpu_util.WS_SCRATCH:].any(), "the call left no scratch: this test has lost its point"
         out = run.gemm(A_dev, ws=Shared)
         assert np.array_equal(out["C"], ref.C) and not out["flags"].any() and out["err_count"] == 0
         assert not Shared.tensor[:64 + 2 * M].any()
