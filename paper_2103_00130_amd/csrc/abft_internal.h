@@ -217,13 +217,16 @@ inline SplitKPlan splitk_plan(int M, int N, int stages, bool whole_a) {
     return pl;
 }
 
-// The split of 64x64 tiles (gemm_tile_async.h): 33 to 64 rows, whose weight these tiles read once, and a K so long that the slices'
-// meeting is paid for.  Its 256 workgroups keep more of a weight in flight than the fewer ones of gemm_tile_wk.h with 32 or 64 columns,
-// which counts where the weight is not in the caches; where the line lies depends on how many of those there are (us, one weight again
-// and again / fresh ones; gemm_tile_wk.h, then this split): 64x4200x9008 15.4 22.0 / 14.5 17.5, 64x5000x16000 21.0 30.5 / 19.8 22.7, 33x5000x9008
-// 14.5 17.8 / 16.7 16.2, 33x4200x12000 17.8 21.0 / 16.3 17.4, 64x3000x12000 14.3 19.3 / 14.6 16.4, 64x2000x16000 15.1 19.4 / 14.5 14.5,
-// 64x6500x16000 22.4 32.5 / 24.2 28.3; but 64x5000x6000 11.4 16.6 / 12.7 14.5, 33x3000x12000 13.3 15.4 / 14.3 16.5, 64x2000x9008 9.1 16.0 /
-// 11.5 12.8, 64x6500x9008 16.4 22.9 / 17.7 22.6, 64x1000x16000 10.7 12.5 / 12.5 14.5; 128 rows 128x3000x12000 17.9 24 / 20.0 24.6.
+// The split of 64x64 tiles (gemm_tile_async.h): 33 to 64 rows, whose weight these tiles read once, or any number where the 32x64 tiles of
+// gemm_tile_wk.h would leave near half of the compute units idle (65 to 85 tiles of 64x64, too many of 32x32), and a K so long that the
+// slices' meeting is paid for.  Its 256 workgroups keep more of a weight in flight than the fewer ones of gemm_tile_wk.h with 32 or 64
+// columns, which counts where the weight is not in the caches; where the line lies depends on how many of those there are (us, one weight
+// again and again / fresh ones; gemm_tile_wk.h, then this split): 64x4200x9008 15.4 22.0 / 14.5 17.5, 64x5000x16000 21.0 30.5 / 19.8 22.7,
+// 33x5000x9008 14.5 17.8 / 16.7 16.2, 33x4200x12000 17.8 21.0 / 16.3 17.4, 64x3000x12000 14.3 19.3 / 14.6 16.4, 64x2000x16000 15.1 19.4 /
+// 14.5 14.5, 64x6500x16000 22.4 32.5 / 24.2 28.3; but 64x5000x6000 11.4 16.6 / 12.7 14.5, 33x3000x12000 13.3 15.4 / 14.3 16.5, 64x2000x9008
+// 9.1 16.0 / 11.5 12.8, 64x6500x9008 16.4 22.9 / 17.7 22.6, 64x1000x16000 10.7 12.5 / 12.5 14.5.  More rows: 164x1440x15312 23.0 24.6 /
+// 20.7 20.6, 746x339x14848 19.7 21.3 / 18.0 18.2, 1100x250x12000 19.0 20.0 / 16.5 16.8; but 192x1500x9008 15.1 / 15.7, 128x3000x12000 17.9 24.0 /
+// 20.0 24.6, and with fewer than 257 tiles of 32x32 130x1400x11600 14.3 14.6 / 17.6 17.5.
 constexpr int kSplit64PartInts = 256 * 17 + 64;   // per workgroup: 256 threads x (16 accumulator values + 1 column sum), 64 rows' checksum shares
 struct Split64Plan {
     int z;                // slices (1 = no split)
@@ -231,10 +234,12 @@ struct Split64Plan {
 };
 inline Split64Plan split64_plan(int M, int N, int stages) {
     Split64Plan pl;
-    const int64_t tiles = ((int64_t)N + 63) / 64;
-    const int line = tiles <= 20 || tiles > 128 ? 1 << 30 : tiles <= 32 ? 120 : tiles <= 64 ? (M > 48 ? 90 : 120) : tiles <= 85 ? 60 : 120;
+    const int64_t tiles = ((int64_t)M + 63) / 64 * (((int64_t)N + 63) / 64);
+    const int64_t t32 = ((int64_t)M + 31) / 32 * (((int64_t)N + 31) / 32);
+    const bool third = tiles > 64 && tiles <= 85 && t32 > 256;   // (three slices)
+    const int line = tiles <= 20 || tiles > 128 ? 1 << 30 : third ? (M > 64 ? 90 : 60) : tiles > 32 && tiles <= 64 && M > 48 ? 90 : 120;
     pl.z = 1;
-    if (M > 32 && M <= 64 && stages >= line) {
+    if (M > 32 && (M <= 64 || third) && stages >= line) {
         const int most = (int)(256 / tiles), z = stages >= 160 ? 16 : 8;
         pl.z = z < most ? z : most;
     }
@@ -298,11 +303,11 @@ __device__ inline shift_v4i shift_down(shift_v4i v, int n) {
 // It has a batch of 2048 k of its 16 or 32 columns in flight at once; the wavefronts of gemm_tile_wk.h have 512 or 1024 k of 32 or 64
 // columns, and wait once per round for what the caches do not hold.  So the lines lie by the stages of 128 k, where the mean of three
 // states favours it: one weight again and again, eight in turn, fresh ones (us each, streaming / gemm_tile_wk.h):
-//  * whole chunks: 1x800x2048 4.2 4.3 4.2 / 4.4 4.5 5.3, 1x800x3200 5.0 5.1 5.0 / 4.8 5.0 6.1, 4x4096x4096 5.5 6.7 6.7 / 5.7 6.3 7.7,
-//    8x2048x4096 5.4 6.3 6.2 / 5.6 6.1 7.3, 1x3000x12000 10.0 10.6 10.6 / 9.5 13.6 13.6, 8x12000x1024 4.9 5.9 6.0 / 4.9 6.1 6.9, 1x15000x3008
-//    9.9 10.7 10.7 / 10.4 11.8 12.1; but 3x3000x9008 9.1 9.5 9.6 / 7.5 8.8 11.6, 1x800x2560 5.0 5.3 5.2 / 4.4 4.7 5.9, 8x3000x6400
-//    8.4 8.9 8.8 / 6.4 7.3 9.4, 8x800x6400 6.9 8.1 7.9 / 6.0 6.8 8.6, 16x4096x4096 6.5 7.5 7.6 / 5.7 6.3 8.0, 4x12000x1152 6.2 / 5.1,
-//    8x15000x5008 15.5 / 14.3
+//  * whole chunks: 1x800x2048 4.2 4.3 4.2 / 4.4 4.5 5.3, 1x800x3200 5.0 5.1 5.0 / 4.8 5.0 6.1, 1x832x5312 6.0 6.2 6.0 / 5.6 6.1 7.6,
+//    4x4096x4096 5.5 6.7 6.7 / 5.7 6.3 7.7, 8x2048x4096 5.4 6.3 6.2 / 5.6 6.1 7.3, 1x3000x12000 10.0 10.6 10.6 / 9.5 13.6 13.6, 8x12000x1024 4.9
+//    5.9 6.0 / 4.9 6.1 6.9, 1x15000x3008 9.9 10.7 10.7 / 10.4 11.8 12.1; but 3x3000x9008 9.1 9.5 9.6 / 7.5 8.8 11.6, 1x800x2560 5.0 5.3 5.2 / 4.4
+//    4.7 5.9, 8x3000x6400 8.4 8.9 8.8 / 6.4 7.3 9.4, 8x800x6400 6.9 8.1 7.9 / 6.0 6.8 8.6, 16x4096x4096 6.5 7.5 7.6 / 5.7 6.3 8.0, 4x12000x1152
+//    6.2 / 5.1, 8x15000x5008 15.5 / 14.3
 //  * 9 to 16 rows, few or middling columns: 10x464x4064 4.9 / 5.4, 1x145x6128 6.0 / 6.4, 16x4096x2048 4.8 / 5.0; but 16x1200x2048 even,
 //    13x144x11067 16.6 / 7.8
 //  * rows that are no whole chunks, which the streaming kernel loads row by row: one row 1x300x2001 4.4 / 5.0, 1x800x3201 5.6 5.8 5.8 /
@@ -319,6 +324,7 @@ inline bool few_rows_stream(int M, int N, int stages, bool whole_a) {
     if (N > 4096) return M <= 8 && N > 12288 && stages >= 24 && stages <= (M <= 4 ? 48 : 32);
     if (stages <= 8) return false;
     if (N <= 640) return stages < 64;
+    if (M == 1 && N <= 2500 && stages > 40 && stages <= 48) return true;
     if (N <= 1500) return M <= 8 && (stages <= 16 || (stages > 24 && stages <= 32));   // (the last batch at least half full)
     return stages <= 20 || (M <= 8 && (stages <= 32 || (N > 2048 && stages >= 72)));
 }

@@ -74,7 +74,7 @@ def test_copy_and_parts_lie_apart(plan):
 
 # (shapes where the streaming kernel measured faster for weights that have not just been used, and neighbours where it did not)
 @pytest.mark.parametrize("M,N,K,streams", [(1, 800, 2048, True), (1, 800, 3200, True), (4, 4096, 4096, True), (8, 2048, 4096, True), (1, 3000, 12000, True), (8, 3000, 16384, True),
-                                           (8, 12000, 1024, True), (1, 15000, 3008, True), (16, 4096, 2048, True), (10, 464, 4064, True), (1, 800, 2560, False),
+                                           (8, 12000, 1024, True), (1, 15000, 3008, True), (16, 4096, 2048, True), (10, 464, 4064, True), (1, 800, 2560, False), (1, 832, 5312, True), (2, 832, 5312, False), (1, 832, 4400, False),
                                            (8, 3000, 6400, False), (8, 800, 6400, False), (16, 4096, 4096, False), (16, 1200, 2048, False), (4, 12000, 1152, False),
                                            (8, 15000, 3008, True), (8, 15000, 5008, False), (4, 15000, 5008, True), (8, 8192, 1001, True), (1, 4096, 9001, True), (3, 3000, 9008, False), (1, 16384, 3008, False), (24, 800, 2048, False), (8, 4096, 512, False), (1, 800, 3201, True),
                                            (1, 300, 2001, True), (1, 800, 1001, True), (4, 300, 2001, True), (1, 6001, 9001, True), (4, 800, 3201, False), (8, 3000, 2049, False),
@@ -101,13 +101,13 @@ def test_copy_ahead_of_the_large_form(plan, M, N, K, copied):
         assert plan(M, N, K, 0).copy and plan.form(M, N, (K + 15) // 16 * 16) == T64X64W4 and M > 32
 
 
-# (33 to 64 rows where the 64x64 tiles with a split K measured faster, by slices, and neighbours where they did not)
+# (where the 64x64 tiles with a split K measured faster, by slices, and neighbours where they did not)
 @pytest.mark.parametrize("M,N,K,z", [(64, 4200, 9008, 3), (64, 5000, 16000, 3), (33, 5000, 9008, 3), (64, 3000, 12000, 5), (64, 2000, 16000, 8), (64, 6500, 16000, 2),
                                      (40, 1360, 20496, 11), (64, 5000, 6000, 1), (33, 3000, 12000, 1), (64, 2000, 9008, 1), (64, 6500, 9008, 1), (64, 1000, 16000, 1),
-                                     (65, 4200, 9008, 1), (32, 4200, 9008, 1), (64, 9000, 16000, 1)])
+                                     (164, 1440, 15312, 3), (746, 339, 14848, 3), (192, 1500, 9008, 1), (130, 1400, 11600, 1), (1100, 250, 12000, 3), (128, 3000, 12000, 1), (128, 1500, 16000, 1), (65, 4200, 9008, 1), (32, 4200, 9008, 1), (64, 9000, 16000, 1)])
 def test_split_of_the_large_tiles(plan, M, N, K, z):
     p = plan(M, N, K, 1)
     assert p.z64 == z
     if z > 1:
-        tiles = (N + 63) // 64
+        tiles = (M + 63) // 64 * ((N + 63) // 64)
         assert 128 < tiles * z <= 256 and tiles <= p.part_off - p.tickets_off and p.split64_ints == p.part_off + tiles * z * (256 * 17 + 64)
