@@ -146,10 +146,11 @@ typedef struct {
  * have contributed) and a few counting words (rows finished, rows corrupted);
  * with Bp given, also room for the parts of a K split across workgroups on the
  * shapes where the library may use one (few tiles, K of about 3000 and more),
- * and for a copy of A with padded rows where K is no multiple of 16 and the product is large enough for the copy to pay.  Such room is used
- * wherever the workspace holds it, whatever it was sized for; a smaller one, of
- * at least the size that this call returns for Bp == NULL, runs without it, with
- * the same results.
+ * and for a copy of A with padded rows where K is no multiple of 16 and the
+ * product is large enough for the copy to pay, if only in calls that ask for a
+ * tile.  Such room is used wherever the workspace holds it, whatever it was
+ * sized for; a smaller one, of at least the size that this call returns for
+ * Bp == NULL, runs without it, with the same results.
  * The memory must be zero before its first use (abft_workspace_init) and every
  * call leaves its words zero again, so one workspace serves any number of calls
  * that are ordered on one stream, of different sizes too.  Calls that may

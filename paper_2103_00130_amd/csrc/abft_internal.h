@@ -172,9 +172,6 @@ inline size_t ws_base_ints(int M) {
     return (size_t)kWsHeaderInts + (rows > streaming ? rows : streaming);
 }
 
-// Calls of so few rows that no copy of A with padded rows is ever made for them: abft_gemm_workspace_bytes leaves its room out.
-inline bool words_suffice(int M, int N, int K) { return M <= 32 || (M <= 48 && N <= 4096 && K > 512 && K <= (M <= 40 ? 4096 : 2048)); }
-
 // What some calls need beyond those words - the tile tickets and partial tiles of a K split, a copy of A with padded rows -
 // lies behind the words of any call of up to kWsRows rows, so that one workspace can serve calls of different sizes: the
 // words (tickets among them) are zero between calls, the scratch behind them holds whatever the last call left (a call of more
@@ -255,8 +252,10 @@ inline Split64Plan split64_plan(int M, int N, int stages) {
 // (measured in us, loads through registers / copy:
 // 2000x1000x1001, 16 stages per unit, 11.5 / 11.8; 256x512x2049, 17, 10.8 / 11.4; 1111x3333x777, 28, 16.5 / 14.9;
 // 1000x1000x4097, 33, 20.3 / 16.9; 4096x2048x1023, 64, 30.2 / 23.1; 4096x4096x4095, 512, 148 / 74).
-// abft_gemm_workspace_bytes includes the room when K is no multiple of 16 and the copy would be made (copies above 512 MiB
-// are not); a workspace without it runs without the copy.
+// abft_gemm_workspace_bytes includes the room when K is no multiple of 16 and the copy may be made (copies above 512 MiB
+// are not): where the choice is the library's own, beyond the grids of gemm_tile_wk.h, ahead of its 64x64 form (copy_first) and of the
+// split of 64x64 tiles, none of which up to 40 rows and 4096 columns and k are; elsewhere the room serves calls that ask for a tile.
+// A workspace without it runs without the copy.
 struct RealignPlan {
     bool copy;
     size_t off, total_ints;    // ints into the workspace; the copy starts on the next 16-byte boundary
@@ -276,6 +275,7 @@ inline RealignPlan realign_plan(int M, int N, int K, int stages) {
     pl.total_ints = pl.off + (size_t)(pl.lda * M / 4) + 4;
     return pl;
 }
+inline bool room_for_copy(int M, int N, int K) { return K % 16 != 0 && (M > 40 || (M > 32 && (N > 4096 || K > 4096))); }
 
 // first unit of block c's share (see share_q, share_r)
 __host__ __device__ inline int share_begin(int c, int q, int r) { return c * q + (c < r ? c : r); }

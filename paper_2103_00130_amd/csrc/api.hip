@@ -152,13 +152,13 @@ void abft_packed_b_destroy(abft_packed_b* Bp) { free_handle(Bp); }
 
 size_t abft_gemm_workspace_bytes(int M, const abft_packed_b* Bp) {
     if (M < 1) return 0;
-    // with the weight known: room for the parts of a K split across workgroups, where one would be used, and, where rows of
-    // Bp->K bytes are no whole chunks, for the copy with padded rows
+    // with the weight known: room for the parts of a K split across workgroups, where one may be used, and, where rows of
+    // Bp->K bytes are no whole chunks, for the copy with padded rows behind them
     if (Bp) {
         const size_t small = abft::splitk_plan(M, Bp->N, Bp->KB / 2, false).room_ints, large = abft::split64_plan(M, Bp->N, Bp->KB / 2).total_ints;
         const size_t split = small > large ? small : large;
         const abft::RealignPlan ra = abft::realign_plan(M, Bp->N, Bp->K, Bp->KB / 2);
-        const bool copy = Bp->K % 16 != 0 && ra.copy && !abft::words_suffice(M, Bp->N, Bp->K);
+        const bool copy = ra.copy && abft::room_for_copy(M, Bp->N, Bp->K);
         return (copy && ra.total_ints > split ? ra.total_ints : split) * sizeof(int32_t);
     }
     return ws_ints(M) * sizeof(int32_t);

@@ -355,7 +355,8 @@ hipError_t launch_any(bool check, bool want_c, bool want_q, const GemmParams& p_
 
 template <int RB, int NCB>
 hipError_t launch_rb(bool check, bool want_c, bool want_q, const GemmParams& p, hipStream_t s) {
-    if constexpr (RB <= 2)   // (more than 32 rows only come here when this kernel is asked for, and then A is aligned)
+    // rows of any alignment: up to 16, or 64 columns per workgroup (what gemm_tile_wk.h leaves)
+    if constexpr (RB == 1 || (RB == 2 && NCB == 4))
         if (!p.a_vec_ok || p.K % 16 != 0) return launch_any<RB, NCB, true>(check, want_c, want_q, p, s);
     return launch_any<RB, NCB, false>(check, want_c, want_q, p, s);
 }
@@ -365,7 +366,7 @@ hipError_t launch_rb(bool check, bool want_c, bool want_q, const GemmParams& p, 
 hipError_t launch_gemm_smallm(bool any_a, bool check, bool want_c, bool want_q, const GemmParams& p, hipStream_t s) {
     if (p.M > 64) return hipErrorNotSupported;
     if (!p.a_vec_ok || p.K % 16 != 0)
-        if (!any_a || p.mod127 || p.K < 16 || p.M > 32) return hipErrorNotSupported;
+        if (!any_a || p.mod127 || p.K < 16 || p.M > 32 || (p.M > 16 && p.N <= kWideN)) return hipErrorNotSupported;
     // As few columns per workgroup as still give every compute unit one workgroup at most (us, NCB = 1 / 2 / 4):
     // 16x4096x4096 7.0 / 8.5 / 11.4; 16x6000x4000 10.3 / 8.8 / 12.4; 16x8192x8192 19.1 / 15.1 / 21.1; 16x12000x12000 37.3 /
     // 34.5 / 29.8; 16x16384x16384 62 / 58 / 43.7 (6.1 TB/s); 32x6000x4000 14.8 / 11.8 / 16.5; 32x16384x16384 90 / 65 / 49.4.

@@ -17,6 +17,7 @@ extern "C" void plan(int M, int N, int K, int stages, int whole, long long* out)
     for (int i = 0; i < 11; ++i) out[i] = v[i];
 }
 extern "C" int form(int M, int N, int stages, int whole) { return abft::wk_form(M, N, stages, whole != 0); }
+extern "C" int room_for_copy(int M, int N, int K) { return abft::room_for_copy(M, N, K); }
 extern "C" int copy_first(int form, int stages) { return abft::copy_first((abft::WkForm)form, stages); }
 """
 NONE, T32X32W4, T32X32W8, T32X64W4, T32X64W8, T64X64W4 = range(6)
@@ -39,6 +40,7 @@ def plan(tmp_path_factory):
         out = (ctypes.c_longlong * 11)()
         so.plan(M, N, K, ((K + 63) // 64 + 1) // 2, whole, out)
         return Plan(out)
+    call.room_for_copy = lambda M, N, K: bool(so.room_for_copy(M, N, K))
     call.copy_first = lambda form, K: bool(so.copy_first(form, ((K + 63) // 64 + 1) // 2))
     call.form = lambda M, N, K: so.form(M, N, ((K + 63) // 64 + 1) // 2, K % 16 == 0)
     return call
@@ -111,3 +113,21 @@ def test_split_of_the_large_tiles(plan, M, N, K, z):
     if z > 1:
         tiles = (M + 63) // 64 * ((N + 63) // 64)
         assert 128 < tiles * z <= 256 and tiles <= p.part_off - p.tickets_off and p.split64_ints == p.part_off + tiles * z * (256 * 17 + 64)
+
+
+def test_calls_of_rows_that_are_no_whole_chunks(plan):
+    """Wherever the library copies such rows on its own account the workspace has room for the copy; and of up to 32 rows only calls that the
+    streaming kernel takes at any alignment are left to it (up to 16 rows, or more than 8192 columns)."""
+    copies = left = 0
+    for M in [*range(1, 34), 40, 41, 48, 49, 64, 65, 100, 128, 200, 256, 500, 1000, 3000, 9000]:
+        for N in (1, 40, 300, 900, 1345, 2000, 3000, 4096, 4097, 4161, 6500, 8191, 8193, 12000, 16383, 16384, 16385, 20000, 33000, 70000):
+            for K in (17, 129, 500, 1001, 1999, 2999, 4095, 4097, 6001, 9001, 12001, 15361, 16383, 33001):
+                form = plan.form(M, N, K)
+                if M <= 32 and form == NONE:
+                    left += 1
+                    assert M <= 16 or N > 8192, (M, N, K)
+                p = plan(M, N, K, 0)
+                if M > 32 and p.copy and (form == NONE or plan.copy_first(form, K) or p.z64 > 1):
+                    copies += 1
+                    assert plan.room_for_copy(M, N, K), (M, N, K)
+    assert copies > 100 and left > 100
