@@ -78,7 +78,7 @@ __global__ __launch_bounds__(W * 64) void gemm_tile_wk_kernel(const GemmParams p
     constexpr bool kWantC = (kOut & kOutC) != 0, kWantQ = (kOut & kOutQ) != 0;
     constexpr int F = W < 4 * TM ? W : 4 * TM;   // wavefronts that finish the tile
     constexpr int PG = 4 * TM / F;               // groups of eight rows that each of them finishes
-    static_assert(4 * TM % F == 0, "equal shares of the tile");
+    static_assert(4 * TM % F == 0 && TM <= 2, "equal shares of the tile; one or two blocks of rows");
 
     extern __shared__ __align__(1024) uint8_t smem[];
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -291,7 +291,10 @@ __global__ __launch_bounds__(W * 64) void gemm_tile_wk_kernel(const GemmParams p
                 if (4 * i + j >= u_lo && 4 * i + j < u_hi)
 #pragma unroll
                     for (int m = 0; m < TM; ++m) mfma_digits(dacc[m], fa[j][m], limb[j]);
-            asm volatile("s_nop 7\n\ts_nop 7");   // (the distance from these matrix instructions to whatever reads their results)
+            // the distance from these matrix instructions to whatever reads their results, which go through the string so that nothing that
+            // the compiler does with them comes before it
+            if constexpr (TM == 1) asm volatile("s_nop 7\n\ts_nop 7" : "+v"(dacc[0]));
+            else asm volatile("s_nop 7\n\ts_nop 7" : "+v"(dacc[0]), "+v"(dacc[1]));
         }
     }
     // ---- the partial tiles meet: every wavefront leaves its own in the part of LDS that its stages went through
