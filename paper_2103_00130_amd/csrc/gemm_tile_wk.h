@@ -78,6 +78,7 @@ __global__ __launch_bounds__(W * 64) void gemm_tile_wk_kernel(const GemmParams p
     constexpr bool kWantC = (kOut & kOutC) != 0, kWantQ = (kOut & kOutQ) != 0;
     constexpr int F = W < 4 * TM ? W : 4 * TM;   // wavefronts that finish the tile
     constexpr int PG = 4 * TM / F;               // groups of eight rows that each of them finishes
+    constexpr bool kMayStream = W == 8 || TM == 2;   // (the other forms' weights are never that large: few stages)
     static_assert(4 * TM % F == 0 && TM <= 2, "equal shares of the tile; one or two blocks of rows");
 
     extern __shared__ __align__(1024) uint8_t smem[];
@@ -200,7 +201,7 @@ __global__ __launch_bounds__(W * 64) void gemm_tile_wk_kernel(const GemmParams p
                 load_to_lds<BM * BK + kbl * (BN * 64), c * 1024, decltype(stream_c)::value>(lds_mine, b_voff, b_base + (int64_t)(2 * s + kbl) * B_KB_STRIDE);
             });
         };
-        if (TN == 2 && stream) load_b(std::true_type{});
+        if (kMayStream && stream) load_b(std::true_type{});
         else load_b(std::false_type{});
         if constexpr (kAny) {
             // rows of any alignment come in through registers (behind the loads of B: the wait for them covers those); nothing
@@ -614,7 +615,8 @@ hipError_t launch_any(bool check, bool want_c, bool want_q, const GemmParams& p_
     // in the program it would not be there at the next call (three weights in turn, us, kept / passed through: 16x16384x16384 52.1 / 46.2,
     // 12000x12000 and 8 rows 30.2 / 27.1, 16384x6400 and 32 rows 22.1 / 20.6; but 16x8192x8192 13.9 / 18.7; read by two rows of tiles,
     // 33x8192x12000, 24.6 / 36.4).  Up to 32 rows, which were always read that way; beyond, only what the cache cannot hold at all
-    // (60 rows of 12000x12000 alone in a loop 28.6 / 38.3).
+    // (60 rows of 12000x12000 alone in a loop 28.6 / 38.3).  With tiles of 32 columns too (8x8192x16384 in a loop 22.0 / 22.6, fresh weights
+    // 28.0 / 23.7).
     p.wk_stream = tiles_m == 1 && (int64_t)p.N * p.K >= (int64_t)(p.M <= 32 ? 96 : 224) << 20;
     const uint32_t per_strip = (uint32_t)(tiles_m < 4 ? tiles_m : 4) * (uint32_t)tiles_n;
     const uint32_t strip_rcp = per_strip == 1 ? 0u : (uint32_t)((0x100000000ull + per_strip - 1) / per_strip);

@@ -1439,12 +1439,13 @@ def test_requantized_full_grid(binding, gpu_util, oracle):
 
 
 # (each tile form with one stage, stages that no wavefront, some or all wavefronts have, tiles and stages cut off, rows of whole chunks
-# and of any length; slots for 64, 128 and 256 rows; K split across workgroups)
+# and of any length; slots for 64, 128 and 256 rows; K split across workgroups; weights of more than 96 MiB, which pass the caches by)
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,N,K", [(1, 1, 16), (17, 33, 17), (31, 31, 128), (33, 65, 1008), (100, 129, 1153), (257, 95, 2049), (65, 200, 4111),
                                    (300, 900, 304), (320, 1000, 1553), (257, 1025, 3090), (1000, 1000, 1296), (1023, 963, 1290), (130, 3500, 70),
                                    (16, 1600, 80), (5, 8000, 200), (64, 1537, 1201), (65, 3200, 250), (128, 3105, 1040), (129, 1700, 144), (256, 1569, 90),
-                                   (40, 70, 8192), (129, 40, 3000), (33, 200, 5001), (3, 100, 9000), (1030, 40, 112), (3001, 80, 160), (1030, 40, 300), (3001, 80, 400), (2100, 300, 1552), (1100, 1800, 131), (700, 1950, 1279)])
+                                   (40, 70, 8192), (129, 40, 3000), (33, 200, 5001), (3, 100, 9000), (1030, 40, 112), (3001, 80, 160), (1030, 40, 300), (3001, 80, 400), (2100, 300, 1552), (1100, 1800, 131), (700, 1950, 1279),
+                                   (16, 12000, 9008), (3, 12100, 8999), (9, 8192, 12400), (2, 7900, 13003)])
 def test_k_split_among_wavefronts(binding, gpu_util, oracle, M, N, K):
     """Grids that do not fill the chip: clean, C and B faults early and late in K and in the last row and column, both outputs,
     unchecked, errCount overwritten, added to and absent, the printed modulus where rows are whole chunks."""
