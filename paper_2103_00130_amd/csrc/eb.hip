@@ -14,12 +14,12 @@
 //    lane; the chip is filled by lookups, and the lanes of a lookup walk its index list in order.
 //  * Group kernel: one, two or four wavefronts per lookup.  Their threads fetch different 16-byte
 //    pieces of the lookup's records into LDS, then, owning columns, walk the staged rows in index order.
-//  * The loads of the records are ordinary ones where lookups are many: rows that come back, in the same batch or a later one, are
-//    then found in the caches (the same 16384 lookups of 100 rows of 80 bytes again and again: 50.4 us, 56.9 marked as streaming;
-//    16987 of 36 rows of 272 bytes 39.9 / 49.7; 65536 of 4 rows of 80 15.6 / 18.7), which costs something where no row comes back
-//    (eight such batches in turn, 2.5 GB of lines: 60.6 / 58.5, rows of whole lines 46.2 / 44.0).  Four wavefronts per lookup, the
-//    form for few lookups, whose time is latency, mark them (10 lookups of 100 rows never read before: 5.0 us, 5.55 without;
-//    read before: 4.5 either way).
+//  * The loads of the records are ordinary ones where lookups are many and the table is no larger than a few times the caches: rows that
+//    come back, in the same batch or a later one, are then found there (16384 lookups of 100 rows of 80 bytes from a table of 320 MB,
+//    ordinary / marked as streaming: the same ones again and again 49.6 us / 56.2, fresh ones at every call 50.5 / 57.0; 65536 of 4 rows
+//    16.0 / 18.1).  Lookups of one or two wavefronts from a larger table mark them (eb_passes_by), and so do four wavefronts per lookup,
+//    the form for few lookups, whose time is latency (10 lookups of 100 rows never read before: 5.0 us, 5.55 without; read before: 4.5
+//    either way).
 //  * Every load is unconditional (clamped position, row 0 in place of a bad index): a load under
 //    `if (valid)` is followed by a wait, which would put the loads of a lookup one after the other.
 //  Both accumulate every output column in the same order (index order, one fused multiply-add
@@ -319,7 +319,7 @@ __global__ __launch_bounds__(256) void eb_batch_kernel(const EbParams p) {
 //  Many lookups of the same total: bound by memory, whole 128-byte lines for every record (16384 lookups of 100 rows of 80
 //  bytes: 59.0 us with four wavefronts each as it was before, 50.4 with two now; 272 bytes: 146 and 100).  Short lookups: by
 //  what a lookup costs beside its rows (9000 of 27 rows: 18.4 -> 12.3 us, 16384 of 10: 32 -> 10.8, 3000 of 5: 6.8 -> 3.5).
-template <int G, int BITS, int W, bool kCheck, bool kWeighted>
+template <int G, int BITS, int W, bool kPassBy, bool kCheck, bool kWeighted>
 __global__ __launch_bounds__(W * 64) void eb_group_kernel(const EbParams p) {
     constexpr int NT = W * 64;
     constexpr int CB = 16 * G;                 // code bytes per row
@@ -400,7 +400,7 @@ __global__ __launch_bounds__(W * 64) void eb_group_kernel(const EbParams p) {
             x.ok[l] = (uint64_t)ix.idx[l] < (uint64_t)p.rows;
             if (kWeighted) x.w[l] = ix.w[l];
             const v4u* rec = reinterpret_cast<const v4u*>(p.tab + (x.ok[l] ? ix.idx[l] : 0) * p.stride + pc * 16);
-            x.v[l] = W == 4 ? __builtin_nontemporal_load(rec) : *rec;
+            x.v[l] = kPassBy ? __builtin_nontemporal_load(rec) : *rec;
         }
     };
     // A row's scalars go to arrays of their own: the weighted scale and bias, and its term of Eq. 4 to a sum.  A row that is not
@@ -608,11 +608,14 @@ hipError_t launch_g(EbKernel kernel, bool check, bool weighted, const EbParams& 
     // per SIMD (measured at 16384 and 65536 lookups of 256 columns: 2 and 4 % faster than two sets;
     // everywhere else two sets are faster, by up to 30 % at 4096 lookups)
     const bool two_sets = G < 16 || p.n_bags * G < (int64_t)4096 * 64;
+    const bool pass_by = eb_passes_by(p.stride, p.rows);
 #define ABFT_EB_LAUNCH(CK, WT)                                                                                     \
     do {                                                                                                           \
-        if (kernel == kEbGroup1) eb_group_kernel<G, BITS, 1, CK, WT><<<dim3((unsigned)p.n_bags), dim3(64), 0, s>>>(p);      \
-        else if (kernel == kEbGroup2) eb_group_kernel<G, BITS, 2, CK, WT><<<dim3((unsigned)p.n_bags), dim3(128), 0, s>>>(p); \
-        else if (kernel == kEbGroup4) eb_group_kernel<G, BITS, 4, CK, WT><<<dim3((unsigned)p.n_bags), dim3(256), 0, s>>>(p); \
+        if (kernel == kEbGroup1 && pass_by) eb_group_kernel<G, BITS, 1, true, CK, WT><<<dim3((unsigned)p.n_bags), dim3(64), 0, s>>>(p);      \
+        else if (kernel == kEbGroup1) eb_group_kernel<G, BITS, 1, false, CK, WT><<<dim3((unsigned)p.n_bags), dim3(64), 0, s>>>(p);      \
+        else if (kernel == kEbGroup2 && pass_by) eb_group_kernel<G, BITS, 2, true, CK, WT><<<dim3((unsigned)p.n_bags), dim3(128), 0, s>>>(p); \
+        else if (kernel == kEbGroup2) eb_group_kernel<G, BITS, 2, false, CK, WT><<<dim3((unsigned)p.n_bags), dim3(128), 0, s>>>(p); \
+        else if (kernel == kEbGroup4) eb_group_kernel<G, BITS, 4, true, CK, WT><<<dim3((unsigned)p.n_bags), dim3(256), 0, s>>>(p); \
         else if (two_sets) eb_batch_kernel<G, BITS, CK, WT, true><<<dim3((unsigned)((p.n_bags * G + 255) / 256)), dim3(256), 0, s>>>(p); \
         else eb_batch_kernel<G, BITS, CK, WT, (G < 16)><<<dim3((unsigned)((p.n_bags * G + 255) / 256)), dim3(256), 0, s>>>(p); \
         return hipGetLastError();                                                                                  \

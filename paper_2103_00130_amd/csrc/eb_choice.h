@@ -13,6 +13,13 @@ inline int64_t eb_work_items(EbKernel kernel, int64_t n_bags, int pieces) {
 }
 constexpr int64_t kEbMaxWorkItems = 0xffffffffll;
 
+// Whether lookups of one or two wavefronts mark their loads of records as passing the caches by: tables of so many bytes that hardly a row
+// that comes back is still in the 256 MiB of the memory-side cache (us, 16384 lookups of 100 rows of 80 bytes, fresh ones at every call, marked /
+// not: tables of 320 MB 57.0 / 50.5, 1.3 GB 57.7 / 56.1, 2.6 GB 57.7 / 60.6, 5.1 GB 58.0 / 63.1; 4096 of 100 rows of 272 bytes, 0.5 GB 33.7 / 30.8,
+// 2.2 GB 34.0 / 35.0; one wavefront each, 9000 of 27 rows of 80 bytes, 2.6 GB 12.8 / 13.6).  The batch kernel's handful of rows per lookup is
+// faster without from any table (65536 of 4, 2.6 GB 18.3 / 17.4).
+inline bool eb_passes_by(int64_t stride, int64_t rows) { return (uint64_t)stride * (uint64_t)rows > (3ull << 29); }
+
 // The choice by the number of lookups and of rows per lookup on average (us, all rows 80 bytes unless said otherwise:
 // batch / 4 / 2 / 1 wavefronts).  Few lookups: the latency of one counts and four wavefronts fetch more of it at once (300 of
 // 30 rows 10.7 / 3.5 / 3.5 / 3.6; 600 of 60: 24.4 / 4.8 / 5.0 / 5.2; 10 of 100: 25.7 / 4.6 / 5.1 / 5.9), except for narrow rows

@@ -14,11 +14,13 @@ MOST = 2 ** 32 - 1      # work-items of one launch
 def rule(tmp_path_factory):
     lib = str(tmp_path_factory.mktemp("rule") / "rule.so")
     src = ('#include "eb_choice.h"\nextern "C" int pick(long long n, long long i, int p) { return abft::eb_pick_kernel(n, i, p); }\n'
-           'extern "C" long long items(int k, long long n, int p) { return abft::eb_work_items((abft::EbKernel)k, n, p); }\n')
+           'extern "C" long long items(int k, long long n, int p) { return abft::eb_work_items((abft::EbKernel)k, n, p); }\n'
+           'extern "C" int passes_by(long long stride, long long rows) { return abft::eb_passes_by(stride, rows); }\n')
     subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", f"-I{CSRC}", "-x", "c++", "-", "-o", lib],
                    input=src, text=True, check=True)
     so = ctypes.CDLL(lib)
     so.pick.argtypes, so.items.argtypes, so.items.restype = [ctypes.c_longlong] * 2 + [ctypes.c_int], [ctypes.c_int, ctypes.c_longlong, ctypes.c_int], ctypes.c_longlong
+    so.passes_by.argtypes = [ctypes.c_longlong] * 2
     return so
 
 
@@ -47,3 +49,9 @@ def test_large_batches_of_longer_lookups(rule, pieces, n, mean, batch):
                                                   (8, 1280, 60, GROUP2), (8, 1024, 110, GROUP4), (8, 1025, 110, GROUP2), (8, 1000, 30, GROUP1)])
 def test_four_wavefronts_for_long_lookups_of_wide_rows(rule, pieces, n, mean, kernel):
     assert rule.pick(n, n * mean, pieces) == kernel
+
+
+@pytest.mark.parametrize("stride,rows,by", [(80, 4_000_000, False), (80, 16_000_000, False), (80, 32_000_000, True), (272, 2_000_000, False), (272, 8_000_000, True),
+                                            (528, 2 ** 40, True), (32, 1, False)])
+def test_records_of_large_tables_pass_the_caches_by(rule, stride, rows, by):
+    assert bool(rule.passes_by(stride, rows)) == by

@@ -347,6 +347,43 @@ def test_table_beyond_4_gib(b):
     Tp.destroy()
 
 
+# (one wavefront per lookup, two of them)
+@pytest.mark.parametrize("n_bags,mean", [(1500, 20), (1100, 60)])
+@pytest.mark.parametrize("code_bytes,bits", [(32, 8), (128, 4), (256, 8), (512, 4)])
+def test_tables_whose_records_pass_the_caches_by(b, code_bytes, bits, n_bags, mean):
+    """Tables just above 1.5 GiB: the same lookups as on a small table of the pooled rows, within the round-off bound of the definition and
+    with the same bits, plain and weighted, checked and not; a planted fault and a bad index are reported."""
+    d = code_bytes * 8 // bits
+    rows = (3 << 29) // (code_bytes + 16) + 1
+    gen = torch.Generator(device="cuda").manual_seed(code_bytes)
+    T = torch.randint(0, 256, (rows, code_bytes), dtype=torch.uint8, device="cuda", generator=gen)
+    scale = torch.rand(rows, device="cuda", generator=gen) * 0.015 + 0.005
+    bias = -0.5 * torch.rand(rows, device="cuda", generator=gen)
+    Tp = b.abft_eb_pack_rowsum(T, scale, bias, b.ABFT_EB_PACK_INT4 if bits == 4 else 0)
+    torch.cuda.synchronize()
+    assert (3 << 29) < b.abft_eb_table_dims(Tp)[2] * rows < (3 << 29) + 4096
+    rng = w.rng_for(43 + mean, code_bytes)
+    indices, offsets = w.draw_bags(rng, rows, n_bags, mean, "spread")
+    indices[:20] = rows - 1 - np.arange(20)
+    uniq, inv = np.unique(indices, return_inverse=True)
+    inv = inv.astype(np.int64)
+    sel = torch.from_numpy(uniq).cuda()
+    small = T[sel].cpu().numpy(), scale[sel].cpu().numpy(), bias[sel].cpu().numpy()
+    del T
+    g = GpuTable.__new__(GpuTable)
+    g.b, g.Tp = b, Tp
+    for weights in (None, w.draw_weights(rng, indices.size)):
+        ref = eb.checked_eb(*small, inv, offsets, weights, bits=bits)
+        compare(g.run(indices, offsets, weights), ref, *small, inv, offsets, weights, bits)
+        assert same_bits(g.run(indices, offsets, weights, check=False)["R"], ref.R)
+    wrong = indices.copy()
+    wrong[int(offsets[7])] = rows
+    b.abft_eb_table_flip_bit(Tp, int(indices[0]), d - 1, 3 if bits == 4 else 7)
+    flags = g.run(wrong, offsets, weights)["flags"]
+    assert flags[0] & 1 and flags[7] & b.ABFT_EB_BAD_INDEX
+    Tp.destroy()
+
+
 @pytest.mark.parametrize("n_bags,mean", [(2 ** 25 + 3, 47), (2 ** 26 + 3, 30)])
 def test_more_lookups_than_wavefronts_in_a_launch(b, n_bags, mean):
     """So many lookups that one or two wavefronts each would be more work-items than a launch takes: the call runs all the same,
