@@ -361,7 +361,10 @@ def clock_trace(b, torch, args):
     return out
 
 
-def splitk_points(b, torch, steps, count_flag, shapes=((256, 1024, 8192), (128, 128, 16384), (256, 512, 4096))):
+WS_SCRATCH_INTS = 64 + 2 * 131072 + 1024    # ints into a workspace: counting words, words of 131072 rows and tickets; then the scratch
+
+
+def splitk_points(b, torch, steps, count_flag, shapes=((64, 64, 16384), (46, 128, 13504), (65, 64, 6144), (45, 1000, 5001), (64, 5000, 12000))):
     """Few tiles and a long K: the library splits K across workgroups when the workspace has room for the
     partial tiles; the same launch on a workspace of the row words alone runs unsplit.  Seeded draws on the device."""
     out = []
@@ -397,15 +400,16 @@ def splitk_points(b, torch, steps, count_flag, shapes=((256, 1024, 8192), (128, 
             e1.record()
             torch.cuda.synchronize()
             return e0.elapsed_time(e1) * 1e3 / n
-        out.append({"M": M, "N": N, "K": K, "split": full.numel() > rows_only.numel(),
-                    "us_checked": timed(full, True), "us_unchecked": timed(full, False),
+        us_checked = timed(full, True)
+        out.append({"M": M, "N": N, "K": K, "split": bool(full[WS_SCRATCH_INTS:].any()),   # (the parts of the slices stay behind in the scratch)
+                    "us_checked": us_checked, "us_unchecked": timed(full, False),
                     "us_checked_unsplit": timed(rows_only, True), "us_unchecked_unsplit": timed(rows_only, False)})
         Bp.destroy()
     return out
 
 
 CALIB_COPY_BYTES = 256 << 20
-GEMM_KERNEL_TAGS = ("gemm_tile_async_kernel", "gemm_smallm_kernel")
+GEMM_KERNEL_TAGS = ("gemm_tile_async_kernel", "gemm_tile_wk_kernel", "gemm_smallm_kernel")
 
 
 def pmc_child(args):
@@ -756,8 +760,9 @@ def main():
         torch.cuda.empty_cache()
         out["smallm_sweep"] = smallm_sweep(b, torch, args.steps, args.warmup, 0 if args.overwrite_count else b.ABFT_ERRCOUNT_ACCUMULATE)
         out["splitk"] = splitk_points(b, torch, args.steps, 0 if args.overwrite_count else b.ABFT_ERRCOUNT_ACCUMULATE)
-        out["splitk_note"] = ("few 32x32 tiles, long K: K split across workgroups (up to 64 tiles from 64 128-k stages on, up to eight from 24) "
-                              "against the same launch unsplit (a workspace without room for the parts)")
+        out["splitk_note"] = ("few tiles, long K: K split across workgroups (32x32 tiles: up to 64 of them from 64 stages of 128 k on, up to eight from 24, "
+                              "rows that are no whole chunks from 36; 64x64 tiles: 33 to 64 rows and a longer K yet) against the same launch on a workspace "
+                              "without room for the parts")
         out["smallm_sweep_note"] = ("M = 16, weights of growing size rotated through >= 768 MiB of packed "
                                     "copies (nothing served from cache): algorithmic bytes / time against 8 TB/s")
     if not args.no_eb:
