@@ -148,8 +148,13 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     const int NS_all = p.KB2;        // stages of 128 k-values
     // ... of this slice of them: as equal as they can be, the first split_r are one stage longer
     const int Z = kSplitK ? p.ksplit : 1, z = kSplitK ? (int)blockIdx.x / (tiles_m * tiles_n) : 0;
-    const int NS = kSplitK ? p.split_q + (z < p.split_r ? 1 : 0) : NS_all;
-    const int s_base = kSplitK ? share_begin(z, p.split_q, p.split_r) : 0;   // its first stage
+    // (Unsplit, Z is one and z zero, and NS_all / Z and z * NS are NS_all and 0.  Written as quotient and product the compiler allocates the
+    // registers of the 256x256 kernel in another way, which is the better one where it stores C alone on a grid that does not fill the
+    // chip: 2446x5760x816 29.9 us against 31.3, 3098x4848x1056 35.9 / 37.0, 3072x3072x3072 39.1 / 39.5; but 4096x4096x4096 66.9 / 65.7,
+    // 8192x4096x2048 79.5 / 78.6; Cq alone or with C the same or up to 2 % slower.)
+    constexpr bool kAsQuotient = BM == 256 && kCheck && kOut == kOutC && kBlockSums;
+    const int NS = kSplitK ? p.split_q + (z < p.split_r ? 1 : 0) : kAsQuotient ? NS_all / Z : NS_all;
+    const int s_base = kSplitK ? share_begin(z, p.split_q, p.split_r) : kAsQuotient ? z * NS : 0;   // its first stage
 
     // ---- direct global->LDS loads ---------------------------------------------------
     // One instruction moves 16 bytes per lane to LDS address m0 + lane*16.  They are issued
