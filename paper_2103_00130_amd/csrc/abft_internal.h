@@ -199,10 +199,15 @@ inline SplitKPlan splitk_plan(int M, int N, int stages, bool whole_a) {
     // eight stages in 0.4 us, 0.85 us where rows are no whole chunks, so slices of sixteen stages pay from 64 stages on, or 36 (us,
     // unsplit / split: 46x128x13504 10.6 / 8.1, 64x64x16384 11.9 / 8.2, 96x96x10000 9.0 / 7.8, 100x1000x8192 in two 8.2 / 9.5;
     // rows that are no whole chunks, 32x240x12600 11.2 / 7.7, 45x1000x5001 8.9 / 7.8, 41x1000x3071 in two slower), and where there
-    // are eight tiles at most from 24 (65x64x6144 7.0 / 6.8, 128x64x3072 5.6 / 6.4).  How the rows lie is known when the call comes;
-    // there is room in the workspace for either.
+    // are eight tiles at most from 24 (65x64x6144 7.0 / 6.8, 128x64x3072 5.6 / 6.4).  Two or three slices pay for weights that are not in the
+    // caches: unsplit, too few workgroups fetch (one weight again and again / fresh ones, unsplit and split: 32x3000x12000 13.0 20.1 / 11.2
+    // 14.9, 16x4096x16000 13.6 19.3 / 15.1 15.9, 64x1100x12000 10.1 18.0 / 9.0 11.2, 64x1500x9008 9.0 15.0 / 9.8 11.9, 256x500x12000 10.2 15.0 /
+    // 10.8 12.2, 1280x80x16176 18.1 19.2 / 15.2 15.0), not where many rows of tiles meet many columns, which are busy enough (100x1000x12000
+    // 10.2 13.5 / 13.1 13.3, 128x1000x12000 10.2 16.6 / 13.5 13.7, 33x2000x12000 10.6 14.0 / 13.4 13.5).  How the rows lie is known when the
+    // call comes; there is room in the workspace for either.
     const bool room = M <= kWsRows && tiles <= 128 && stages >= (M > 40 ? 24 : 40);
-    if (room && (whole_a ? (tiles <= 64 && stages >= 64) || (tiles <= 8 && M > 40) : stages >= 36)) {
+    if (room && (whole_a ? (tiles <= 64 && stages >= 64) || (tiles <= 8 && M > 40) || (stages >= 70 && (M <= 32 || tiles <= 96 || N <= 768))
+                         : stages >= 36)) {
         const int64_t most = (stages + 15) / 16, fit = 256 / tiles;
         pl.z = (int)(most < fit ? most : fit);
         if (pl.z > 16) pl.z = 16;
@@ -303,11 +308,11 @@ __device__ inline shift_v4i shift_down(shift_v4i v, int n) {
 // It has a batch of 2048 k of its 16 or 32 columns in flight at once; the wavefronts of gemm_tile_wk.h have 512 or 1024 k of 32 or 64
 // columns, and wait once per round for what the caches do not hold.  So the lines lie by the stages of 128 k, where the mean of three
 // states favours it: one weight again and again, eight in turn, fresh ones (us each, streaming / gemm_tile_wk.h):
-//  * whole chunks: 1x800x2048 4.2 4.3 4.2 / 4.4 4.5 5.3, 1x800x3200 5.0 5.1 5.0 / 4.8 5.0 6.1, 1x832x5312 6.0 6.2 6.0 / 5.6 6.1 7.6,
-//    4x4096x4096 5.5 6.7 6.7 / 5.7 6.3 7.7, 8x2048x4096 5.4 6.3 6.2 / 5.6 6.1 7.3, 1x3000x12000 10.0 10.6 10.6 / 9.5 13.6 13.6, 8x12000x1024 4.9
-//    5.9 6.0 / 4.9 6.1 6.9, 1x15000x3008 9.9 10.7 10.7 / 10.4 11.8 12.1; but 3x3000x9008 9.1 9.5 9.6 / 7.5 8.8 11.6, 1x800x2560 5.0 5.3 5.2 / 4.4
-//    4.7 5.9, 8x3000x6400 8.4 8.9 8.8 / 6.4 7.3 9.4, 8x800x6400 6.9 8.1 7.9 / 6.0 6.8 8.6, 16x4096x4096 6.5 7.5 7.6 / 5.7 6.3 8.0, 4x12000x1152
-//    6.2 / 5.1, 8x15000x5008 15.5 / 14.3
+//  * whole chunks: 1x800x2048 4.2 4.3 4.2 / 4.4 4.5 5.3, 1x800x3200 5.0 5.1 5.0 / 4.8 5.0 6.1, 1x832x5312 6.0 6.2 6.0 / 5.6 6.1 7.6, 4x774x5280
+//    6.0 6.4 6.2 / 5.8 6.4 7.9, 4x4096x4096 5.5 6.7 6.7 / 5.7 6.3 7.7, 8x2048x4096 5.4 6.3 6.2 / 5.6 6.1 7.3, 1x3500x12000 10.3 10.9 11.0 / 11.1
+//    12.6 12.6, 8x12000x1024 4.9 5.9 6.0 / 4.9 6.1 6.9, 1x15000x3008 9.9 10.7 10.7 / 10.4 11.8 12.1; but 8x3000x16000 14.1 14.3 14.4 / 10.2 14.3
+//    14.1, 1x800x2560 5.0 5.3 5.2 / 4.4 4.7 5.9, 8x3000x6400 8.4 8.9 8.8 / 6.4 7.3 9.4, 8x800x6400 6.9 8.1 7.9 / 6.0 6.8 8.6, 16x4096x4096 6.5
+//    7.5 7.6 / 5.7 6.3 8.0, 4x12000x1152 6.2 / 5.1, 8x15000x5008 15.5 / 14.3
 //  * 9 to 16 rows, few or middling columns: 10x464x4064 4.9 / 5.4, 1x145x6128 6.0 / 6.4, 16x4096x2048 4.8 / 5.0; but 16x1200x2048 even,
 //    13x144x11067 16.6 / 7.8
 //  * rows that are no whole chunks, which the streaming kernel loads row by row: one row 1x300x2001 4.4 / 5.0, 1x800x3201 5.6 5.8 5.8 /
@@ -324,9 +329,9 @@ inline bool few_rows_stream(int M, int N, int stages, bool whole_a) {
     if (N > 4096) return M <= 8 && N > 12288 && stages >= 24 && stages <= (M <= 4 ? 48 : 32);
     if (stages <= 8) return false;
     if (N <= 640) return stages < 64;
-    if (M == 1 && N <= 2500 && stages > 40 && stages <= 48) return true;
+    if (N <= (M == 1 ? 2500 : 1000) && M <= 4 && stages > 40 && stages <= 48) return true;
     if (N <= 1500) return M <= 8 && (stages <= 16 || (stages > 24 && stages <= 32));   // (the last batch at least half full)
-    return stages <= 20 || (M <= 8 && (stages <= 32 || (N > 2048 && stages >= 72)));
+    return stages <= 20 || (M <= 8 && (stages <= 32 || (stages >= 72 && N > (M <= 4 ? 2816 : 3264))));
 }
 
 // Which form of gemm_tile_wk.h (K split among the wavefronts of a workgroup) takes a call, if any: rows x columns of the tile, wavefronts.

@@ -75,8 +75,8 @@ def test_copy_and_parts_lie_apart(plan):
 
 
 # (shapes where the streaming kernel measured faster for weights that have not just been used, and neighbours where it did not)
-@pytest.mark.parametrize("M,N,K,streams", [(1, 800, 2048, True), (1, 800, 3200, True), (4, 4096, 4096, True), (8, 2048, 4096, True), (1, 3000, 12000, True), (8, 3000, 16384, True),
-                                           (8, 12000, 1024, True), (1, 15000, 3008, True), (16, 4096, 2048, True), (10, 464, 4064, True), (1, 800, 2560, False), (1, 832, 5312, True), (2, 832, 5312, False), (1, 832, 4400, False),
+@pytest.mark.parametrize("M,N,K,streams", [(1, 800, 2048, True), (1, 800, 3200, True), (4, 4096, 4096, True), (8, 2048, 4096, True), (1, 3000, 12000, True), (8, 3000, 16384, False), (8, 3500, 12000, True), (4, 2500, 12000, False), (4, 774, 5280, True),
+                                           (8, 12000, 1024, True), (1, 15000, 3008, True), (16, 4096, 2048, True), (10, 464, 4064, True), (1, 800, 2560, False), (1, 832, 5312, True), (2, 832, 5312, True), (2, 1200, 5312, False), (1, 832, 4400, False),
                                            (8, 3000, 6400, False), (8, 800, 6400, False), (16, 4096, 4096, False), (16, 1200, 2048, False), (4, 12000, 1152, False),
                                            (8, 15000, 3008, True), (8, 15000, 5008, False), (4, 15000, 5008, True), (8, 8192, 1001, True), (1, 4096, 9001, True), (3, 3000, 9008, False), (1, 16384, 3008, False), (24, 800, 2048, False), (8, 4096, 512, False), (1, 800, 3201, True),
                                            (1, 300, 2001, True), (1, 800, 1001, True), (4, 300, 2001, True), (1, 6001, 9001, True), (4, 800, 3201, False), (8, 3000, 2049, False),
@@ -131,3 +131,11 @@ def test_calls_of_rows_that_are_no_whole_chunks(plan):
                     copies += 1
                     assert plan.room_for_copy(M, N, K), (M, N, K)
     assert copies > 100 and left > 100
+
+
+# (slices of 32x32 tiles with rows of whole chunks; where two or three pay, and neighbours that run unsplit)
+@pytest.mark.parametrize("M,N,K,z", [(64, 64, 16384, 8), (46, 128, 13504, 7), (32, 3000, 12000, 2), (16, 2500, 9008, 3), (64, 1100, 12000, 3), (64, 1500, 9008, 2),
+                                     (256, 500, 12000, 2), (1280, 80, 16176, 2), (100, 1000, 12000, 1), (33, 2000, 12000, 1), (128, 1000, 8192, 1), (32, 3000, 8192, 1)])
+def test_split_of_the_small_tiles(plan, M, N, K, z):
+    p = plan(M, N, K, 1)
+    assert p.z == z and (z == 1 or (p.split_ints <= p.room_ints and 4 * ((M + 31) // 32) * ((N + 31) // 32) <= p.part_off - p.tickets_off))

@@ -1013,7 +1013,7 @@ def test_recompute_flagged_rows_without_a_host_round_trip(binding, gpu_util, ora
 # eleven; shapes next to them that run unsplit)
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,N,K,split", [(65, 64, 3072, True), (65, 64, 6144, True), (46, 128, 13504, True), (100, 500, 8208, True), (128, 128, 16384, True), (40, 32, 32000, True),
-                                         (45, 1000, 5001, True), (32, 240, 12600, True), (33, 4161, 7712, True), (64, 1345, 15376, True), (49, 1345, 20496, True), (130, 1640, 11600, True),
+                                         (45, 1000, 5001, True), (32, 240, 12600, True), (64, 1100, 9008, True), (20, 2500, 9104, True), (250, 500, 9008, True), (33, 4161, 7712, True), (64, 1345, 15376, True), (49, 1345, 20496, True), (130, 1640, 11600, True),
                                          (256, 512, 8192, False), (200, 300, 5120, False), (130, 70, 5264, False), (100, 1000, 8192, False)])
 def test_k_split_across_workgroups(binding, gpu_util, oracle, M, N, K, split):
     """Few tiles and a long K: the library splits K across workgroups, the slices of a tile meet through the
