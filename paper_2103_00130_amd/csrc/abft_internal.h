@@ -235,17 +235,17 @@ struct Split64Plan {
     size_t total_ints;    // tickets from kWsTicketsOff on, parts from kWsScratchOff on
 };
 inline Split64Plan split64_plan(int M, int N, int stages) {
-    Split64Plan pl;
+    Split64Plan pl = {1, ws_base_ints(M)};
+    if (M <= 32 || stages < 60) return pl;
     const int64_t tiles = ((int64_t)M + 63) / 64 * (((int64_t)N + 63) / 64);
     const int64_t t32 = ((int64_t)M + 31) / 32 * (((int64_t)N + 31) / 32);
     const bool third = tiles > 64 && tiles <= 85 && t32 > 256;   // (three slices)
     const int line = tiles <= 20 || tiles > 128 ? 1 << 30 : third ? (M > 64 ? 90 : 60) : tiles > 32 && tiles <= 64 && M > 48 ? 90 : 120;
-    pl.z = 1;
-    if (M > 32 && (M <= 64 || third) && stages >= line) {
+    if ((M <= 64 || third) && stages >= line) {
         const int most = (int)(256 / tiles), z = stages >= 160 ? 16 : 8;
         pl.z = z < most ? z : most;
     }
-    pl.total_ints = pl.z > 1 ? kWsScratchOff + (size_t)tiles * pl.z * kSplit64PartInts : ws_base_ints(M);
+    if (pl.z > 1) pl.total_ints = kWsScratchOff + (size_t)tiles * pl.z * kSplit64PartInts;
     return pl;
 }
 

@@ -265,8 +265,9 @@ int abft_gemm_u8s8s32_checked(const uint8_t* A, int64_t lda, int M, const abft_p
     };
     hipError_t e;
     const bool whole_a = p.a_vec_ok && p.K % 16 == 0;
-    const abft::RealignPlan ra = abft::realign_plan(M, Bp->N, Bp->K, p.KB2);
-    const bool can_copy = !whole_a && !mod127 && ra.copy && workspace && p.ws_ints >= ra.total_ints;
+    abft::RealignPlan ra = {};
+    if (!whole_a && !mod127) ra = abft::realign_plan(M, Bp->N, Bp->K, p.KB2);   // (short calls pay for what the host does)
+    const bool can_copy = ra.copy && workspace && p.ws_ints >= ra.total_ints;
     if (!chosen) {
         if (whole_a) {
             e = abft::launch_gemm_split64(check, want_c, want_q, p, (hipStream_t)stream);

@@ -45,7 +45,7 @@ hipError_t launch_gemm_wk(WkForm form, bool check, bool want_c, bool want_q, con
 }
 
 hipError_t launch_gemm_split64(bool check, bool want_c, bool want_q, const GemmParams& p, hipStream_t s) {
-    if (!whole_chunks(p)) return hipErrorNotSupported;
+    if (split64_plan(p.M, p.N, p.KB2).z < 2 || !whole_chunks(p)) return hipErrorNotSupported;
     return launch_gemm_tile_a64s(check, want_c, want_q, p, s);
 }
 
