@@ -15,11 +15,14 @@
 //    so that no wavefront has more than its share of it.
 //  * kSplit: K split across workgroups as well (few tiles, a long K).  Each finishing wavefront stores its rows' part of the
 //    workgroup's sums in the workspace and takes a ticket of those rows; the last one adds the others' parts and goes on.
-// Bound: launch and latency below about 6 us; with a long K the rate at which a compute unit takes stages from its L2 (55 bytes a
-// cycle, 64 at most).  Measured, this kernel against the 64x64 tiles of gemm_tile_async.h or the streaming kernel that ran before
-// (us): 64x256x512 4.9 -> 4.0, 256x512x1024 requantized 6.8 -> 4.9, 64x1024x1024 5.9 -> 4.5, 130x65x2064 8.8 -> 5.4, 500x500x2000
-// 9.1 -> 6.2, 441x479x1255 8.7 -> 5.2, 32x4096x4096 9.4 -> 6.1, 29x9088x1872 10.6 -> 6.1, 64x8192x2048 10.0 -> 8.5, 1024x1024x4096 requantized 11.8 -> 11.3.  Of 64x256x512: 0.5 until
-// the first load is out, 0.7 for its only stage, 0.4 until the sums are there, 0.6 for the arrival; an empty launch takes 1.6.
+// Bound: launch and latency below about 6 us; with a long K what a wavefront with one stage in flight gets from its L2: 1024x1024x4096 takes
+// 0.85 us for the stages of its four wavefronts, 77 KB/us a compute unit (41 to 44 bytes a cycle at the 1.75 to 1.9 GHz of a counter run),
+// six to seven tenths of what such loads reach alone; the matrix pipes are busy 0.17 of the time, the LDS 0.18, wavefronts wait 0.37.
+// Measured, this kernel against the 64x64 tiles of gemm_tile_async.h or the streaming kernel that ran before (us): 64x256x512 4.9 -> 4.0,
+// 256x512x1024 requantized 6.8 -> 4.9, 64x1024x1024 5.9 -> 4.5, 130x65x2064 8.8 -> 5.4, 500x500x2000 9.1 -> 6.2, 441x479x1255 8.7 -> 5.2,
+// 32x4096x4096 9.4 -> 6.1, 29x9088x1872 10.6 -> 6.1, 64x8192x2048 10.0 -> 8.5, 1024x1024x4096 requantized 13.1 -> 12.1 (11.6 on another
+// device).  Of 64x256x512: 0.5 until the first load is out, 0.7 for its only stage, 0.4 until the sums are there, 0.6 for the arrival; an
+// empty launch takes 1.6.
 #pragma once
 #include <type_traits>
 #include <utility>

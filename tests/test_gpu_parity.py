@@ -284,10 +284,10 @@ def test_paper_shaped_workloads_full_size(binding, gpu_util, oracle, cfg):
     assert np.array_equal(acc["flags"], want) and acc["err_count"] == 6
 
 
-@pytest.mark.parametrize("M,N,K", [(300, 520, 1536), (16, 4096, 2048), (256, 512, 8192)])
+@pytest.mark.parametrize("M,N,K", [(300, 520, 1536), (16, 4096, 2048), (256, 512, 8192), (1040, 1100, 640), (46, 128, 13504), (64, 1345, 15376), (65, 5505, 4111)])
 def test_graph_replays_match_oracle(binding, gpu_util, oracle, M, N, K):
-    """Three checked launches captured in a graph (tiled kernel with row words, streaming kernel, K split across
-    workgroups), replayed several times with eager work between the replays: every replay is compared with the
+    """Three checked launches captured in a graph (small tiles with row words, streaming kernel, 64x64 tiles, K split across
+    workgroups on both tiles, a copy with padded rows ahead), replayed several times with eager work between the replays: every replay is compared with the
     oracle, clean and with a fault planted in the weight between two replays (the graph itself is unchanged)."""
     import torch
     say(f"graph replays {M}x{N}x{K}")
@@ -1237,7 +1237,7 @@ def test_pack_of_strided_weights(binding, gpu_util, oracle, K, N, transposed):
 @pytest.mark.parametrize("M,N,K,words_only", [(1, 800, 4095, True), (32, 300, 2049, True), (40, 1000, 3071, True), (48, 4096, 2048, True), (33, 8192, 4095, False),
                                               (41, 1000, 3071, False), (64, 512, 4096, False)])
 def test_workspace_holds_what_calls_use(binding, gpu_util, M, N, K, words_only):
-    """Shapes that go to the streaming kernel are asked for the row and counting words alone, others for scratch as well; either way
+    """Shapes that neither split K nor copy A are asked for the row and counting words alone, others for scratch as well; either way
     the call runs on what was asked for and leaves the words zero."""
     A, B = operands(M, N, K, M)
     run = gpu_util.GpuRun(binding, B)
