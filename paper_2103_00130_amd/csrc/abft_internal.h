@@ -144,6 +144,7 @@ struct GemmParams {
     RequantDev rq;
     const void* inj;           // abft_inject_t[n_inj]
     int n_inj;
+    int limb_lot;              // stages whose checksum digits are staged in LDS at a time (small tiles, set by the launcher)
     int ksplit;                // K slices across workgroups (split-K kernels; 1 elsewhere)
     int split_q, split_r;      // stages of a slice; the first split_r take one more
     int32_t* ws_tickets;       // split-K: one arrival counter per tile (and finishing wavefront)

@@ -97,10 +97,18 @@ __device__ inline int32_t floor_mod127(long long v) {
 // LDS bytes of a workgroup of WGM x WGN wavefronts: the stage ring, the scratch of the epilogue, the staged
 // checksum digits (kLimbStages stages of 512 bytes)
 constexpr int kLimbStages = 32;
-template <int BM, int BN, int WGN, int kStages>
-constexpr size_t lds_bytes() {
-    return kStages * (size_t)(BM + BN) * BK + (4 * BN + WGN * BM + BM + 4) * sizeof(int32_t) + kLimbStages * 512;
+template <int BM, int BN, int WGN>
+constexpr size_t lds_bytes(int stages, int limb_stages) {
+    return stages * (size_t)(BM + BN) * BK + ((4 * BN + WGN * BM + BM + 4) * sizeof(int32_t) + 127) / 128 * 128 + (limb_stages + 1) / 2 * 1024;
 }
+// Double-buffered small tiles run as several workgroups to a compute unit, and what bounds a grid of them is what each waits for (0.5 to 1 us
+// for its first stage, 1 us for the row words to come back) times how many are under way.  So they take the LDS that their K needs and no more:
+// one stage where there is one, digits for the stages of their share, 18 or 36 KiB instead of 51 (five by registers or four to a compute unit, not
+// three); no stage is loaded that does not exist (one of 128 k fetched three); the loads of a stage go out as soon as its slot is free; and nobody
+// waits for his last stores.  Us, before / after: 797x4896x208 C and Cq 13.4 / 11.6, 2237x1797x3120 39.0 / 32.3, 3367x4396x112 Cq 23.9 / 20.5,
+// 1092x10212x223 Cq 21.2 / 18.8, 3319x433x129 Cq 8.0 / 6.8, 918x2560x608 8.3 / 8.1; 1457x672x160, which fits the chip either way, 6.3 / 6.4.
+template <int BM, int BN, int WGM, int WGN, int kStages, bool kSplitK>
+constexpr bool lean() { return BM / WGM * (BN / WGN) <= 4096 && kStages == 2 && !kSplitK; }
 
 // kSplitK: K split across workgroups.  p.ksplit workgroups per tile take consecutive runs of stages; each stores its partial tile
 // (accumulators, column sums, and its share of the checksum product for the tile's rows) in the workspace and takes a ticket on the
@@ -120,10 +128,16 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     constexpr int B_LD = (BN / 8) / NW;            // async B loads per wave per stage (1 KiB each)
     constexpr int CB = (WTM / 16) / WGN;           // 16-row checksum blocks per wave
     constexpr bool kWantC = (kOut & kOutC) != 0, kWantQ = (kOut & kOutQ) != 0;
+    constexpr bool kLean = lean<BM, BN, WGM, WGN, kStages, kSplitK>();
+    // LDS offsets of the stages' parts
+    constexpr int A_STRIDE = kLean ? A_STAGE + B_STAGE : A_STAGE, B_STRIDE = kLean ? A_STAGE + B_STAGE : B_STAGE;
+    constexpr int SCRATCH = (4 * BN + WGN * BM + BM + 4) * (int)sizeof(int32_t);   // of the epilogue
+    constexpr int A_FIRST = kLean ? (SCRATCH + 127) / 128 * 128 : 0, B_FIRST = A_FIRST + (kLean ? A_STAGE : S * A_STAGE);
     static_assert(A_LD >= 1 && B_LD >= 1 && CB >= 1 && (WTM / 16) % WGN == 0, "tile too small for the workgroup");
     static_assert(BN >= 64 && NT <= 4 * BN, "epilogue scratch layout");
 
-    // LDS: [S][A_STAGE] then [S][B_STAGE], then the scratch of the epilogue, then the digits
+    // LDS: [S][A_STAGE] then [S][B_STAGE], then the scratch of the epilogue, then the digits; lean: the scratch, then as many
+    // [A_STAGE][B_STAGE] as there are stages, two at most, then the digits
     extern __shared__ __align__(1024) uint8_t smem[];
     const uint32_t lds_base = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) uint8_t*)smem);
 
@@ -183,7 +197,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
             const uint32_t rowoff = (uint32_t)min(row0 + r, p.M - 1) * (uint32_t)p.lda;
             a_voff[i] = rowoff + (uint32_t)c16;
             a_voff_last[i] = rowoff + (uint32_t)(z == Z - 1 ? min(c16, c16_max) : c16);   // only the last slice meets K's end
-            a_lds[i] = lds_base + (wave * A_LD + i) * 1024;
+            a_lds[i] = lds_base + A_FIRST + (wave * A_LD + i) * 1024;
         }
     }
     constexpr int TILES_PER_NT = kTileN / BN;
@@ -199,7 +213,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
         const int bc0 = wave * B_LD, kbl = bc0 / B_CHUNKS_PER_KB, cc0 = bc0 % B_CHUNKS_PER_KB;
         b_wave = p.packed + packed_unit_offset(tile_n / TILES_PER_NT, 0, (tile_n % TILES_PER_NT) * (BN / 32), p.KB2 * 2) +
                  (int64_t)kbl * B_KB_STRIDE + cc0 * 1024 + (int64_t)s_base * (2 * B_KB_STRIDE);
-        b_lds = lds_base + S * A_STAGE + kbl * (BN * 64) + cc0 * 1024;
+        b_lds = lds_base + B_FIRST + kbl * (BN * 64) + cc0 * 1024;
     }
 
     // load n of stage s into buffer buf: n < A_LD is an A load (8 rows x 128 B), the rest are
@@ -208,11 +222,11 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     auto issue_load = [&](int s, int buf, int n) __attribute__((always_inline)) {
         if (n < A_LD) {
             const uint32_t voff = (s == NS - 1) ? a_voff_last[n] : a_voff[n];
-            dma(a_lds[n] + buf * A_STAGE, voff, p.A + (int64_t)(s_base + s) * BK, std::integral_constant<int, 0>{});
+            dma(a_lds[n] + buf * A_STRIDE, voff, p.A + (int64_t)(s_base + s) * BK, std::integral_constant<int, 0>{});
         } else {
             const int j = n - A_LD, g = j >> 2;
             const int8_t* const base = b_wave + (int64_t)s * (2 * B_KB_STRIDE) + g * 4096;
-            const uint32_t l = b_lds + buf * B_STAGE + g * 4096;
+            const uint32_t l = b_lds + buf * B_STRIDE + g * 4096;
             switch (j & 3) {
                 case 0: dma(l, b_voff, base, std::integral_constant<int, 0>{}); break;
                 case 1: dma(l, b_voff, base, std::integral_constant<int, 1024>{}); break;
@@ -255,8 +269,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     const int a_swz = (lane >> 1) & 7;
     int a_off[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) a_off[j] = (wm * WTM + (lane & 31)) * BK + (((2 * j + (lane >> 5)) ^ a_swz) << 4);
-    const int b_off = S * A_STAGE + wn * TN * 2048 + lane * 16;
+    for (int j = 0; j < 4; ++j) a_off[j] = A_FIRST + (wm * WTM + (lane & 31)) * BK + (((2 * j + (lane >> 5)) ^ a_swz) << 4);
+    const int b_off = B_FIRST + wn * TN * 2048 + lane * 16;
 
     v16i acc[TM][TN];
 #pragma unroll
@@ -293,10 +307,10 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
                 const v4i m = shift_down(v, over);
                 v = end_chunk ? m : v;
             }
-            *reinterpret_cast<v4i*>(smem + buf * A_STAGE + r * BK + ((lane & 7) ^ ((r >> 1) & 7)) * 16) = v;
+            *reinterpret_cast<v4i*>(smem + A_FIRST + buf * A_STRIDE + r * BK + ((lane & 7) ^ ((r >> 1) & 7)) * 16) = v;
         }
 #pragma unroll
-        for (int j = 0; j < B_LD; ++j) *reinterpret_cast<v4i*>(smem + (b_lds - lds_base) + buf * B_STAGE + j * 1024 + b_voff) = rb[j];
+        for (int j = 0; j < B_LD; ++j) *reinterpret_cast<v4i*>(smem + (b_lds - lds_base) + buf * B_STRIDE + j * 1024 + b_voff) = rb[j];
     };
 
 
@@ -308,8 +322,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     constexpr int NSETS = kAhead2 ? 4 : 2;
     v4i fa[NSETS][TM], fb[NSETS][TN];
     auto read_frags = [&](int buf, int j, int f) __attribute__((always_inline)) {
-        const uint8_t* sA = smem + buf * A_STAGE;
-        const uint8_t* sB = smem + buf * B_STAGE;
+        const uint8_t* sA = smem + buf * A_STRIDE;
+        const uint8_t* sB = smem + buf * B_STRIDE;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
             fa[f][i] = *reinterpret_cast<const v4i*>(sA + a_off[j] + i * 32 * BK);
@@ -337,7 +351,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     }
     const int ck_lo = kCheck ? share_begin(tile_n, share_q, share_r) : 0;
     const int ck_hi = kCheck ? share_begin(tile_n + 1, share_q, share_r) : 0;
-    uint8_t* const s_limb = smem + S * (A_STAGE + B_STAGE) + (4 * BN + WGN * BM + BM + 4) * sizeof(int32_t);
+    // stages resident, and stages of digits staged at a time
+    const int ring = kLean ? min(S, NS) : S, limb_lot = kLean ? p.limb_lot : kLimbStages;
+    uint8_t* const s_limb = smem + (kLean ? A_FIRST : SCRATCH) + ring * (A_STAGE + B_STAGE);
     // sum_k S_B[k], which the first tile column needs at the very end (the u8 -> s8 shift of A moves every
     // checksum product by 128 times it): fetched now, so that the epilogue does not wait for memory
     int32_t total_sb = (kCheck && tile_n == 0) ? *p.total : 0;
@@ -355,9 +371,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     // registers, and no wait that the compiler would place - it does not see the direct loads and would
     // wait for every one of them.  A lot that ends in half an instruction re-reads its last chunk into
     // LDS words behind the lot, which nobody reads.)
-    const uint32_t lds_limb = lds_base + (uint32_t)(S * (A_STAGE + B_STAGE) + (4 * BN + WGN * BM + BM + 4) * sizeof(int32_t));
+    const uint32_t lds_limb = lds_base + (uint32_t)((kLean ? A_FIRST : SCRATCH) + ring * (A_STAGE + B_STAGE));
     auto stage_limbs = [&](int s0) __attribute__((always_inline)) {
-        const int n = min(ck_hi - s0, kLimbStages);
+        const int n = min(ck_hi - s0, limb_lot);
         const int8_t* const src = p.limbs + (int64_t)(s_base + s0) * 512;
         for (int i = wave; i * 2 < n; i += NW)
             dma(lds_limb + i * 1024, (uint32_t)min(i * 1024 + lane * 16, n * 512 - 16), src, std::integral_constant<int, 0>{});
@@ -383,7 +399,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     int ck_off[2];
 #pragma unroll
     for (int kbl = 0; kbl < 2; ++kbl)
-        ck_off[kbl] = (wm * WTM + wn * CB * 16 + (lane & 15)) * BK + (((4 * kbl + (lane >> 4)) ^ a_swz) << 4);
+        ck_off[kbl] = A_FIRST + (wm * WTM + wn * CB * 16 + (lane & 15)) * BK + (((4 * kbl + (lane >> 4)) ^ a_swz) << 4);
     auto wait_lds = []() __attribute__((always_inline)) { __builtin_amdgcn_s_waitcnt(0xC07F); };
     auto wait_vmem = []() __attribute__((always_inline)) { __builtin_amdgcn_s_waitcnt(0x0F70); };
     // at most n LDS operations still in flight (they complete in order)
@@ -417,8 +433,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
         constexpr bool SUM_B = decltype(sum_b_c)::value;
         constexpr int Q = TM * TN, NR = Q / 2, R = TM + TN, RR = NR >= 2 ? NR / 2 : 1, D = 4 * TN;
         static_assert(TN % 2 == 0, "regions pair the MFMAs of one row of blocks");
-        const uint8_t* const sA = smem + rbuf * A_STAGE + a_off[jn];
-        const uint8_t* const sB = smem + rbuf * B_STAGE + (jn >> 1) * (BN * 64) + b_off + (jn & 1) * 1024;
+        const uint8_t* const sA = smem + rbuf * A_STRIDE + a_off[jn];
+        const uint8_t* const sB = smem + rbuf * B_STRIDE + (jn >> 1) * (BN * 64) + b_off + (jn & 1) * 1024;
         v4i a_cur = fa[f][0] ^ (int)0x80808080, a_nxt = a_cur;
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
@@ -451,8 +467,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     auto phase_small = [&](int f, int fr, int rbuf, int jn, auto sum_b_c, int ld_s, int ld_buf, int ld_lo, int ld_hi)
                            __attribute__((always_inline)) {
         constexpr bool SUM_B = decltype(sum_b_c)::value;
-        const uint8_t* const sA = smem + rbuf * A_STAGE + a_off[jn];
-        const uint8_t* const sB = smem + rbuf * B_STAGE + (jn >> 1) * (BN * 64) + b_off + (jn & 1) * 1024;
+        const uint8_t* const sA = smem + rbuf * A_STRIDE + a_off[jn];
+        const uint8_t* const sB = smem + rbuf * B_STRIDE + (jn >> 1) * (BN * 64) + b_off + (jn & 1) * 1024;
 #pragma unroll
         for (int x = 0; x < TM; ++x) fa[fr][x] = *reinterpret_cast<const v4i*>(sA + x * 32 * BK);
 #pragma unroll
@@ -500,18 +516,20 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
         // (loads return in order: a wavefront that has its first stage has its share of the digits too)
         if (kCheck && ck_hi > ck_lo) stage_limbs(ck_lo);
 #pragma unroll
-        for (int st = 0; st < P; ++st) reg_load(min(st, NS - 1), ra[st], rb[st]);
+        for (int st = 0; st < P; ++st)
+            if (!kLean || st < NS) reg_load(min(st, NS - 1), ra[st], rb[st]);
 #pragma unroll
         for (int st = 0; st < S; ++st) {
+            if (kLean && st >= NS) break;
             reg_store(st, st, ra[st % P], rb[st % P]);
-            reg_load(min(st + P, NS - 1), ra[st % P], rb[st % P]);
+            if (!kLean || st + P < NS) reg_load(min(st + P, NS - 1), ra[st % P], rb[st % P]);
         }
         if (p.K < 16 && (lane & 7) == 0) {
             // rows shorter than a chunk: the first chunk of the one stage, byte by byte
             for (int i = 0; i < A_LD; ++i) {
                 const int r = (wave * A_LD + i) * 8 + (lane >> 3);
                 const uint8_t* const src = p.A + (int64_t)min(row0 + r, p.M - 1) * p.lda;
-                uint8_t* const dst = smem + r * BK + ((r >> 1) & 7) * 16;
+                uint8_t* const dst = smem + A_FIRST + r * BK + ((r >> 1) & 7) * 16;
                 for (int b = 0; b < p.K; ++b) dst[b] = src[b];
             }
         }
@@ -524,10 +542,13 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     } else if constexpr (kAhead2) {
         if (kCheck && ck_hi > ck_lo) stage_limbs(ck_lo);
 #pragma unroll
-        for (int st = 0; st < S; ++st)
+        for (int st = 0; st < S; ++st) {
+            if (kLean && st >= NS) break;
 #pragma unroll
             for (int n = 0; n < N_LD; ++n) issue_load(min(st, NS - 1), st, n);
-        wait_vmem_but(std::integral_constant<int, (S - 1) * N_LD>{});
+        }
+        if (kLean && NS == 1) wait_vmem();
+        else wait_vmem_but(std::integral_constant<int, (S - 1) * N_LD>{});
         __syncthreads();
         read_frags(0, 0, 0);
         read_frags(0, 1, 1);
@@ -572,7 +593,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
         // checksum-digit columns for this wave's share of the rows (16-row blocks wn*CB ..) over both
         // k-blocks of the stage in slot `buf`; the A operands are re-read from the resident stage
         auto digit_block = [&](int buf) __attribute__((always_inline)) {
-            const uint8_t* sA = smem + buf * A_STAGE;
+            const uint8_t* sA = smem + buf * A_STRIDE;
 #pragma unroll
             for (int kbl = 0; kbl < 2; ++kbl) {
                 v4i av[CB];
@@ -590,7 +611,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
         // digit MFMAs follow the wait that those need anyway.
         v4i dig_a[2][CB];
         auto digit_reads = [&](int buf) __attribute__((always_inline)) {
-            const uint8_t* sA = smem + buf * A_STAGE;
+            const uint8_t* sA = smem + buf * A_STRIDE;
 #pragma unroll
             for (int kbl = 0; kbl < 2; ++kbl)
 #pragma unroll
@@ -606,7 +627,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
         };
         if constexpr (kAhead2) {
             for (int s = s_begin; s < s_end; ++s) {
-                const int nxt = cur + 1 == S ? 0 : cur + 1;
+                const int nxt = cur + 1 == ring ? 0 : cur + 1;
                 const int s_new = min(s + S, NS - 1);  // refills the slot of this stage once it is released
                 // the digit operands of this stage (it is resident) are read ahead of the fragments of its
                 // first k-step and are there, reads completing in order, when the wait behind that k-step ends:
@@ -625,10 +646,15 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
                 wait_vmem_but(pending_c{});
                 __syncthreads();
                 __builtin_amdgcn_sched_barrier(0);
-                phase_small(2, 0, nxt, 0, even_c{}, s_new, cur, 0, N_LD / 2);
+                if (kLean && s + S < NS) {   // (at once: 3466x276x13984 60.5 us with half of them behind either k-step, 55.5 this way)
+#pragma unroll
+                    for (int n = 0; n < N_LD; ++n) issue_load(s_new, cur, n);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                phase_small(2, 0, nxt, 0, even_c{}, s_new, cur, 0, kLean ? 0 : N_LD / 2);
                 wait_lds_but(frag_reads_c{});
                 __builtin_amdgcn_sched_barrier(0);
-                phase_small(3, 1, nxt, 1, odd_c{}, s_new, cur, N_LD / 2, N_LD);
+                phase_small(3, 1, nxt, 1, odd_c{}, s_new, cur, kLean ? N_LD : N_LD / 2, N_LD);
                 wait_lds_but(frag_reads_c{});
                 __builtin_amdgcn_sched_barrier(0);
                 cur = nxt;
@@ -667,7 +693,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     auto run_all = [&](auto ph_c) __attribute__((always_inline)) {
         if (kCheck) {
             run(0, ck_lo, std::false_type{}, ph_c);
-            for (int c0 = ck_lo; c0 < ck_hi; c0 += kLimbStages) {
+            for (int c0 = ck_lo; c0 < ck_hi; c0 += limb_lot) {
                 if (c0 > ck_lo) {
                     // every wave has left the stages that read the previous lot (their digits were in
                     // registers before the barrier that ended the last of them)
@@ -675,7 +701,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
                     wait_vmem();
                     __syncthreads();
                 }
-                run(c0, min(c0 + kLimbStages, ck_hi), std::true_type{}, ph_c);
+                run(c0, min(c0 + limb_lot, ck_hi), std::true_type{}, ph_c);
             }
             run(ck_hi, NS, std::false_type{}, ph_c);
         } else {
@@ -693,10 +719,10 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
             for (int u = 0; u < P; ++u) {
                 const int s = s0 + u;
                 if (s >= NS) break;
-                const int buf = u & 1, nxt = buf ^ 1;
+                const int buf = u & 1, nxt = kLean && ring == 1 ? buf : buf ^ 1;
                 phase_small(0, 2, buf, 2, std::false_type{}, 0, 0, 0, 0);
                 if (kCheck && s >= ck_lo && s < ck_hi) {
-                    if (s - limb_base == kLimbStages) {
+                    if (s - limb_base == limb_lot) {
                         // a further lot of digits (every wave has its last use of the previous lot behind it)
                         __syncthreads();
                         stage_limbs(s);
@@ -704,7 +730,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
                         __syncthreads();
                     }
                     load_limbs(s);
-                    const uint8_t* const sA = smem + buf * A_STAGE;
+                    const uint8_t* const sA = smem + buf * A_STRIDE;
 #pragma unroll
                     for (int kbl = 0; kbl < 2; ++kbl)
 #pragma unroll
@@ -716,8 +742,10 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
                 wait_lds();   // every fragment of this stage is in registers, and what this wave wrote of the next one is in LDS
                 __syncthreads();
                 __builtin_amdgcn_sched_barrier(0);
-                reg_store(s + 2, buf, ra[(u + 2) % P], rb[(u + 2) % P]);
-                reg_load(min(s + 2 + P, NS - 1), ra[(u + 2) % P], rb[(u + 2) % P]);
+                if (!kLean || s + 2 < NS) {
+                    reg_store(s + 2, buf, ra[(u + 2) % P], rb[(u + 2) % P]);
+                    if (!kLean || s + 2 + P < NS) reg_load(min(s + 2 + P, NS - 1), ra[(u + 2) % P], rb[(u + 2) % P]);
+                }
                 phase_small(2, 0, nxt, 0, std::false_type{}, 0, 0, 0, 0);
                 phase_small(3, 1, nxt, 1, std::false_type{}, 0, 0, 0, 0);
             }
@@ -742,7 +770,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
 #endif
     // LDS scratch behind the stage buffers: [4][BN] column sums, [WGN][BM] row-sum parts,
     // [BM] checksum parts, 4 control words
-    int32_t* const s_bs = reinterpret_cast<int32_t*>(smem + S * (A_STAGE + B_STAGE));
+    int32_t* const s_bs = reinterpret_cast<int32_t*>(smem + (kLean ? 0 : S * (A_STAGE + B_STAGE)));
     int32_t* const s_rs = s_bs + 4 * BN;
     int32_t* const s_ck = s_rs + WGN * BM;
     // Checksum shares of the rows from the digit products: 16x16 accumulator, lane l, element e is row 4*(l/16) + e, column l%16;
@@ -1094,7 +1122,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
         }
     }
     // direct-to-LDS loads that are still in flight must not outlive the workgroup's LDS
-    wait_vmem();
+    if (!kLean) wait_vmem();
 #ifdef ABFT_CLOCK_TRACE
     if (p.clock_trace && threadIdx.x == 0) {
         unsigned long long* const o = p.clock_trace + (size_t)blockIdx.x * 6;
@@ -1123,7 +1151,11 @@ hipError_t launch_cfg(bool check, bool want_c, bool want_q, const GemmParams& p_
     p.share_q = shortest / tiles_n;   // ... and, of those, of the checksum product per tile column
     p.share_r = shortest % tiles_n;
     const dim3 grid((unsigned)(tiles_m * tiles_n * (kSplitK ? p.ksplit : 1))), block(WGM * WGN * 64);
-    const size_t lds = (lds_bytes<BM, BN, WGN, kStages>() + 1023) / 1024 * 1024;
+    constexpr bool kLean = lean<BM, BN, WGM, WGN, kStages, kSplitK>();
+    const int most_digits = p.share_q + (p.share_r > 0 ? 1 : 0);
+    p.limb_lot = kLean && most_digits < kLimbStages ? (check ? most_digits : 0) : kLimbStages;
+    const size_t lds_most = (lds_bytes<BM, BN, WGN>(kStages, kLimbStages) + 1023) / 1024 * 1024;
+    const size_t lds = kLean ? (lds_bytes<BM, BN, WGN>(p.KB2 < kStages ? p.KB2 : kStages, p.limb_lot) + 1023) / 1024 * 1024 : lds_most;
     // Row sums in block form or per row.  Small wave tiles: always the block form, which halves the
     // vector work of an epilogue that is short anyway.  The 128x128 wave tile: per row when the grid
     // fills the chip - the stores then take the time memory needs and the arithmetic between them is
@@ -1143,7 +1175,7 @@ hipError_t launch_cfg(bool check, bool want_c, bool want_q, const GemmParams& p_
     do {                                                                                                  \
         auto kern = gemm_tile_async_kernel<BM, BN, WGM, WGN, kStages, CK, OUT, ((BS) || !(CK)), kAnyA, kSplitK>; \
         static std::atomic<uint64_t> lds_allowed{0};                                                      \
-        const hipError_t e_attr = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed);\
+        const hipError_t e_attr = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds_most, lds_allowed);\
         if (e_attr != hipSuccess) return e_attr;                                                          \
         kern<<<grid, block, lds, s>>>(p, tiles_m, tiles_n);                                               \
         return hipGetLastError();                                                                         \

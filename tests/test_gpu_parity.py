@@ -1477,3 +1477,12 @@ def test_k_split_among_wavefronts(binding, gpu_util, oracle, M, N, K):
         out = run.gemm(A, injections=inj, mod127=True)
         assert np.array_equal(out["C"], C127) and np.array_equal(out["flags"], flags127) and out["err_count"] == count127
     assert not run.gemm(A)["flags"].any()
+
+
+# (64x64 tiles on grids beyond the chip, with one, two and more stages than the two that LDS holds, rows of whole chunks, of any length
+# and shorter than a chunk)
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(1100, 1030, 16), (1100, 1030, 128), (1025, 1100, 144), (1100, 1030, 256), (1090, 1030, 272), (1100, 1030, 640), (2100, 1030, 100),
+                                   (2100, 1030, 131), (2100, 1030, 300), (2100, 1030, 401), (2100, 1030, 13), (8200, 130, 384)])
+def test_64x64_tiles_of_few_stages(binding, gpu_util, oracle, M, N, K):
+    test_k_split_among_wavefronts(binding, gpu_util, oracle, M, N, K)
