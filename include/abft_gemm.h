@@ -19,7 +19,7 @@
  *     elements.  `stream` is a hipStream_t passed as void* (NULL = default
  *     stream).  Calls enqueue work on `stream` and return; they never
  *     synchronise.  Only abft_pack_b_checksum / abft_packed_b_destroy
- *     allocate or free device memory.  A packed B belongs to the device that
+ *     allocate or free device memory and may wait for the device.  A packed B belongs to the device that
  *     was current when it was packed; the checked GEMM returns ABFT_EINVAL
  *     when called with another device current.
  *   - Return value: ABFT_OK, or a negative code for a usage or runtime error;
@@ -114,8 +114,10 @@ int abft_packed_b_flip_checksum_bit(abft_packed_b* Bp, int k, int bit, void* str
  * (sign-extended when bit 7 was inverted). */
 int abft_packed_b_flip_checksum_bit_mod127(abft_packed_b* Bp, int k, int bit, void* stream);
 
-/* Host call.  Frees the handle; the caller has synchronised every stream that
- * used it. */
+/* Host call.  Frees the handle; nothing that uses it may be enqueued (or
+ * replayed) afterwards.  What was enqueued before need not have ended: the
+ * memory (up to 256 MiB a device is kept for weights to come, until the last
+ * one is destroyed) is used again, or given back, after a wait for the device. */
 void abft_packed_b_destroy(abft_packed_b* Bp);
 
 /* Requantization parameters (Section III-B; Eq. 1 with beta_B = 0):

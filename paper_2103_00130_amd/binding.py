@@ -153,8 +153,7 @@ class PackedB:
 
     def destroy(self):
         if self.handle:
-            torch.cuda.synchronize()
-            lib.abft_packed_b_destroy(self.handle)
+            lib.abft_packed_b_destroy(self.handle)   # (work that still reads the weight is waited for before its memory is used again)
             self.handle = None
 
     def __del__(self):

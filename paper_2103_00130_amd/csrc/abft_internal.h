@@ -47,6 +47,7 @@ struct abft_packed_b {
     int KB;            // k-blocks of 64, rounded up to an even count (zero padded)
     int NT;            // n-tiles of 256
     int device;
+    size_t block_bytes;   // of the block that holds everything below
     int8_t* packed;    // NT*KB*8 units
     int8_t* limbs;     // KB*64*4 bytes
     int32_t* S_B;      // [KB*64], zero past K

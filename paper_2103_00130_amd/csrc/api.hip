@@ -4,6 +4,7 @@
 #include <cstdio>
 #include <atomic>
 #include <cstring>
+#include <mutex>
 #include <new>
 
 #include "../../include/abft_gemm.h"
@@ -34,9 +35,140 @@ int hip_fail(hipError_t e, const char* what) {
         if (e_ != hipSuccess) return hip_fail(e_, #expr);  \
     } while (0)
 
+// Blocks of destroyed weights, kept for weights to come.  A program that replaces weights while it runs pays more for hipMalloc and
+// hipFree of their blocks, and for the wait for the whole device that goes with them, than for encoding and packing them (4096x4096, us a
+// replacement with its first batch of 64 rows: 86, kept blocks BBB; 900x700 45 / CCC).
+//  * A freed block may still be read by work that was enqueued before.  It is used again only after a wait for the whole device, once
+//    for all blocks freed until then.  The wait is a hipFree of a few bytes, which waits for every stream of the device (documented, and
+//    measured on blocking, non-blocking and null streams) and, unlike hipDeviceSynchronize, leaves graphs alone that another thread
+//    captures - what hipFree of the block itself would do.
+//  * At most kMost blocks and kMostBytes a device; what does not fit is freed at once.  All are given back when the last weight on
+//    the device is destroyed, and when the device has no memory for a new one.
+class KeptBlocks {
+public:
+    // a block of at least `need` bytes on the current device `dev`; *size: its real size
+    hipError_t get(int dev, size_t need, void** out, size_t* size) {
+        hipError_t e = hipSuccess;
+        *out = nullptr;
+        if (Device* const d = of(dev)) {
+            bool found = take(*d, need, out, size);
+            if (!found && worth_a_wait(*d, need) && wait_for_device(*d)) found = take(*d, need, out, size);
+            if (!found) {
+                e = hipMalloc(out, *size = need);
+                if (e == hipErrorOutOfMemory && give_back(*d)) {
+                    (void)hipGetLastError();
+                    e = hipMalloc(out, need);
+                }
+            }
+            if (e == hipSuccess) {
+                std::lock_guard<std::mutex> lock(d->mutex);
+                ++d->live;
+            }
+            return e;
+        }
+        return hipMalloc(out, *size = need);
+    }
+    void put(int dev, void* block, size_t size) {
+        Device* const d = of(dev);
+        if (!d) {
+            (void)hipFree(block);
+            return;
+        }
+        bool last, kept = false;
+        {
+            std::lock_guard<std::mutex> lock(d->mutex);
+            last = --d->live == 0;
+            if (!last && d->n < kMost && size <= kMostBytes - d->bytes) {
+                d->blocks[d->n++] = {block, size, ++d->released, false};
+                d->bytes += size;
+                kept = true;
+            }
+        }
+        if (last) (void)give_back(*d);
+        if (!kept) (void)hipFree(block);
+    }
+
+private:
+    static constexpr int kMost = 4, kDevices = 64;
+    static constexpr size_t kMostBytes = 256u << 20;
+    struct Block {
+        void* at;
+        size_t size;
+        unsigned long long number;   // of its release
+        bool idle;                   // a wait for the device lies behind that
+    };
+    struct Device {
+        std::mutex mutex;
+        Block blocks[kMost];
+        int n = 0;
+        size_t bytes = 0;
+        unsigned long long released = 0;
+        long long live = 0;   // blocks in use
+    };
+    Device devices_[kDevices];
+
+    Device* of(int dev) { return dev >= 0 && dev < kDevices ? &devices_[dev] : nullptr; }
+    static bool fits(const Block& b, size_t need) { return b.size >= need && b.size - need <= need / 4; }
+    static void drop(Device& d, int i) {
+        d.bytes -= d.blocks[i].size;
+        d.blocks[i] = d.blocks[--d.n];
+    }
+    static bool take(Device& d, size_t need, void** out, size_t* size) {
+        std::lock_guard<std::mutex> lock(d.mutex);
+        for (int i = 0; i < d.n; ++i)
+            if (d.blocks[i].idle && fits(d.blocks[i], need)) {
+                *out = d.blocks[i].at;
+                *size = d.blocks[i].size;
+                drop(d, i);
+                return true;
+            }
+        return false;
+    }
+    // (while there is room for a further block, another one is allocated instead: a wait for four of them costs as much as for one)
+    static bool worth_a_wait(Device& d, size_t need) {
+        std::lock_guard<std::mutex> lock(d.mutex);
+        if (d.n < kMost && need <= kMostBytes - d.bytes) return false;
+        for (int i = 0; i < d.n; ++i)
+            if (!d.blocks[i].idle && fits(d.blocks[i], need)) return true;
+        return false;
+    }
+    static bool wait_for_device(Device& d) {
+        unsigned long long until;   // (blocks that other threads release during the wait are not covered)
+        {
+            std::lock_guard<std::mutex> lock(d.mutex);
+            until = d.released;
+        }
+        void* p = nullptr;
+        if (hipMalloc(&p, 256) != hipSuccess || hipFree(p) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        std::lock_guard<std::mutex> lock(d.mutex);
+        for (int i = 0; i < d.n; ++i) d.blocks[i].idle |= d.blocks[i].number <= until;
+        return true;
+    }
+    static bool give_back(Device& d) {
+        Block blocks[kMost];
+        int n;
+        {
+            std::lock_guard<std::mutex> lock(d.mutex);
+            n = d.n;
+            for (int i = 0; i < n; ++i) blocks[i] = d.blocks[i];
+            d.n = 0;
+            d.bytes = 0;
+        }
+        for (int i = 0; i < n; ++i) (void)hipFree(blocks[i].at);
+        return n > 0;
+    }
+};
+KeptBlocks& kept_blocks() {
+    static KeptBlocks* const k = new KeptBlocks;   // (lives as long as the process: weights may be destroyed at its very end)
+    return *k;
+}
+
 void free_handle(abft_packed_b* h) {
     if (!h) return;
-    (void)hipFree(h->packed);   // (one block holds everything)
+    if (h->packed) kept_blocks().put(h->device, h->packed, h->block_bytes);   // (one block holds everything)
     delete h;
 }
 
@@ -79,7 +211,11 @@ int abft_pack_b_checksum(const int8_t* B, int64_t ldb, int K, int N, int b_is_tr
     const size_t digits = (size_t)h->KB * abft::kUnitK * abft::kLimbs, n_ints = (size_t)h->NT * abft::kTileN * sizeof(int32_t);
     const size_t o_limbs = up(units), o_limbs127 = o_limbs + up(digits), o_sb = o_limbs127 + up(digits), o_colsum = o_sb + up(k_ints);
     const size_t o_total = o_colsum + up(n_ints), o_sb127 = o_total + 256;
-    if (e == hipSuccess) e = hipMalloc(&h->packed, o_sb127 + k_ints);
+    if (e == hipSuccess) {
+        void* block = nullptr;
+        e = kept_blocks().get(h->device, o_sb127 + k_ints, &block, &h->block_bytes);
+        h->packed = (int8_t*)block;
+    }
     if (e == hipSuccess) {
         h->limbs = h->packed + o_limbs;
         h->limbs127 = h->packed + o_limbs127;

@@ -1486,3 +1486,62 @@ def test_k_split_among_wavefronts(binding, gpu_util, oracle, M, N, K):
                                    (2100, 1030, 131), (2100, 1030, 300), (2100, 1030, 401), (2100, 1030, 13), (8200, 130, 384)])
 def test_64x64_tiles_of_few_stages(binding, gpu_util, oracle, M, N, K):
     test_k_split_among_wavefronts(binding, gpu_util, oracle, M, N, K)
+
+
+@pytest.mark.gpu
+def test_weights_replaced_while_others_are_in_use(binding, gpu_util, oracle):
+    """Blocks of destroyed weights serve later ones: never while work enqueued before still reads them, on whatever stream, from several
+    threads at once, blocks of other sizes among them; all memory is given back with the last weight."""
+    import threading
+
+    import torch
+
+    say("weights replaced while others are in use")
+    M, N, K = 40, 700, 1500
+    rng = np.random.default_rng(5)
+    A = rng.integers(0, 256, size=(M, K), dtype=np.uint8)
+    weights = [rng.integers(-127, 128, size=(K, N), dtype=np.int8) for _ in range(6)]
+    wants = [torch.from_numpy(oracle.checked_gemm(A, B).C).cuda() for B in weights]
+    A_dev, B_dev = gpu_util.dev(A), [gpu_util.dev(B) for B in weights]
+    torch.cuda.synchronize()
+    free0 = torch.cuda.mem_get_info()[0]
+    failed = []
+
+    def work(first):
+        try:
+            stream, side = torch.cuda.Stream(), torch.cuda.Stream()
+            done = []
+            with torch.cuda.stream(stream):
+                Bp, ws = None, None
+                for r in range(18):
+                    w = (first + r) % len(weights)
+                    if r == 9:    # another size in between
+                        binding.abft_pack_b_checksum(B_dev[0][: K // 3].contiguous())
+                    Bp = binding.abft_pack_b_checksum(B_dev[w])    # (the one before is destroyed; its products may not even have begun)
+                    ws = binding.Workspace(M, Bp) if ws is None else ws
+                    side.wait_stream(stream)
+                    C = [torch.empty(M, N, dtype=torch.int32, device="cuda") for _ in range(12)]
+                    flags = torch.empty(M, dtype=torch.int32, device="cuda")
+                    with torch.cuda.stream(side):
+                        for c in C:
+                            binding.abft_gemm_u8s8s32_checked(A_dev, Bp, c, flags, None, workspace=ws.tensor)
+                    done.append((w, C, flags, Bp if r == 17 else None))
+            side.synchronize()
+            for w, C, flags, _ in done:
+                if not all(torch.equal(c, wants[w]) for c in C) or bool(flags.any()):
+                    failed.append(("wrong product", first, w))
+        except Exception as e:    # (a failure in a thread is the test's)
+            failed.append(repr(e))
+
+    work(0)
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed, failed[:3]
+    big = [binding.abft_pack_b_checksum(torch.zeros(8192, 9000, dtype=torch.int8, device="cuda")) for _ in range(6)]    # more than is kept
+    del big
+    torch.cuda.empty_cache()
+    torch.cuda.synchronize()
+    assert torch.cuda.mem_get_info()[0] >= free0 - (96 << 20)    # (torch's own pools of the new streams; six blocks of 74 MB were there)
