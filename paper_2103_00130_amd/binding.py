@@ -125,8 +125,9 @@ def _check(rc: int):
 
 
 def _stream(stream=None) -> int:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    if stream is None:   # (torch.cuda.current_stream(), which makes a Stream object, takes 2.7 us)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def _ptr(t, dtype, name):

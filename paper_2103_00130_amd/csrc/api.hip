@@ -37,7 +37,7 @@ int hip_fail(hipError_t e, const char* what) {
 
 // Blocks of destroyed weights, kept for weights to come.  A program that replaces weights while it runs pays more for hipMalloc and
 // hipFree of their blocks, and for the wait for the whole device that goes with them, than for encoding and packing them (4096x4096, us a
-// replacement with its first batch of 64 rows: 86, kept blocks BBB; 900x700 45 / CCC).
+// replacement with its first batch of 64 rows: 86 before, 30 with kept blocks; 900x700 45 and 32).
 //  * A freed block may still be read by work that was enqueued before.  It is used again only after a wait for the whole device, once
 //    for all blocks freed until then.  The wait is a hipFree of a few bytes, which waits for every stream of the device (documented, and
 //    measured on blocking, non-blocking and null streams) and, unlike hipDeviceSynchronize, leaves graphs alone that another thread
@@ -89,7 +89,7 @@ public:
     }
 
 private:
-    static constexpr int kMost = 4, kDevices = 64;
+    static constexpr int kMost = 16, kDevices = 64;
     static constexpr size_t kMostBytes = 256u << 20;
     struct Block {
         void* at;
@@ -124,7 +124,7 @@ private:
             }
         return false;
     }
-    // (while there is room for a further block, another one is allocated instead: a wait for four of them costs as much as for one)
+    // (while there is room for a further block, another one is allocated instead: a wait for many of them costs as much as for one)
     static bool worth_a_wait(Device& d, size_t need) {
         std::lock_guard<std::mutex> lock(d.mutex);
         if (d.n < kMost && need <= kMostBytes - d.bytes) return false;

@@ -1513,9 +1513,9 @@ def test_weights_replaced_while_others_are_in_use(binding, gpu_util, oracle):
             done = []
             with torch.cuda.stream(stream):
                 Bp, ws = None, None
-                for r in range(18):
+                for r in range(40):
                     w = (first + r) % len(weights)
-                    if r == 9:    # another size in between
+                    if r % 9 == 8:    # another size in between
                         binding.abft_pack_b_checksum(B_dev[0][: K // 3].contiguous())
                     Bp = binding.abft_pack_b_checksum(B_dev[w])    # (the one before is destroyed; its products may not even have begun)
                     ws = binding.Workspace(M, Bp) if ws is None else ws
@@ -1525,7 +1525,7 @@ def test_weights_replaced_while_others_are_in_use(binding, gpu_util, oracle):
                     with torch.cuda.stream(side):
                         for c in C:
                             binding.abft_gemm_u8s8s32_checked(A_dev, Bp, c, flags, None, workspace=ws.tensor)
-                    done.append((w, C, flags, Bp if r == 17 else None))
+                    done.append((w, C, flags, Bp if r == 39 else None))
             side.synchronize()
             for w, C, flags, _ in done:
                 if not all(torch.equal(c, wants[w]) for c in C) or bool(flags.any()):
