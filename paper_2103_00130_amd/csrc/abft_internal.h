@@ -47,7 +47,6 @@ struct abft_packed_b {
     int KB;            // k-blocks of 64, rounded up to an even count (zero padded)
     int NT;            // n-tiles of 256
     int device;
-    size_t block_bytes;   // of the block that holds everything below
     int8_t* packed;    // NT*KB*8 units
     int8_t* limbs;     // KB*64*4 bytes
     int32_t* S_B;      // [KB*64], zero past K
@@ -55,6 +54,7 @@ struct abft_packed_b {
     int32_t* total;    // [0] sum of S_B (wrap-around), [1] sum of S_B127
     int8_t* limbs127;  // as limbs, for rowSum = S_B mod 127 (digit 0 only)
     int32_t* S_B127;   // [KB*64] S_B mod 127 in [0,126], zero past K
+    size_t block_bytes;   // of the block that holds all of them, which begins at `packed`
 };
 
 namespace abft {
@@ -145,6 +145,7 @@ struct GemmParams {
     RequantDev rq;
     const void* inj;           // abft_inject_t[n_inj]
     int n_inj;
+    int slots, slot_rows;      // 0, or so many words between the arrivals of many tile columns and a row's word (small tiles, set by the launcher)
     int limb_lot;              // stages whose checksum digits are staged in LDS at a time (small tiles, set by the launcher)
     int ksplit;                // K slices across workgroups (split-K kernels; 1 elsewhere)
     int split_q, split_r;      // stages of a slice; the first split_r take one more
@@ -172,6 +173,21 @@ inline size_t ws_base_ints(int M) {
     // streaming kernel: one 64-bit word per (slot, row) and one per row
     const size_t streaming = 2 * ((size_t)kSmallMSlots * kSmallMRows + kSmallMRows);
     return (size_t)kWsHeaderInts + (rows > streaming ? rows : streaming);
+}
+
+// Arrivals of tile columns at a row's word follow each other at 10 to 20 ns.  From 49 tile columns on (never fewer than slots), and as long as
+// the words that every call has (2112) hold the slots' too, they meet in slots first: 32 of them for up to 64 rows, 8 for up to 192, 4 for up to 384 (us,
+// directly / by slots, 32x32 tiles: 41 columns, 60x1300x128 4.5 / 4.7; 63, 20x2000x900 5.0 / 4.7; 125, 20x3985x848 5.7 / 4.7; 32x64 tiles, 284 columns,
+// 29x9088x1872 7.9 / 6.1; 64x64 tiles, 150 columns, 147x9536x112 7.8 / 6.1, 125, 200x8000x128 7.6 / 6.1, 234, 93x14960x2640 21.5 / 18.4).
+struct RowSlots {
+    int slots, rows;   // (0: none) and the words of a slot
+};
+inline RowSlots row_slots(int M, int tiles_n) {
+    if (tiles_n <= 48 || M > 384) return {0, 0};
+    const int rows = (M + 63) / 64 * 64;
+    int slots = 32;
+    while ((slots + 1) * rows > kSmallMSlots * kSmallMRows + kSmallMRows) slots /= 2;
+    return {slots, rows};
 }
 
 // What some calls need beyond those words - the tile tickets and partial tiles of a K split, a copy of A with padded rows -

@@ -1086,14 +1086,24 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
                 p.row_flags[row0 + r] = bad ? 1 : 0;
                 fin = true;
             } else {
-                const unsigned long long old = __hip_atomic_fetch_add(ws_rows + row0 + r, ((unsigned long long)d << 32) | 1ull,
-                                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if ((uint32_t)old == (uint32_t)arrivals - 1u) {
-                    const uint32_t diff = (uint32_t)(old >> 32) + d;
-                    bad = mod127 ? (diff % 127u != 0) : (diff != 0);
-                    __hip_atomic_store(ws_rows + row0 + r, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    p.row_flags[row0 + r] = bad ? 1 : 0;
+                // (lean: where many tile columns would arrive one after the other, those of a slot meet at a word of their own first)
+                const int slots = kLean ? p.slots : 0, slot = slots > 0 ? tile_n & (slots - 1) : 0;
+                const uint32_t expected = slots > 0 ? (uint32_t)(arrivals - slot + slots - 1) >> __builtin_ctz((unsigned)slots) : (uint32_t)arrivals;
+                unsigned long long* word = ws_rows + (slots > 0 ? slot * p.slot_rows : 0) + row0 + r;
+                unsigned long long old = __hip_atomic_fetch_add(word, ((unsigned long long)d << 32) | 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if ((uint32_t)old == expected - 1u) {
+                    uint32_t diff = (uint32_t)(old >> 32) + d;
+                    __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     fin = true;
+                    if (kLean && slots > 0) {
+                        word = ws_rows + slots * p.slot_rows + row0 + r;
+                        old = __hip_atomic_fetch_add(word, ((unsigned long long)diff << 32) | 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        diff += (uint32_t)(old >> 32);
+                        fin = (uint32_t)old == (uint32_t)slots - 1u;
+                        if (fin) __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                    bad = fin && (mod127 ? (diff % 127u != 0) : (diff != 0));
+                    if (fin) p.row_flags[row0 + r] = bad ? 1 : 0;
                 }
             }
         }
@@ -1153,6 +1163,9 @@ hipError_t launch_cfg(bool check, bool want_c, bool want_q, const GemmParams& p_
     const dim3 grid((unsigned)(tiles_m * tiles_n * (kSplitK ? p.ksplit : 1))), block(WGM * WGN * 64);
     constexpr bool kLean = lean<BM, BN, WGM, WGN, kStages, kSplitK>();
     const int most_digits = p.share_q + (p.share_r > 0 ? 1 : 0);
+    const RowSlots rs = kLean ? row_slots(p.M, tiles_n) : RowSlots{0, 0};
+    p.slots = rs.slots;
+    p.slot_rows = rs.rows;
     p.limb_lot = kLean && most_digits < kLimbStages ? (check ? most_digits : 0) : kLimbStages;
     const size_t lds_most = (lds_bytes<BM, BN, WGN>(kStages, kLimbStages) + 1023) / 1024 * 1024;
     const size_t lds = kLean ? (lds_bytes<BM, BN, WGN>(p.KB2 < kStages ? p.KB2 : kStages, p.limb_lot) + 1023) / 1024 * 1024 : lds_most;

@@ -623,14 +623,8 @@ hipError_t launch_any(bool check, bool want_c, bool want_q, const GemmParams& p_
     p.wk_stream = tiles_m == 1 && (int64_t)p.N * p.K >= (int64_t)(p.M <= 32 ? 96 : 224) << 20;
     const uint32_t per_strip = (uint32_t)(tiles_m < 4 ? tiles_m : 4) * (uint32_t)tiles_n;
     const uint32_t strip_rcp = per_strip == 1 ? 0u : (uint32_t)((0x100000000ull + per_strip - 1) / per_strip);
-    // Arrivals at one word follow each other at 10 to 20 ns.  From 49 tile columns on (never fewer than slots), and as long as the
-    // words that every call has (2112) hold the slots' too, they meet in slots first: 32 for up to 64 rows, 8 for up to 128, 4 for
-    // up to 256 (us, directly / by slots: 41 columns, 60x1300x128 4.5 / 4.7; 63, 20x2000x900 5.0 / 4.7; 125, 20x3985x848 5.7 / 4.7;
-    // 284, 29x9088x1872 with 32x64 tiles 7.9 / 6.1).
-    const int slot_rows = p.M <= 64 ? 64 : p.M <= 128 ? 128 : 256;
-    const int slots = tiles_n <= 48 || p.M > 256 ? 0 : p.M <= 64 ? 32 : p.M <= 128 ? 8 : 4;
-    static_assert((32 + 1) * 64 <= kSmallMSlots * kSmallMRows + kSmallMRows && (8 + 1) * 128 <= kSmallMSlots * kSmallMRows && (4 + 1) * 256 <= kSmallMSlots * kSmallMRows,
-                  "the slots fit the words of every call");
+    const RowSlots rs = row_slots(p.M, tiles_n);
+    const int slots = rs.slots, slot_rows = rs.rows;
     const dim3 grid((unsigned)(tiles_m * tiles_n * (kSplit ? p.ksplit : 1))), block(W * 64);
     const size_t lds = (size_t)W * wave_bytes<TM, TN>() + 64;   // (the wavefronts' parts, and their reports)
 #define ABFT_LAUNCH(CK, OUT)                                                                              \

@@ -1483,7 +1483,9 @@ def test_k_split_among_wavefronts(binding, gpu_util, oracle, M, N, K):
 # and shorter than a chunk)
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,N,K", [(1100, 1030, 16), (1100, 1030, 128), (1025, 1100, 144), (1100, 1030, 256), (1090, 1030, 272), (1100, 1030, 640), (2100, 1030, 100),
-                                   (2100, 1030, 131), (2100, 1030, 300), (2100, 1030, 401), (2100, 1030, 13), (8200, 130, 384)])
+                                   (2100, 1030, 131), (2100, 1030, 300), (2100, 1030, 401), (2100, 1030, 13), (8200, 130, 384),
+                                   # (slots between many tile columns and a row's word: 32, 8 and 4 of them, at the last number of rows for each, and none)
+                                   (40, 17000, 256), (128, 9000, 128), (150, 1630, 272), (192, 6500, 160), (193, 8000, 131), (384, 3200, 144), (385, 3200, 144)])
 def test_64x64_tiles_of_few_stages(binding, gpu_util, oracle, M, N, K):
     test_k_split_among_wavefronts(binding, gpu_util, oracle, M, N, K)
 
