@@ -385,6 +385,66 @@ inline WkForm wk_form(int M, int N, int stages, bool whole_a) {
 // 256x3000x5001 17.9 / 16.9, 128x6500x9001 30.4 / 24.6, 200x4096x9001 30.8 / 24.7; but 256x4096x3001 13.1 / 13.5, 100x5000x2001 10.4 / 12.8).
 inline bool copy_first(WkForm form, int stages) { return form == kWk64x64w4 && stages >= 32; }
 
+// Grids of more tiles than compute units, beyond those for which wk_form has a rule of its own: what the kernels take there, in us, as fits of
+// about 220 products with rows of whole chunks and 110 without (sizes, outputs and ratios of the sides at random, one weight again and again and fresh
+// ones), 7 to 9 % off in the root mean square.  A kernel's time is a fixed part; its stages of 128 k, each at the rate at which a compute unit works
+// through the tiles it has, but no less than the wait for one; the end of its tiles by what they store; and a little for every row and column
+// (arrivals, reports).  Tiles of 128 and 256 run one to a compute unit in full rounds; the smaller ones several at a time, and hardly in rounds.
+struct FormCost {
+    float fixed, stage, wait, end_c, end_q, end_both, per_row, per_col;
+};
+enum LargeForm { kLarge256 = 0, kLarge128, kLarge64, kLargeWk32x64, kLargeWk64x64 };
+constexpr FormCost kWholeCost[5] = {{-5.95f, 1.283f, 0.409f, 21.4f, 21.0f, 29.8f, 0.60e-3f, 0.136e-3f}, {1.57f, 0.549f, 0.537f, 4.69f, 5.17f, 6.88f, 0.35e-3f, 0.239e-3f},
+                                    {4.25f, 0.293f, 0.512f, 0.87f, 0.66f, 1.29f, -0.12e-3f, 0.041e-3f}, {3.88f, 0.163f, 0.293f, 0.66f, 0.58f, 0.84f, 0.22e-3f, 0.058e-3f},
+                                    {3.73f, 0.249f, 0.401f, 1.48f, 1.37f, 1.87f, 0.25e-3f, 0.061e-3f}};
+// rows that are no whole chunks, taken as they lie (gemm_tile_g64.hip and the forms of gemm_tile_wk.h)
+constexpr FormCost kAnyCost[3] = {{4.09f, 0.407f, 0.866f, 0.90f, 0.99f, 1.55f, -0.08e-3f, 0.027e-3f}, {4.17f, 0.198f, 0.339f, 0.72f, 0.73f, 0.90f, 0.10e-3f, 0.002e-3f},
+                                  {4.42f, 0.353f, 0.355f, 1.55f, 1.53f, 2.11f, 0.21e-3f, -0.008e-3f}};
+constexpr float kCopyFixed = 3.8f, kCopyPerByte = 0.25e-6f;   // the copy with padded rows ahead of a kernel
+inline float form_us(const FormCost& c, LargeForm f, int M, int N, int stages, bool want_c, bool want_q) {
+    const int bm = f == kLarge256 ? 256 : f == kLarge128 ? 128 : f == kLargeWk32x64 ? 32 : 64, bn = f == kLarge256 ? 256 : f == kLarge128 ? 128 : 64;
+    const int64_t tiles = (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+    const float rounds = f <= kLarge128 ? (float)((tiles + 255) / 256) : (float)tiles / 256;
+    const float work = rounds * stages * c.stage, wait = stages * c.wait, end = want_c && want_q ? c.end_both : want_c ? c.end_c : c.end_q;
+    return c.fixed + (work > wait ? work : wait) + (rounds > 1 ? rounds : 1) * end + (M < 4096 ? M : 4096) * c.per_row + (N < 16384 ? N : 16384) * c.per_col;
+}
+struct LargeChoice {
+    LargeForm form;
+    bool copy;   // rows that are no whole chunks: copied with padded rows first
+};
+// (calls of more rows than kWsRows, part of whose words has to be zeroed first, are the tiled kernels' alone)
+inline bool beyond_wk_form(int M, int N, int stages) {
+    const int64_t t32 = (int64_t)((M + 31) / 32) * ((N + 31) / 32), t3264 = (int64_t)((M + 31) / 32) * ((N + 63) / 64), t64 = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
+    return M > 32 && M <= kWsRows && t32 > 256 && t3264 > 256 && !(t64 <= 256 && stages >= 12);
+}
+// The cheapest by that; `pick`, which older thresholds on tiles and K choose, unless another one is 5 % cheaper, 10 % where rows are no whole
+// chunks and the fits are of fewer (257x7264x1629 17.2 / 19.2 with 5 %; of the 218 products that lie
+// there the choice is 1.8 % off the best of the five, the thresholds alone 9.4 %; us, thresholds / now: 214x4369x2434 19.1 / 12.0, 2545x7104x528 C and Cq
+// 87 / 40, 3350x2688x288 C and Cq 31.5 / 19.4, 1277x814x8832 C and Cq 41.2 / 33.0, 90x8237x3824 Cq 23.8 / 15.8, 2085x506x12288 53.3 / 40.4,
+// 1702x816x2431 Cq 20.4 / 15.7, 134x13568x96 C and Cq 11.5 / 8.4; of all of them 297x7168x3056 Cq 20.1 / 23.0 and 1295x14192x2256 Cq 88.7 / 94.4 lose most).
+inline LargeChoice large_choice(LargeChoice pick, bool whole_a, bool can_copy, int M, int N, int K, int stages, bool want_c, bool want_q) {
+    LargeChoice best = pick;
+    float least = 0, own = 0;
+    bool any = false;
+    auto look = [&](const FormCost& c, LargeForm f, bool copy, float more) {
+        const float t = form_us(c, f, M, N, stages, want_c, want_q) + more;
+        if (f == pick.form && copy == pick.copy) own = t;
+        if (!any || t < least) {
+            least = t;
+            best = {f, copy};
+            any = true;
+        }
+    };
+    if (!whole_a && K >= 16) {
+        if (!pick.copy) look(kAnyCost[0], kLarge64, false, 0);   // (where the copy is worth more than that: realign_plan)
+        look(kAnyCost[1], kLargeWk32x64, false, 0);
+        look(kAnyCost[2], kLargeWk64x64, false, 0);
+    }
+    if (whole_a || can_copy)
+        for (int f = 0; f < 5; ++f) look(kWholeCost[f], (LargeForm)f, !whole_a, whole_a ? 0.0f : kCopyFixed + kCopyPerByte * (float)M * (float)K);
+    return any && least < (whole_a ? 0.95f : 0.9f) * own ? best : pick;
+}
+
 enum Variant { kTile256 = 1, kTile128 = 2, kTile64 = 3, kSmallM = 4, kTile256w24 = 5, kTile256w42 = 6, kVariantEnd = 7 };
 
 // launchers (each returns the hipError_t of its launch)

@@ -404,6 +404,8 @@ int abft_gemm_u8s8s32_checked(const uint8_t* A, int64_t lda, int M, const abft_p
     abft::RealignPlan ra = {};
     if (!whole_a && !mod127) ra = abft::realign_plan(M, Bp->N, Bp->K, p.KB2);   // (short calls pay for what the host does)
     const bool can_copy = ra.copy && workspace && p.ws_ints >= ra.total_ints;
+    bool copy = can_copy;
+    abft::WkForm wk = abft::kWkNone;
     if (!chosen) {
         if (whole_a) {
             e = abft::launch_gemm_split64(check, want_c, want_q, p, (hipStream_t)stream);
@@ -411,14 +413,28 @@ int abft_gemm_u8s8s32_checked(const uint8_t* A, int64_t lda, int M, const abft_p
             if (e != hipErrorNotSupported) return hip_fail(e, fn);
         }
         const abft::WkForm form = abft::wk_form(M, Bp->N, p.KB2, whole_a);
-        if (!(can_copy && (abft::copy_first(form, p.KB2) || abft::split64_plan(M, Bp->N, p.KB2).z > 1))) {
-            e = abft::launch_gemm_wk(form, check, want_c, want_q, p, (hipStream_t)stream);
-            if (e == hipSuccess) return ABFT_OK;
-            if (e != hipErrorNotSupported) return hip_fail(e, fn);
+        const bool copy_ahead = can_copy && (abft::copy_first(form, p.KB2) || abft::split64_plan(M, Bp->N, p.KB2).z > 1);
+        if (!copy_ahead && abft::beyond_wk_form(M, Bp->N, p.KB2) && (whole_a || (!mod127 && p.K >= 16))) {
+            // what the rules so far take, and whether something else is cheaper
+            abft::LargeChoice now = {form == abft::kWk32x64w4 ? abft::kLargeWk32x64 : abft::kLargeWk64x64, false};
+            if (form == abft::kWkNone) {
+                const int tile = pick_tile();
+                now = {whole_a || can_copy ? (tile == abft::kTile256 ? abft::kLarge256 : tile == abft::kTile128 ? abft::kLarge128 : abft::kLarge64) : abft::kLarge64, can_copy};
+            }
+            now = abft::large_choice(now, whole_a, can_copy, M, Bp->N, p.K, p.KB2, want_c, want_q);
+            copy = now.copy;
+            wk = now.form == abft::kLargeWk32x64 ? abft::kWk32x64w4 : now.form == abft::kLargeWk64x64 ? abft::kWk64x64w4 : abft::kWkNone;
+            variant = now.form == abft::kLarge256 ? abft::kTile256 : now.form == abft::kLarge128 ? abft::kTile128 : abft::kTile64;
+        } else {
+            if (!copy_ahead) {
+                e = abft::launch_gemm_wk(form, check, want_c, want_q, p, (hipStream_t)stream);
+                if (e == hipSuccess) return ABFT_OK;
+                if (e != hipErrorNotSupported) return hip_fail(e, fn);
+            }
+            variant = M <= 32 ? (int)abft::kSmallM : pick_tile();
         }
-        variant = M <= 32 ? (int)abft::kSmallM : pick_tile();
     }
-    if (variant != abft::kSmallM && can_copy) {
+    if (variant != abft::kSmallM && copy) {
         uint8_t* const A2 = (uint8_t*)(((uintptr_t)(p.ws + ra.off) + 15) & ~(uintptr_t)15);
         e = abft::launch_realign(A, lda, M, p.K, A2, ra.lda, (hipStream_t)stream);
         if (e != hipSuccess) return hip_fail(e, fn);
@@ -427,7 +443,11 @@ int abft_gemm_u8s8s32_checked(const uint8_t* A, int64_t lda, int M, const abft_p
         p.a_vec_ok = 1;
         p.K = (int)ra.lda;    // (the padding meets rows of zeros in the packed weight)
     }
-    if (variant == abft::kSmallM) {
+    if (wk != abft::kWkNone) {
+        e = abft::launch_gemm_wk(wk, check, want_c, want_q, p, (hipStream_t)stream);
+        if (e == hipErrorNotSupported)   // (more tiles than that kernel's quotients are exact for)
+            e = abft::launch_gemm_tile(variant, check, want_c, want_q, p, (hipStream_t)stream);
+    } else if (variant == abft::kSmallM) {
         if (M > 64) return fail(ABFT_EUNSUPPORTED, "%s: the streaming variant takes M <= 64, got %d", fn, M);
         e = abft::launch_gemm_smallm(!chosen, check, want_c, want_q, p, (hipStream_t)stream);
         if (e == hipErrorNotSupported && !chosen)  // rows shorter than a 16-byte chunk: the tiled path takes them

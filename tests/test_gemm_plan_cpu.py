@@ -18,6 +18,11 @@ extern "C" void plan(int M, int N, int K, int stages, int whole, long long* out)
 }
 extern "C" int form(int M, int N, int stages, int whole) { return abft::wk_form(M, N, stages, whole != 0); }
 extern "C" int room_for_copy(int M, int N, int K) { return abft::room_for_copy(M, N, K); }
+extern "C" int beyond(int M, int N, int stages) { return abft::beyond_wk_form(M, N, stages); }
+extern "C" int large(int M, int N, int K, int stages, int whole, int can_copy, int pick, int pick_copy, int want_c, int want_q) {
+    const abft::LargeChoice c = abft::large_choice({(abft::LargeForm)pick, pick_copy != 0}, whole != 0, can_copy != 0, M, N, K, stages, want_c != 0, want_q != 0);
+    return c.form + (c.copy ? 8 : 0);
+}
 extern "C" int copy_first(int form, int stages) { return abft::copy_first((abft::WkForm)form, stages); }
 """
 NONE, T32X32W4, T32X32W8, T32X64W4, T32X64W8, T64X64W4 = range(6)
@@ -43,6 +48,9 @@ def plan(tmp_path_factory):
     call.room_for_copy = lambda M, N, K: bool(so.room_for_copy(M, N, K))
     call.copy_first = lambda form, K: bool(so.copy_first(form, ((K + 63) // 64 + 1) // 2))
     call.form = lambda M, N, K: so.form(M, N, ((K + 63) // 64 + 1) // 2, K % 16 == 0)
+    call.beyond = lambda M, N, K: bool(so.beyond(M, N, ((K + 63) // 64 + 1) // 2))
+    call.large = lambda M, N, K, pick, out="C", can_copy=False: so.large(M, N, K, ((K + 63) // 64 + 1) // 2, K % 16 == 0, can_copy, pick & 7, pick >> 3,
+                                                                         out != "q", out != "C")
     return call
 
 
@@ -139,3 +147,26 @@ def test_calls_of_rows_that_are_no_whole_chunks(plan):
 def test_split_of_the_small_tiles(plan, M, N, K, z):
     p = plan(M, N, K, 1)
     assert p.z == z and (z == 1 or (p.split_ints <= p.room_ints and 4 * ((M + 31) // 32) * ((N + 31) // 32) <= p.part_off - p.tickets_off))
+
+
+def test_grids_beyond_the_compute_units(plan):
+    """What the fits choose there: small tiles for a short K and for grids that large ones would leave idle, large ones for many rows, columns
+    and a long K; a copy only where there is room for one; never where wk_form has a rule."""
+    L256, L128, L64, W32X64, W64X64, COPY = 0, 1, 2, 3, 4, 8
+    assert plan.large(2545, 7104, 528, L256, "both") == L64 and plan.large(3350, 2688, 288, L256, "both") == L64
+    assert plan.large(4096, 4096, 4096, L256) == L256 and plan.large(4096, 4096, 1024, L256, "q") == L256 and plan.large(2048, 2048, 4096, L128) == L128
+    assert plan.large(90, 8237, 3824, L64, "q") == W32X64 and plan.large(214, 4369, 2434, L64 + COPY, "both", True) == W32X64
+    assert plan.large(2085, 506, 12288, L64) in (W32X64, W64X64)
+    for M in (33, 64, 100, 300, 1000, 4096, 100000):
+        for N in (100, 1000, 4000, 16384):
+            for K in (17, 64, 100, 500, 1040, 4096, 9001):
+                if not plan.beyond(M, N, K):
+                    continue
+                assert plan.form(M, N, K) in (NONE, T32X64W4, T64X64W4)
+                for out in ("C", "q", "both"):
+                    for pick in (L256, L128, L64):
+                        assert plan.large(M, N, K, pick, out) < COPY
+                        assert plan.large(M, N, K, pick + (COPY if K % 16 else 0), out, True) in ((L256, L128, L64, W32X64, W64X64) if K % 16 == 0 else
+                                                                                                 (L64, W32X64, W64X64, *(COPY + f for f in range(5))))
+    assert plan.beyond(131072, 258, 32) and not plan.beyond(131073, 258, 32)    # (row words that reach into the scratch)
+    assert not plan.beyond(32, 100000, 4096) and not plan.beyond(64, 256, 512) and not plan.beyond(1024, 1024, 4096) and plan.beyond(1024, 1040, 4096)

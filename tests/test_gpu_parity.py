@@ -1485,7 +1485,10 @@ def test_k_split_among_wavefronts(binding, gpu_util, oracle, M, N, K):
 @pytest.mark.parametrize("M,N,K", [(1100, 1030, 16), (1100, 1030, 128), (1025, 1100, 144), (1100, 1030, 256), (1090, 1030, 272), (1100, 1030, 640), (2100, 1030, 100),
                                    (2100, 1030, 131), (2100, 1030, 300), (2100, 1030, 401), (2100, 1030, 13), (8200, 130, 384),
                                    # (slots between many tile columns and a row's word: 32, 8 and 4 of them, at the last number of rows for each, and none)
-                                   (40, 17000, 256), (128, 9000, 128), (150, 1630, 272), (192, 6500, 160), (193, 8000, 131), (384, 3200, 144), (385, 3200, 144)])
+                                   (40, 17000, 256), (128, 9000, 128), (150, 1630, 272), (192, 6500, 160), (193, 8000, 131), (384, 3200, 144), (385, 3200, 144),
+                                   # (more tiles than two to a compute unit on the kernel that splits K among wavefronts: 32x64 and 64x64 tiles, rows of whole
+                                   # chunks and of any length, with and without a copy ahead; large grids and a short K on 64x64 tiles)
+                                   (215, 4173, 1690), (90, 8237, 1040), (1100, 1001, 2064), (1350, 900, 2500), (700, 3100, 1313), (396, 4325, 2309), (1423, 1227, 303), (2300, 3000, 300), (1953, 4100, 96)])
 def test_64x64_tiles_of_few_stages(binding, gpu_util, oracle, M, N, K):
     test_k_split_among_wavefronts(binding, gpu_util, oracle, M, N, K)
 
