@@ -145,15 +145,24 @@ struct GemmParams {
     RequantDev rq;
     const void* inj;           // abft_inject_t[n_inj]
     int n_inj;
-    int slots, slot_rows;      // 0, or so many words between the arrivals of many tile columns and a row's word (small tiles, set by the launcher)
-    int limb_lot;              // stages whose checksum digits are staged in LDS at a time (small tiles, set by the launcher)
     int ksplit;                // K slices across workgroups (split-K kernels; 1 elsewhere)
     int split_q, split_r;      // stages of a slice; the first split_r take one more
     int32_t* ws_tickets;       // split-K: one arrival counter per tile (and finishing wavefront)
     int32_t* ws_part;          // split-K: parts, [tile][slice][value][thread] or [tile][finishing wavefront][slice][value][lane]
-    int wk_stages;             // K split among wavefronts: stages of the wavefronts with fewest; those with one more deal out
+    // (shared places: with the members of GemmParams anywhere else a kernel's first loads fall apart, 0.1 to 0.2 us of a short call)
+    union {
+        int wk_stages;         // K split among wavefronts: stages of the wavefronts with fewest; those with one more deal out
+        int limb_lot;          // 64x64 tiles: stages whose checksum digits are staged in LDS at a time
+    };
     int wk_stream;             // ... the weight is not kept in the caches
-    int wk_share_q1, wk_share_r1;  // their k-steps of the checksum product by these instead of share_q, share_r
+    union {
+        struct {
+            int wk_share_q1, wk_share_r1;   // their k-steps of the checksum product by these instead of share_q, share_r
+        };
+        struct {
+            int slots, slot_rows;           // 64x64 tiles: the words between the arrivals of many tile columns and a row's word (RowSlots)
+        };
+    };
     size_t ws_ints;            // ints the caller's workspace holds
     unsigned long long* clock_trace;  // diagnostic builds (ABFT_CLOCK_TRACE): 6 words per workgroup, else NULL
     int32_t* ws;               // workspace: counting words in the first kWsHeaderInts ints, then the per-row words
@@ -418,7 +427,8 @@ inline bool beyond_wk_form(int M, int N, int stages) {
     return M > 32 && M <= kWsRows && t32 > 256 && t3264 > 256 && !(t64 <= 256 && stages >= 12);
 }
 // The cheapest by that; `pick`, which older thresholds on tiles and K choose, unless another one is 5 % cheaper, 10 % where rows are no whole
-// chunks and the fits are of fewer (257x7264x1629 17.2 / 19.2 with 5 %; of the 218 products that lie
+// chunks and the fits are of fewer (257x7264x1629 17.2 / 19.2 with 5 %), 15 % where those lie within a measured line of wk_form (2000x1000x479 C and Cq
+// 9.4 / 9.9 with 10 %; of the 218 products that lie
 // there the choice is 1.8 % off the best of the five, the thresholds alone 9.4 %; us, thresholds / now: 214x4369x2434 19.1 / 12.0, 2545x7104x528 C and Cq
 // 87 / 40, 3350x2688x288 C and Cq 31.5 / 19.4, 1277x814x8832 C and Cq 41.2 / 33.0, 90x8237x3824 Cq 23.8 / 15.8, 2085x506x12288 53.3 / 40.4,
 // 1702x816x2431 Cq 20.4 / 15.7, 134x13568x96 C and Cq 11.5 / 8.4; of all of them 297x7168x3056 Cq 20.1 / 23.0 and 1295x14192x2256 Cq 88.7 / 94.4 lose most).
@@ -442,7 +452,8 @@ inline LargeChoice large_choice(LargeChoice pick, bool whole_a, bool can_copy, i
     }
     if (whole_a || can_copy)
         for (int f = 0; f < 5; ++f) look(kWholeCost[f], (LargeForm)f, !whole_a, whole_a ? 0.0f : kCopyFixed + kCopyPerByte * (float)M * (float)K);
-    return any && least < (whole_a ? 0.95f : 0.9f) * own ? best : pick;
+    const float line = whole_a ? 0.95f : pick.form >= kLargeWk32x64 ? 0.85f : 0.9f;
+    return any && least < line * own ? best : pick;
 }
 
 enum Variant { kTile256 = 1, kTile128 = 2, kTile64 = 3, kSmallM = 4, kTile256w24 = 5, kTile256w42 = 6, kVariantEnd = 7 };
