@@ -149,13 +149,9 @@ struct GemmParams {
     int split_q, split_r;      // stages of a slice; the first split_r take one more
     int32_t* ws_tickets;       // split-K: one arrival counter per tile (and finishing wavefront)
     int32_t* ws_part;          // split-K: parts, [tile][slice][value][thread] or [tile][finishing wavefront][slice][value][lane]
-    // (shared places: with the members of GemmParams anywhere else a kernel's first loads fall apart, 0.1 to 0.2 us of a short call)
-    union {
-        int wk_stages;         // K split among wavefronts: stages of the wavefronts with fewest; those with one more deal out
-        int limb_lot;          // 64x64 tiles: stages whose checksum digits are staged in LDS at a time
-    };
+    int wk_stages;             // K split among wavefronts: stages of the wavefronts with fewest; those with one more deal out
     int wk_stream;             // ... the weight is not kept in the caches
-    union {
+    union {   // (shared places: with the other members anywhere else a kernel's first loads fall apart, 0.1 to 0.2 us of a short call)
         struct {
             int wk_share_q1, wk_share_r1;   // their k-steps of the checksum product by these instead of share_q, share_r
         };

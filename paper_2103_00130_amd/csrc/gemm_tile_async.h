@@ -351,8 +351,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     }
     const int ck_lo = kCheck ? share_begin(tile_n, share_q, share_r) : 0;
     const int ck_hi = kCheck ? share_begin(tile_n + 1, share_q, share_r) : 0;
-    // stages resident, and stages of digits staged at a time
-    const int ring = kLean ? min(S, NS) : S, limb_lot = kLean ? p.limb_lot : kLimbStages;
+    const int ring = kLean ? min(S, NS) : S;   // stages resident
     uint8_t* const s_limb = smem + (kLean ? A_FIRST : SCRATCH) + ring * (A_STAGE + B_STAGE);
     // sum_k S_B[k], which the first tile column needs at the very end (the u8 -> s8 shift of A moves every
     // checksum product by 128 times it): fetched now, so that the epilogue does not wait for memory
@@ -373,7 +372,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     // LDS words behind the lot, which nobody reads.)
     const uint32_t lds_limb = lds_base + (uint32_t)((kLean ? A_FIRST : SCRATCH) + ring * (A_STAGE + B_STAGE));
     auto stage_limbs = [&](int s0) __attribute__((always_inline)) {
-        const int n = min(ck_hi - s0, limb_lot);
+        const int n = min(ck_hi - s0, kLimbStages);
         const int8_t* const src = p.limbs + (int64_t)(s_base + s0) * 512;
         for (int i = wave; i * 2 < n; i += NW)
             dma(lds_limb + i * 1024, (uint32_t)min(i * 1024 + lane * 16, n * 512 - 16), src, std::integral_constant<int, 0>{});
@@ -571,6 +570,12 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     }
 
     asm volatile("" : "+s"(total_sb));  // (the value is in its register from here on)
+    int slots = 0, slot_rows = 0;
+    if constexpr (kLean) {   // (fetched now: where they are used, a trip to memory at the end of a workgroup, 607x1872x96 5.67 -> 5.87 us)
+        slots = p.slots;
+        slot_rows = p.slot_rows;
+        asm volatile("" : "+s"(slots), "+s"(slot_rows));
+    }
 #ifdef ABFT_CLOCK_TRACE
     // Diagnostic build only: the first thread of every workgroup samples the shader-clock cycle counter and the
     // constant 100 MHz wall counter before the K loop, after it and at the end of the kernel (6 words per
@@ -693,7 +698,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
     auto run_all = [&](auto ph_c) __attribute__((always_inline)) {
         if (kCheck) {
             run(0, ck_lo, std::false_type{}, ph_c);
-            for (int c0 = ck_lo; c0 < ck_hi; c0 += limb_lot) {
+            for (int c0 = ck_lo; c0 < ck_hi; c0 += kLimbStages) {
                 if (c0 > ck_lo) {
                     // every wave has left the stages that read the previous lot (their digits were in
                     // registers before the barrier that ended the last of them)
@@ -701,7 +706,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
                     wait_vmem();
                     __syncthreads();
                 }
-                run(c0, min(c0 + limb_lot, ck_hi), std::true_type{}, ph_c);
+                run(c0, min(c0 + kLimbStages, ck_hi), std::true_type{}, ph_c);
             }
             run(ck_hi, NS, std::false_type{}, ph_c);
         } else {
@@ -722,7 +727,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
                 const int buf = u & 1, nxt = kLean && ring == 1 ? buf : buf ^ 1;
                 phase_small(0, 2, buf, 2, std::false_type{}, 0, 0, 0, 0);
                 if (kCheck && s >= ck_lo && s < ck_hi) {
-                    if (s - limb_base == limb_lot) {
+                    if (s - limb_base == kLimbStages) {
                         // a further lot of digits (every wave has its last use of the previous lot behind it)
                         __syncthreads();
                         stage_limbs(s);
@@ -1086,24 +1091,36 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
                 p.row_flags[row0 + r] = bad ? 1 : 0;
                 fin = true;
             } else {
-                // (lean: where many tile columns would arrive one after the other, those of a slot meet at a word of their own first)
-                const int slots = kLean ? p.slots : 0, slot = slots > 0 ? tile_n & (slots - 1) : 0;
-                const uint32_t expected = slots > 0 ? (uint32_t)(arrivals - slot + slots - 1) >> __builtin_ctz((unsigned)slots) : (uint32_t)arrivals;
-                unsigned long long* word = ws_rows + (slots > 0 ? slot * p.slot_rows : 0) + row0 + r;
-                unsigned long long old = __hip_atomic_fetch_add(word, ((unsigned long long)d << 32) | 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if ((uint32_t)old == expected - 1u) {
-                    uint32_t diff = (uint32_t)(old >> 32) + d;
-                    __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    fin = true;
-                    if (kLean && slots > 0) {
-                        word = ws_rows + slots * p.slot_rows + row0 + r;
-                        old = __hip_atomic_fetch_add(word, ((unsigned long long)diff << 32) | 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        diff += (uint32_t)(old >> 32);
-                        fin = (uint32_t)old == (uint32_t)slots - 1u;
-                        if (fin) __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if constexpr (!kLean) {
+                    const unsigned long long old = __hip_atomic_fetch_add(ws_rows + row0 + r, ((unsigned long long)d << 32) | 1ull,
+                                                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if ((uint32_t)old == (uint32_t)arrivals - 1u) {
+                        const uint32_t diff = (uint32_t)(old >> 32) + d;
+                        bad = mod127 ? (diff % 127u != 0) : (diff != 0);
+                        __hip_atomic_store(ws_rows + row0 + r, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        p.row_flags[row0 + r] = bad ? 1 : 0;
+                        fin = true;
                     }
-                    bad = fin && (mod127 ? (diff % 127u != 0) : (diff != 0));
-                    if (fin) p.row_flags[row0 + r] = bad ? 1 : 0;
+                } else {
+                    // (where many tile columns would arrive one after the other, those of a slot meet at a word of their own first)
+                    const int slot = tile_n & (slots - 1);
+                    const uint32_t expected = slots > 0 ? (uint32_t)(arrivals - slot + slots - 1) >> __builtin_ctz((unsigned)slots) : (uint32_t)arrivals;
+                    unsigned long long* word = ws_rows + (slots > 0 ? slot * slot_rows : 0) + row0 + r;
+                    unsigned long long old = __hip_atomic_fetch_add(word, ((unsigned long long)d << 32) | 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if ((uint32_t)old == expected - 1u) {
+                        uint32_t diff = (uint32_t)(old >> 32) + d;
+                        __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        fin = true;
+                        if (slots > 0) {
+                            word = ws_rows + slots * slot_rows + row0 + r;
+                            old = __hip_atomic_fetch_add(word, ((unsigned long long)diff << 32) | 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            diff += (uint32_t)(old >> 32);
+                            fin = (uint32_t)old == (uint32_t)slots - 1u;
+                            if (fin) __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        }
+                        bad = fin && (mod127 ? (diff % 127u != 0) : (diff != 0));
+                        if (fin) p.row_flags[row0 + r] = bad ? 1 : 0;
+                    }
                 }
             }
         }
@@ -1162,13 +1179,12 @@ hipError_t launch_cfg(bool check, bool want_c, bool want_q, const GemmParams& p_
     p.share_r = shortest % tiles_n;
     const dim3 grid((unsigned)(tiles_m * tiles_n * (kSplitK ? p.ksplit : 1))), block(WGM * WGN * 64);
     constexpr bool kLean = lean<BM, BN, WGM, WGN, kStages, kSplitK>();
-    const int most_digits = p.share_q + (p.share_r > 0 ? 1 : 0);
+    const int share_most = p.share_q + (p.share_r > 0 ? 1 : 0), digits = !check ? 0 : share_most < kLimbStages ? share_most : kLimbStages;   // stages of them in LDS
     const RowSlots rs = kLean ? row_slots(p.M, tiles_n) : RowSlots{0, 0};
     p.slots = rs.slots;
     p.slot_rows = rs.rows;
-    p.limb_lot = kLean && most_digits < kLimbStages ? (check ? most_digits : 0) : kLimbStages;
     const size_t lds_most = (lds_bytes<BM, BN, WGN>(kStages, kLimbStages) + 1023) / 1024 * 1024;
-    const size_t lds = kLean ? (lds_bytes<BM, BN, WGN>(p.KB2 < kStages ? p.KB2 : kStages, p.limb_lot) + 1023) / 1024 * 1024 : lds_most;
+    const size_t lds = kLean ? (lds_bytes<BM, BN, WGN>(p.KB2 < kStages ? p.KB2 : kStages, digits) + 1023) / 1024 * 1024 : lds_most;
     // Row sums in block form or per row.  Small wave tiles: always the block form, which halves the
     // vector work of an epilogue that is short anyway.  The 128x128 wave tile: per row when the grid
     // fills the chip - the stores then take the time memory needs and the arithmetic between them is
