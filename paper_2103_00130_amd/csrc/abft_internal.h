@@ -55,9 +55,17 @@ struct abft_packed_b {
     int8_t* limbs127;  // as limbs, for rowSum = S_B mod 127 (digit 0 only)
     int32_t* S_B127;   // [KB*64] S_B mod 127 in [0,126], zero past K
     size_t block_bytes;   // of the block that holds all of them, which begins at `packed`
+    int32_t* parts;       // sums of the packing tiles before they are added up (pack_parts), or NULL
 };
 
 namespace abft {
+
+// Ints for the sums of the tiles of 256 columns x 128 k as a weight is packed (a twentieth of the weight), or 0 where they are added up by atomics:
+// from 65 tiles in a row or 129 in a column on, where adding them up afterwards would take longer than the kernel that clears the sums for the
+// atomics (3 us of the host, 3 to 4 of the device).
+inline size_t pack_parts(int KB, int NT) {
+    return NT <= 64 && KB <= 256 ? (size_t)NT * KB * kUnitK + (size_t)(KB / 2) * NT * kTileN : 0;
+}
 
 struct RequantDev {
     int32_t zA, zC;

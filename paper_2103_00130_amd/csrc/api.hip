@@ -210,15 +210,16 @@ int abft_pack_b_checksum(const int8_t* B, int64_t ldb, int K, int N, int b_is_tr
     h->KB = ((K + 2 * abft::kUnitK - 1) / (2 * abft::kUnitK)) * 2;
     h->NT = (N + abft::kTileN - 1) / abft::kTileN;
     hipError_t e = hipGetDevice(&h->device);
-    // one block: the units, the digits, then S_B, colsum and total (cleared together before packing), S_B mod 127
+    // one block: the units, the digits, then S_B, colsum and total (cleared together before packing where there are no parts), S_B mod 127, the parts
     const auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
     const size_t units = (size_t)h->NT * h->KB * abft::kUnitsPerTile * abft::kUnitBytes, k_ints = (size_t)h->KB * abft::kUnitK * sizeof(int32_t);
     const size_t digits = (size_t)h->KB * abft::kUnitK * abft::kLimbs, n_ints = (size_t)h->NT * abft::kTileN * sizeof(int32_t);
     const size_t o_limbs = up(units), o_limbs127 = o_limbs + up(digits), o_sb = o_limbs127 + up(digits), o_colsum = o_sb + up(k_ints);
     const size_t o_total = o_colsum + up(n_ints), o_sb127 = o_total + 256;
+    const size_t part_ints = abft::pack_parts(h->KB, h->NT), o_parts = o_sb127 + up(k_ints);
     if (e == hipSuccess) {
         void* block = nullptr;
-        e = kept_blocks().get(h->device, o_sb127 + k_ints, &block, &h->block_bytes);
+        e = kept_blocks().get(h->device, o_parts + part_ints * sizeof(int32_t), &block, &h->block_bytes);
         h->packed = (int8_t*)block;
     }
     if (e == hipSuccess) {
@@ -228,6 +229,7 @@ int abft_pack_b_checksum(const int8_t* B, int64_t ldb, int K, int N, int b_is_tr
         h->colsum = reinterpret_cast<int32_t*>(h->packed + o_colsum);
         h->total = reinterpret_cast<int32_t*>(h->packed + o_total);
         h->S_B127 = reinterpret_cast<int32_t*>(h->packed + o_sb127);
+        h->parts = part_ints > 0 ? reinterpret_cast<int32_t*>(h->packed + o_parts) : nullptr;
     }
     if (e == hipSuccess) e = abft::launch_pack(B, ldb, b_is_transposed ? 1 : 0, h, (hipStream_t)stream);
     if (e != hipSuccess) {

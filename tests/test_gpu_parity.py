@@ -1550,3 +1550,11 @@ def test_weights_replaced_while_others_are_in_use(binding, gpu_util, oracle):
     torch.cuda.empty_cache()
     torch.cuda.synchronize()
     assert torch.cuda.mem_get_info()[0] >= free0 - (96 << 20)    # (torch's own pools of the new streams; six blocks of 74 MB were there)
+
+
+# (the tiles' sums added up afterwards, in whole and half blocks of 256 k, and by atomics: on either side of the line between them)
+@pytest.mark.gpu
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("K,N", [(64, 20), (300, 1100), (16384, 20), (16385, 20), (20, 16384), (20, 16385)])
+def test_pack_of_many_tiles(binding, gpu_util, oracle, K, N, transposed):
+    test_pack_of_strided_weights(binding, gpu_util, oracle, K, N, transposed)
