@@ -75,7 +75,7 @@ public:
             (void)hipFree(block);
             return;
         }
-        bool last, kept = false;
+        bool last, kept = false, in_a_run = false;
         {
             std::lock_guard<std::mutex> lock(d->mutex);
             last = --d->live == 0;
@@ -83,15 +83,18 @@ public:
                 d->blocks[d->n++] = {block, size, ++d->released, false};
                 d->bytes += size;
                 kept = true;
+                in_a_run = d->since_last < kRun;
             }
         }
         if (last) (void)give_back(*d);
         if (!kept) (void)hipFree(block);
+        else if (!in_a_run) (void)wait_for_device(*d);
     }
 
 private:
     static constexpr int kMost = 16, kDevices = 64;
     static constexpr size_t kMostBytes = 256u << 20;
+    static constexpr std::chrono::microseconds kRun{50};   // between the weights of a run, at most (25 to 30 where it is measured; made and used one by one 80 and more)
     struct Block {
         void* at;
         size_t size;
@@ -131,11 +134,11 @@ private:
         return false;
     }
     // (A wait costs 10 us on an idle device and 60 to 90 where weights are replaced one after the other, for one block or for many; a further block
-    // that the device has not had yet 60 to 250.  So a weight now and then waits, and one of a run of them, less than 100 us behind the last,
-    // has another block allocated as long as there is room.)
+    // that the device has not had yet 60 to 250.  So the wait for a weight replaced now and then comes as it is destroyed, where hipFree had it, and in a
+    // run of them another block is allocated as long as there is room.)
     static bool worth_a_wait(Device& d, size_t need) {
         std::lock_guard<std::mutex> lock(d.mutex);
-        if (d.n < kMost && need <= kMostBytes - d.bytes && d.since_last < std::chrono::microseconds(100)) return false;
+        if (d.n < kMost && need <= kMostBytes - d.bytes && d.since_last < kRun) return false;
         for (int i = 0; i < d.n; ++i)
             if (!d.blocks[i].idle && fits(d.blocks[i], need)) return true;
         return false;
