@@ -71,7 +71,7 @@ __device__ __attribute__((always_inline)) inline void for_each_impl(Fn&& fn, std
 template <int N, class Fn>
 __device__ __attribute__((always_inline)) inline void for_each(Fn&& fn) { for_each_impl<N>(fn, std::make_integer_sequence<int, N>{}); }
 
-// slots: 0, or so many words between the arrivals of many tile columns and a row's word (see launch_any)
+// slots: 0, or so many words between the arrivals of many tile columns and a row's word (row_slots)
 template <int TM, int TN, int W, bool kCheck, int kOut, bool kAny, bool kSplit>
 __global__ __launch_bounds__(W * 64) void gemm_tile_wk_kernel(const GemmParams p, const int tiles_m, const int tiles_n, const uint32_t strip_rcp,
                                                               const int slots, const int slot_rows) {
