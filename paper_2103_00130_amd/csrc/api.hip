@@ -38,7 +38,7 @@ int hip_fail(hipError_t e, const char* what) {
 
 // Blocks of destroyed weights, kept for weights to come.  A program that replaces weights while it runs pays more for hipMalloc and
 // hipFree of their blocks, and for the wait for the whole device that goes with them, than for encoding and packing them (4096x4096, us a
-// replacement with its first batch of 64 rows: 86 before, 30 with kept blocks; 900x700 45 and 32).
+// replacement with its first batch of 64 rows: 86 before, 30 with kept blocks; 900x700 45 and 28; packing in two kernels since takes 1 to 3 more off).
 //  * A freed block may still be read by work that was enqueued before.  It is used again only after a wait for the whole device, once
 //    for all blocks freed until then.  The wait is a hipFree of a few bytes, which waits for every stream of the device (documented, and
 //    measured on blocking, non-blocking and null streams) and, unlike hipDeviceSynchronize, leaves graphs alone that another thread

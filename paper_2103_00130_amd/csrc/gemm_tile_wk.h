@@ -18,6 +18,8 @@
 // Bound: launch and latency below about 6 us; with a long K what a wavefront with one stage in flight gets from its L2: 1024x1024x4096 takes
 // 0.85 us for the stages of its four wavefronts, 77 KB/us a compute unit (41 to 44 bytes a cycle at the 1.75 to 1.9 GHz of a counter run),
 // six to seven tenths of what such loads reach alone; the matrix pipes are busy 0.17 of the time, the LDS 0.18, wavefronts wait 0.37.
+// More in flight is no help: loads alone take 7.2 us of that shape's 11.5, with fragment reads and matrix instructions 8.4, one stage or two in flight,
+// and sixteen workgroups draw 151 KB/us each with one, a compute unit's 64 bytes a cycle (99x108x6176: 7.5 us, 8.2 with two).
 // Measured, this kernel against the 64x64 tiles of gemm_tile_async.h or the streaming kernel that ran before (us): 64x256x512 4.9 -> 4.0,
 // 256x512x1024 requantized 6.8 -> 4.9, 64x1024x1024 5.9 -> 4.5, 130x65x2064 8.8 -> 5.4, 500x500x2000 9.1 -> 6.2, 441x479x1255 8.7 -> 5.2,
 // 32x4096x4096 9.4 -> 6.1, 29x9088x1872 10.6 -> 6.1, 64x8192x2048 10.0 -> 8.5, 1024x1024x4096 requantized 13.1 -> 12.1 (11.6 on another
