@@ -53,7 +53,7 @@ public:
         *out = nullptr;
         if (Device* const d = of(dev)) {
             bool found = take(*d, need, out, size);
-            if (!found && worth_a_wait(*d, need) && wait_for_device(*d)) found = take(*d, need, out, size);
+            if (!found && worth_a_wait(*d, need) && wait_for_device(*d, dev)) found = take(*d, need, out, size);
             if (!found) {
                 e = hipMalloc(out, *size = need);
                 if (e == hipErrorOutOfMemory && give_back(*d)) {
@@ -88,7 +88,7 @@ public:
         }
         if (last) (void)give_back(*d);
         if (!kept) (void)hipFree(block);
-        else if (!in_a_run) (void)wait_for_device(*d);
+        else if (!in_a_run) (void)wait_for_device(*d, dev);
     }
 
 private:
@@ -143,7 +143,9 @@ private:
             if (!d.blocks[i].idle && fits(d.blocks[i], need)) return true;
         return false;
     }
-    static bool wait_for_device(Device& d) {
+    static bool wait_for_device(Device& d, int dev) {
+        int current = -1;   // (a weight may be destroyed with another device current, for which the wait would be)
+        if (hipGetDevice(&current) != hipSuccess || current != dev) return false;
         unsigned long long until;   // (blocks that other threads release during the wait are not covered)
         {
             std::lock_guard<std::mutex> lock(d.mutex);
