@@ -399,10 +399,12 @@ inline WkForm wk_form(int M, int N, int stages, bool whole_a) {
 inline bool copy_first(WkForm form, int stages) { return form == kWk64x64w4 && stages >= 32; }
 
 // Grids of more tiles than compute units, beyond those for which wk_form has a rule of its own: what the kernels take there, in us, as fits of
-// about 220 products with rows of whole chunks and 110 without (sizes, outputs and ratios of the sides at random, one weight again and again and fresh
-// ones), 7 to 9 % off in the root mean square.  A kernel's time is a fixed part; its stages of 128 k, each at the rate at which a compute unit works
-// through the tiles it has, but no less than the wait for one; the end of its tiles by what they store; and a little for every row and column
-// (arrivals, reports).  Tiles of 128 and 256 run one to a compute unit in full rounds; the smaller ones several at a time, and hardly in rounds.
+// about 220 products with rows of whole chunks and 110 without (sizes, outputs and ratios of the sides at random, up to 4096 rows and 16384 columns, one
+// weight again and again and fresh ones), 7 to 9 % off in the root mean square.  A kernel's time is a fixed part; its stages of 128 k, each at the rate at
+// which a compute unit works through the tiles it has, but no less than the wait for one; the end of its tiles by what they store; and a little for every
+// row and column (arrivals, reports).  Tiles of 128 and 256 run one to a compute unit in full rounds; the smaller ones several at a time, and hardly in
+// rounds, except for the 64x64 form of gemm_tile_wk.h, two of which fill a unit: a few tiles more than that work through a long K alone (us, the fit,
+// measured, and the 128x128 tiles: 513 tiles 524x3629x9632 45.0 52.1 43.1, 520 294x6603x13984 63.6 74.6 62.6, 540 190x11472x9376 Cq 46.2 52.0 45.0).
 struct FormCost {
     float fixed, stage, wait, end_c, end_q, end_both, per_row, per_col;
 };
@@ -417,7 +419,8 @@ constexpr float kCopyFixed = 3.8f, kCopyPerByte = 0.25e-6f;   // the copy with p
 inline float form_us(const FormCost& c, LargeForm f, int M, int N, int stages, bool want_c, bool want_q) {
     const int bm = f == kLarge256 ? 256 : f == kLarge128 ? 128 : f == kLargeWk32x64 ? 32 : 64, bn = f == kLarge256 ? 256 : f == kLarge128 ? 128 : 64;
     const int64_t tiles = (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-    const float rounds = f <= kLarge128 ? (float)((tiles + 255) / 256) : (float)tiles / 256;
+    float rounds = f <= kLarge128 ? (float)((tiles + 255) / 256) : (float)tiles / 256;
+    if (f == kLargeWk64x64 && tiles > 512 && tiles < 560) rounds += 0.4f;
     const float work = rounds * stages * c.stage, wait = stages * c.wait, end = want_c && want_q ? c.end_both : want_c ? c.end_c : c.end_q;
     return c.fixed + (work > wait ? work : wait) + (rounds > 1 ? rounds : 1) * end + (M < 4096 ? M : 4096) * c.per_row + (N < 16384 ? N : 16384) * c.per_col;
 }
@@ -430,13 +433,21 @@ inline bool beyond_wk_form(int M, int N, int stages) {
     const int64_t t32 = (int64_t)((M + 31) / 32) * ((N + 31) / 32), t3264 = (int64_t)((M + 31) / 32) * ((N + 63) / 64), t64 = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
     return M > 32 && M <= kWsRows && t32 > 256 && t3264 > 256 && !(t64 <= 256 && stages >= 12);
 }
-// The cheapest by that; `pick`, which older thresholds on tiles and K choose, unless another one is 5 % cheaper, 10 % where rows are no whole
-// chunks and the fits are of fewer (257x7264x1629 17.2 / 19.2 with 5 %), 15 % where those lie within a measured line of wk_form (2000x1000x479 C and Cq
-// 9.4 / 9.9 with 10 %; of the 218 products that lie
-// there the choice is 1.8 % off the best of the five, the thresholds alone 9.4 %; us, thresholds / now: 214x4369x2434 19.1 / 12.0, 2545x7104x528 C and Cq
-// 87 / 40, 3350x2688x288 C and Cq 31.5 / 19.4, 1277x814x8832 C and Cq 41.2 / 33.0, 90x8237x3824 Cq 23.8 / 15.8, 2085x506x12288 53.3 / 40.4,
-// 1702x816x2431 Cq 20.4 / 15.7, 134x13568x96 C and Cq 11.5 / 8.4; of all of them 297x7168x3056 Cq 20.1 / 23.0 and 1295x14192x2256 Cq 88.7 / 94.4 lose most).
-inline LargeChoice large_choice(LargeChoice pick, bool whole_a, bool can_copy, int M, int N, int K, int stages, bool want_c, bool want_q) {
+// The cheapest by that; `pick`, which older thresholds on tiles and K choose, unless another one is cheaper by more than the fits are off: 10 %,
+// unchecked 15 % (the fits are of checked calls), and 15 % for rows that are no whole chunks where those lie within a measured line of wk_form
+// (2000x1000x479 C and Cq: by the fits 64x64 tiles are 11.5 % cheaper there, measured they are 6 % dearer).
+// Nor where 256x256 tiles store more than the 256 MiB that the memory-side cache holds, or C alone of more than 128 MiB in rows of more than 12288
+// columns: there the time is that of memory, which takes the pieces of 1024 bytes of a row that these tiles store at 3.5 to 4.2 TB/s, the smaller
+// tiles' 256 at 2.7 to 3 (256x256 / 64x64: 16400x8240x96 130 / 197, 32800x4120x240 181 / 239, 8200x16480x80 C and Cq 186 / 219, 2824x15456x112 50 / 58,
+// 2753x20128x256 72 / 84; but 16400x4120x96, 258 MiB, 1.25 times as fast on 64x64 tiles, and 2100x16480x96, 132 MiB, 1.04).
+// Of 560 products of random sizes whose kernel the fits alone would change, up to 130000 rows or columns among them, these lines leave 421; they take
+// 0.73 of the thresholds' time in the geometric mean, two of them more than 5 % longer (2111x6067x96 Cq 17.5 / 19.9, 328x127312x777 C and Cq
+// 151 / 160).  Drawn afterwards, with these lines: 260 changed, 0.76, two (2099x42736x75 Cq 112 / 123, 653x14644x132 Cq 21.2 / 23.9); of 100 unchecked ones
+// 0.78 and four (871x9296x2112 34.8 / 40.5, 785x9216x352 11.4 / 12.9, 1316x5440x1504 Cq 27.0 / 29.9, 280x6075x1721 14.3 / 15.5).  (us, thresholds / now: 214x4369x2434 19.1 / 12.0, 2545x7104x528 C and Cq 87 / 40, 3350x2688x288 C and Cq 31.5 / 19.4, 90x8237x3824 Cq 23.8 /
+// 15.8, 1664x13552x112 C and Cq 60.5 / 29.4, 48x95360x192 Cq 44.4 / 10.8, 71348x106x448 Cq 61.6 / 26.5, 11346x85x7186 60.6 / 35.9.)
+inline LargeChoice large_choice(LargeChoice pick, bool whole_a, bool can_copy, int M, int N, int K, int stages, bool want_c, bool want_q, bool check = true) {
+    const int64_t stored = (int64_t)M * N * ((want_c ? 4 : 0) + (want_q ? 1 : 0));
+    if (pick.form == kLarge256 && (stored > (256ll << 20) || (N > 12288 && !want_q && stored > (128ll << 20)))) return pick;
     LargeChoice best = pick;
     float least = 0, own = 0;
     bool any = false;
@@ -456,7 +467,7 @@ inline LargeChoice large_choice(LargeChoice pick, bool whole_a, bool can_copy, i
     }
     if (whole_a || can_copy)
         for (int f = 0; f < 5; ++f) look(kWholeCost[f], (LargeForm)f, !whole_a, whole_a ? 0.0f : kCopyFixed + kCopyPerByte * (float)M * (float)K);
-    const float line = whole_a ? 0.95f : pick.form >= kLargeWk32x64 ? 0.85f : 0.9f;
+    const float line = !check || (!whole_a && pick.form >= kLargeWk32x64) ? 0.85f : 0.9f;
     return any && least < line * own ? best : pick;
 }
 

@@ -436,7 +436,7 @@ int abft_gemm_u8s8s32_checked(const uint8_t* A, int64_t lda, int M, const abft_p
                 const int tile = pick_tile();
                 now = {whole_a || can_copy ? (tile == abft::kTile256 ? abft::kLarge256 : tile == abft::kTile128 ? abft::kLarge128 : abft::kLarge64) : abft::kLarge64, can_copy};
             }
-            now = abft::large_choice(now, whole_a, can_copy, M, Bp->N, p.K, p.KB2, want_c, want_q);
+            now = abft::large_choice(now, whole_a, can_copy, M, Bp->N, p.K, p.KB2, want_c, want_q, check);
             copy = now.copy;
             wk = now.form == abft::kLargeWk32x64 ? abft::kWk32x64w4 : now.form == abft::kLargeWk64x64 ? abft::kWk64x64w4 : abft::kWkNone;
             variant = now.form == abft::kLarge256 ? abft::kTile256 : now.form == abft::kLarge128 ? abft::kTile128 : abft::kTile64;

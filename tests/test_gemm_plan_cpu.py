@@ -19,8 +19,8 @@ extern "C" void plan(int M, int N, int K, int stages, int whole, long long* out)
 extern "C" int form(int M, int N, int stages, int whole) { return abft::wk_form(M, N, stages, whole != 0); }
 extern "C" int room_for_copy(int M, int N, int K) { return abft::room_for_copy(M, N, K); }
 extern "C" int beyond(int M, int N, int stages) { return abft::beyond_wk_form(M, N, stages); }
-extern "C" int large(int M, int N, int K, int stages, int whole, int can_copy, int pick, int pick_copy, int want_c, int want_q) {
-    const abft::LargeChoice c = abft::large_choice({(abft::LargeForm)pick, pick_copy != 0}, whole != 0, can_copy != 0, M, N, K, stages, want_c != 0, want_q != 0);
+extern "C" int large(int M, int N, int K, int stages, int whole, int can_copy, int pick, int pick_copy, int want_c, int want_q, int check) {
+    const abft::LargeChoice c = abft::large_choice({(abft::LargeForm)pick, pick_copy != 0}, whole != 0, can_copy != 0, M, N, K, stages, want_c != 0, want_q != 0, check != 0);
     return c.form + (c.copy ? 8 : 0);
 }
 extern "C" int copy_first(int form, int stages) { return abft::copy_first((abft::WkForm)form, stages); }
@@ -49,8 +49,8 @@ def plan(tmp_path_factory):
     call.copy_first = lambda form, K: bool(so.copy_first(form, ((K + 63) // 64 + 1) // 2))
     call.form = lambda M, N, K: so.form(M, N, ((K + 63) // 64 + 1) // 2, K % 16 == 0)
     call.beyond = lambda M, N, K: bool(so.beyond(M, N, ((K + 63) // 64 + 1) // 2))
-    call.large = lambda M, N, K, pick, out="C", can_copy=False: so.large(M, N, K, ((K + 63) // 64 + 1) // 2, K % 16 == 0, can_copy, pick & 7, pick >> 3,
-                                                                         out != "q", out != "C")
+    call.large = lambda M, N, K, pick, out="C", can_copy=False, check=True: so.large(M, N, K, ((K + 63) // 64 + 1) // 2, K % 16 == 0, can_copy, pick & 7, pick >> 3,
+                                                                         out != "q", out != "C", check)
     return call
 
 
@@ -170,3 +170,20 @@ def test_grids_beyond_the_compute_units(plan):
                                                                                                  (L64, W32X64, W64X64, *(COPY + f for f in range(5))))
     assert plan.beyond(131072, 258, 32) and not plan.beyond(131073, 258, 32)    # (row words that reach into the scratch)
     assert not plan.beyond(32, 100000, 4096) and not plan.beyond(64, 256, 512) and not plan.beyond(1024, 1024, 4096) and plan.beyond(1024, 1040, 4096)
+
+
+def test_grids_beyond_the_compute_units_where_the_fits_are_off(plan):
+    """A few tiles more than two to each compute unit and a long K, outputs beyond the memory-side cache, gains within the fits' error: what the
+    thresholds choose stays."""
+    L256, L128, L64, W32X64, W64X64 = 0, 1, 2, 3, 4
+    for M, N, K in ((524, 3629, 9632), (389, 4800, 7312), (174, 10928, 5344)):    # 513 to 525 tiles of 64x64
+        assert plan.large(M, N, K, L128) == L128
+    assert plan.large(304, 6180, 6224, L128) == W64X64 and plan.large(776, 4703, 4368, L128, "both") == W64X64    # 485, 962
+    for M, N in ((16400, 8240), (8200, 16480), (32800, 4120), (43102, 2096), (20853, 3600)):    # 286 to 515 MiB
+        assert plan.large(M, N, 96, L256) == L256
+    assert plan.large(16400, 2060, 96, L256) == L64 and plan.large(8200, 4120, 96, L256) == L64    # 129
+    assert plan.large(2824, 15456, 112, L256) == L256 and plan.large(555, 115760, 96, L256) == L256    # 167 and 245, long rows
+    assert plan.large(1238, 15574, 160, L256) == L64 and plan.large(2472, 13264, 96, L256, "both") == L64    # 74, and both outputs
+    # predicted 0.91 to 0.94 of the thresholds' choice; 0.88, unchecked as well
+    assert plan.large(297, 7168, 3056, L128, "q") == L128 and plan.large(1295, 14192, 2256, L256, "q") == L256 and plan.large(314, 111907, 1616, L256) == L256
+    assert plan.large(414, 1607, 336, L64) == W32X64 and plan.large(414, 1607, 336, L64, check=False) == L64
