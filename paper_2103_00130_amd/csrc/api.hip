@@ -3,13 +3,12 @@
 #include <cstdarg>
 #include <cstdio>
 #include <atomic>
-#include <chrono>
 #include <cstring>
-#include <mutex>
 #include <new>
 
 #include "../../include/abft_gemm.h"
 #include "abft_internal.h"
+#include "kept_blocks.h"
 
 namespace {
 
@@ -36,152 +35,47 @@ int hip_fail(hipError_t e, const char* what) {
         if (e_ != hipSuccess) return hip_fail(e_, #expr);  \
     } while (0)
 
-// Blocks of destroyed weights, kept for weights to come.  A program that replaces weights while it runs pays more for hipMalloc and
-// hipFree of their blocks, and for the wait for the whole device that goes with them, than for encoding and packing them (4096x4096, us a
-// replacement with its first batch of 64 rows: 86 before, 30 with kept blocks; 900x700 45 and 28; packing in two kernels since takes 1 to 3 more off).
-//  * A freed block may still be read by work that was enqueued before.  It is used again only after a wait for the whole device, once
-//    for all blocks freed until then.  The wait is a hipFree of a few bytes, which waits for every stream of the device (documented, and
-//    measured on blocking, non-blocking and null streams) and, unlike hipDeviceSynchronize, leaves graphs alone that another thread
-//    captures - what hipFree of the block itself would do.
-//  * At most kMost blocks and kMostBytes a device; what does not fit is freed at once.  All are given back when the last weight on
-//    the device is destroyed, and when the device has no memory for a new one.
-class KeptBlocks {
-public:
-    // a block of at least `need` bytes on the current device `dev`; *size: its real size
-    hipError_t get(int dev, size_t need, void** out, size_t* size) {
-        hipError_t e = hipSuccess;
-        *out = nullptr;
-        if (Device* const d = of(dev)) {
-            bool found = take(*d, need, out, size);
-            if (!found && worth_a_wait(*d, need) && wait_for_device(*d, dev)) found = take(*d, need, out, size);
-            if (!found) {
-                e = hipMalloc(out, *size = need);
-                if (e == hipErrorOutOfMemory && give_back(*d)) {
-                    (void)hipGetLastError();
-                    e = hipMalloc(out, need);
-                }
-            }
-            if (e == hipSuccess) {
-                std::lock_guard<std::mutex> lock(d->mutex);
-                ++d->live;
-            }
-            return e;
-        }
-        return hipMalloc(out, *size = need);
+// What kept_blocks.h needs of a device.  The wait is a hipFree of a few bytes, which waits for every stream of the device (documented, and
+// measured on blocking, non-blocking and null streams) and, unlike hipDeviceSynchronize, leaves graphs alone that another thread captures - what
+// hipFree of the blocks themselves would do.
+struct DeviceMemory {
+    hipError_t allocate(void** out, size_t size) {
+        const hipError_t e = hipMalloc(out, size);
+        if (e == hipErrorOutOfMemory) (void)hipGetLastError();
+        return e;
     }
-    void put(int dev, void* block, size_t size) {
-        Device* const d = of(dev);
-        if (!d) {
-            (void)hipFree(block);
-            return;
-        }
-        bool last, kept = false, in_a_run = false;
-        {
-            std::lock_guard<std::mutex> lock(d->mutex);
-            last = --d->live == 0;
-            if (!last && d->n < kMost && size <= kMostBytes - d->bytes) {
-                d->blocks[d->n++] = {block, size, ++d->released, false};
-                d->bytes += size;
-                kept = true;
-                in_a_run = d->since_last < kRun;
-            }
-        }
-        if (last) (void)give_back(*d);
-        if (!kept) (void)hipFree(block);
-        else if (!in_a_run) (void)wait_for_device(*d, dev);
-    }
-
-private:
-    static constexpr int kMost = 16, kDevices = 64;
-    static constexpr size_t kMostBytes = 256u << 20;
-    static constexpr std::chrono::microseconds kRun{50};   // between the weights of a run, at most (25 to 30 where it is measured; made and used one by one 80 and more)
-    struct Block {
-        void* at;
-        size_t size;
-        unsigned long long number;   // of its release
-        bool idle;                   // a wait for the device lies behind that
-    };
-    struct Device {
-        std::mutex mutex;
-        Block blocks[kMost];
-        int n = 0;
-        size_t bytes = 0;
-        unsigned long long released = 0;
-        long long live = 0;   // blocks in use
-        std::chrono::steady_clock::time_point last{};   // when the last block was asked for, and how long after the one before
-        std::chrono::steady_clock::duration since_last = std::chrono::hours(1);
-    };
-    Device devices_[kDevices];
-
-    Device* of(int dev) { return dev >= 0 && dev < kDevices ? &devices_[dev] : nullptr; }
-    static bool fits(const Block& b, size_t need) { return b.size >= need && b.size - need <= need / 4; }
-    static void drop(Device& d, int i) {
-        d.bytes -= d.blocks[i].size;
-        d.blocks[i] = d.blocks[--d.n];
-    }
-    static bool take(Device& d, size_t need, void** out, size_t* size) {
-        std::lock_guard<std::mutex> lock(d.mutex);
-        const auto now = std::chrono::steady_clock::now();
-        d.since_last = now - d.last;
-        d.last = now;
-        for (int i = 0; i < d.n; ++i)
-            if (d.blocks[i].idle && fits(d.blocks[i], need)) {
-                *out = d.blocks[i].at;
-                *size = d.blocks[i].size;
-                drop(d, i);
-                return true;
-            }
-        return false;
-    }
-    // (A wait costs 10 us on an idle device and 60 to 90 where weights are replaced one after the other, for one block or for many; a further block
-    // that the device has not had yet 60 to 250.  So the wait for a weight replaced now and then comes as it is destroyed, where hipFree had it, and in a
-    // run of them another block is allocated as long as there is room.)
-    static bool worth_a_wait(Device& d, size_t need) {
-        std::lock_guard<std::mutex> lock(d.mutex);
-        if (d.n < kMost && need <= kMostBytes - d.bytes && d.since_last < kRun) return false;
-        for (int i = 0; i < d.n; ++i)
-            if (!d.blocks[i].idle && fits(d.blocks[i], need)) return true;
-        return false;
-    }
-    static bool wait_for_device(Device& d, int dev) {
-        int current = -1;   // (a weight may be destroyed with another device current, for which the wait would be)
-        if (hipGetDevice(&current) != hipSuccess || current != dev) return false;
-        unsigned long long until;   // (blocks that other threads release during the wait are not covered)
-        {
-            std::lock_guard<std::mutex> lock(d.mutex);
-            until = d.released;
-        }
+    void release(void* block) { (void)hipFree(block); }
+    bool wait() {
         void* p = nullptr;
-        if (hipMalloc(&p, 256) != hipSuccess || hipFree(p) != hipSuccess) {
-            (void)hipGetLastError();
-            return false;
-        }
-        std::lock_guard<std::mutex> lock(d.mutex);
-        for (int i = 0; i < d.n; ++i) d.blocks[i].idle |= d.blocks[i].number <= until;
-        return true;
-    }
-    static bool give_back(Device& d) {
-        Block blocks[kMost];
-        int n;
-        {
-            std::lock_guard<std::mutex> lock(d.mutex);
-            n = d.n;
-            for (int i = 0; i < n; ++i) blocks[i] = d.blocks[i];
-            d.n = 0;
-            d.bytes = 0;
-        }
-        for (int i = 0; i < n; ++i) (void)hipFree(blocks[i].at);
-        return n > 0;
+        if (hipMalloc(&p, 256) == hipSuccess && hipFree(p) == hipSuccess) return true;
+        (void)hipGetLastError();
+        return false;
     }
 };
-KeptBlocks& kept_blocks() {
-    static KeptBlocks* const k = new KeptBlocks;   // (lives as long as the process: weights may be destroyed at its very end)
-    return *k;
+using Kept = abft::KeptBlocks<DeviceMemory>;
+// of the device, or null beyond the ones that blocks are kept for
+Kept* kept_blocks(int dev) {
+    static Kept* const k = new Kept[64];   // (live as long as the process: weights may be destroyed at its very end)
+    return dev >= 0 && dev < 64 ? &k[dev] : nullptr;
+}
+
+// a block on the current device, `dev`, for a weight that is packed on `s`
+hipError_t get_block(int dev, hipStream_t s, size_t need, void** out, size_t* size) {
+    Kept* const kept = kept_blocks(dev);
+    if (!kept) return hipMalloc(out, *size = need);
+    return kept->get(need, out, size, [s] {
+        const bool idle = hipStreamQuery(s) == hipSuccess;
+        if (!idle) (void)hipGetLastError();
+        return idle;
+    });
 }
 
 void free_handle(abft_packed_b* h) {
     if (!h) return;
-    if (h->packed) kept_blocks().put(h->device, h->packed, h->block_bytes);   // (one block holds everything)
+    if (h->packed) {   // (one block holds everything)
+        if (Kept* const kept = kept_blocks(h->device)) kept->put(h->packed, h->block_bytes);
+        else (void)hipFree(h->packed);
+    }
     delete h;
 }
 
@@ -227,7 +121,7 @@ int abft_pack_b_checksum(const int8_t* B, int64_t ldb, int K, int N, int b_is_tr
     const size_t part_ints = abft::pack_parts(h->KB, h->NT), o_parts = o_sb127 + up(k_ints);
     if (e == hipSuccess) {
         void* block = nullptr;
-        e = kept_blocks().get(h->device, o_parts + part_ints * sizeof(int32_t), &block, &h->block_bytes);
+        e = get_block(h->device, (hipStream_t)stream, o_parts + part_ints * sizeof(int32_t), &block, &h->block_bytes);
         h->packed = (int8_t*)block;
     }
     if (e == hipSuccess) {

@@ -1,0 +1,127 @@
+// Blocks of destroyed weights, kept for weights to come (host code, one object per device).  A program that replaces weights while it
+// runs pays more for hipMalloc and hipFree of their blocks, and for the wait for the whole device that goes with them, than for encoding and packing them.
+#pragma once
+#include <hip/hip_runtime_api.h>
+
+#include <cstddef>
+#include <mutex>
+
+namespace abft {
+
+// A freed block may still be read by work that was enqueued before.  It is used again only after a wait for the whole device, once for all
+// blocks freed until then.  When that wait comes is decided by counts alone: a block that fits and has been waited for is taken at once; else, if
+// kMostWaiting blocks that fit have not been, if there is no room to keep another one, or if the caller says that the device seems to be idle, the
+// device is waited for; else another block is allocated.  So a weight replaced again and again settles at kMostWaiting blocks and a wait for as many
+// replacements, at whatever rate, and one replaced while the device idles at a single block.
+// Measured, us a replacement with its first batch (64 rows of 4096x4096, 32 of 700x900), hipMalloc and hipFree / this: back to back 69 and 36 / 31 and 28, 100 us of
+// other host work between them 81 and 39 / 31 and 30, 1 ms 87 and 40 / 32 and 33 (a wait by the time since the last replacement, with a limit of 50 us, took 33 and
+// 27, 43 and 38, 43 and 38, and 68 for 8192x8192, whose packing alone takes that long, / 66).  The wait takes 10 us on an idle device and 60 to 90 on a busy
+// one, for one block or for eight; a block that the device has not had yet 60 to 250.
+//
+// Memory: allocate(void**, size_t) and release(void*) as hipMalloc and hipFree, wait(): true once everything enqueued on the device before the call has ended.
+template <class Memory>
+class KeptBlocks {
+public:
+    static constexpr int kMost = 16, kMostWaiting = 8;
+    static constexpr size_t kMostBytes = 256u << 20;
+
+    explicit KeptBlocks(Memory memory = Memory()) : memory_(memory) {}
+
+    // a block of at least `need` bytes; *size: its real size.  idle(): whether the device seems to be (a wrong answer costs time, no more)
+    template <class Idle>
+    hipError_t get(size_t need, void** out, size_t* size, Idle idle) {
+        *out = nullptr;
+        if (take(need, out, size)) return hipSuccess;
+        if (const int waiting = count_waiting(need)) {
+            if ((waiting >= kMostWaiting || !has_room(need) || idle()) && wait() && take(need, out, size)) return hipSuccess;
+        }
+        hipError_t e = memory_.allocate(out, *size = need);
+        if (e == hipErrorOutOfMemory && give_back()) e = memory_.allocate(out, need);
+        if (e == hipSuccess) {
+            std::lock_guard<std::mutex> lock(mutex_);
+            ++live_;
+        }
+        return e;
+    }
+    // the block of a weight that is destroyed
+    void put(void* block, size_t size) {
+        bool last, kept = false;
+        {
+            std::lock_guard<std::mutex> lock(mutex_);
+            last = --live_ == 0;
+            if (!last && n_ < kMost && size <= kMostBytes - bytes_) {
+                blocks_[n_++] = {block, size, ++released_, false};
+                bytes_ += size;
+                kept = true;
+            }
+        }
+        if (last) (void)give_back();
+        if (!kept) memory_.release(block);
+    }
+
+private:
+    struct Block {
+        void* at;
+        size_t size;
+        unsigned long long number;   // of its release
+        bool idle;                   // a wait for the device lies behind that
+    };
+    Memory memory_;
+    std::mutex mutex_;
+    Block blocks_[kMost];
+    int n_ = 0;
+    size_t bytes_ = 0;
+    unsigned long long released_ = 0;
+    long long live_ = 0;   // blocks in use
+
+    static bool fits(const Block& b, size_t need) { return b.size >= need && b.size - need <= need / 4; }
+    bool take(size_t need, void** out, size_t* size) {
+        std::lock_guard<std::mutex> lock(mutex_);
+        for (int i = 0; i < n_; ++i)
+            if (blocks_[i].idle && fits(blocks_[i], need)) {
+                *out = blocks_[i].at;
+                *size = blocks_[i].size;
+                bytes_ -= blocks_[i].size;
+                blocks_[i] = blocks_[--n_];
+                ++live_;
+                return true;
+            }
+        return false;
+    }
+    int count_waiting(size_t need) {
+        std::lock_guard<std::mutex> lock(mutex_);
+        int n = 0;
+        for (int i = 0; i < n_; ++i) n += !blocks_[i].idle && fits(blocks_[i], need);
+        return n;
+    }
+    bool has_room(size_t need) {
+        std::lock_guard<std::mutex> lock(mutex_);
+        return n_ < kMost && need <= kMostBytes - bytes_;
+    }
+    bool wait() {
+        unsigned long long until;   // (blocks that other threads release during the wait are not covered)
+        {
+            std::lock_guard<std::mutex> lock(mutex_);
+            until = released_;
+        }
+        if (!memory_.wait()) return false;
+        std::lock_guard<std::mutex> lock(mutex_);
+        for (int i = 0; i < n_; ++i) blocks_[i].idle |= blocks_[i].number <= until;
+        return true;
+    }
+    bool give_back() {
+        Block blocks[kMost];
+        int n;
+        {
+            std::lock_guard<std::mutex> lock(mutex_);
+            n = n_;
+            for (int i = 0; i < n; ++i) blocks[i] = blocks_[i];
+            n_ = 0;
+            bytes_ = 0;
+        }
+        for (int i = 0; i < n; ++i) memory_.release(blocks[i].at);
+        return n > 0;
+    }
+};
+
+}  // namespace abft

@@ -1552,6 +1552,41 @@ def test_weights_replaced_while_others_are_in_use(binding, gpu_util, oracle):
     assert torch.cuda.mem_get_info()[0] >= free0 - (96 << 20)    # (torch's own pools of the new streams; six blocks of 74 MB were there)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("late", [False, True])
+def test_weights_replaced_back_to_back(binding, gpu_util, oracle, late):
+    """Replacements with nothing else between them, each used once on another stream: the kept blocks run full, and the one wait that follows comes
+    before any of them is written again.  late: that stream has work of some milliseconds ahead of the first product."""
+    import torch
+
+    say(f"weights replaced back to back, late={late}")
+    M, N, K = 24, 700, 1500
+    rng = np.random.default_rng(6)
+    A = rng.integers(0, 256, size=(M, K), dtype=np.uint8)
+    weights = [rng.integers(-127, 128, size=(K, N), dtype=np.int8) for _ in range(5)]
+    wants = [torch.from_numpy(oracle.checked_gemm(A, B).C).cuda() for B in weights]
+    A_dev, B_dev = gpu_util.dev(A), [gpu_util.dev(B) for B in weights]
+    Bp = binding.abft_pack_b_checksum(B_dev[0])
+    ws = binding.Workspace(M, Bp)
+    C = [torch.full((M, N), -7, dtype=torch.int32, device="cuda") for _ in range(60)]
+    flags = [torch.full((M,), -1, dtype=torch.int32, device="cuda") for _ in C]
+    side = torch.cuda.Stream()
+    busy = torch.zeros(1 << 28, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    if late:
+        with torch.cuda.stream(side):
+            for _ in range(30):
+                busy.add_(1)
+    for r in range(len(C)):
+        Bp = binding.abft_pack_b_checksum(B_dev[r % len(weights)])
+        side.wait_stream(torch.cuda.current_stream())
+        binding.abft_gemm_u8s8s32_checked(A_dev, Bp, C[r], flags[r], None, workspace=ws.tensor, stream=side)
+    torch.cuda.synchronize()
+    for r in range(len(C)):
+        assert torch.equal(C[r], wants[r % len(weights)]), r
+        assert not bool(flags[r].any()), r
+
+
 # (the tiles' sums added up afterwards, in whole and half blocks of 256 k, and by atomics: on either side of the line between them)
 @pytest.mark.gpu
 @pytest.mark.parametrize("transposed", [False, True])

@@ -1,0 +1,172 @@
+"""Which blocks of destroyed weights are used again, and when the device is waited for (csrc/kept_blocks.h, host code), on a simulated device."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2103_00130_amd", "csrc")
+SRC = """
+#include <map>
+#include "kept_blocks.h"
+struct Device {                       // blocks are numbers from 1 on
+    std::map<long, size_t> held;
+    std::map<long, long> put_at;      // time of its last release by its weight
+    long next = 1, now = 0, waited = -1, allocations = 0, releases = 0, waits = 0, early = 0;
+    size_t bytes = 0, most = ~(size_t)0;
+    int idle = 0;
+};
+struct Memory {
+    Device* d = nullptr;
+    hipError_t allocate(void** out, size_t size) {
+        if (d->bytes + size > d->most) return hipErrorOutOfMemory;
+        d->held[d->next] = size;
+        d->bytes += size;
+        ++d->allocations;
+        *out = (void*)d->next++;
+        return hipSuccess;
+    }
+    void release(void* p) {
+        d->bytes -= d->held.at((long)p);
+        d->held.erase((long)p);
+        ++d->releases;
+        d->waited = d->now++;         // (hipFree waits for the device)
+    }
+    bool wait() {
+        ++d->waits;
+        d->waited = d->now++;
+        return true;
+    }
+};
+struct Sim {
+    Device d;
+    abft::KeptBlocks<Memory> kept{Memory{&d}};
+};
+extern "C" {
+Sim* make() { return new Sim; }
+void drop(Sim* s) { delete s; }
+void set(Sim* s, int idle, size_t most) { s->d.idle = idle; s->d.most = most; }
+long get(Sim* s, size_t need, size_t* size) {
+    void* p = nullptr;
+    if (s->kept.get(need, &p, size, [s] { return s->d.idle != 0; }) != hipSuccess) return 0;
+    const long b = (long)p;
+    if (s->d.held.at(b) != *size || *size < need) return -1;
+    if (s->d.put_at.count(b) && s->d.put_at[b] > s->d.waited) ++s->d.early;    // handed out before a wait
+    return b;
+}
+void put(Sim* s, long b, size_t size) {
+    s->d.put_at[b] = s->d.now++;
+    s->kept.put((void*)b, size);
+}
+void counts(Sim* s, long* out) {
+    const long v[] = {s->d.allocations, s->d.releases, s->d.waits, s->d.early, (long)s->d.held.size(), (long)s->d.bytes};
+    for (int i = 0; i < 6; ++i) out[i] = v[i];
+}
+}
+"""
+MIB = 1 << 20
+
+
+@pytest.fixture(scope="module")
+def so(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("kept") / "kept.so")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-shared", "-fPIC", f"-I{CSRC}", f"-I{rocm}/include", "-x", "c++", "-",
+                    "-o", lib], input=SRC, text=True, check=True)
+    so = ctypes.CDLL(lib)
+    so.make.restype = ctypes.c_void_p
+    so.drop.argtypes = [ctypes.c_void_p]
+    so.set.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_size_t]
+    so.get.argtypes = [ctypes.c_void_p, ctypes.c_size_t, ctypes.POINTER(ctypes.c_size_t)]
+    so.get.restype = ctypes.c_long
+    so.put.argtypes = [ctypes.c_void_p, ctypes.c_long, ctypes.c_size_t]
+    so.counts.argtypes = [ctypes.c_void_p, ctypes.POINTER(ctypes.c_long)]
+    return so
+
+
+class Sim:
+    def __init__(self, so):
+        self.so, self.at = so, so.make()
+
+    def idle(self, idle, most=(1 << 64) - 1):
+        self.so.set(self.at, idle, most)
+
+    def pack(self, need):
+        size = ctypes.c_size_t()
+        b = self.so.get(self.at, need, ctypes.byref(size))
+        assert b >= 0
+        return (b, size.value) if b else None
+
+    def destroy(self, weight):
+        self.so.put(self.at, *weight)
+
+    def replace(self, weight, need=None):
+        new = self.pack(need or weight[1])
+        self.destroy(weight)
+        return new
+
+    @property
+    def n(self):
+        v = (ctypes.c_long * 6)()
+        self.so.counts(self.at, v)
+        d = dict(zip(("allocations", "releases", "waits", "early", "held", "bytes"), v))
+        assert d["early"] == 0, "a block was handed out that the device had not been waited for since its release"
+        return d
+
+
+@pytest.fixture
+def sim(so):
+    s = Sim(so)
+    yield s
+    so.drop(s.at)
+
+
+def test_a_weight_replaced_again_and_again_waits_once_for_several(sim):
+    """The same whatever the rate: nothing but the blocks counts."""
+    w = sim.pack(16 * MIB)
+    waits = []
+    for i in range(200):
+        before = sim.n["waits"]
+        w = sim.replace(w)
+        waits.append(sim.n["waits"] - before)
+    assert max(waits) == 1 and sum(waits[20:]) <= 180 // 8 + 1
+    assert not any(a and b for a, b in zip(waits, waits[1:]))
+    assert sim.n["allocations"] == 9 and sim.n["releases"] == 0    # eight and the one in use, no more
+
+
+def test_a_weight_replaced_on_an_idle_device_keeps_one_block(sim):
+    sim.idle(1)
+    w = sim.pack(16 * MIB)
+    for i in range(50):
+        w = sim.replace(w)
+    n = sim.n
+    assert n["allocations"] == 2 and n["held"] == 2 and n["waits"] == 49
+    sim.idle(0)    # then a run of them
+    for i in range(100):
+        w = sim.replace(w)
+    assert sim.n["allocations"] == 9 and sim.n["waits"] - n["waits"] <= 100 // 8 + 1
+
+
+def test_large_blocks(sim):
+    w = sim.pack(100 * MIB)    # two of them may be kept
+    for i in range(30):
+        w = sim.replace(w)
+    assert sim.n["allocations"] == 3 and sim.n["waits"] == 14
+    big = sim.pack(300 * MIB)
+    big = sim.replace(big)
+    assert sim.n["releases"] == 1    # more than is kept
+    sim.destroy(w)
+    sim.destroy(big)
+    n = sim.n
+    assert n["held"] == 0 and n["bytes"] == 0 and n["releases"] == n["allocations"]    # all given back with the last weight
+
+
+def test_no_memory_for_a_new_block(sim):
+    a, b = sim.pack(10 * MIB), sim.pack(50 * MIB)
+    sim.destroy(a)
+    sim.idle(0, 90 * MIB)
+    c = sim.pack(40 * MIB)    # (the kept ten are given back)
+    assert c and sim.n["held"] == 2
+    assert sim.pack(40 * MIB) is None
+    sim.destroy(b)
+    assert sim.pack(40 * MIB)
