@@ -44,7 +44,11 @@ struct DeviceMemory {
         if (e == hipErrorOutOfMemory) (void)hipGetLastError();
         return e;
     }
-    void release(void* block) { (void)hipFree(block); }
+    bool release(void* block) {
+        if (hipFree(block) == hipSuccess) return true;
+        (void)hipGetLastError();
+        return false;
+    }
     bool wait() {
         void* p = nullptr;
         if (hipMalloc(&p, 256) == hipSuccess && hipFree(p) == hipSuccess) return true;
@@ -73,7 +77,8 @@ hipError_t get_block(int dev, hipStream_t s, size_t need, void** out, size_t* si
 void free_handle(abft_packed_b* h) {
     if (!h) return;
     if (h->packed) {   // (one block holds everything)
-        if (Kept* const kept = kept_blocks(h->device)) kept->put(h->packed, h->block_bytes);
+        int current = -1;   // (a weight may be destroyed with another device current)
+        if (Kept* const kept = kept_blocks(h->device)) kept->put(h->packed, h->block_bytes, hipGetDevice(&current) == hipSuccess && current == h->device);
         else (void)hipFree(h->packed);
     }
     delete h;

@@ -18,11 +18,12 @@ namespace abft {
 // 27, 43 and 38, 43 and 38, and 68 for 8192x8192, whose packing alone takes that long, / 66).  The wait takes 10 us on an idle device and 60 to 90 on a busy
 // one, for one block or for eight; a block that the device has not had yet 60 to 250.
 //
-// Memory: allocate(void**, size_t) and release(void*) as hipMalloc and hipFree, wait(): true once everything enqueued on the device before the call has ended.
+// Memory: allocate(void**, size_t) as hipMalloc; wait() and release(void*): true once everything that was enqueued on the device before the call has
+// ended, and the block given back.
 template <class Memory>
 class KeptBlocks {
 public:
-    static constexpr int kMost = 16, kMostWaiting = 8;
+    static constexpr int kMost = 16, kMostWaiting = 8, kStale = 2 * kMost;
     static constexpr size_t kMostBytes = 256u << 20;
 
     explicit KeptBlocks(Memory memory = Memory()) : memory_(memory) {}
@@ -43,20 +44,34 @@ public:
         }
         return e;
     }
-    // the block of a weight that is destroyed
-    void put(void* block, size_t size) {
-        bool last, kept = false;
+    // the block of a weight that is destroyed; here: with its device current.  Where there is no room for it, blocks that have lain unused while
+    // kStale others came make room; not younger ones, of which a program that replaces several weights in turn will need the oldest next
+    void put(void* block, size_t size, bool here) {
+        void* out[kMost + 1];
+        int n_out = 0;
+        bool last;
+        unsigned long long until;
         {
             std::lock_guard<std::mutex> lock(mutex_);
             last = --live_ == 0;
-            if (!last && n_ < kMost && size <= kMostBytes - bytes_) {
-                blocks_[n_++] = {block, size, ++released_, false};
+            ++released_;
+            if (!last && size <= kMostBytes)
+                for (int i = oldest(); !room(size) && stale(i); i = oldest()) {
+                    out[n_out++] = blocks_[i].at;
+                    drop(i);
+                }
+            if (!last && room(size)) {
+                blocks_[n_++] = {block, size, released_, false};
                 bytes_ += size;
-                kept = true;
+            } else {
+                out[n_out++] = block;
             }
+            until = released_;
         }
         if (last) (void)give_back();
-        if (!kept) memory_.release(block);
+        bool freed = n_out > 0;
+        for (int i = 0; i < n_out; ++i) freed &= memory_.release(out[i]);
+        if (freed && here) waited(until);   // (to give a block back is a wait for the device, where it is not refused: another thread may capture a graph)
     }
 
 private:
@@ -74,6 +89,18 @@ private:
     unsigned long long released_ = 0;
     long long live_ = 0;   // blocks in use
 
+    bool room(size_t size) const { return n_ < kMost && size <= kMostBytes - bytes_; }
+    int oldest() const {
+        int o = 0;
+        for (int i = 1; i < n_; ++i)
+            if (blocks_[i].number < blocks_[o].number) o = i;
+        return o;
+    }
+    bool stale(int i) const { return i < n_ && released_ - blocks_[i].number >= kStale; }
+    void drop(int i) {
+        bytes_ -= blocks_[i].size;
+        blocks_[i] = blocks_[--n_];
+    }
     static bool fits(const Block& b, size_t need) { return b.size >= need && b.size - need <= need / 4; }
     bool take(size_t need, void** out, size_t* size) {
         std::lock_guard<std::mutex> lock(mutex_);
@@ -81,8 +108,7 @@ private:
             if (blocks_[i].idle && fits(blocks_[i], need)) {
                 *out = blocks_[i].at;
                 *size = blocks_[i].size;
-                bytes_ -= blocks_[i].size;
-                blocks_[i] = blocks_[--n_];
+                drop(i);
                 ++live_;
                 return true;
             }
@@ -94,9 +120,9 @@ private:
         for (int i = 0; i < n_; ++i) n += !blocks_[i].idle && fits(blocks_[i], need);
         return n;
     }
-    bool has_room(size_t need) {
+    bool has_room(size_t need) {   // (now, or once a stale block is gone)
         std::lock_guard<std::mutex> lock(mutex_);
-        return n_ < kMost && need <= kMostBytes - bytes_;
+        return room(need) || (need <= kMostBytes && stale(oldest()));
     }
     bool wait() {
         unsigned long long until;   // (blocks that other threads release during the wait are not covered)
@@ -105,9 +131,12 @@ private:
             until = released_;
         }
         if (!memory_.wait()) return false;
+        waited(until);
+        return true;
+    }
+    void waited(unsigned long long until) {
         std::lock_guard<std::mutex> lock(mutex_);
         for (int i = 0; i < n_; ++i) blocks_[i].idle |= blocks_[i].number <= until;
-        return true;
     }
     bool give_back() {
         Block blocks[kMost];
@@ -119,7 +148,7 @@ private:
             n_ = 0;
             bytes_ = 0;
         }
-        for (int i = 0; i < n; ++i) memory_.release(blocks[i].at);
+        for (int i = 0; i < n; ++i) (void)memory_.release(blocks[i].at);
         return n > 0;
     }
 };

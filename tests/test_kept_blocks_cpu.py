@@ -14,7 +14,7 @@ struct Device {                       // blocks are numbers from 1 on
     std::map<long, long> put_at;      // time of its last release by its weight
     long next = 1, now = 0, waited = -1, allocations = 0, releases = 0, waits = 0, early = 0;
     size_t bytes = 0, most = ~(size_t)0;
-    int idle = 0;
+    int idle = 0, refuses = 0;
 };
 struct Memory {
     Device* d = nullptr;
@@ -26,13 +26,16 @@ struct Memory {
         *out = (void*)d->next++;
         return hipSuccess;
     }
-    void release(void* p) {
+    bool release(void* p) {
+        if (d->refuses) return false;
         d->bytes -= d->held.at((long)p);
         d->held.erase((long)p);
         ++d->releases;
         d->waited = d->now++;         // (hipFree waits for the device)
+        return true;
     }
     bool wait() {
+        if (d->refuses) return false;
         ++d->waits;
         d->waited = d->now++;
         return true;
@@ -45,7 +48,7 @@ struct Sim {
 extern "C" {
 Sim* make() { return new Sim; }
 void drop(Sim* s) { delete s; }
-void set(Sim* s, int idle, size_t most) { s->d.idle = idle; s->d.most = most; }
+void set(Sim* s, int idle, size_t most, int refuses) { s->d.idle = idle; s->d.most = most; s->d.refuses = refuses; }
 long get(Sim* s, size_t need, size_t* size) {
     void* p = nullptr;
     if (s->kept.get(need, &p, size, [s] { return s->d.idle != 0; }) != hipSuccess) return 0;
@@ -56,7 +59,7 @@ long get(Sim* s, size_t need, size_t* size) {
 }
 void put(Sim* s, long b, size_t size) {
     s->d.put_at[b] = s->d.now++;
-    s->kept.put((void*)b, size);
+    s->kept.put((void*)b, size, true);
 }
 void counts(Sim* s, long* out) {
     const long v[] = {s->d.allocations, s->d.releases, s->d.waits, s->d.early, (long)s->d.held.size(), (long)s->d.bytes};
@@ -76,7 +79,7 @@ def so(tmp_path_factory):
     so = ctypes.CDLL(lib)
     so.make.restype = ctypes.c_void_p
     so.drop.argtypes = [ctypes.c_void_p]
-    so.set.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_size_t]
+    so.set.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_size_t, ctypes.c_int]
     so.get.argtypes = [ctypes.c_void_p, ctypes.c_size_t, ctypes.POINTER(ctypes.c_size_t)]
     so.get.restype = ctypes.c_long
     so.put.argtypes = [ctypes.c_void_p, ctypes.c_long, ctypes.c_size_t]
@@ -88,8 +91,8 @@ class Sim:
     def __init__(self, so):
         self.so, self.at = so, so.make()
 
-    def idle(self, idle, most=(1 << 64) - 1):
-        self.so.set(self.at, idle, most)
+    def idle(self, idle, most=(1 << 64) - 1, refuses=0):
+        self.so.set(self.at, idle, most, refuses)
 
     def pack(self, need):
         size = ctypes.c_size_t()
@@ -159,6 +162,56 @@ def test_large_blocks(sim):
     sim.destroy(big)
     n = sim.n
     assert n["held"] == 0 and n["bytes"] == 0 and n["releases"] == n["allocations"]    # all given back with the last weight
+
+
+def test_blocks_of_weights_that_are_gone_make_room(sim):
+    """Sixteen weights of other sizes are destroyed; the one that goes on to be replaced gets blocks of its own size all the same."""
+    other = [sim.pack((1 + i) * MIB * 2) for i in range(15)] + [sim.pack(300000)]    # 240 MiB
+    w = sim.pack(7 * MIB + 4096)
+    for b in other:
+        sim.destroy(b)
+    for i in range(48):    # (they are given back one by one once 32 releases lie behind theirs)
+        w = sim.replace(w)
+    before = sim.n
+    for i in range(100):
+        w = sim.replace(w)
+    n = sim.n
+    assert n["allocations"] - before["allocations"] <= 4 and n["releases"] - before["releases"] <= 4
+    assert n["waits"] - before["waits"] <= 100 // 8 + 1
+
+
+@pytest.mark.parametrize("weights", [2, 5, 10, 16, 24])
+def test_weights_of_several_sizes_replaced_in_turn(sim, weights):
+    w = [sim.pack((1 + i) * MIB // 2) for i in range(weights)]
+    for i in range(10 * weights):
+        w[i % weights] = sim.replace(w[i % weights])
+    before = sim.n
+    rounds = 50
+    for i in range(rounds * weights):
+        w[i % weights] = sim.replace(w[i % weights])
+    n = sim.n
+    assert n["allocations"] - before["allocations"] <= rounds * weights // 20
+    assert n["waits"] - before["waits"] <= 2 * rounds and n["bytes"] - sum(b[1] for b in w) <= 256 * MIB
+
+
+def test_sizes_that_come_once(sim):
+    w = sim.pack(MIB)
+    for i in range(200):
+        sim.destroy(sim.pack((40 + 3 * i % 200) * MIB))
+        n = sim.n
+        assert n["held"] <= 17 and n["bytes"] <= 256 * MIB + w[1]
+
+
+def test_a_wait_that_is_refused_makes_nothing_idle(sim):
+    """As while another thread captures a graph: what has not been waited for is not handed out (Sim.n looks)."""
+    w = sim.pack(100 * MIB)
+    sim.idle(0, refuses=1)
+    for i in range(10):
+        w = sim.replace(w)
+    assert sim.n["waits"] == 0 and sim.n["allocations"] == 11
+    sim.idle(1)
+    w = sim.replace(w)
+    assert sim.n["waits"] == 1 and sim.n["allocations"] == 11
 
 
 def test_no_memory_for_a_new_block(sim):
