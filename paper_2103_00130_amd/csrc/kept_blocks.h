@@ -47,7 +47,7 @@ public:
     // the block of a weight that is destroyed; here: with its device current.  Where there is no room for it, blocks that have lain unused while
     // kStale others came make room; not younger ones, of which a program that replaces several weights in turn will need the oldest next
     void put(void* block, size_t size, bool here) {
-        void* out[kMost + 1];
+        Block out[kMost + 1];
         int n_out = 0;
         bool last;
         unsigned long long until;
@@ -57,21 +57,15 @@ public:
             ++released_;
             if (!last && size <= kMostBytes)
                 for (int i = oldest(); !room(size) && stale(i); i = oldest()) {
-                    out[n_out++] = blocks_[i].at;
+                    out[n_out++] = blocks_[i];
                     drop(i);
                 }
-            if (!last && room(size)) {
-                blocks_[n_++] = {block, size, released_, false};
-                bytes_ += size;
-            } else {
-                out[n_out++] = block;
-            }
+            if (!last && room(size)) add({block, size, released_, false});
+            else out[n_out++] = {block, size, released_, false};
             until = released_;
         }
         if (last) (void)give_back();
-        bool freed = n_out > 0;
-        for (int i = 0; i < n_out; ++i) freed &= memory_.release(out[i]);
-        if (freed && here) waited(until);   // (to give a block back is a wait for the device, where it is not refused: another thread may capture a graph)
+        if (n_out > 0 && release(out, n_out) && here) waited(until);   // (to give a block back is a wait for the device)
     }
 
 private:
@@ -97,6 +91,10 @@ private:
         return o;
     }
     bool stale(int i) const { return i < n_ && released_ - blocks_[i].number >= kStale; }
+    void add(const Block& b) {
+        blocks_[n_++] = b;
+        bytes_ += b.size;
+    }
     void drop(int i) {
         bytes_ -= blocks_[i].size;
         blocks_[i] = blocks_[--n_];
@@ -148,8 +146,18 @@ private:
             n_ = 0;
             bytes_ = 0;
         }
-        for (int i = 0; i < n; ++i) (void)memory_.release(blocks[i].at);
-        return n > 0;
+        return n > 0 && release(blocks, n);
+    }
+    // (refused, as hipFree is while another thread captures a graph in a mode that forbids it: kept after all, as far as there is room)
+    bool release(const Block* blocks, int n) {
+        bool all = true;
+        for (int i = 0; i < n; ++i)
+            if (!memory_.release(blocks[i].at)) {
+                std::lock_guard<std::mutex> lock(mutex_);
+                if (room(blocks[i].size)) add(blocks[i]);
+                all = false;
+            }
+        return all;
     }
 };
 

@@ -214,6 +214,20 @@ def test_a_wait_that_is_refused_makes_nothing_idle(sim):
     assert sim.n["waits"] == 1 and sim.n["allocations"] == 11
 
 
+def test_what_cannot_be_given_back_is_kept(sim):
+    """The last weight goes while hipFree is refused: its block and the kept ones serve later weights, or are given back with the last of those."""
+    w = sim.pack(MIB)
+    for i in range(5):
+        w = sim.replace(w)
+    sim.idle(0, refuses=1)
+    sim.destroy(w)
+    assert sim.n["held"] == 6 and sim.n["releases"] == 0
+    sim.idle(1)
+    sim.destroy(sim.pack(MIB))
+    n = sim.n
+    assert n["held"] == 0 and n["allocations"] == 6
+
+
 def test_no_memory_for_a_new_block(sim):
     a, b = sim.pack(10 * MIB), sim.pack(50 * MIB)
     sim.destroy(a)
