@@ -54,7 +54,7 @@ struct abft_packed_b {
     int32_t* total;    // [0] sum of S_B (wrap-around), [1] sum of S_B127
     int8_t* limbs127;  // as limbs, for rowSum = S_B mod 127 (digit 0 only)
     int32_t* S_B127;   // [KB*64] S_B mod 127 in [0,126], zero past K
-    size_t block_bytes;   // of the block that holds all of them, which begins at `packed`
+    size_t block_bytes;   // of the block that holds all of them, which begins at `packed`; 0: not to be kept for another weight
     int32_t* parts;       // sums of the packing tiles before they are added up (pack_parts), or NULL
 };
 

@@ -1587,6 +1587,66 @@ def test_weights_replaced_back_to_back(binding, gpu_util, oracle, late):
         assert not bool(flags[r].any()), r
 
 
+@pytest.mark.gpu
+def test_pack_while_streams_are_captured(binding, gpu_util, oracle):
+    """Kept blocks change nothing there: a weight packed on a captured stream gets a block of its own, into which every replay packs anew; a call that
+    another stream's capture forbids is refused although a block is kept."""
+    import ctypes
+    import types
+
+    import torch
+
+    say("pack while streams are captured")
+    M, N, K = 40, 300, 700
+    rng = np.random.default_rng(8)
+    A = rng.integers(0, 256, size=(M, K), dtype=np.uint8)
+    weights = [rng.integers(-127, 128, size=(K, N), dtype=np.int8) for _ in range(3)]
+    wants = [torch.from_numpy(oracle.checked_gemm(A, B).C).cuda() for B in weights]
+    A_dev, B_dev = gpu_util.dev(A), [gpu_util.dev(B) for B in weights]
+    held = binding.abft_pack_b_checksum(B_dev[0])
+    ws = binding.Workspace(M, held)
+    C = torch.full((M, N), -7, dtype=torch.int32, device="cuda")
+    flags = torch.full((M,), -1, dtype=torch.int32, device="cuda")
+    into = B_dev[0].clone()
+    for _ in range(2):    # blocks are kept, waited for and not
+        spare = [binding.abft_pack_b_checksum(B_dev[1]) for _ in range(3)]
+        del spare
+        torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, capture_error_mode="relaxed"):
+        captured = binding.abft_pack_b_checksum(into)
+        binding.abft_gemm_u8s8s32_checked(A_dev, captured, C, flags, None, workspace=ws.tensor)
+    for r in range(6):
+        into.copy_(B_dev[r % 3])
+        graph.replay()
+        others = [binding.abft_pack_b_checksum(B) for B in B_dev]    # (between the replays, other weights come and go)
+        assert torch.equal(C, wants[r % 3]) and not bool(flags.any())
+        for B, want in zip(others, wants):
+            binding.abft_gemm_u8s8s32_checked(A_dev, B, C, flags, None, workspace=ws.tensor)
+            assert torch.equal(C, want)
+        del others
+    torch.cuda.synchronize()
+    del graph, captured
+
+    with open("/proc/self/maps") as maps:
+        runtime = next(line.split()[-1] for line in maps if "libamdhip64.so" in line)
+    hip = ctypes.CDLL(runtime)
+    stream = ctypes.c_void_p()
+    assert hip.hipStreamCreateWithFlags(ctypes.byref(stream), 1) == 0
+    assert hip.hipStreamBeginCapture(stream, 0) == 0    # (global: unsafe calls of any thread are refused, and end the capture)
+    current = types.SimpleNamespace(cuda_stream=torch._C._cuda_getCurrentRawStream(0))
+    with pytest.raises(binding.AbftError) as refused:
+        binding.abft_pack_b_checksum(B_dev[0], stream=current)
+    assert refused.value.code == binding.ABFT_EHIP
+    recorded = ctypes.c_void_p()
+    hip.hipStreamEndCapture(stream, ctypes.byref(recorded))
+    hip.hipGetLastError()
+    assert hip.hipStreamDestroy(stream) == 0
+    again = binding.abft_pack_b_checksum(B_dev[2])
+    binding.abft_gemm_u8s8s32_checked(A_dev, again, C, flags, None, workspace=ws.tensor)
+    assert torch.equal(C, wants[2])
+
+
 # (the tiles' sums added up afterwards, in whole and half blocks of 256 k, and by atomics: on either side of the line between them)
 @pytest.mark.gpu
 @pytest.mark.parametrize("transposed", [False, True])
