@@ -28,7 +28,7 @@ public:
 
     explicit KeptBlocks(Memory memory = Memory()) : memory_(memory) {}
 
-    // a block of at least `need` bytes; *size: its real size.  idle(): whether the device seems to be (a wrong answer costs time, no more)
+    // a block of at least `need` bytes, up to a sixteenth more; *size: its real size.  idle(): whether the device seems to be (a wrong answer costs time, no more)
     template <class Idle>
     hipError_t get(size_t need, void** out, size_t* size, Idle idle) {
         *out = nullptr;
@@ -99,7 +99,7 @@ private:
         bytes_ -= blocks_[i].size;
         blocks_[i] = blocks_[--n_];
     }
-    static bool fits(const Block& b, size_t need) { return b.size >= need && b.size - need <= need / 4; }
+    static bool fits(const Block& b, size_t need) { return b.size >= need && b.size - need <= need / 16; }
     bool take(size_t need, void** out, size_t* size) {
         std::lock_guard<std::mutex> lock(mutex_);
         for (int i = 0; i < n_; ++i)

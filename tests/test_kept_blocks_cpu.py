@@ -190,7 +190,8 @@ def test_weights_of_several_sizes_replaced_in_turn(sim, weights):
     for i in range(rounds * weights):
         w[i % weights] = sim.replace(w[i % weights])
     n = sim.n
-    assert n["allocations"] - before["allocations"] <= rounds * weights // 20
+    # (more sizes than blocks are kept of: those that there is no room for are allocated and freed)
+    assert n["allocations"] - before["allocations"] <= (rounds * weights // 10 if weights <= 16 else rounds * (weights - 16))
     assert n["waits"] - before["waits"] <= 2 * rounds and n["bytes"] - sum(b[1] for b in w) <= 256 * MIB
 
 
@@ -226,6 +227,16 @@ def test_what_cannot_be_given_back_is_kept(sim):
     sim.destroy(sim.pack(MIB))
     n = sim.n
     assert n["held"] == 0 and n["allocations"] == 6
+
+
+def test_a_block_serves_weights_of_about_its_size(sim):
+    sim.idle(1)
+    held = sim.pack(MIB)
+    sim.destroy(sim.pack(16 * MIB))
+    small = sim.pack(14 * MIB)    # (an eighth of it would lie idle for as long as the weight lives)
+    assert small[1] == 14 * MIB
+    assert sim.pack(15 * MIB + MIB // 2)[1] == 16 * MIB
+    assert held
 
 
 def test_no_memory_for_a_new_block(sim):
