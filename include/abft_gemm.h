@@ -18,10 +18,11 @@
  *     says "host".  Matrices are row-major with a leading dimension in
  *     elements.  `stream` is a hipStream_t passed as void* (NULL = default
  *     stream).  Calls enqueue work on `stream` and return; they never
- *     synchronise.  Only abft_pack_b_checksum / abft_packed_b_destroy
- *     allocate or free device memory and may wait for the device.  A packed B belongs to the device that
- *     was current when it was packed; the checked GEMM returns ABFT_EINVAL
- *     when called with another device current.
+ *     synchronise.  Only abft_pack_b_checksum / abft_packed_b_destroy /
+ *     abft_packed_b_trim allocate or free device memory and may wait for the
+ *     device.  A packed B belongs to the device that was current when it was
+ *     packed; the checked GEMM returns ABFT_EINVAL when called with another
+ *     device current.
  *   - Return value: ABFT_OK, or a negative code for a usage or runtime error;
  *     abft_last_error() then gives a message (thread-local, host).  Nothing is
  *     enqueued when a call returns ABFT_EINVAL or ABFT_EUNSUPPORTED.
@@ -80,8 +81,9 @@ typedef struct abft_packed_b abft_packed_b;
  *   B    int8, K x N row-major with ldb >= N when b_is_transposed == 0;
  *        N x K row-major with ldb >= K (a torch Linear weight) when 1.
  *   out  host pointer receiving the handle.
- * Allocates with hipMalloc; the packing kernels are enqueued on `stream`, and
- * B must stay valid until they have run. */
+ * Allocates with hipMalloc, or takes memory that a destroyed weight has left;
+ * the packing kernels are enqueued on `stream`, and B must stay valid until they
+ * have run. */
 int abft_pack_b_checksum(const int8_t* B, int64_t ldb, int K, int N, int b_is_transposed,
                          void* stream, abft_packed_b** out);
 
@@ -119,6 +121,10 @@ int abft_packed_b_flip_checksum_bit_mod127(abft_packed_b* Bp, int k, int bit, vo
  * memory (up to 256 MiB a device is kept for weights to come, until the last
  * one is destroyed) is used again, or given back, after a wait for the device. */
 void abft_packed_b_destroy(abft_packed_b* Bp);
+
+/* Host call.  Gives what is kept on the current device back to it at once (for
+ * a program whose other allocations need it); waits for the device. */
+int abft_packed_b_trim(void);
 
 /* Requantization parameters (Section III-B; Eq. 1 with beta_B = 0):
  *   t = C_temp[i][j] - zA * colsum_B[j] (+ bias[j]);  y = clamp(rne(float(t) * mult) + zC, 0, 255)

@@ -27,7 +27,7 @@ EXPORTS = (
     "abft_pack_b_checksum", "abft_packed_b_dims", "abft_packed_b_get_checksum", "abft_packed_b_get_checksum_mod127",
     "abft_packed_b_get_col_offsets",
     "abft_packed_b_flip_bit", "abft_packed_b_flip_checksum_bit", "abft_packed_b_flip_checksum_bit_mod127",
-    "abft_packed_b_destroy",
+    "abft_packed_b_destroy", "abft_packed_b_trim",
     "abft_gemm_workspace_bytes", "abft_workspace_init", "abft_gemm_u8s8s32_checked", "abft_gemm_u8s8s32_checked_static",
     "abft_requantize_u8",
     "abft_verify_rows", "abft_row_checksum", "abft_recover_scratch_bytes", "abft_recompute_flagged_rows",
@@ -76,6 +76,7 @@ def _load() -> ctypes.CDLL:
     L.abft_packed_b_flip_checksum_bit_mod127.argtypes = [vp, i32, i32, vp]
     L.abft_packed_b_destroy.argtypes = [vp]
     L.abft_packed_b_destroy.restype = None
+    L.abft_packed_b_trim.argtypes = []
     L.abft_gemm_workspace_bytes.argtypes = [i32, vp]
     L.abft_gemm_workspace_bytes.restype = sz
     L.abft_workspace_init.argtypes = [vp, sz, vp]
@@ -172,6 +173,11 @@ def abft_pack_b_checksum(B: torch.Tensor, b_is_transposed: bool = False, stream=
     out = ctypes.c_void_p()
     _check(lib.abft_pack_b_checksum(ptr, ldb, K, N, int(b_is_transposed), _stream(stream), ctypes.byref(out)))
     return PackedB(out.value, K, N)
+
+
+def abft_packed_b_trim():
+    """Gives the memory that is kept for weights to come on the current device back to it."""
+    _check(lib.abft_packed_b_trim())
 
 
 def abft_packed_b_dims(Bp: PackedB):

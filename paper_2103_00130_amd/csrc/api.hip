@@ -206,6 +206,14 @@ int abft_packed_b_flip_checksum_bit_mod127(abft_packed_b* Bp, int k, int bit, vo
 
 void abft_packed_b_destroy(abft_packed_b* Bp) { free_handle(Bp); }
 
+int abft_packed_b_trim(void) {
+    int dev = -1;
+    HIP_TRY(hipGetDevice(&dev));
+    Kept* const kept = kept_blocks(dev);
+    if (kept && !kept->trim()) return fail(ABFT_EHIP, "abft_packed_b_trim: hipFree was refused");
+    return ABFT_OK;
+}
+
 size_t abft_gemm_workspace_bytes(int M, const abft_packed_b* Bp) {
     if (M < 1) return 0;
     // with the weight known: room for the parts of a K split across workgroups, where one may be used, and, where rows of

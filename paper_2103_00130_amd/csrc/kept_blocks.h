@@ -68,6 +68,13 @@ public:
         if (n_out > 0 && release(out, n_out) && here) waited(until);   // (to give a block back is a wait for the device)
     }
 
+    // all that are kept, back to the device; false: refused for some
+    bool trim() {
+        (void)give_back();
+        std::lock_guard<std::mutex> lock(mutex_);
+        return n_ == 0;
+    }
+
 private:
     struct Block {
         void* at;

@@ -1647,6 +1647,24 @@ def test_pack_while_streams_are_captured(binding, gpu_util, oracle):
     assert torch.equal(C, wants[2])
 
 
+@pytest.mark.gpu
+def test_kept_memory_is_given_back(binding):
+    import torch
+
+    say("kept memory is given back")
+    held = binding.abft_pack_b_checksum(torch.zeros(64, 64, dtype=torch.int8, device="cuda"))
+    B = torch.zeros(8192, 8192, dtype=torch.int8, device="cuda")
+    binding.abft_packed_b_trim()
+    free = torch.cuda.mem_get_info()[0]
+    weights = [binding.abft_pack_b_checksum(B) for _ in range(3)]
+    del weights
+    torch.cuda.synchronize()
+    assert torch.cuda.mem_get_info()[0] < free - (180 << 20)    # (three blocks of 64 MiB and more)
+    binding.abft_packed_b_trim()
+    assert torch.cuda.mem_get_info()[0] > free - (8 << 20)
+    held.destroy()
+
+
 # (the tiles' sums added up afterwards, in whole and half blocks of 256 k, and by atomics: on either side of the line between them)
 @pytest.mark.gpu
 @pytest.mark.parametrize("transposed", [False, True])

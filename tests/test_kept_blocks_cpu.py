@@ -61,6 +61,7 @@ void put(Sim* s, long b, size_t size) {
     s->d.put_at[b] = s->d.now++;
     s->kept.put((void*)b, size, true);
 }
+int trim(Sim* s) { return s->kept.trim(); }
 void counts(Sim* s, long* out) {
     const long v[] = {s->d.allocations, s->d.releases, s->d.waits, s->d.early, (long)s->d.held.size(), (long)s->d.bytes};
     for (int i = 0; i < 6; ++i) out[i] = v[i];
@@ -83,6 +84,7 @@ def so(tmp_path_factory):
     so.get.argtypes = [ctypes.c_void_p, ctypes.c_size_t, ctypes.POINTER(ctypes.c_size_t)]
     so.get.restype = ctypes.c_long
     so.put.argtypes = [ctypes.c_void_p, ctypes.c_long, ctypes.c_size_t]
+    so.trim.argtypes = [ctypes.c_void_p]
     so.counts.argtypes = [ctypes.c_void_p, ctypes.POINTER(ctypes.c_long)]
     return so
 
@@ -227,6 +229,18 @@ def test_what_cannot_be_given_back_is_kept(sim):
     sim.destroy(sim.pack(MIB))
     n = sim.n
     assert n["held"] == 0 and n["allocations"] == 6
+
+
+def test_kept_blocks_are_given_back_when_asked_for(sim):
+    w = sim.pack(MIB)
+    for i in range(5):
+        w = sim.replace(w)
+    assert sim.so.trim(sim.at) and sim.n["held"] == 1
+    w = sim.replace(w)
+    sim.idle(0, refuses=1)
+    assert not sim.so.trim(sim.at) and sim.n["held"] == 2
+    sim.idle(0)
+    assert sim.so.trim(sim.at) and sim.n["held"] == 1
 
 
 def test_a_block_serves_weights_of_about_its_size(sim):
