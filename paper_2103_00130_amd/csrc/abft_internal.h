@@ -55,16 +55,30 @@ struct abft_packed_b {
     int8_t* limbs127;  // as limbs, for rowSum = S_B mod 127 (digit 0 only)
     int32_t* S_B127;   // [KB*64] S_B mod 127 in [0,126], zero past K
     size_t block_bytes;   // of the block that holds all of them, which begins at `packed`; 0: not to be kept for another weight
-    int32_t* parts;       // sums of the packing tiles before they are added up (pack_parts), or NULL
+    int32_t* sums;        // accumulators of the packing, [KB*64] for S_B and then [NT*256] for colsum: zero before a weight is packed and after
+    bool sums_zero;       // they are, once what is enqueued has run
 };
 
 namespace abft {
 
-// Ints for the sums of the tiles of 256 columns x 128 k as a weight is packed (a twentieth of the weight), or 0 where they are added up by atomics:
-// from 65 tiles in a row or 129 in a column on, where adding them up afterwards would take longer than the kernel that clears the sums for the
-// atomics (3 us of the host, 3 to 4 of the device).
-inline size_t pack_parts(int KB, int NT) {
-    return NT <= 64 && KB <= 256 ? (size_t)NT * KB * kUnitK + (size_t)(KB / 2) * NT * kTileN : 0;
+// What the one block of a packed weight holds, by offsets in bytes.
+struct PackedLayout {
+    size_t limbs, limbs127, S_B, colsum, total, S_B127, sums, bytes;
+};
+inline PackedLayout packed_layout(int KB, int NT) {
+    const auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
+    const size_t units = (size_t)NT * KB * kUnitsPerTile * kUnitBytes, digits = (size_t)KB * kUnitK * kLimbs;
+    const size_t k_ints = (size_t)KB * kUnitK * sizeof(int32_t), n_ints = (size_t)NT * kTileN * sizeof(int32_t);
+    PackedLayout l;
+    l.limbs = up(units);
+    l.limbs127 = l.limbs + up(digits);
+    l.S_B = l.limbs127 + up(digits);
+    l.colsum = l.S_B + up(k_ints);
+    l.total = l.colsum + up(n_ints);
+    l.S_B127 = l.total + 256;
+    l.sums = l.S_B127 + up(k_ints);
+    l.bytes = l.sums + k_ints + n_ints;
+    return l;
 }
 
 struct RequantDev {

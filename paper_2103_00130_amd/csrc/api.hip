@@ -63,28 +63,35 @@ Kept* kept_blocks(int dev) {
     return dev >= 0 && dev < 64 ? &k[dev] : nullptr;
 }
 
-// A block on the current device, `dev`, for a weight that is packed on `s`; *size: 0 if it is not to be kept.  While `s` is captured that is always so:
+// which weights' accumulators lie in the same places of their blocks
+uint64_t layout_id(const abft_packed_b* h) { return (uint64_t)(uint32_t)h->KB << 32 | (uint32_t)h->NT; }
+
+// A block on the current device, `dev`, for a weight that is packed on `s`; *size: 0 if it is not to be kept; *sums_zero: its accumulators are.  While `s` is captured that is always so:
 // the block belongs to the graph, whose replays write to it.  Otherwise, whether there is a kept block or not, a call is refused where hipMalloc is (as
 // another stream is captured in a mode that forbids it): hipMalloc of nothing allocates nothing and says so, in 0.07 us.
-hipError_t get_block(int dev, hipStream_t s, size_t need, void** out, size_t* size) {
+hipError_t get_block(int dev, hipStream_t s, size_t need, uint64_t layout, void** out, size_t* size, bool* sums_zero) {
     Kept* const kept = kept_blocks(dev);
     hipStreamCaptureStatus capture;
     *size = 0;
+    *sums_zero = false;
     if (!kept || hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) return hipMalloc(out, need);
     const hipError_t e = hipMalloc(out, 0);
     if (e != hipSuccess) return e;
-    return kept->get(need, out, size, [s] {
+    uint64_t left = 0;
+    const hipError_t e_get = kept->get(need, out, size, &left, [s] {
         const bool idle = hipStreamQuery(s) == hipSuccess;
         if (!idle) (void)hipGetLastError();
         return idle;
     });
+    *sums_zero = left == layout;
+    return e_get;
 }
 
 void free_handle(abft_packed_b* h) {
     if (!h) return;
     if (h->packed) {   // (one block holds everything)
         int current = -1;   // (a weight may be destroyed with another device current)
-        if (h->block_bytes > 0) kept_blocks(h->device)->put(h->packed, h->block_bytes, hipGetDevice(&current) == hipSuccess && current == h->device);
+        if (h->block_bytes > 0) kept_blocks(h->device)->put(h->packed, h->block_bytes, h->sums_zero ? layout_id(h) : 0, hipGetDevice(&current) == hipSuccess && current == h->device);
         else (void)hipFree(h->packed);
     }
     delete h;
@@ -123,26 +130,20 @@ int abft_pack_b_checksum(const int8_t* B, int64_t ldb, int K, int N, int b_is_tr
     h->KB = ((K + 2 * abft::kUnitK - 1) / (2 * abft::kUnitK)) * 2;
     h->NT = (N + abft::kTileN - 1) / abft::kTileN;
     hipError_t e = hipGetDevice(&h->device);
-    // one block: the units, the digits, then S_B, colsum and total (cleared together before packing where there are no parts), S_B mod 127, the parts
-    const auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
-    const size_t units = (size_t)h->NT * h->KB * abft::kUnitsPerTile * abft::kUnitBytes, k_ints = (size_t)h->KB * abft::kUnitK * sizeof(int32_t);
-    const size_t digits = (size_t)h->KB * abft::kUnitK * abft::kLimbs, n_ints = (size_t)h->NT * abft::kTileN * sizeof(int32_t);
-    const size_t o_limbs = up(units), o_limbs127 = o_limbs + up(digits), o_sb = o_limbs127 + up(digits), o_colsum = o_sb + up(k_ints);
-    const size_t o_total = o_colsum + up(n_ints), o_sb127 = o_total + 256;
-    const size_t part_ints = abft::pack_parts(h->KB, h->NT), o_parts = o_sb127 + up(k_ints);
+    const abft::PackedLayout l = abft::packed_layout(h->KB, h->NT);
     if (e == hipSuccess) {
         void* block = nullptr;
-        e = get_block(h->device, (hipStream_t)stream, o_parts + part_ints * sizeof(int32_t), &block, &h->block_bytes);
+        e = get_block(h->device, (hipStream_t)stream, l.bytes, layout_id(h), &block, &h->block_bytes, &h->sums_zero);
         h->packed = (int8_t*)block;
     }
     if (e == hipSuccess) {
-        h->limbs = h->packed + o_limbs;
-        h->limbs127 = h->packed + o_limbs127;
-        h->S_B = reinterpret_cast<int32_t*>(h->packed + o_sb);
-        h->colsum = reinterpret_cast<int32_t*>(h->packed + o_colsum);
-        h->total = reinterpret_cast<int32_t*>(h->packed + o_total);
-        h->S_B127 = reinterpret_cast<int32_t*>(h->packed + o_sb127);
-        h->parts = part_ints > 0 ? reinterpret_cast<int32_t*>(h->packed + o_parts) : nullptr;
+        h->limbs = h->packed + l.limbs;
+        h->limbs127 = h->packed + l.limbs127;
+        h->S_B = reinterpret_cast<int32_t*>(h->packed + l.S_B);
+        h->colsum = reinterpret_cast<int32_t*>(h->packed + l.colsum);
+        h->total = reinterpret_cast<int32_t*>(h->packed + l.total);
+        h->S_B127 = reinterpret_cast<int32_t*>(h->packed + l.S_B127);
+        h->sums = reinterpret_cast<int32_t*>(h->packed + l.sums);
     }
     if (e == hipSuccess) e = abft::launch_pack(B, ldb, b_is_transposed ? 1 : 0, h, (hipStream_t)stream);
     if (e != hipSuccess) {

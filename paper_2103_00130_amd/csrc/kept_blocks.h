@@ -4,6 +4,7 @@
 #include <hip/hip_runtime_api.h>
 
 #include <cstddef>
+#include <cstdint>
 #include <mutex>
 
 namespace abft {
@@ -14,9 +15,9 @@ namespace abft {
 // device is waited for; else another block is allocated.  So a weight replaced again and again settles at kMostWaiting blocks and a wait for as many
 // replacements, at whatever rate, and one replaced while the device idles at a single block.
 // Measured, us a replacement with its first batch (64 rows of 4096x4096, 32 of 700x900), hipMalloc and hipFree / this: back to back 69 and 36 / 31 and 28, 100 us of
-// other host work between them 81 and 39 / 31 and 30, 1 ms 87 and 40 / 32 and 33 (a wait by the time since the last replacement, with a limit of 50 us, took 33 and
-// 27, 43 and 38, 43 and 38, and 68 for 8192x8192, whose packing alone takes that long, / 66).  The wait takes 10 us on an idle device and 60 to 90 on a busy
-// one, for one block or for eight; a block that the device has not had yet 60 to 250.
+// other host work between them 81 and 39 / 32 and 30, 1 ms 87 and 40 / 40 and 41 (a wait by the time since the last replacement, with a limit of 50 us, took 31 and
+// 27, 42 and 37, 42 and 37).  The wait takes 10 us on an idle device, 60 to 90 on a busy one and, when it is the first in some milliseconds, 150 to 250 (the
+// runtime catches up with all that has ended), for one block or for eight; a block that the device has not had yet takes 60 to 250.
 //
 // Memory: allocate(void**, size_t) as hipMalloc; wait() and release(void*): true once everything that was enqueued on the device before the call has
 // ended, and the block given back.
@@ -28,13 +29,15 @@ public:
 
     explicit KeptBlocks(Memory memory = Memory()) : memory_(memory) {}
 
-    // a block of at least `need` bytes, up to a sixteenth more; *size: its real size.  idle(): whether the device seems to be (a wrong answer costs time, no more)
+    // a block of at least `need` bytes, up to a sixteenth more; *size: its real size, *mark: with what it was put back, 0: a new
+    // one.  idle(): whether the device seems to be (a wrong answer costs time, no more)
     template <class Idle>
-    hipError_t get(size_t need, void** out, size_t* size, Idle idle) {
+    hipError_t get(size_t need, void** out, size_t* size, uint64_t* mark, Idle idle) {
         *out = nullptr;
-        if (take(need, out, size)) return hipSuccess;
+        *mark = 0;
+        if (take(need, out, size, mark)) return hipSuccess;
         if (const int waiting = count_waiting(need)) {
-            if ((waiting >= kMostWaiting || !has_room(need) || idle()) && wait() && take(need, out, size)) return hipSuccess;
+            if ((waiting >= kMostWaiting || !has_room(need) || idle()) && wait() && take(need, out, size, mark)) return hipSuccess;
         }
         hipError_t e = memory_.allocate(out, *size = need);
         if (e == hipErrorOutOfMemory && give_back()) e = memory_.allocate(out, need);
@@ -46,7 +49,7 @@ public:
     }
     // the block of a weight that is destroyed; here: with its device current.  Where there is no room for it, blocks that have lain unused while
     // kStale others came make room; not younger ones, of which a program that replaces several weights in turn will need the oldest next
-    void put(void* block, size_t size, bool here) {
+    void put(void* block, size_t size, uint64_t mark, bool here) {
         Block out[kMost + 1];
         int n_out = 0;
         bool last;
@@ -60,8 +63,8 @@ public:
                     out[n_out++] = blocks_[i];
                     drop(i);
                 }
-            if (!last && room(size)) add({block, size, released_, false});
-            else out[n_out++] = {block, size, released_, false};
+            if (!last && room(size)) add({block, size, mark, released_, false});
+            else out[n_out++] = {block, size, mark, released_, false};
             until = released_;
         }
         if (last) (void)give_back();
@@ -79,6 +82,7 @@ private:
     struct Block {
         void* at;
         size_t size;
+        uint64_t mark;
         unsigned long long number;   // of its release
         bool idle;                   // a wait for the device lies behind that
     };
@@ -107,12 +111,13 @@ private:
         blocks_[i] = blocks_[--n_];
     }
     static bool fits(const Block& b, size_t need) { return b.size >= need && b.size - need <= need / 16; }
-    bool take(size_t need, void** out, size_t* size) {
+    bool take(size_t need, void** out, size_t* size, uint64_t* mark) {
         std::lock_guard<std::mutex> lock(mutex_);
         for (int i = 0; i < n_; ++i)
             if (blocks_[i].idle && fits(blocks_[i], need)) {
                 *out = blocks_[i].at;
                 *size = blocks_[i].size;
+                *mark = blocks_[i].mark;
                 drop(i);
                 ++live_;
                 return true;

@@ -29,16 +29,17 @@ __device__ inline int32_t sum_bytes(v4i v, int32_t s) {
 
 // One pass over B: the packed units, and what the tile adds to the encoded column S_B (sums over the columns) and to the
 // column sums of Eq. 1 (sums over k).  A workgroup takes one packed n-tile of 256 columns by 128 k, 32 KiB, eight 16-byte
-// chunks per thread in flight at once; both sums are formed from the bytes in hand.  They are stored per tile (row_part, col_part) and
-// added up by encode_kernel; where there are many tiles in a row or column (pack_parts) they leave with one integer atomic per row and per column
-// of the tile instead, to S_B and colsum, which a kernel ahead has cleared (integer addition makes the order irrelevant).
-// Bound by memory: 9.7 us at 4096 x 4096, 134 us (4.0 TB/s, a large copy reaches 4.8) at 16384 x 16384, as a torch Linear
+// chunks per thread in flight at once; both sums are formed from the bytes in hand and leave with one integer atomic per row and per column
+// of the tile (integer addition makes the order irrelevant).  They meet in accumulators of the weight's block that are zero before: encode_kernel, which
+// takes them over, clears them again, so that a block that an earlier weight of these dimensions has left needs no kernel that does it ahead.
+// Bound by memory: 9.4 us at 4096 x 4096 (and 3.6 of encode_kernel; 9.8 and 4.8 with the tiles' sums stored and added up there, which
+// took 4.7 % of a weight's memory for as long as it lived), 134 us (4.0 TB/s, a large copy reaches 4.8) at 16384 x 16384, as a torch Linear
 // holds it; 13 and 154 us with K along the rows.  Three passes, two of them strided, took 130 and 2900 us.
 constexpr int kPackK = 128;
 template <bool kTransposed>
 __global__ __launch_bounds__(256) void pack_kernel(const int8_t* __restrict__ B, int64_t ldb, int K, int N, int KB,
-                                                   v4i* __restrict__ packed, int32_t* __restrict__ S_B, int32_t* __restrict__ colsum,
-                                                   int32_t* __restrict__ row_part, int32_t* __restrict__ col_part, int32_t* __restrict__ total) {
+                                                   v4i* __restrict__ packed, int32_t* __restrict__ row_sums, int32_t* __restrict__ col_sums,
+                                                   int32_t* __restrict__ total) {
     __shared__ __align__(16) int8_t s_tile[kTileN * kPackK];
     __shared__ int32_t s_col[kTileN], s_row[kPackK];
     const int tid = threadIdx.x;
@@ -128,27 +129,9 @@ __global__ __launch_bounds__(256) void pack_kernel(const int8_t* __restrict__ B,
         }
     }
     __syncthreads();
-    if (row_part != nullptr) {   // (padded rows and columns: zeros)
-        if (blockIdx.x == 0 && blockIdx.y == 0 && tid < 2) total[tid] = 0;   // (encode_kernel adds to it)
-        col_part[(int64_t)blockIdx.x * gridDim.y * kTileN + j0 + tid] = s_col[tid];
-        if (tid < kPackK) row_part[(int64_t)ntile * KB * kUnitK + k0 + tid] = s_row[tid];
-    } else {
-        if (j0 + tid < N && s_col[tid] != 0) atomicAdd(&colsum[j0 + tid], s_col[tid]);
-        if (tid < kPackK && k0 + tid < K && s_row[tid] != 0) atomicAdd(&S_B[k0 + tid], s_row[tid]);
-    }
-}
-
-// Sums of n arrays of `length` ints, of the 256 from `first` on, to LDS: a quarter of the arrays per 64 threads, four ints a thread.
-__device__ inline void sum_parts(const int32_t* __restrict__ part, int n, int64_t length, int64_t first, int32_t (*s_quarter)[256], int32_t* s_sum) {
-    const int lane = threadIdx.x & 63, quarter = threadIdx.x >> 6;
-    const v4i* const at = reinterpret_cast<const v4i*>(part + first) + lane;
-    v4i sum = {0, 0, 0, 0};
-#pragma unroll 8
-    for (int i = quarter; i < n; i += 4) sum += at[(int64_t)i * (length / 4)];
-    *reinterpret_cast<v4i*>(&s_quarter[quarter][lane * 4]) = sum;
-    __syncthreads();
-    s_sum[threadIdx.x] = s_quarter[0][threadIdx.x] + s_quarter[1][threadIdx.x] + s_quarter[2][threadIdx.x] + s_quarter[3][threadIdx.x];
-    __syncthreads();
+    if (blockIdx.x == 0 && blockIdx.y == 0 && tid < 2) total[tid] = 0;   // (encode_kernel adds to it)
+    if (j0 + tid < N && s_col[tid] != 0) atomicAdd(&col_sums[j0 + tid], s_col[tid]);
+    if (tid < kPackK && k0 + tid < K && s_row[tid] != 0) atomicAdd(&row_sums[k0 + tid], s_row[tid]);
 }
 
 // Digit `digit` of s, the four signed base-256 digits: d0 in [-128,127] with s = d0 + 256*s1, and so on; the last digit
@@ -175,45 +158,23 @@ __device__ inline int32_t floor_mod127(int32_t s) {
 // What follows from the finished encoded column: its digits, and for Algorithm 1 as printed (Section IV-A-2) rowSum[k] =
 // S_B[k] mod 127 in [0,126], as an int32 array and, in the digit layout, as a single live digit column; the sums over k
 // of both (wrap-around) go to total[0] and total[1].  One thread per digit of sixteen k, the digit layout's 16 bytes.
-// Rows k >= K (padding) hold zeros.  kParts: a workgroup takes 256 k, whose sums it adds up first, or, the last n_col_blocks of the grid, 256
-// columns of colsum.
-template <bool kParts>
-__global__ __launch_bounds__(256) void encode_kernel(int32_t* __restrict__ S_B, int n_chunks, v4i* __restrict__ limbs, v4i* __restrict__ S_B127,
-                                                     v4i* __restrict__ limbs127, int32_t* __restrict__ total, const int32_t* __restrict__ row_part, int NT,
-                                                     const int32_t* __restrict__ col_part, int KB2, int32_t* __restrict__ colsum, int n_row_blocks) {
-    __shared__ int32_t part[2];
-    __shared__ __align__(16) int32_t s_quarter[kParts ? 4 : 1][256], s_sum[256];
-    if (threadIdx.x < 2) part[threadIdx.x] = 0;
-    int t = blockIdx.x * 256 + threadIdx.x;
-    const v4i* src = reinterpret_cast<const v4i*>(S_B) + (t >> 2) * 4;
-    bool mine = t < n_chunks;
-    if constexpr (kParts) {
-        if ((int)blockIdx.x >= n_row_blocks) {
-            const int64_t first = (int64_t)((int)blockIdx.x - n_row_blocks) * 256;
-            sum_parts(col_part, KB2, (int64_t)NT * kTileN, first, s_quarter, s_sum);
-            colsum[first + threadIdx.x] = s_sum[threadIdx.x];
-            return;
-        }
-        // (there is an even number of k-blocks of 64, so that a workgroup's 256 k may be half past the end)
-        const int64_t first = (int64_t)blockIdx.x * 256, length = (int64_t)n_chunks * 4;
-        const int live = length - first < 256 ? (int)(length - first) : 256;
-        if (live == 256) {
-            sum_parts(row_part, NT, length, first, s_quarter, s_sum);
-        } else {
-            int32_t sum = 0;
-            if ((int)threadIdx.x < live)
-                for (int i = 0; i < NT; ++i) sum += row_part[(int64_t)i * length + first + threadIdx.x];
-            s_sum[threadIdx.x] = sum;
-            __syncthreads();
-        }
-        if ((int)threadIdx.x < live) S_B[first + threadIdx.x] = s_sum[threadIdx.x];
-        // 64 threads go on: sixteen groups of sixteen k, four digits each
-        t = blockIdx.x * 64 + threadIdx.x;
-        src = reinterpret_cast<const v4i*>(s_sum) + (threadIdx.x >> 2) * 4;
-        mine = threadIdx.x < 64 && t < n_chunks;
-    } else {
-        __syncthreads();
+// Rows k >= K (padding) hold zeros.  The accumulators of pack_kernel are taken over and cleared: 1024 k a workgroup, then, behind the first
+// n_row_blocks of the grid, 256 columns.
+__global__ __launch_bounds__(256) void encode_kernel(v4i* __restrict__ row_sums, int32_t* __restrict__ col_sums, int n_chunks, int n_row_blocks, v4i* __restrict__ S_B,
+                                                     v4i* __restrict__ limbs, v4i* __restrict__ S_B127, v4i* __restrict__ limbs127, int32_t* __restrict__ total,
+                                                     int32_t* __restrict__ colsum) {
+    if ((int)blockIdx.x >= n_row_blocks) {
+        const int64_t j = (int64_t)((int)blockIdx.x - n_row_blocks) * 256 + threadIdx.x;
+        colsum[j] = col_sums[j];
+        col_sums[j] = 0;
+        return;
     }
+    __shared__ int32_t part[2];
+    if (threadIdx.x < 2) part[threadIdx.x] = 0;
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    const v4i* const src = row_sums + (t >> 2) * 4;
+    const bool mine = t < n_chunks;
+    __syncthreads();
     const int digit = t & (kLimbs - 1);
     int32_t s = 0, r = 0;   // sums of this thread's quarter of the sixteen
     if (mine) {
@@ -232,7 +193,8 @@ __global__ __launch_bounds__(256) void encode_kernel(int32_t* __restrict__ S_B, 
             out[q] = (int)w;
             if (digit == 0) out127[q] = (int)w127;
             if (digit == q) {
-                S_B127[t] = m;   // (chunk t of the array: group t / 4, its quarter)
+                S_B[t] = v;      // (chunk t of the array: group t / 4, its quarter)
+                S_B127[t] = m;
                 s = (int32_t)((uint32_t)v[0] + (uint32_t)v[1] + (uint32_t)v[2] + (uint32_t)v[3]);
                 r = m[0] + m[1] + m[2] + m[3];
             }
@@ -249,6 +211,7 @@ __global__ __launch_bounds__(256) void encode_kernel(int32_t* __restrict__ S_B, 
         atomicAdd(&part[1], r);
     }
     __syncthreads();
+    if (mine) row_sums[t] = v4i{0, 0, 0, 0};   // (each chunk is read by four threads, on the other side of the barrier)
     if (threadIdx.x < 2) atomicAdd(&total[threadIdx.x], part[threadIdx.x]);
 }
 
@@ -283,23 +246,21 @@ __global__ void fill_zero_kernel(int32_t* p, size_t n) {
 hipError_t launch_pack(const int8_t* B, int64_t ldb, int transposed, abft_packed_b* h, hipStream_t s) {
     const dim3 grid((unsigned)(h->KB / 2), (unsigned)h->NT);
     v4i* const out = reinterpret_cast<v4i*>(h->packed);
-    const bool parts = h->parts != nullptr;
-    const int n_chunks = h->KB * kUnitK / 16 * kLimbs;
-    int32_t* const row_part = h->parts;
-    int32_t* const col_part = parts ? h->parts + (size_t)h->NT * h->KB * kUnitK : nullptr;
-    if (!parts) {
-        // S_B, colsum and total lie one after the other
-        const hipError_t e = launch_fill_zero(h->S_B, (size_t)(h->total - h->S_B) + 16, s);
+    const int n_chunks = h->KB * kUnitK / 16 * kLimbs, n_row_blocks = (n_chunks + 255) / 256;
+    int32_t* const col_sums = h->sums + (size_t)h->KB * kUnitK;
+    if (!h->sums_zero) {
+        const hipError_t e = launch_fill_zero(h->sums, (size_t)h->KB * kUnitK + (size_t)h->NT * kTileN, s);
         if (e != hipSuccess) return e;
     }
-    if (transposed) pack_kernel<true><<<grid, dim3(256), 0, s>>>(B, ldb, h->K, h->N, h->KB, out, h->S_B, h->colsum, row_part, col_part, h->total);
-    else pack_kernel<false><<<grid, dim3(256), 0, s>>>(B, ldb, h->K, h->N, h->KB, out, h->S_B, h->colsum, row_part, col_part, h->total);
-    const int n_row_blocks = parts ? (h->KB * kUnitK + 255) / 256 : (n_chunks + 255) / 256;
-    auto kernel = parts ? encode_kernel<true> : encode_kernel<false>;
-    kernel<<<dim3((unsigned)(n_row_blocks + (parts ? h->NT : 0))), dim3(256), 0, s>>>(
-        h->S_B, n_chunks, reinterpret_cast<v4i*>(h->limbs), reinterpret_cast<v4i*>(h->S_B127), reinterpret_cast<v4i*>(h->limbs127), h->total, row_part, h->NT,
-        col_part, h->KB / 2, h->colsum, n_row_blocks);
-    return hipGetLastError();
+    h->sums_zero = false;
+    if (transposed) pack_kernel<true><<<grid, dim3(256), 0, s>>>(B, ldb, h->K, h->N, h->KB, out, h->sums, col_sums, h->total);
+    else pack_kernel<false><<<grid, dim3(256), 0, s>>>(B, ldb, h->K, h->N, h->KB, out, h->sums, col_sums, h->total);
+    encode_kernel<<<dim3((unsigned)(n_row_blocks + h->NT)), dim3(256), 0, s>>>(
+        reinterpret_cast<v4i*>(h->sums), col_sums, n_chunks, n_row_blocks, reinterpret_cast<v4i*>(h->S_B), reinterpret_cast<v4i*>(h->limbs),
+        reinterpret_cast<v4i*>(h->S_B127), reinterpret_cast<v4i*>(h->limbs127), h->total, h->colsum);
+    const hipError_t e = hipGetLastError();
+    h->sums_zero = e == hipSuccess;
+    return e;
 }
 
 hipError_t launch_flip_bit(abft_packed_b* h, int k, int j, int bit, hipStream_t s) {

@@ -23,6 +23,13 @@ extern "C" int large(int M, int N, int K, int stages, int whole, int can_copy, i
     const abft::LargeChoice c = abft::large_choice({(abft::LargeForm)pick, pick_copy != 0}, whole != 0, can_copy != 0, M, N, K, stages, want_c != 0, want_q != 0, check != 0);
     return c.form + (c.copy ? 8 : 0);
 }
+extern "C" void packed(int K, int N, long long* out) {
+    const int KB = (K + 127) / 128 * 2, NT = (N + 255) / 256;
+    const abft::PackedLayout l = abft::packed_layout(KB, NT);
+    const long long v[] = {(long long)NT * 256 * KB * 64, 0, (long long)l.limbs, (long long)l.limbs127, (long long)l.S_B, (long long)l.colsum, (long long)l.total, (long long)l.S_B127,
+                           (long long)l.sums, (long long)l.bytes, KB * 64, NT * 256};
+    for (int i = 0; i < 12; ++i) out[i] = v[i];
+}
 extern "C" int copy_first(int form, int stages) { return abft::copy_first((abft::WkForm)form, stages); }
 """
 NONE, T32X32W4, T32X32W8, T32X64W4, T32X64W8, T64X64W4 = range(6)
@@ -48,6 +55,7 @@ def plan(tmp_path_factory):
     call.room_for_copy = lambda M, N, K: bool(so.room_for_copy(M, N, K))
     call.copy_first = lambda form, K: bool(so.copy_first(form, ((K + 63) // 64 + 1) // 2))
     call.form = lambda M, N, K: so.form(M, N, ((K + 63) // 64 + 1) // 2, K % 16 == 0)
+    call.packed = lambda K, N: (lambda out: (so.packed(K, N, out), list(out))[1])((ctypes.c_longlong * 12)())
     call.beyond = lambda M, N, K: bool(so.beyond(M, N, ((K + 63) // 64 + 1) // 2))
     call.large = lambda M, N, K, pick, out="C", can_copy=False, check=True: so.large(M, N, K, ((K + 63) // 64 + 1) // 2, K % 16 == 0, can_copy, pick & 7, pick >> 3,
                                                                          out != "q", out != "C", check)
@@ -187,3 +195,16 @@ def test_grids_beyond_the_compute_units_where_the_fits_are_off(plan):
     # predicted 0.91 to 0.94 of the thresholds' choice; 0.88, unchecked as well
     assert plan.large(297, 7168, 3056, L128, "q") == L128 and plan.large(1295, 14192, 2256, L256, "q") == L256 and plan.large(314, 111907, 1616, L256) == L256
     assert plan.large(414, 1607, 336, L64) == W32X64 and plan.large(414, 1607, 336, L64, check=False) == L64
+
+
+@pytest.mark.parametrize("K,N", [(1, 1), (64, 256), (129, 257), (300, 16384), (16385, 20), (1024, 1024), (4096, 4096), (16384, 16384)])
+def test_what_a_packed_weight_takes(plan, K, N):
+    """Digits, sums and totals beside the weight itself: 20 bytes a row and 8 a column of it (accumulators among them), whatever the number of tiles."""
+    units, *at, total, k, n = plan.packed(K, N)
+    ints = (k, k, k, n, 64, k)    # 4 bytes a place: both kinds of digits, S_B, colsum, the totals, S_B mod 127
+    assert at[0] == 0 and at[1] == units
+    for i, count in enumerate(ints):
+        assert at[i + 1] % 256 == 0 and at[i + 2] - at[i + 1] >= 4 * count
+    assert total == at[-1] + 4 * (k + n) and total - units <= 24 * k + 8 * n + 8 * 256
+    if K >= 4096 and N >= 4096:
+        assert total <= 1.01 * units

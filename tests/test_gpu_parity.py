@@ -1665,7 +1665,35 @@ def test_kept_memory_is_given_back(binding):
     held.destroy()
 
 
-# (the tiles' sums added up afterwards, in whole and half blocks of 256 k, and by atomics: on either side of the line between them)
+@pytest.mark.gpu
+@pytest.mark.parametrize("transposed", [False, True])
+def test_pack_into_blocks_of_other_weights(binding, gpu_util, oracle, transposed):
+    """The sums of a weight meet in accumulators that the one before it has left at zero, or, where that one's lay elsewhere in the block, that are cleared
+    first: weights of the same tiles, of others whose block is of about the same size, with what was flipped in between and where it takes a new one."""
+    import torch
+
+    say(f"pack into blocks of other weights, transposed={transposed}")
+    rng = np.random.default_rng(12)
+    held = binding.abft_pack_b_checksum(gpu_util.dev(rng.integers(-127, 128, size=(64, 64), dtype=np.int8)))
+    sizes = [(3000, 700), (2999, 690), (3000, 700), (2900, 700), (3060, 513), (2900, 768), (16384, 20), (16300, 256), (20, 16385), (100, 16400), (3000, 700)]
+    for r in range(3):
+        for K, N in sizes:
+            B = rng.integers(-128, 128, size=(K, N)).astype(np.int8)
+            run = gpu_util.GpuRun(binding, B, transposed)
+            wide = B.astype(np.int64)
+            assert np.array_equal(run.checksum(), wide.sum(1)) and np.array_equal(run.colsum(), wide.sum(0)), (r, K, N)
+            residues = torch.empty(K, dtype=torch.int32, device="cuda")
+            binding.abft_packed_b_get_checksum_mod127(run.Bp, residues)
+            assert np.array_equal(residues.cpu().numpy(), wide.sum(1) % 127)
+            A = rng.integers(0, 256, size=(3, K), dtype=np.uint8)
+            out = run.gemm(A)
+            assert np.array_equal(out["C"], oracle.checked_gemm(A, B).C) and not out["flags"].any()
+            binding.abft_packed_b_flip_checksum_bit(run.Bp, K // 2, r)
+            binding.abft_packed_b_flip_bit(run.Bp, K // 3, N // 2, r)
+    assert held
+
+
+# (weights of many tiles in a row or a column)
 @pytest.mark.gpu
 @pytest.mark.parametrize("transposed", [False, True])
 @pytest.mark.parametrize("K,N", [(64, 20), (300, 1100), (16384, 20), (16385, 20), (20, 16384), (20, 16385)])

@@ -51,15 +51,17 @@ void drop(Sim* s) { delete s; }
 void set(Sim* s, int idle, size_t most, int refuses) { s->d.idle = idle; s->d.most = most; s->d.refuses = refuses; }
 long get(Sim* s, size_t need, size_t* size) {
     void* p = nullptr;
-    if (s->kept.get(need, &p, size, [s] { return s->d.idle != 0; }) != hipSuccess) return 0;
+    uint64_t mark = ~0ull;
+    if (s->kept.get(need, &p, size, &mark, [s] { return s->d.idle != 0; }) != hipSuccess) return 0;
     const long b = (long)p;
     if (s->d.held.at(b) != *size || *size < need) return -1;
+    if (mark != (s->d.put_at.count(b) ? 1000 + b : 0)) return -1;
     if (s->d.put_at.count(b) && s->d.put_at[b] > s->d.waited) ++s->d.early;    // handed out before a wait
     return b;
 }
 void put(Sim* s, long b, size_t size) {
     s->d.put_at[b] = s->d.now++;
-    s->kept.put((void*)b, size, true);
+    s->kept.put((void*)b, size, 1000 + b, true);
 }
 int trim(Sim* s) { return s->kept.trim(); }
 void counts(Sim* s, long* out) {
