@@ -114,7 +114,9 @@ constexpr bool lean() { return BM / WGM * (BN / WGN) <= 4096 && kStages == 2 && 
 // (accumulators, column sums, and its share of the checksum product for the tile's rows) in the workspace and takes a ticket on the
 // tile's counter, and the one that arrives last adds the others' partials to its own and runs the epilogue.  The checksum product of
 // every run of stages is dealt out to the tile columns as before (the comparison of Eq. 2b is linear in the K slices).
-template <int BM, int BN, int WGM, int WGN, int kStages, bool kCheck, int kOut, bool kBlockSums, int kAnyA = 0, bool kSplitK = false>
+// kSlots: arrivals of many tile columns by slots (row_slots), in a kernel of their own: with both ways in one, the other calls took up to 3 % longer (us, one
+// kernel / two: 3156x364x256 6.19 / 6.08, 2247x500x176 C and Cq 6.77 / 6.60, 908x1343x320 C and Cq 7.71 / 7.60; 36 products of 200 to 520 tiles 1 %).
+template <int BM, int BN, int WGM, int WGN, int kStages, bool kCheck, int kOut, bool kBlockSums, int kAnyA = 0, bool kSplitK = false, bool kSlots = false>
 __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const GemmParams p, const int tiles_m,
                                                                              const int tiles_n) {
     constexpr int NW = WGM * WGN, NT = NW * 64;    // wavefronts and threads
@@ -571,7 +573,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
 
     asm volatile("" : "+s"(total_sb));  // (the value is in its register from here on)
     int slots = 0, slot_rows = 0;
-    if constexpr (kLean) {   // (fetched now: where they are used, a trip to memory at the end of a workgroup, 607x1872x96 5.67 -> 5.87 us)
+    if constexpr (kSlots) {   // (fetched now: where they are used, a trip to memory at the end of a workgroup, 0.2 us)
         slots = p.slots;
         slot_rows = p.slot_rows;
         asm volatile("" : "+s"(slots), "+s"(slot_rows));
@@ -1091,7 +1093,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
                 p.row_flags[row0 + r] = bad ? 1 : 0;
                 fin = true;
             } else {
-                if constexpr (!kLean) {
+                if constexpr (!kSlots) {
                     const unsigned long long old = __hip_atomic_fetch_add(ws_rows + row0 + r, ((unsigned long long)d << 32) | 1ull,
                                                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     if ((uint32_t)old == (uint32_t)arrivals - 1u) {
@@ -1104,20 +1106,17 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_tile_async_kernel(const Ge
                 } else {
                     // (where many tile columns would arrive one after the other, those of a slot meet at a word of their own first)
                     const int slot = tile_n & (slots - 1);
-                    const uint32_t expected = slots > 0 ? (uint32_t)(arrivals - slot + slots - 1) >> __builtin_ctz((unsigned)slots) : (uint32_t)arrivals;
-                    unsigned long long* word = ws_rows + (slots > 0 ? slot * slot_rows : 0) + row0 + r;
+                    const uint32_t expected = (uint32_t)(arrivals - slot + slots - 1) >> __builtin_ctz((unsigned)slots);
+                    unsigned long long* word = ws_rows + slot * slot_rows + row0 + r;
                     unsigned long long old = __hip_atomic_fetch_add(word, ((unsigned long long)d << 32) | 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     if ((uint32_t)old == expected - 1u) {
                         uint32_t diff = (uint32_t)(old >> 32) + d;
                         __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        fin = true;
-                        if (slots > 0) {
-                            word = ws_rows + slots * slot_rows + row0 + r;
-                            old = __hip_atomic_fetch_add(word, ((unsigned long long)diff << 32) | 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            diff += (uint32_t)(old >> 32);
-                            fin = (uint32_t)old == (uint32_t)slots - 1u;
-                            if (fin) __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        }
+                        word = ws_rows + slots * slot_rows + row0 + r;
+                        old = __hip_atomic_fetch_add(word, ((unsigned long long)diff << 32) | 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        diff += (uint32_t)(old >> 32);
+                        fin = (uint32_t)old == (uint32_t)slots - 1u;
+                        if (fin) __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         bad = fin && (mod127 ? (diff % 127u != 0) : (diff != 0));
                         if (fin) p.row_flags[row0 + r] = bad ? 1 : 0;
                     }
@@ -1202,7 +1201,14 @@ hipError_t launch_cfg(bool check, bool want_c, bool want_q, const GemmParams& p_
     } while (0)
 #define ABFT_LAUNCH_FORM(CK, OUT, BS)                                                                     \
     do {                                                                                                  \
-        auto kern = gemm_tile_async_kernel<BM, BN, WGM, WGN, kStages, CK, OUT, ((BS) || !(CK)), kAnyA, kSplitK>; \
+        if constexpr (kLean && (CK)) {                                                                    \
+            if (rs.slots > 0) ABFT_LAUNCH_KERNEL(CK, OUT, BS, true);                                      \
+        }                                                                                                 \
+        ABFT_LAUNCH_KERNEL(CK, OUT, BS, false);                                                           \
+    } while (0)
+#define ABFT_LAUNCH_KERNEL(CK, OUT, BS, SLOTS)                                                            \
+    do {                                                                                                  \
+        auto kern = gemm_tile_async_kernel<BM, BN, WGM, WGN, kStages, CK, OUT, ((BS) || !(CK)), kAnyA, kSplitK, SLOTS>; \
         static std::atomic<uint64_t> lds_allowed{0};                                                      \
         const hipError_t e_attr = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds_most, lds_allowed);\
         if (e_attr != hipSuccess) return e_attr;                                                          \
@@ -1220,6 +1226,7 @@ hipError_t launch_cfg(bool check, bool want_c, bool want_q, const GemmParams& p_
 #undef ABFT_OUT
 #undef ABFT_LAUNCH
 #undef ABFT_LAUNCH_FORM
+#undef ABFT_LAUNCH_KERNEL
 }
 
 }  // namespace atile
