@@ -30,6 +30,8 @@ extern "C" void packed(int K, int N, long long* out) {
                            (long long)l.sums, (long long)l.bytes, KB * 64, NT * 256};
     for (int i = 0; i < 12; ++i) out[i] = v[i];
 }
+extern "C" int slots(int M, int tiles_n) { return abft::row_slots(M, tiles_n).slots; }
+extern "C" int slot_rows(int M, int tiles_n) { return abft::row_slots(M, tiles_n).rows; }
 extern "C" int copy_first(int form, int stages) { return abft::copy_first((abft::WkForm)form, stages); }
 """
 NONE, T32X32W4, T32X32W8, T32X64W4, T32X64W8, T64X64W4 = range(6)
@@ -56,6 +58,7 @@ def plan(tmp_path_factory):
     call.copy_first = lambda form, K: bool(so.copy_first(form, ((K + 63) // 64 + 1) // 2))
     call.form = lambda M, N, K: so.form(M, N, ((K + 63) // 64 + 1) // 2, K % 16 == 0)
     call.packed = lambda K, N: (lambda out: (so.packed(K, N, out), list(out))[1])((ctypes.c_longlong * 12)())
+    call.slots = lambda M, tiles_n: (so.slots(M, tiles_n), so.slot_rows(M, tiles_n))
     call.beyond = lambda M, N, K: bool(so.beyond(M, N, ((K + 63) // 64 + 1) // 2))
     call.large = lambda M, N, K, pick, out="C", can_copy=False, check=True: so.large(M, N, K, ((K + 63) // 64 + 1) // 2, K % 16 == 0, can_copy, pick & 7, pick >> 3,
                                                                          out != "q", out != "C", check)
@@ -208,3 +211,17 @@ def test_what_a_packed_weight_takes(plan, K, N):
     assert total == at[-1] + 4 * (k + n) and total - units <= 24 * k + 8 * n + 8 * 256
     if K >= 4096 and N >= 4096:
         assert total <= 1.01 * units
+
+
+def test_slots_of_the_row_words(plan):
+    """Two kernels index the workspace by them: slots and the row words behind them lie within the words that every call has, a slot has a word
+    for every row, and every slot meets at least one tile column (one that nobody arrives at would be waited for)."""
+    words = (plan(1, 64, 64, 1).words - 64) // 2    # the least that a workspace holds
+    for M in range(1, 400):
+        for tiles_n in (1, 31, 32, 33, 48, 49, 50, 63, 64, 65, 150, 1000, 131072):
+            n, rows = plan.slots(M, tiles_n)
+            if tiles_n <= 48 or M > 384:
+                assert (n, rows) == (0, 0)
+                continue
+            assert n >= 4 and n & (n - 1) == 0 and n < tiles_n and rows >= M
+            assert (n + 1) * rows <= words and n == (32 if M <= 64 else 8 if M <= 192 else 4)
