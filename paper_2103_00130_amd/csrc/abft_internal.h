@@ -449,7 +449,8 @@ inline bool beyond_wk_form(int M, int N, int stages) {
 }
 // The cheapest by that; `pick`, which older thresholds on tiles and K choose, unless another one is cheaper by more than the fits are off: 10 %,
 // unchecked 15 % (the fits are of checked calls), and 15 % for rows that are no whole chunks where those lie within a measured line of wk_form
-// (2000x1000x479 C and Cq: by the fits 64x64 tiles are 11.5 % cheaper there, measured they are 6 % dearer).
+// (of 50 products there for which the fits promise 5 to 15 % six are 6 to 15 % slower, 0.955 in the mean: 209x8035x1218 Cq 11.1 / 12.4, 474x3836x206 C and Cq 8.0
+// / 9.0, 151x10871x168 Cq 7.2 / 7.9; 2086x497x66 Cq 7.2 / 5.8).
 // Nor where 256x256 tiles store more than the 256 MiB that the memory-side cache holds, or C alone of more than 128 MiB in rows of more than 12288
 // columns: there the time is that of memory, which takes the pieces of 1024 bytes of a row that these tiles store at 3.5 to 4.2 TB/s, the smaller
 // tiles' 256 at 2.7 to 3 (256x256 / 64x64: 16400x8240x96 130 / 197, 32800x4120x240 181 / 239, 8200x16480x80 C and Cq 186 / 219, 2824x15456x112 50 / 58,
@@ -457,7 +458,8 @@ inline bool beyond_wk_form(int M, int N, int stages) {
 // Of 560 products of random sizes whose kernel the fits alone would change, up to 130000 rows or columns among them, these lines leave 421; they take
 // 0.73 of the thresholds' time in the geometric mean, two of them more than 5 % longer (2111x6067x96 Cq 17.5 / 19.9, 328x127312x777 C and Cq
 // 151 / 160).  Drawn afterwards, with these lines: 260 changed, 0.76, two (2099x42736x75 Cq 112 / 123, 653x14644x132 Cq 21.2 / 23.9); of 100 unchecked ones
-// 0.78 and four (871x9296x2112 34.8 / 40.5, 785x9216x352 11.4 / 12.9, 1316x5440x1504 Cq 27.0 / 29.9, 280x6075x1721 14.3 / 15.5).  (us, thresholds / now: 214x4369x2434 19.1 / 12.0, 2545x7104x528 C and Cq 87 / 40, 3350x2688x288 C and Cq 31.5 / 19.4, 90x8237x3824 Cq 23.8 /
+// 0.78 and four (871x9296x2112 34.8 / 40.5, 785x9216x352 11.4 / 12.9, 1316x5440x1504 Cq 27.0 / 29.9, 280x6075x1721 14.3 / 15.5).
+// (us, thresholds / now: 214x4369x2434 19.1 / 12.0, 2545x7104x528 C and Cq 87 / 40, 3350x2688x288 C and Cq 31.5 / 19.4, 90x8237x3824 Cq 23.8 /
 // 15.8, 1664x13552x112 C and Cq 60.5 / 29.4, 48x95360x192 Cq 44.4 / 10.8, 71348x106x448 Cq 61.6 / 26.5, 11346x85x7186 60.6 / 35.9.)
 inline LargeChoice large_choice(LargeChoice pick, bool whole_a, bool can_copy, int M, int N, int K, int stages, bool want_c, bool want_q, bool check = true) {
     const int64_t stored = (int64_t)M * N * ((want_c ? 4 : 0) + (want_q ? 1 : 0));

@@ -103,10 +103,10 @@ constexpr size_t lds_bytes(int stages, int limb_stages) {
 }
 // Double-buffered small tiles run as several workgroups to a compute unit, and what bounds a grid of them is what each waits for (0.5 to 1 us
 // for its first stage, 1 us for the row words to come back) times how many are under way.  So they take the LDS that their K needs and no more:
-// one stage where there is one, digits for the stages of their share, 18 or 36 KiB instead of 51 (five by registers or four to a compute unit, not
-// three); no stage is loaded that does not exist (one of 128 k fetched three); the loads of a stage go out as soon as its slot is free; and nobody
+// one stage where there is one, digits for the stages of their share: 19 KiB for one stage, 35 for two (18 and 34 unchecked) instead of 50, five by
+// registers or four to a compute unit, not three (a share of 32 stages, which one tile column of 4096 k has, takes 50 again); no stage is loaded that does not exist (one of 128 k fetched three); the loads of a stage go out as soon as its slot is free; and nobody
 // waits for his last stores.  Us, before / after: 797x4896x208 C and Cq 13.4 / 11.6, 2237x1797x3120 39.0 / 32.3, 3367x4396x112 Cq 23.9 / 20.5,
-// 1092x10212x223 Cq 21.2 / 18.8, 3319x433x129 Cq 8.0 / 6.8, 918x2560x608 8.3 / 8.1; 1457x672x160, which fits the chip either way, 6.3 / 6.4.
+// 1092x10212x223 Cq 21.2 / 18.8, 3319x433x129 Cq 8.0 / 6.8, 918x2560x608 8.3 / 8.1, 1457x672x160, which fits the chip either way, 5.5 / 5.6.
 template <int BM, int BN, int WGM, int WGN, int kStages, bool kSplitK>
 constexpr bool lean() { return BM / WGM * (BN / WGN) <= 4096 && kStages == 2 && !kSplitK; }
 

@@ -83,7 +83,7 @@ __global__ __launch_bounds__(W * 64) void gemm_tile_wk_kernel(const GemmParams p
     constexpr bool kWantC = (kOut & kOutC) != 0, kWantQ = (kOut & kOutQ) != 0;
     constexpr int F = W < 4 * TM ? W : 4 * TM;   // wavefronts that finish the tile
     constexpr int PG = 4 * TM / F;               // groups of eight rows that each of them finishes
-    constexpr bool kMayStream = W == 8 || TM == 2;   // (the other forms' weights are never that large: few stages)
+    constexpr bool kMayStream = W == 8 || TM == 2;   // (the other forms never: of one row of tiles they have few stages, wk_form, and of more, of which 32x64 has any number, none streams)
     static_assert(4 * TM % F == 0 && TM <= 2, "equal shares of the tile; one or two blocks of rows");
 
     extern __shared__ __align__(1024) uint8_t smem[];
