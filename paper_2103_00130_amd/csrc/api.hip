@@ -57,18 +57,28 @@ struct DeviceMemory {
     }
 };
 using Kept = abft::KeptBlocks<DeviceMemory>;
+constexpr int kKeptDevices = 64;
 // of the device, or null beyond the ones that blocks are kept for
 Kept* kept_blocks(int dev) {
-    static Kept* const k = new Kept[64];   // (live as long as the process: weights may be destroyed at its very end)
-    return dev >= 0 && dev < 64 ? &k[dev] : nullptr;
+    static Kept* const k = new Kept[kKeptDevices];   // (live as long as the process: weights may be destroyed at its very end)
+    return dev >= 0 && dev < kKeptDevices ? &k[dev] : nullptr;
 }
+
+bool is_idle(hipStream_t s) {
+    if (hipStreamQuery(s) == hipSuccess) return true;
+    if (hipPeekAtLastError() == hipErrorNotReady) (void)hipGetLastError();   // (no error, and not one that a launch should report)
+    return false;
+}
+// Whether the weight last packed on a device was packed on its null stream: only that one can be asked later on, another may be gone.
+std::atomic<bool> g_null_stream[kKeptDevices];
 
 // which weights' accumulators lie in the same places of their blocks
 uint64_t layout_id(const abft_packed_b* h) { return (uint64_t)(uint32_t)h->KB << 32 | (uint32_t)h->NT; }
 
-// A block on the current device, `dev`, for a weight that is packed on `s`; *size: 0 if it is not to be kept; *sums_zero: its accumulators are.  While `s` is captured that is always so:
-// the block belongs to the graph, whose replays write to it.  Otherwise, whether there is a kept block or not, a call is refused where hipMalloc is (as
-// another stream is captured in a mode that forbids it): hipMalloc of nothing allocates nothing and says so, in 0.07 us.
+// A block on the current device, `dev`, for a weight that is packed on `s`; *sums_zero: its accumulators are; *size: 0 if it is not to be kept.  That is
+// always so while `s` is captured: the block belongs to the graph, whose replays write to it.  Otherwise, whether there is a kept block or not, a
+// call is refused where hipMalloc is (as another stream is captured in a mode that forbids it): hipMalloc of nothing allocates nothing and says so,
+// in 0.07 us.
 hipError_t get_block(int dev, hipStream_t s, size_t need, uint64_t layout, void** out, size_t* size, bool* sums_zero) {
     Kept* const kept = kept_blocks(dev);
     hipStreamCaptureStatus capture;
@@ -78,11 +88,8 @@ hipError_t get_block(int dev, hipStream_t s, size_t need, uint64_t layout, void*
     const hipError_t e = hipMalloc(out, 0);
     if (e != hipSuccess) return e;
     uint64_t left = 0;
-    const hipError_t e_get = kept->get(need, out, size, &left, [s] {
-        const bool idle = hipStreamQuery(s) == hipSuccess;
-        if (!idle) (void)hipGetLastError();
-        return idle;
-    });
+    const hipError_t e_get = kept->get(need, out, size, &left, [s] { return is_idle(s); });
+    g_null_stream[dev].store(s == nullptr, std::memory_order_relaxed);
     *sums_zero = left == layout;
     return e_get;
 }
@@ -91,7 +98,9 @@ void free_handle(abft_packed_b* h) {
     if (!h) return;
     if (h->packed) {   // (one block holds everything)
         int current = -1;   // (a weight may be destroyed with another device current)
-        if (h->block_bytes > 0) kept_blocks(h->device)->put(h->packed, h->block_bytes, h->sums_zero ? layout_id(h) : 0, hipGetDevice(&current) == hipSuccess && current == h->device);
+        const bool here = hipGetDevice(&current) == hipSuccess && current == h->device;
+        const auto idle = [h] { return g_null_stream[h->device].load(std::memory_order_relaxed) && is_idle(nullptr); };
+        if (h->block_bytes > 0) kept_blocks(h->device)->put(h->packed, h->block_bytes, h->sums_zero ? layout_id(h) : 0, here, idle);
         else (void)hipFree(h->packed);
     }
     delete h;

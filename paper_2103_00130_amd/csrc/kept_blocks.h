@@ -13,11 +13,13 @@ namespace abft {
 // blocks freed until then.  When that wait comes is decided by counts alone: a block that fits and has been waited for is taken at once; else, if
 // kMostWaiting blocks that fit have not been, if there is no room to keep another one, or if the caller says that the device seems to be idle, the
 // device is waited for; else another block is allocated.  So a weight replaced again and again settles at kMostWaiting blocks and a wait for as many
-// replacements, at whatever rate, and one replaced while the device idles at a single block.
-// Measured, us a replacement with its first batch (64 rows of 4096x4096, 32 of 700x900), hipMalloc and hipFree / this: back to back 69 and 36 / 31 and 28, 100 us of
-// other host work between them 81 and 39 / 32 and 30, 1 ms 87 and 40 / 40 and 41 (a wait by the time since the last replacement, with a limit of 50 us, took 31 and
-// 27, 42 and 37, 42 and 37).  The wait takes 10 us on an idle device, 60 to 90 on a busy one and, when it is the first in some milliseconds, 150 to 250 (the
-// runtime catches up with all that has ended), for one block or for eight; a block that the device has not had yet takes 60 to 250.
+// replacements, at whatever rate, and one replaced while the device idles at a single block.  A weight that is destroyed while the device seems to be idle
+// is waited for there and then if no other block would serve the next one like it: that one often comes behind the kernels that make it, on a busy stream.
+// Measured, us a replacement with its first batch (64 rows of 4096x4096, 32 of 700x900), hipMalloc and hipFree / this: back to back 69 and 36 / 26 and 24, 100 us of
+// other host work between them 81 and 39 / 25 and 24, 1 ms 87 and 40 / 24 and 25 (a wait by the time since the last replacement, with a limit of 50 us, took 29 and
+// 23, 43 and 38, 43 and 38).  A weight of 16 MiB made anew in a program that has given up another: 95 us with its 16 MiB of random numbers, 240 without
+// the wait as that one was destroyed.  The wait takes 10 us on an idle device, 60 to 90 on a busy one and, when it is the first in some milliseconds, 150 to
+// 250 (the runtime catches up with all that has ended), for one block or for eight; a block that the device has not had yet takes 60 to 250.
 //
 // Memory: allocate(void**, size_t) as hipMalloc; wait() and release(void*): true once everything that was enqueued on the device before the call has
 // ended, and the block given back.
@@ -47,12 +49,13 @@ public:
         }
         return e;
     }
-    // the block of a weight that is destroyed; here: with its device current.  Where there is no room for it, blocks that have lain unused while
+    // the block of a weight that is destroyed; here: with its device current; idle() as above.  Where there is no room for it, blocks that have lain unused while
     // kStale others came make room; not younger ones, of which a program that replaces several weights in turn will need the oldest next
-    void put(void* block, size_t size, uint64_t mark, bool here) {
+    template <class Idle>
+    void put(void* block, size_t size, uint64_t mark, bool here, Idle idle) {
         Block out[kMost + 1];
         int n_out = 0;
-        bool last;
+        bool last, ready = true;   // (ready: a block of that size need not be waited for)
         unsigned long long until;
         {
             std::lock_guard<std::mutex> lock(mutex_);
@@ -63,12 +66,18 @@ public:
                     out[n_out++] = blocks_[i];
                     drop(i);
                 }
-            if (!last && room(size)) add({block, size, mark, released_, false});
-            else out[n_out++] = {block, size, mark, released_, false};
+            if (!last && room(size)) {
+                ready = false;
+                for (int i = 0; i < n_; ++i) ready |= blocks_[i].idle && fits(blocks_[i], size);
+                add({block, size, mark, released_, false});
+            } else {
+                out[n_out++] = {block, size, mark, released_, false};
+            }
             until = released_;
         }
         if (last) (void)give_back();
-        if (n_out > 0 && release(out, n_out) && here) waited(until);   // (to give a block back is a wait for the device)
+        if (n_out > 0 && release(out, n_out) && here) waited(until);   // (to give a block back is a wait for the device, where it is not refused)
+        else if (!ready && here && idle()) (void)wait();
     }
 
     // all that are kept, back to the device; false: refused for some

@@ -61,7 +61,7 @@ long get(Sim* s, size_t need, size_t* size) {
 }
 void put(Sim* s, long b, size_t size) {
     s->d.put_at[b] = s->d.now++;
-    s->kept.put((void*)b, size, 1000 + b, true);
+    s->kept.put((void*)b, size, 1000 + b, true, [s] { return s->d.idle > 1; });
 }
 int trim(Sim* s) { return s->kept.trim(); }
 void counts(Sim* s, long* out) {
@@ -149,9 +149,27 @@ def test_a_weight_replaced_on_an_idle_device_keeps_one_block(sim):
     n = sim.n
     assert n["allocations"] == 2 and n["held"] == 2 and n["waits"] == 49
     sim.idle(0)    # then a run of them
+    n = sim.n
     for i in range(100):
         w = sim.replace(w)
     assert sim.n["allocations"] == 9 and sim.n["waits"] - n["waits"] <= 100 // 8 + 1
+
+
+def test_a_weight_destroyed_on_an_idle_device_is_waited_for_at_once(sim):
+    """... so that the next one, whose stream will be busy, finds a block; not again while there is one."""
+    sim.idle(2)
+    held = [sim.pack(16 * MIB) for _ in range(3)]
+    sim.destroy(held.pop())
+    assert sim.n["waits"] == 1
+    sim.destroy(held.pop())
+    assert sim.n["waits"] == 1
+    sim.idle(0)
+    held.append(sim.pack(16 * MIB))
+    n = sim.n
+    assert n["allocations"] == 3 and n["waits"] == 1
+    sim.idle(2)
+    sim.destroy(held.pop())
+    assert sim.n["waits"] == 2
 
 
 def test_large_blocks(sim):
