@@ -1553,13 +1553,14 @@ def test_weights_replaced_while_others_are_in_use(binding, gpu_util, oracle):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("late", [False, True])
-def test_weights_replaced_back_to_back(binding, gpu_util, oracle, late):
+@pytest.mark.parametrize("late,others", [(False, 0), (True, 0), (True, 18)])
+def test_weights_replaced_back_to_back(binding, gpu_util, oracle, late, others):
     """Replacements with nothing else between them, each used once on another stream: the kept blocks run full, and the one wait that follows comes
-    before any of them is written again.  late: that stream has work of some milliseconds ahead of the first product."""
+    before any of them is written again.  late: that stream has work of some milliseconds ahead of the first product.  others: so many weights of
+    other sizes have been destroyed before, whose blocks fill the list."""
     import torch
 
-    say(f"weights replaced back to back, late={late}")
+    say(f"weights replaced back to back, late={late}, others={others}")
     M, N, K = 24, 700, 1500
     rng = np.random.default_rng(6)
     A = rng.integers(0, 256, size=(M, K), dtype=np.uint8)
@@ -1572,6 +1573,8 @@ def test_weights_replaced_back_to_back(binding, gpu_util, oracle, late):
     flags = [torch.full((M,), -1, dtype=torch.int32, device="cuda") for _ in C]
     side = torch.cuda.Stream()
     busy = torch.zeros(1 << 28, dtype=torch.int32, device="cuda")
+    spare = [binding.abft_pack_b_checksum(torch.zeros(2000 + 300 * i, 700, dtype=torch.int8, device="cuda")) for i in range(others)]
+    del spare
     torch.cuda.synchronize()
     if late:
         with torch.cuda.stream(side):
